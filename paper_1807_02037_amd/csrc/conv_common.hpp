@@ -148,8 +148,7 @@ hipError_t launch_rf(IgemmP& p, hipStream_t s);
 // filters [split][tap][cx][ky]; the caller sums them.
 bool wgrad_patch_eligible(int cx, int ky, const int* filt, const int* stride);
 int wgrad_patch_splits(long long batch, const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky);
-// cs_part (only where wgrad_patch_colsum says so, else null): partial column sums of dy [split][ky] on the side.
-bool wgrad_patch_colsum(const int* filt, int cx, int ky);
+// cs_part (or null): partial column sums of dy [split][ky] on the side.
 hipError_t launch_wgrad_patch(const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* asp,
                               const int* osp, const int* filt, const int* pad, int cx, int ky, float* cs_part, hipStream_t s);
 
@@ -169,10 +168,11 @@ bool conv_small_eligible(const IgemmP& p);
 hipError_t launch_conv_small(IgemmP& p, hipStream_t s);
 
 // Weight gradient for convolutions with at most 4 input channels (wgrad_small.hip): per-split partial filters [split][tap][cx][ky].
+// cs_part (or null): partial column sums of dy [split][ky] on the side.
 bool wgrad_small_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride);
 int wgrad_small_splits(long long rows, const int* osp);
 hipError_t launch_wgrad_small(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp,
-                              const int* osp, const int* filt, const int* stride, const int* pad, hipStream_t s);
+                              const int* osp, const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s);
 
 // Streaming weight gradient for 1x1 filters without padding (wgrad_rows.hip): per-split partial filters [split][cx][ky].
 bool wgrad_rows_eligible(int cx, int ky, const int* filt, const int* stride, const int* pad);

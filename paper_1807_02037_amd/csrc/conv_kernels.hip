@@ -564,11 +564,17 @@ __global__ void wgrad_reduce_kernel(const float* part, float* dw, long long per_
 }
 
 // Same sum for the common case (no transpose, element count a multiple of 4): every thread adds one eighth
-// of the splits for four neighbouring elements, the eight partial sums are then added in a fixed order.
-__global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* part, float4* dw, long long per4, int splits) {
+// of the splits for four neighbouring elements, the eight partial sums are then added in a fixed order.  The
+// work-groups from `blocks` on do the same for the column sums of dy (cs_per4 vectors of four, the same splits), which
+// the same pass left behind: one launch for both parameter gradients instead of two (a launch of its own cost the column
+// sums 2.5 to 4.5 us a layer, whatever their size).
+__global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* part, float4* dw, long long per4, int splits, int blocks,
+                                                               const float4* cs_part, float4* cs_out, int cs_per4) {
   __shared__ float4 sh[8][32];
   const int o = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const long long idx = (long long)blockIdx.x * 32 + o;
+  const bool cs = (int)blockIdx.x >= blocks;                // uniform
+  if (cs) { part = cs_part; dw = cs_out; per4 = cs_per4; }
+  const long long idx = (long long)((int)blockIdx.x - (cs ? blocks : 0)) * 32 + o;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (idx < per4) {
     int i = g;
@@ -593,6 +599,15 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* par
     for (int j = 1; j < 8; ++j) { t.x += sh[j][o].x; t.y += sh[j][o].y; t.z += sh[j][o].z; t.w += sh[j][o].w; }
     dw[idx] = t;
   }
+}
+
+// cs_part / cs_out (or null): the partial column sums of dy of the same splits, ky of them (a multiple of 4).
+static hipError_t launch_wgrad_reduce(const void* part, float* dw, long long per, int splits, hipStream_t s, const float* cs_part = nullptr,
+                                      float* cs_out = nullptr, int ky = 0) {
+  const int blocks = (int)((per / 4 + 31) / 32), cs_blocks = cs_part ? (ky / 4 + 31) / 32 : 0;
+  hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(blocks + cs_blocks), dim3(256), 0, s, (const float4*)part, (float4*)dw, per / 4, splits, blocks,
+                     (const float4*)cs_part, (float4*)cs_out, ky / 4);
+  return hipGetLastError();
 }
 
 // Filter packing: dst[tap][k][c] = w[tap][c][k] (transpose == 1) or dst = w (transpose == 0), times scale[k].
@@ -887,16 +902,16 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long per = (long long)cx * ky;
-    hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(cdiv(per / 4, 32)), dim3(256), 0, s, (const float4*)ws, (float4*)dw, per / 4, wgs);
-    return hipGetLastError();
+    return launch_wgrad_reduce(ws, dw, per, wgs, s);
   }
   if (!transpose && wgrad_use_small(cx, ky, asp, osp, filt, stride)) {
-    hipError_t e = launch_wgrad_small(X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, asp, osp, filt, stride, pad, s);
-    if (e != hipSuccess) return e;
     const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
-    hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(cdiv(per / 4, 32)), dim3(256), 0, s, (const float4*)ws, (float4*)dw, per / 4,
-                       wgrad_small_splits(rows, osp));
-    return hipGetLastError();
+    const int splits = wgrad_small_splits(rows, osp);
+    float* cs = side ? colsum_part(ws, splits, per) : nullptr;
+    hipError_t e = launch_wgrad_small(X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
+    if (e != hipSuccess) return e;
+    colsum_done = cs != nullptr;
+    return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
   }
   if (!transpose && wgrad_rows_eligible(cx, ky, filt, stride, pad)) {
     const long long per = (long long)cx * ky;
@@ -904,25 +919,19 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
     float* cs = side ? colsum_part(ws, splits, per) : nullptr;
     hipError_t e = launch_wgrad_rows(X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, asp, osp, stride, cs, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(cdiv(per / 4, 32)), dim3(256), 0, s, (const float4*)ws, (float4*)dw, per / 4, splits);
-    e = hipGetLastError();
-    if (e != hipSuccess || !cs) return e;
-    colsum_done = true;
-    return col_reduce(cs, splits, ky, colsum_out, s);
+    colsum_done = cs != nullptr;
+    return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
   }
   static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;   // tuning aid
   if (!transpose && !no_patch && wgrad_patch_eligible(cx, ky, filt, stride)) {
     const long long batch = rows / ((long long)osp[0] * osp[1] * osp[2]);
     const int splits = wgrad_patch_splits(batch, asp, osp, filt, pad, cx, ky);
     const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
-    float* cs = side && wgrad_patch_colsum(filt, cx, ky) ? colsum_part(ws, splits, per) : nullptr;
+    float* cs = side ? colsum_part(ws, splits, per) : nullptr;
     hipError_t e = launch_wgrad_patch(X, DY, reinterpret_cast<float*>(ws), batch, asp, osp, filt, pad, cx, ky, cs, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(cdiv(per / 4, 32)), dim3(256), 0, s, (const float4*)ws, (float4*)dw, per / 4, splits);
-    e = hipGetLastError();
-    if (e != hipSuccess || !cs) return e;
-    colsum_done = true;
-    return col_reduce(cs, splits, ky, colsum_out, s);
+    colsum_done = cs != nullptr;
+    return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
   }
   WgradP p{};
   p.X = X; p.DY = DY; p.part = reinterpret_cast<float*>(ws);
@@ -939,7 +948,7 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
   if (e != hipSuccess) return e;
   const long long per = (long long)p.taps * cx * ky;
   if (!transpose && (per & 3) == 0)
-    hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(cdiv(per / 4, 32)), dim3(256), 0, s, (const float4*)p.part, (float4*)dw, per / 4, w.splits);
+    return launch_wgrad_reduce(p.part, dw, per, w.splits, s);
   else
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(cdiv(per, 256)), dim3(256), 0, s, p.part, dw, per, w.splits, p.taps, cx, ky, transpose);
   return hipGetLastError();

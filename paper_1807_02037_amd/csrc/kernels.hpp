@@ -75,8 +75,6 @@ hipError_t softmax_ce_grad(int64_t rows, int classes, const void* z, const int32
 hipError_t grad_sum(int64_t numel, int n, const void* const* g, const void* mask, void* out, hipStream_t s);
 // out[c] (fp32) = sum over rows of dy[row][c]; ws: reduce_ws(rows, c) bytes
 hipError_t colsum(int64_t rows, int c, const void* dy, float* out, void* ws, hipStream_t s);
-// out[c] = part[0][c] + part[1][c] + ... (fp32, `parts` rows, fixed order)
-hipError_t col_reduce(const float* part, int64_t parts, int c, float* out, hipStream_t s);
 // dw[j][k] = raw[j][k] * scale[k]
 hipError_t scale_cols(int64_t j, int k, const float* raw, const float* scale, float* out, hipStream_t s);
 // out[k] = sum_j w[j][k] * raw[j][k]

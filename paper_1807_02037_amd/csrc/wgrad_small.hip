@@ -39,6 +39,7 @@ struct WSmallP {
   long long stages;            // batch * osp[0] * osp[1] * segs
   long long stages_per_split;
   int splits;
+  float* cs_part;              // column sums of dy on the side: partial sums [split][ky], or null
 };
 
 __device__ __forceinline__ bf16x8 ws_tr_frag(const uint16_t* p0, const uint16_t* p1) {
@@ -107,6 +108,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void wgrad_small_kernel(WSmallP p) {
       if (q < ok && cv < yv) dy_next[i] = *reinterpret_cast<const uint4*>(p.DY + ((row * p.osp[2] + w0 + q) * p.ky) + cv * 8);
     }
   };
+  float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};     // channels (tid & 7) * 8 .. + 7 of all this thread's vectors
   if (s_begin < s_end) {
     load_dy((nb * p.osp[0] + od) * p.osp[1] + oh, seg * WS_ROWS);
     sg_load_rows<NH>(rows_next, p.X, rw, nb, od, oh, seg * WS_ROWS, p.asp, p.stride, p.pad, p.filt, p.cx);
@@ -120,6 +122,14 @@ __global__ __launch_bounds__(NTHREADS, 2) void wgrad_small_kernel(WSmallP p) {
       }
     }
 
+    if (p.cs_part) {                                    // uniform: the bias / shift gradient out of the same pass over dy
+#pragma unroll
+      for (int i = 0; i < YV; ++i) {
+        const uint32_t w[4] = {dy_next[i].x, dy_next[i].y, dy_next[i].z, dy_next[i].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) csum[e] += __uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
+      }
+    }
     __syncthreads();                                    // the previous segment is fully consumed
     // ---- gradient tile: 64 positions x ky channels, zero beyond the row end and beyond ky ----
 #pragma unroll
@@ -163,6 +173,20 @@ __global__ __launch_bounds__(NTHREADS, 2) void wgrad_small_kernel(WSmallP p) {
       if (j < p.J && k < p.ky) out[(long long)j * p.ky + k] = acc[q][v];
     }
   }
+  if (p.cs_part) {
+    // lanes with the same channels by shuffles, then the four waves in order
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      for (int dist = 8; dist < 64; dist <<= 1) csum[e] += __shfl_xor(csum[e], dist, 64);
+    float* sh = reinterpret_cast<float*>(sY);
+    __syncthreads();                                    // the last segment is fully consumed
+    if (lane < 8) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sh[wave * 64 + lane * 8 + e] = csum[e];
+    }
+    __syncthreads();
+    if (tid < p.ky) p.cs_part[(long long)blockIdx.x * p.ky + tid] = (sh[tid] + sh[64 + tid]) + (sh[128 + tid] + sh[192 + tid]);
+  }
 }
 
 long long ws_stages(long long rows, const int* osp) {
@@ -198,8 +222,9 @@ int wgrad_small_splits(long long rows, const int* osp) {
 }
 
 hipError_t launch_wgrad_small(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp,
-                              const int* osp, const int* filt, const int* stride, const int* pad, hipStream_t s) {
+                              const int* osp, const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s) {
   WSmallP p{};
+  p.cs_part = cs_part;
   p.X = X; p.DY = DY; p.part = part;
   p.cx = cx; p.ky = ky; p.J = filt[0] * filt[1] * filt[2] * cx;
   for (int i = 0; i < 3; ++i) { p.asp[i] = asp[i]; p.osp[i] = osp[i]; p.filt[i] = filt[i]; p.stride[i] = stride[i]; p.pad[i] = pad[i]; }
