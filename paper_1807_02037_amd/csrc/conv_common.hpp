@@ -16,6 +16,7 @@ struct IgemmP {
   const uint16_t* mask;
   int relu;
   long long M;
+  long long M_in;  // pointwise kernel, forward with a stride: input rows
   int nout, red;
   int asp[3], osp[3], filt[3], stride[3], pad[3];
   int mode;     // 0: src = o*stride + tap - pad (forward); 1: src = (o + pad - tap)/stride (transposed)
@@ -152,7 +153,8 @@ int wgrad_patch_splits(long long batch, const int* asp, const int* osp, const in
 hipError_t launch_wgrad_patch(const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* asp,
                               const int* osp, const int* filt, const int* pad, int cx, int ky, float* cs_part, hipStream_t s);
 
-// Pointwise (1x1, stride 1) forward convolution (conv_pw.hip).  p.B is the filter as stored, [c][k].
+// Pointwise (1x1, no padding, any stride) forward convolution and data gradient (conv_pw.hip).  p.B is the filter as
+// stored, [c][k] (data gradient: times the scale).
 bool pw_eligible(const IgemmP& p);
 bool pw_up_eligible(const IgemmP& p);   // p.up set, p.M = input rows, p.asp / p.osp = input / output extents
 hipError_t launch_pw(IgemmP& p, hipStream_t s);

@@ -1,17 +1,27 @@
-// Pointwise (1x1 / 1x1x1, stride 1, no padding) forward convolution:
-//   out[m][k] = epi(sum_c x[m][c] * w[c][k]),  m over positions, channels-last rows.
+// Pointwise (1x1 / 1x1x1, no padding) convolutions as one matrix product over channels-last rows:
+//   forward          out[m][k] = epi(sum_c x[row(m)][c] * w[c][k])        (row(m): the input row under a stride)
+//   data gradient    dx[row(m)][c] = epi(sum_k dy[m][k] * w[c][k])
+//   transposed convolution with window = stride: see UP below.
 //
-// Without filter taps the operation is a plain GEMM whose long side is the position count, and with the
-// channel counts of CNN bottlenecks it is bound by the one pass over the activations.  This kernel stages
-// 128 positions x 64 input channels per step with contiguous 16-byte loads and keeps the filter in the
-// layout it has in memory ([c][k]): the filter tile is stored [c][k] in LDS and the MFMA operand (8 consecutive
-// c per lane) is read with the gfx950 LDS transpose read, so no filter repacking kernel runs before it.
-// LDS is double-buffered (one barrier per stage); the epilogue (scale/shift, residual add, ReLU) is the
-// shared 8-channel vector epilogue.  (The data gradient of a pointwise convolution reads the filter along
-// its contiguous axis already and stays on the general kernel, which measured faster for it.)
+// With the channel counts of CNN bottlenecks these layers are bound by the passes over the activations, or, on the small
+// maps of the late stages, by how fast tiles can be fed: both ask for loads in flight.  Tiles of both operands go from
+// memory straight to LDS (16-byte buffer loads that write LDS: no registers, no LDS store instructions; offsets beyond
+// the descriptor read zeros, so ragged tiles need no branches), 64 reduction channels a stage (a whole 128-byte line of
+// a row: with 32 every line crossed from the L2 twice) in two buffers with one barrier per stage; the second work-group
+// of the compute unit covers what one stage of lookahead does not (three buffers and one work-group: 40 % slower).  The
+// filter stays as it lies in memory: the forward pass reads its [c][k] tile with the gfx950 LDS transpose read, the data
+// gradient reads rows [c][k] as they are ([n][r] for it).  A wave of the widest tile owns 64 x 64 outputs, one LDS read
+// per product.  Products are taken transposed (filter fragment first): a lane holds four consecutive channels of a
+// position and writes them to LDS as one vector; each wave turns 32 positions at a time through its own piece of LDS,
+// without a barrier, and stores full lines.  The stores go around the L2s: a result is as large as what the L2s hold,
+// and on its way through evicts the operand tiles that neighbouring work-groups share (forward 2048 -> 512 on 7 x 7 at
+// batch 256 45 -> 34 us, data gradient 64 <- 256 on 56 x 56 at batch 128 86 -> 73 us; nowhere slower).
+//
+// Measured: see launch_pw_shape.
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "conv_common.hpp"
@@ -23,264 +33,399 @@ namespace {
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 
-constexpr int PM = 128;       // positions per tile
 constexpr int PK = 64;        // reduction channels per stage
-constexpr int PLA = PK + 8;   // pitch of [row][r] tiles (144 bytes: conflict-free 16-byte reads)
+constexpr int SL = PK / 8;    // 16-byte slots of a row of PK channels
+constexpr unsigned PW_OOB = 0x80000000u;
+__device__ __forceinline__ int pw_swz(int row) { return (row >> 1) & 7; }
 
-template <int BN>
+enum { PW_FWD = 0, PW_DGRAD = 1, PW_UP = 2 };
+
+template <int BM_, int BN_, int WM_, int WN_, int NBUF_>
 struct PwTile {
-  static constexpr int LBT = BN + 32;                       // pitch of the [r][n] filter tile (64-byte row shift)
-  static constexpr int A_EL = PM * PLA;
-  static constexpr int B_EL = PK * LBT;
-  static constexpr int STAGE = A_EL + B_EL;
-  static constexpr int LDC = BN + 4;
-  static constexpr int MAIN_BYTES = 2 * STAGE * 2, EPI_BYTES = PM * LDC * 4;
-  static constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NBUF = NBUF_;
+  static constexpr int NT = 64 * WM * WN;                         // threads
+  static constexpr int WTM = BM / WM, WTN = BN / WN;              // outputs of a wave
+  static constexpr int TM = WTM / 32, TN = WTN / 32;
+  static constexpr int A_BYTES = BM * PK * 2, B_BYTES = BN * PK * 2;
+  static constexpr int STAGE = A_BYTES + B_BYTES;
+  static constexpr int AV = A_BYTES / (16 * NT), BV = B_BYTES / (16 * NT);   // loads per thread and stage
+  static constexpr int LDC = WTN + 4;                             // fp32 pitch of the epilogue's 32-position tile
+  static constexpr int EPI_WAVE = 32 * LDC * 4;
+  static constexpr int LDS_BYTES = NBUF * STAGE > WM * WN * EPI_WAVE ? NBUF * STAGE : WM * WN * EPI_WAVE;
+  static constexpr int LPR = WTN / 8;                             // lanes per output row in the epilogue
+  static constexpr int RPI = 64 / LPR;                            // rows per instruction
+  static constexpr int QV = 32 / RPI;                             // vectors per lane and 32 positions
+  static constexpr int OCC = 163840 / LDS_BYTES * (NT / 256) < 4 ? 163840 / LDS_BYTES * (NT / 256) : 4;   // waves per SIMD
 };
 
-__device__ __forceinline__ bf16x8 pw_tr_frag(const uint16_t* p0, const uint16_t* p1) {
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+// Results are stored around the L2s (see launch_pw_shape).
+__device__ __forceinline__ void put_vec(uint16_t* q, const uint4& d) {
+  __builtin_nontemporal_store(__builtin_bit_cast(v4u, d), reinterpret_cast<v4u*>(q));
+}
+// 16 bytes per lane from buffer offset voff + soff to LDS bytes lds + 16 * lane (lds: the same for the whole wave; offsets
+// outside the buffer write zeros).  Written in assembly because the compiler, seeing such a load, waits for all of
+// them before any LDS transpose read; it has no register output, and pw_wait_barrier does the waiting.
+__device__ __forceinline__ void pw_load_lds(v4u rsrc, unsigned lds, unsigned voff, unsigned soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ v4u pw_rsrc(const void* base, long long bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  return v4u{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, (unsigned)(bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000u};
+}
+
+// At most N of this wave's memory loads may still be in flight, and its LDS reads have come back; then every wave of the
+// work-group has got here.
+template <int N>
+__device__ __forceinline__ void pw_wait_barrier() {
+  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+__device__ __forceinline__ bf16x8 pw_tr_frag(const unsigned char* p0, const unsigned char* p1) {
   const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p0);
   const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p1);
   const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   return __builtin_bit_cast(bf16x8, r);
 }
 
-// UP: the transposed-convolution variant (one product per tap parity, output rows remapped); a template parameter so
-// that the plain pointwise kernel keeps its 32-bit tile-relative addressing.
-template <int BN, bool UP>
-__global__ __launch_bounds__(NTHREADS, (BN == 64 ? 3 : 2)) void pw_kernel(IgemmP p) {
-  typedef PwTile<BN> T;
-  constexpr int TN = BN / 32;
-  constexpr int AV = PM * (PK / 8) / NTHREADS;                              // 4 activation vectors per thread
-  constexpr int BV = PK * (BN / 8) / NTHREADS;                              // filter vectors per thread
-  constexpr int LDC = T::LDC;
+// Row of the strided grid (extents big) under row m of the small one (extents small).
+__device__ __forceinline__ long long pw_strided_row(long long m, const int* small, const int* big, const int* stride) {
+  unsigned t = (unsigned)m;                                       // host guarantees M < 2^31
+  const unsigned w = t % (unsigned)small[2]; t /= (unsigned)small[2];
+  const unsigned h = t % (unsigned)small[1]; t /= (unsigned)small[1];
+  const unsigned d = t % (unsigned)small[0]; t /= (unsigned)small[0];
+  return (((long long)t * big[0] + d * stride[0]) * big[1] + h * stride[1]) * (long long)big[2] + w * stride[2];
+}
+
+// UP: transposed convolution with window = stride.  Every output position takes one filter tap (the parity of its
+// coordinates), so the layer is one product of the input with taps x k virtual output channels: column n is channel
+// n % k of tap n / k, filter element w[tap][c][n % k], written to the output position stride * input position + tap.
+// The input tile is read once for all taps of a column tile, and the taps that differ in the last coordinate only are
+// neighbours in memory, so their channels leave as one contiguous run.
+// STRIDED: rows are gathered (forward) or scattered (data gradient: only the positions a stride leaves under a dy row;
+// the others are strided_rest_kernel's).
+template <typename T, int MODE, bool STRIDED>
+__global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
+  constexpr bool UP = MODE == PW_UP;
+  constexpr int BN = T::BN, PM = T::BM, NBUF = T::NBUF, TM = T::TM, TN = T::TN, AV = T::AV, BV = T::BV;
+  constexpr int ROWB = BN * 2;                                    // bytes of a filter row of the [r][n] tile
   extern __shared__ __attribute__((aligned(16))) unsigned char pw_smem[];
-  uint16_t* sA = reinterpret_cast<uint16_t*>(pw_smem);
-  float* sC = reinterpret_cast<float*>(pw_smem);
 
   const int per_xcd = (p.ntiles + 7) / 8;
-  int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (tile >= p.ntiles) return;
-  // Transposed convolution with window = stride: every output position takes one filter tap (the parity of its
-  // coordinates), so the layer is one pointwise product of the input with taps x k virtual output channels: column
-  // n is channel n % k of tap n / k, filter element w[tap][c][n % k], written to the output position
-  // stride * input position + tap.  The input tile is read once for all taps of a column tile, and the taps that
-  // differ in the last coordinate only are neighbours in memory, so their channels leave as one contiguous run.
-  const int npar = UP ? p.up[0] * p.up[1] * p.up[2] : 1;
-  const int nv = npar * p.nout;                           // virtual output channels
+  const int nv = (UP ? p.up[0] * p.up[1] * p.up[2] : 1) * p.nout;           // columns, virtual ones included
   const int n0 = (tile % p.ntiles_n) * BN;
   const long long m0 = (long long)(tile / p.ntiles_n) * PM;
-  const uint16_t* Bp = p.B;
-  // element offset, in the output tensor, of column n of input row m (UP only)
-  auto out_off = [&](long long m, int n) -> long long {
-    int t = n / p.nout;
-    const int kk = n - t * p.nout;
-    const int tw = t % p.up[2]; t /= p.up[2];
-    const int th = t % p.up[1];
-    const int td = t / p.up[1];
-    const int w = (int)(m % p.asp[2]); long long q = m / p.asp[2];
-    const int h = (int)(q % p.asp[1]); q /= p.asp[1];
-    const int d = (int)(q % p.asp[0]); q /= p.asp[0];
-    return (((q * p.osp[0] + d * p.up[0] + td) * p.osp[1] + h * p.up[1] + th) * p.osp[2] + w * p.up[2] + tw) * (long long)p.nout + kk;
-  };
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  // UP: output row of tap 0 for each input row of the tile (read by the epilogue after the main loop's barriers)
-  __shared__ unsigned s_row0[UP ? PM : 1];
-  if (UP && tid < PM) {
-    const long long m = m0 + tid < p.M ? m0 + tid : 0;
-    const int w = (int)(m % p.asp[2]); long long q = m / p.asp[2];
-    const int h = (int)(q % p.asp[1]); q /= p.asp[1];
-    const int d = (int)(q % p.asp[0]); q /= p.asp[0];
-    s_row0[tid] = (unsigned)(((q * p.osp[0] + d * p.up[0]) * p.osp[1] + h * p.up[1]) * p.osp[2] + w * p.up[2]);
-  }
+  const int wm = wave / T::WN, wn = wave % T::WN;
+  const int half = lane >> 5, li = lane & 15, lg = lane >> 4;
 
-  // global offsets of this thread's vectors for stage 0
-  long long a_off[AV];
-  bool a_ok[AV];
-#pragma unroll
-  for (int j = 0; j < AV; ++j) {
-    const int v = tid + j * NTHREADS;
-    const long long m = m0 + (v >> 3);
-    a_ok[j] = m < p.M;
-    a_off[j] = m * p.red + (v & 7) * 8;
+  // ---- operand of the epilogue: row and column of this lane's vectors; output rows relative to that of m0 ----
+  const int cg = (lane % T::LPR) * 8, n = n0 + wn * T::WTN + cg;
+  const int er = wm * T::WTM + lane / T::LPR;                     // tile row of vector (0, 0)
+  __shared__ unsigned s_row[UP || (STRIDED && MODE == PW_DGRAD) ? PM : 1];
+  long long o_base = m0;                                          // output row that s_row counts from
+  if constexpr (UP || (STRIDED && MODE == PW_DGRAD)) {
+    const int* big = p.osp;
+    const int* st = UP ? p.up : p.stride;
+    o_base = pw_strided_row(m0, p.asp, big, st);
+    if (tid < PM) s_row[tid] = (unsigned)(pw_strided_row(m0 + tid < p.M ? m0 + tid : m0, p.asp, big, st) - o_base);
+    __syncthreads();
   }
-  long long b_off[BV];
-  bool b_ok[BV];
-#pragma unroll
-  for (int j = 0; j < BV; ++j) {
-    const int v = tid + j * NTHREADS;
-    const int r = v / (BN / 8), col = (v % (BN / 8)) * 8;
-    b_ok[j] = n0 + col < nv;
-    b_off[j] = (long long)r * p.nout + n0 + col;
-    if (UP) {                                             // column of tap t: w[t][r][kk]
-      const int t = (n0 + col) / p.nout;
-      b_off[j] = ((long long)t * p.red + r) * p.nout + (n0 + col - t * p.nout);
-    }
+  long long up_tap = 0;                                           // UP: this lane's columns lie in one tap
+  int up_n = n;
+  if (UP && n < nv) {
+    int t = n / p.nout;
+    up_n = n - t * p.nout;
+    const int tw = t % p.up[2]; t /= p.up[2];
+    const int th = t % p.up[1];
+    up_tap = ((long long)(t / p.up[1]) * p.osp[1] + th) * p.osp[2] + tw;
   }
-  const int niter = (p.red + PK - 1) / PK;
-
-  uint4 ra[AV], rb[BV];
-  auto load_stage = [&](int it) {
-    const int k0 = it * PK;
-#pragma unroll
-    for (int j = 0; j < AV; ++j) {
-      const int cv = ((tid + j * NTHREADS) & 7) * 8;
-      ra[j] = make_uint4(0, 0, 0, 0);
-      if (a_ok[j] && k0 + cv < p.red) ra[j] = *reinterpret_cast<const uint4*>(p.A + a_off[j] + k0);
-    }
-#pragma unroll
-    for (int j = 0; j < BV; ++j) {
-      const int v = tid + j * NTHREADS;
-      rb[j] = make_uint4(0, 0, 0, 0);
-      const int r = v / (BN / 8);
-      if (b_ok[j] && k0 + r < p.red) rb[j] = *reinterpret_cast<const uint4*>(Bp + b_off[j] + (long long)k0 * p.nout);
-    }
+  const long long out0 = (o_base + up_tap) * p.nout + up_n;
+  auto out_off = [&](int r) -> long long {
+    if constexpr (UP || (STRIDED && MODE == PW_DGRAD)) return out0 + (long long)s_row[r] * p.nout;
+    else return out0 + (unsigned)(r * p.nout);
   };
-  auto store_stage = [&](int buf) {
-    uint16_t* a = sA + buf * T::STAGE;
-    uint16_t* b = a + T::A_EL;
-#pragma unroll
-    for (int j = 0; j < AV; ++j) {
-      const int v = tid + j * NTHREADS;
-      *reinterpret_cast<uint4*>(a + (v >> 3) * PLA + (v & 7) * 8) = ra[j];
-    }
-#pragma unroll
-    for (int j = 0; j < BV; ++j) {
-      const int v = tid + j * NTHREADS;
-      *reinterpret_cast<uint4*>(b + (v / (BN / 8)) * T::LBT + (v % (BN / 8)) * 8) = rb[j];
-    }
-  };
-
-  f32x16 acc[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-
-  load_stage(0);
-
-  // operands of the epilogue do not depend on the main loop: fetch them now
-  constexpr int EV = PM * (BN / 8) / NTHREADS;
+  constexpr int EV = TM * T::QV;
   uint4 pre_add[EV], pre_mask[EV];
 #pragma unroll
   for (int q = 0; q < EV; ++q) {
     pre_add[q] = make_uint4(0, 0, 0, 0);
     pre_mask[q] = make_uint4(0, 0, 0, 0);
-    const int idx = tid + q * NTHREADS;
-    const int r = idx / (BN / 8), cg = (idx % (BN / 8)) * 8;
-    if (m0 + r < p.M && n0 + cg < nv && (!UP || p.add || p.mask)) {
-      const long long off = UP ? out_off(m0 + r, n0 + cg) : m0 * p.nout + n0 + (unsigned)(r * p.nout + cg);
-      if (p.add) pre_add[q] = *reinterpret_cast<const uint4*>(p.add + off);
-      if (p.mask) pre_mask[q] = *reinterpret_cast<const uint4*>(p.mask + off);
+    const int r = er + (q / T::QV) * 32 + (q % T::QV) * T::RPI;
+    if (m0 + r < p.M && n < nv) {
+      if (p.add) pre_add[q] = *reinterpret_cast<const uint4*>(p.add + out_off(r));
+      if (p.mask) pre_mask[q] = *reinterpret_cast<const uint4*>(p.mask + out_off(r));
     }
   }
 
-  const long long tile_base = m0 * p.nout + n0;
-  store_stage(0);
-  __syncthreads();
-  for (int it = 0; it < niter; ++it) {
-    if (it + 1 < niter) load_stage(it + 1);
-    const uint16_t* a = sA + (it & 1) * T::STAGE;
-    const uint16_t* b = a + T::A_EL;
+  // ---- loads: vector v of a stage's tile goes to LDS bytes [16 v, 16 v + 16); which channels it holds is permuted within
+  // a row so that the reads below fall into different banks ----
+  const long long a_row0 = STRIDED && MODE == PW_FWD ? pw_strided_row(m0, p.osp, p.asp, p.stride) : m0;
+  const long long a_rows = STRIDED && MODE == PW_FWD ? p.M_in - a_row0 : p.M - m0;
+  const v4u rs_a = pw_rsrc(p.A + a_row0 * p.red, a_rows * p.red * 2), rs_b = pw_rsrc(p.B, (long long)nv * p.red * 2);
+  const unsigned lds0 = (unsigned)(uintptr_t)pw_smem;             // LDS address: the low half of the generic one
+  unsigned a_off[AV], b_off[BV];
+  int a_k[AV], b_k[BV];                                           // reduction channel of the vector within the stage
 #pragma unroll
-    for (int ks = 0; ks < PK / 16; ++ks) {
-      const bf16x8 af = *reinterpret_cast<const bf16x8*>(a + (wave * 32 + (lane & 31)) * PLA + ks * 16 + (lane >> 5) * 8);
-      bf16x8 bfr[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const uint16_t* q = b + (ks * 16 + 8 * (lg >> 1) + (li >> 2)) * T::LBT + 32 * j + 16 * (lg & 1) + 4 * (li & 3);
-        bfr[j] = pw_tr_frag(q, q + 4 * T::LBT);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr[j], acc[j], 0, 0, 0);
-    }
-    if (it + 1 < niter) store_stage((it + 1) & 1);
-    __syncthreads();
+  for (int j = 0; j < AV; ++j) {
+    const int v = tid + j * T::NT, row = v / SL;
+    a_k[j] = ((v % SL) ^ pw_swz(row)) * 8;
+    long long src = row;
+    if constexpr (STRIDED && MODE == PW_FWD) src = pw_strided_row(m0 + row < p.M ? m0 + row : m0, p.osp, p.asp, p.stride) - a_row0;
+    a_off[j] = m0 + row < p.M ? (unsigned)((src * p.red + a_k[j]) * 2) : PW_OOB;
   }
+#pragma unroll
+  for (int j = 0; j < BV; ++j) {
+    const int v = tid + j * T::NT;
+    if constexpr (MODE == PW_DGRAD) {                             // rows n of 32 reduction channels
+      const int row = v / SL;
+      b_k[j] = ((v % SL) ^ pw_swz(row)) * 8;
+      b_off[j] = n0 + row < nv ? (unsigned)(((n0 + row) * p.red + b_k[j]) * 2) : PW_OOB;
+    } else {                                                      // rows r of BN columns
+      const int r = v / (BN / 8), slot = v % (BN / 8);
+      const int blk = (slot >> 2) ^ (BN == 128 ? r & 3 : (r >> 1) & 1);
+      const int col = n0 + blk * 32 + (slot & 3) * 8;
+      b_k[j] = r;
+      const int t = UP ? col / p.nout : 0;
+      b_off[j] = col < nv ? (unsigned)(((t * p.red + r) * p.nout + col - t * p.nout) * 2) : PW_OOB;
+    }
+  }
+  const unsigned a_step = PK * 2, b_step = MODE == PW_DGRAD ? PK * 2 : (unsigned)(PK * p.nout * 2);
+  const int niter = (p.red + PK - 1) / PK;
+  auto fetch = [&](int it, int buf) {
+    const unsigned a = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024) + buf * T::STAGE;
+    const bool whole = (it + 1) * PK <= p.red;                    // the last stage may be partial: zeros, whatever lies behind
+#pragma unroll
+    for (int j = 0; j < AV; ++j)
+      pw_load_lds(rs_a, a + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : PW_OOB, it * a_step);
+#pragma unroll
+    for (int j = 0; j < BV; ++j)
+      pw_load_lds(rs_b, a + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : PW_OOB, it * b_step);
+  };
 
-  // epilogue: accumulators -> LDS (row-major fp32) -> 8-channel vectors
+  // ---- LDS read addresses ----
+  int a_rd[PK / 16], b_rd[TN][PK / 16];
+  {
+    const int row = wm * T::WTM + (lane & 31);
+#pragma unroll
+    for (int ks = 0; ks < PK / 16; ++ks) a_rd[ks] = row * (PK * 2) + (((ks * 2 + half) ^ pw_swz(row)) << 4);
+  }
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      sC[row * LDC + j * 32 + (lane & 31)] = acc[j][v];
+    for (int ks = 0; ks < PK / 16; ++ks) {
+      if constexpr (MODE == PW_DGRAD) {
+        const int row = wn * T::WTN + j * 32 + (lane & 31);
+        b_rd[j][ks] = row * (PK * 2) + (((ks * 2 + half) ^ pw_swz(row)) << 4);
+      } else {
+        const int r = ks * 16 + 8 * (lg >> 1) + (li >> 2);
+        const int blk = (wn * TN + j) ^ (BN == 128 ? r & 3 : (r >> 1) & 1);
+        b_rd[j][ks] = r * ROWB + blk * 64 + 32 * (lg & 1) + 8 * (li & 3);
+      }
     }
-  __syncthreads();
-  // every vector of this thread has the same channels (the thread count is a multiple of the vectors per row)
-  const int cg = (tid % (BN / 8)) * 8, n = n0 + cg;
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  constexpr int LD = AV + BV;
+#pragma unroll
+  for (int s = 0; s < NBUF - 1; ++s)
+    if (s < niter) fetch(s, s);
+  auto stage = [&](int it, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    // stage `it` has landed once at most the loads of the (up to two) stages after it are in flight; the barrier says so
+    // for every wave, and that every wave is done with the buffer that the next request writes
+    if (NBUF > 3 && it + 2 < niter) pw_wait_barrier<(NBUF > 3 ? 2 : 0) * LD>();
+    else if (NBUF > 2 && it + 1 < niter) pw_wait_barrier<(NBUF > 2 ? 1 : 0) * LD>();
+    else pw_wait_barrier<0>();
+    if (it + NBUF - 1 < niter) fetch(it + NBUF - 1, (buf + NBUF - 1) % NBUF);
+    const unsigned char* a = pw_smem + buf * T::STAGE;
+    const unsigned char* b = a + T::A_BYTES;
+    constexpr int NKS = PK / 16;
+    bf16x8 af[2][TM], bfr[2][TN];                                 // operands are read one step ahead of their products
+    auto load = [&](int ks) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (MODE == PW_DGRAD) bfr[ks & 1][j] = *reinterpret_cast<const bf16x8*>(b + b_rd[j][ks]);
+        else bfr[ks & 1][j] = pw_tr_frag(b + b_rd[j][ks], b + b_rd[j][ks] + 4 * ROWB);
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[ks & 1][i] = *reinterpret_cast<const bf16x8*>(a + a_rd[ks] + i * 64 * PK);
+    };
+    load(0);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      if (ks + 1 < NKS) load(ks + 1);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
+    }
+    constexpr int NRD = TM + (MODE == PW_DGRAD ? 1 : 2) * TN;     // LDS reads of a step
+    __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      if (ks + 1 < NKS) __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
+    }
+  };
+  for (int it = 0; it < niter; it += NBUF) {
+    stage(it, std::integral_constant<int, 0>{});
+    if (it + 1 < niter) stage(it + 1, std::integral_constant<int, 1>{});
+    if constexpr (NBUF > 2) { if (it + 2 < niter) stage(it + 2, std::integral_constant<int, 2>{}); }
+    if constexpr (NBUF > 3) { if (it + 3 < niter) stage(it + 3, std::integral_constant<int, 3>{}); }
+  }
+  __syncthreads();                                                // the ring is free for the epilogue
+
+  // ---- epilogue.  Lane l of a transposed 32 x 32 accumulator holds position l % 32, channels 8 * (v / 4) + 4 * (l / 32) + v % 4 ----
+  float* sC = reinterpret_cast<float*>(pw_smem + wave * T::EPI_WAVE);
   EpiCoef coef;
-  if (n < nv) epilogue_coef(p, UP ? n % p.nout : n, 8, coef);
-  // UP: this thread's columns lie in one tap: its row offset in the output grid and the channel within the tap
-  long long up_tap_row = 0;
-  int up_kk = 0;
-  if (UP && n < nv) {
-    int t = n / p.nout;
-    up_kk = n - t * p.nout;
-    const int tw = t % p.up[2]; t /= p.up[2];
-    const int th = t % p.up[1];
-    const int td = t / p.up[1];
-    up_tap_row = ((long long)td * p.osp[1] + th) * p.osp[2] + tw;
-  }
-  uint4 outw[EV];
+  if (n < nv) epilogue_coef(p, UP ? up_n : n, 8, coef);
 #pragma unroll
-  for (int q = 0; q < EV; ++q) {
-    const int r = (tid + q * NTHREADS) / (BN / 8);
-    outw[q] = make_uint4(0, 0, 0, 0);
-    if (m0 + r >= p.M || n >= nv) continue;
-    const float4 lo = *reinterpret_cast<const float4*>(sC + r * LDC + cg);
-    const float4 hi = *reinterpret_cast<const float4*>(sC + r * LDC + cg + 4);
-    const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    outw[q] = epilogue_pack8(p, coef, v, pre_add[q], pre_mask[q]);
-  }
+  for (int i = 0; i < TM; ++i) {
 #pragma unroll
-  for (int q = 0; q < EV; ++q) {
-    const int r = (tid + q * NTHREADS) / (BN / 8);
-    if (m0 + r < p.M && n < nv)
-      epilogue_put8(p, outw[q], 8, UP ? ((long long)s_row0[r] + up_tap_row) * p.nout + up_kk : tile_base + (unsigned)(r * p.nout + cg), true);
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        *reinterpret_cast<float4*>(sC + (lane & 31) * T::LDC + j * 32 + 8 * v + 4 * half) =
+            make_float4(acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]);
+    uint4 outw[T::QV];
+#pragma unroll
+    for (int q = 0; q < T::QV; ++q) {                             // this wave's own writes: in order, no barrier
+      const float* row = sC + (lane / T::LPR + q * T::RPI) * T::LDC + cg;
+      const float4 lo = *reinterpret_cast<const float4*>(row), hi = *reinterpret_cast<const float4*>(row + 4);
+      const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      outw[q] = epilogue_pack8(p, coef, v, pre_add[i * T::QV + q], pre_mask[i * T::QV + q]);
+    }
+#pragma unroll
+    for (int q = 0; q < T::QV; ++q) {
+      const int r = er + i * 32 + q * T::RPI;
+      if (m0 + r < p.M && n < nv) put_vec(p.out + out_off(r), outw[q]);
+    }
   }
 }
 
-template <int BN, bool UP>
+// Data gradient of a strided pointwise layer, the positions no dy row lies under: the epilogue of zero.  A pure stream
+// (addend and mask in, dx out), one 8-channel vector per thread and round, rows of the grid in memory order.
+__global__ __launch_bounds__(NTHREADS) void strided_rest_kernel(IgemmP p, long long rows, int vpr) {
+  const long long total = rows * vpr, step = (long long)gridDim.x * NTHREADS;
+  for (long long i = (long long)blockIdx.x * NTHREADS + threadIdx.x; i < total; i += step) {
+    const long long row = i / vpr;
+    unsigned t = (unsigned)row;                                   // host guarantees rows < 2^31
+    const unsigned w = t % (unsigned)p.osp[2]; t /= (unsigned)p.osp[2];
+    const unsigned h = t % (unsigned)p.osp[1]; t /= (unsigned)p.osp[1];
+    const unsigned d = t % (unsigned)p.osp[0];
+    if (w % p.stride[2] == 0 && h % p.stride[1] == 0 && d % p.stride[0] == 0) continue;
+    uint4 addq = make_uint4(0, 0, 0, 0), maskq = addq;
+    if (p.add) addq = *reinterpret_cast<const uint4*>(p.add + i * 8);
+    if (p.mask) maskq = *reinterpret_cast<const uint4*>(p.mask + i * 8);
+    EpiCoef none;
+    const float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    put_vec(p.out + i * 8, epilogue_pack8(p, none, v, addq, maskq));
+  }
+}
+
+template <typename T, int MODE, bool STRIDED>
 hipError_t launch_pw_t(IgemmP& p, hipStream_t s) {
-  typedef PwTile<BN> T;
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pw_kernel<BN, UP>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pw_kernel<T, MODE, STRIDED>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
   if (attr != hipSuccess) return attr;
-  const int npar = UP ? p.up[0] * p.up[1] * p.up[2] : 1;
-  p.ntiles_n = (npar * p.nout + BN - 1) / BN;
-  const long long mt = (p.M + PM - 1) / PM;
+  const int npar = MODE == PW_UP ? p.up[0] * p.up[1] * p.up[2] : 1;
+  p.ntiles_n = (npar * p.nout + T::BN - 1) / T::BN;
+  const long long mt = (p.M + T::BM - 1) / T::BM;
   if (mt * p.ntiles_n > 0x7fffff00LL || p.M >= 0x7fffffffLL) return hipErrorInvalidValue;
   p.ntiles = (int)(mt * p.ntiles_n);
   const int grid = 8 * ((p.ntiles + 7) / 8);
-  hipLaunchKernelGGL((pw_kernel<BN, UP>), dim3(grid), dim3(NTHREADS), T::LDS_BYTES, s, p);
+  const int ring = p.red > PK ? T::NBUF * T::STAGE : T::STAGE, epi = T::WM * T::WN * T::EPI_WAVE;
+  hipLaunchKernelGGL((pw_kernel<T, MODE, STRIDED>), dim3(grid), dim3(T::NT), ring > epi ? ring : epi, s, p);
   return hipGetLastError();
+}
+
+typedef PwTile<128, 128, 2, 2, 2> Tile0;
+typedef PwTile<64, 128, 2, 2, 2> Tile1;
+typedef PwTile<128, 64, 2, 2, 2> Tile2;
+typedef PwTile<64, 64, 2, 2, 2> Tile3;
+
+// Tile by shape (us on ResNet-50 layers, three sets of tensors in turn so that nothing stays cached; batch 128 at 56 x 56 and
+// 28 x 28, 256 below; before: 128-position tiles staged through registers, data gradients of narrowing layers on the general
+// kernel with 64 x 128 tiles):
+//                                           before   128x128  64x128  128x64  64x64
+//   forward 64 -> 256, 56 x 56, residual      95       88       97      99     101     long stores: wide tiles
+//   forward 1024 -> 256, 14 x 14              61       53       63      64      68     long reductions: fewest re-reads
+//   forward 2048 -> 512, 7 x 7                50       34       48      48      49     (392 tiles of 128 x 128)
+//   data gradient 64 <- 256, 56 x 56          89       93       85      73      72     64 channels: no wider than they are
+//   data gradient 256 <- 64, 56 x 56         134      147      130     135     138     mask and addend in, short reduction:
+//   data gradient 1024 <- 256, 14 x 14       105       96       89      91      93     more work-groups in flight
+//   forward 400 -> 176, 16 x 21 x 24          14.4     12.4     11.0    11.8     9.8   few tiles: smaller ones fill the chip
+// Products with a ReLU mask and at most 512 reduction channels take 64 x 128, others 128 x 128, and both step down
+// to tiles of which there are at least 256, one per compute unit.
+template <int MODE, bool STRIDED>
+hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
+  const long long cols = (MODE == PW_UP ? (long long)p.up[0] * p.up[1] * p.up[2] : 1) * p.nout;
+  auto tiles = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * ((cols + bn - 1) / bn); };
+  if (cols <= 64) return tiles(128, 64) >= 256 ? launch_pw_t<Tile2, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
+  if (!(p.mask && p.red <= 512) && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);
+  return tiles(64, 128) >= 256 ? launch_pw_t<Tile1, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
+}
+
+bool pw_channels(const IgemmP& p, long long columns) {
+  // 16-byte vectors of both operands, 32-bit filter offsets, tiles not mostly padding
+  return !p.small && (p.red & 7) == 0 && (p.nout & 7) == 0 && p.nout >= 32 && p.red >= 32 && columns * p.red < 0x3fffffffLL;
 }
 
 }  // namespace
 
 bool pw_eligible(const IgemmP& p) {
   static const bool off = getenv("LMS_NO_PW") != nullptr;   // tuning aid
-  if (off || p.small || p.taps != 1) return false;
-  for (int i = 0; i < 3; ++i)
-    if (p.filt[i] != 1 || p.stride[i] != 1 || p.pad[i] != 0) return false;
-  return (p.red & 7) == 0 && (p.nout & 7) == 0 && p.nout >= 32 && p.red >= 32;
+  if (off || p.taps != 1) return false;
+  bool strided = false;
+  long long rows = 4LL * 256;                               // rows of the wider grid that a tile may span: 32-bit offsets from its first one
+  for (int i = 0; i < 3; ++i) {
+    if (p.filt[i] != 1 || p.stride[i] < 1 || p.pad[i] != 0) return false;
+    rows *= p.stride[i];
+    strided = strided || p.stride[i] != 1;
+  }
+  const int* big = p.mode == 0 ? p.asp : p.osp;
+  rows += 2LL * p.stride[1] * big[2] + 2LL * p.stride[0] * big[1] * (long long)big[2];
+  return pw_channels(p, p.nout) && (!strided || rows * (p.red > p.nout ? p.red : p.nout) < 0x3fffffffLL);
 }
 
-// Transposed convolution with window = stride (1 or 2 per axis) as pointwise products, filter read as stored.
+// Transposed convolution with window = stride (1 or 2 per axis), filter read as stored.
 bool pw_up_eligible(const IgemmP& p) {
   static const bool off = getenv("LMS_NO_PW") != nullptr;   // tuning aid
   if (off) return false;
   for (int i = 0; i < 3; ++i)
     if (p.up[i] < 1 || p.up[i] > 2 || p.osp[i] != p.asp[i] * p.up[i]) return false;
-  return (p.red & 7) == 0 && (p.nout & 7) == 0 && p.nout >= 32 && p.red >= 32;
+  return pw_channels(p, 8LL * p.nout);
 }
 
 hipError_t launch_pw(IgemmP& p, hipStream_t s) {
-  if (p.up[0] > 0) return p.up[0] * p.up[1] * p.up[2] * p.nout <= 64 ? launch_pw_t<64, true>(p, s) : launch_pw_t<128, true>(p, s);
-  return p.nout <= 64 ? launch_pw_t<64, false>(p, s) : launch_pw_t<128, false>(p, s);
+  if (p.up[0] > 0) return launch_pw_shape<PW_UP, false>(p, s);
+  const bool strided = p.stride[0] != 1 || p.stride[1] != 1 || p.stride[2] != 1;
+  if (p.mode == 0) {
+    p.M_in = p.M / ((long long)p.osp[0] * p.osp[1] * p.osp[2]) * p.asp[0] * p.asp[1] * p.asp[2];
+    if (strided) return launch_pw_shape<PW_FWD, true>(p, s);
+    return launch_pw_shape<PW_FWD, false>(p, s);
+  }
+  if (!strided) return launch_pw_shape<PW_DGRAD, false>(p, s);
+  const long long rows = p.M;                               // dx rows; the product runs over the dy rows
+  if (rows >= 0x7fffffffLL) return hipErrorInvalidValue;
+  p.M = rows / ((long long)p.osp[0] * p.osp[1] * p.osp[2]) * p.asp[0] * p.asp[1] * p.asp[2];
+  const int vpr = p.nout / 8;
+  const long long blocks = (rows * vpr + NTHREADS * 4 - 1) / (NTHREADS * 4);
+  hipLaunchKernelGGL(strided_rest_kernel, dim3((unsigned)(blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks))), dim3(NTHREADS), 0, s, p, rows, vpr);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_pw_shape<PW_DGRAD, true>(p, s);
 }
 
 }  // namespace lms

@@ -1,0 +1,101 @@
+"""Pointwise layers (1x1, any stride) at the edges of the kernel's tiles and of its choice between them: positions that
+fill no tile, output channels beyond the last column tile, reductions that end inside a stage of 64 channels, grids with
+odd extents under a stride, enough and too few tiles for the wider shapes.  Reference: the same sums in float64 on the
+GPU's own bf16 inputs.  Bound per element: 2^-8 of the value (one rounding of the result, half of it, and the rounding
+of the scaled filter where there is a scale) plus 2^-8 of the root mean square for sums that cancel."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# n, extents, c, k, stride
+CASES = [
+    (1, (5, 7), 32, 32, 1),            # one partial tile, half a stage
+    (2, (9, 13), 40, 72, 1),           # ragged in positions, channels and reduction
+    (1, (64, 65), 64, 64, 1),          # exactly one stage, 64 columns
+    (3, (75, 150), 72, 64, 1),         # 264 tiles of 128 x 64, one position over
+    (2, (91, 90), 96, 136, 1),         # 128 x 128 and 64 x 128 tiles, 8 columns over
+    (1, (128, 129), 200, 256, 1),      # 128 x 128 tiles (forward), partial last stage
+    (1, (33, 31), 520, 104, 1),        # long reduction, few tiles: 64 x 64
+    (4, (15, 17), 64, 128, 2),         # odd extents under a stride
+    (1, (64, 130), 128, 96, 2),
+    (1, (7, 6, 9), 48, 40, 2),         # 3-D, strided
+    (1, (10, 11), 32, 64, 3),
+    (2, (5, 6, 7), 64, 200, 1),
+]
+
+
+def close(got, ref):
+    got, ref = got.double(), ref
+    rms = float(ref.square().mean().sqrt())
+    err = (got - ref).abs()
+    lim = 2.0 ** -8 * (ref.abs() + rms)
+    assert bool((err <= lim).all()), float((err / lim).max())
+
+
+@pytest.mark.parametrize("terms", ["all", "none", "mask"])
+@pytest.mark.parametrize("n,sp,c,k,stride", CASES)
+def test_forward_and_data_gradient(n, sp, c, k, stride, terms):
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c * 1000 + k)
+
+    def rnd(shape, std=1.0):
+        return (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+
+    osp = tuple((e - 1) // stride + 1 for e in sp)
+    x, w, dy = rnd((n,) + sp + (c,)), rnd((c, k), c ** -0.5), rnd((n,) + osp + (k,))
+    scale, shift = (1 + 0.1 * torch.randn(k, generator=g, device="cuda"), torch.randn(k, generator=g, device="cuda")) if terms == "all" else (None, None)
+    res, addend = (rnd(dy.shape), rnd(x.shape)) if terms == "all" else (None, None)
+    mask = rnd(x.shape) if terms != "none" else None
+    d = L.conv_desc(n, sp, c, k, (1,) * len(sp), stride, 0, A.F_RELU if terms == "all" else 0)
+    ws = torch.empty(max(L.conv_workspace_bytes(d, A.CONV_FWD), L.conv_workspace_bytes(d, A.CONV_DGRAD), 256), dtype=torch.uint8, device="cuda")
+    y, dx = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    s = torch.cuda.current_stream().cuda_stream
+    p = lambda t: None if t is None else t.data_ptr()
+    L.conv_fwd(d, p(x), p(w), p(scale), p(shift), p(res), p(y), p(ws), s)
+    L.conv_dgrad(d, p(dy), p(w), p(scale), p(addend), p(mask), p(dx), p(ws), s)
+    torch.cuda.synchronize()
+    grid = (slice(None),) + (slice(None, None, stride),) * len(sp)
+    ref = (x[grid].double().reshape(-1, c) @ w.double()).reshape(dy.shape)
+    if scale is not None:
+        ref = torch.relu(ref * scale.double() + shift.double() + res.double())
+    close(y, ref)
+    ws64 = w.double() if scale is None else (w.float() * scale).to(torch.bfloat16).double()
+    ref = torch.zeros(x.shape, dtype=torch.float64, device="cuda")
+    ref[grid] = (dy.double().reshape(-1, k) @ ws64.t()).reshape(ref[grid].shape)
+    if addend is not None:
+        ref = ref + addend.double()
+    if mask is not None:
+        ref = ref * (mask > 0)
+    close(dx, ref)
+
+
+@pytest.mark.parametrize("c,k", [(40, 72), (104, 136)])
+def test_positions_do_not_leak_into_each_other(c, k):
+    """A reduction that ends inside a stage reads past the end of its row: what lies there must not count, NaN included."""
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    x = torch.ones((1, 8, 20, c), dtype=torch.bfloat16, device="cuda")
+    x[0, 3, 5] = float("nan")
+    x[0, 6, 1] = float("inf")
+    dy = torch.ones((1, 8, 20, k), dtype=torch.bfloat16, device="cuda")
+    dy[0, 2, 2] = float("nan")
+    w = torch.ones((c, k), dtype=torch.bfloat16, device="cuda")
+    d = L.conv_desc(1, (8, 20), c, k, (1, 1), 1, 0, 0)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    y, dx = torch.empty_like(dy), torch.empty_like(x)
+    s = torch.cuda.current_stream().cuda_stream
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), s)
+    L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), None, None, None, dx.data_ptr(), ws.data_ptr(), s)
+    torch.cuda.synchronize()
+    want = torch.full_like(y, float(c))
+    want[0, 3, 5] = float("nan")
+    want[0, 6, 1] = float("inf")
+    assert np.array_equal(y.float().cpu().numpy(), want.float().cpu().numpy(), equal_nan=True)
+    want = torch.full_like(dx, float(k))
+    want[0, 2, 2] = float("nan")
+    assert np.array_equal(dx.float().cpu().numpy(), want.float().cpu().numpy(), equal_nan=True)
