@@ -16,7 +16,7 @@ struct IgemmP {
   const uint16_t* mask;
   int relu;
   long long M;
-  long long M_in;  // pointwise kernel, forward with a stride: input rows
+  long long M_in, M_out;  // pointwise kernel: input rows (forward with a stride), output rows (where not M)
   int nout, red;
   int asp[3], osp[3], filt[3], stride[3], pad[3];
   int mode;     // 0: src = o*stride + tap - pad (forward); 1: src = (o + pad - tap)/stride (transposed)
@@ -140,6 +140,10 @@ __device__ __forceinline__ void epilogue_put8(const IgemmP& p, const uint4& w, i
 // Patch-tiled kernel for 3x3 / 3x3x3 stride-1 filters (conv_halo.hip).
 bool halo_eligible(const IgemmP& p);
 hipError_t launch_halo(IgemmP& p, hipStream_t s);
+
+// 2-D 3x3 stride-1 convolutions with padding 1, tiles of consecutive positions (conv_flat.hip).
+bool flat_eligible(const IgemmP& p);
+hipError_t launch_flat(IgemmP& p, hipStream_t s);
 
 // Resident-filter kernel for 2-D 3x3 64->64 and 3-D 3x3x3 32->32 channels, stride 1 (conv_rf.hip).
 bool rf_eligible(const IgemmP& p);

@@ -752,6 +752,7 @@ hipError_t launch_igemm_g(IgemmP& p, hipStream_t s) {
 hipError_t launch_igemm(IgemmP& p, hipStream_t s) {
   static const bool no_halo = getenv("LMS_NO_HALO") != nullptr;   // tuning aid: force the per-tap gather kernel
   if (!no_halo && p.mode == 1 && rf_eligible(p)) return launch_rf(p, s);   // the forward pass takes this path before packing
+  if (!no_halo && flat_eligible(p)) return launch_flat(p, s);
   if (!no_halo && halo_eligible(p)) return launch_halo(p, s);
   if (p.small) return launch_igemm_g<GM_SMALL>(p, s);
   if (p.mode == 0) return launch_igemm_g<GM_FWD>(p, s);

@@ -25,6 +25,7 @@
 
 #include "kernels.hpp"
 #include "conv_common.hpp"
+#include "conv_dma.hpp"
 
 namespace lms {
 
@@ -35,7 +36,6 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 
 constexpr int PK = 64;        // reduction channels per stage
 constexpr int SL = PK / 8;    // 16-byte slots of a row of PK channels
-constexpr unsigned PW_OOB = 0x80000000u;
 __device__ __forceinline__ int pw_swz(int row) { return (row >> 1) & 7; }
 
 enum { PW_FWD = 0, PW_DGRAD = 1, PW_UP = 2 };
@@ -49,38 +49,13 @@ struct PwTile {
   static constexpr int A_BYTES = BM * PK * 2, B_BYTES = BN * PK * 2;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int AV = A_BYTES / (16 * NT), BV = B_BYTES / (16 * NT);   // loads per thread and stage
-  static constexpr int LDC = WTN + 4;                             // fp32 pitch of the epilogue's 32-position tile
-  static constexpr int EPI_WAVE = 32 * LDC * 4;
+  static constexpr int EPI_WAVE = epi_wave_bytes(WTN);
   static constexpr int LDS_BYTES = NBUF * STAGE > WM * WN * EPI_WAVE ? NBUF * STAGE : WM * WN * EPI_WAVE;
   static constexpr int LPR = WTN / 8;                             // lanes per output row in the epilogue
   static constexpr int RPI = 64 / LPR;                            // rows per instruction
   static constexpr int QV = 32 / RPI;                             // vectors per lane and 32 positions
   static constexpr int OCC = 163840 / LDS_BYTES * (NT / 256) < 4 ? 163840 / LDS_BYTES * (NT / 256) : 4;   // waves per SIMD
 };
-
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-// Results are stored around the L2s (see launch_pw_shape).
-__device__ __forceinline__ void put_vec(uint16_t* q, const uint4& d) {
-  __builtin_nontemporal_store(__builtin_bit_cast(v4u, d), reinterpret_cast<v4u*>(q));
-}
-// 16 bytes per lane from buffer offset voff + soff to LDS bytes lds + 16 * lane (lds: the same for the whole wave; offsets
-// outside the buffer write zeros).  Written in assembly because the compiler, seeing such a load, waits for all of
-// them before any LDS transpose read; it has no register output, and pw_wait_barrier does the waiting.
-__device__ __forceinline__ void pw_load_lds(v4u rsrc, unsigned lds, unsigned voff, unsigned soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-}
-__device__ __forceinline__ v4u pw_rsrc(const void* base, long long bytes) {
-  const uint64_t a = (uint64_t)(uintptr_t)base;
-  return v4u{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, (unsigned)(bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000u};
-}
-
-// At most N of this wave's memory loads may still be in flight, and its LDS reads have come back; then every wave of the
-// work-group has got here.
-template <int N>
-__device__ __forceinline__ void pw_wait_barrier() {
-  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
 
 __device__ __forceinline__ bf16x8 pw_tr_frag(const unsigned char* p0, const unsigned char* p1) {
   const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p0);
@@ -144,29 +119,27 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
     const int th = t % p.up[1];
     up_tap = ((long long)(t / p.up[1]) * p.osp[1] + th) * p.osp[2] + tw;
   }
-  const long long out0 = (o_base + up_tap) * p.nout + up_n;
-  auto out_off = [&](int r) -> long long {
-    if constexpr (UP || (STRIDED && MODE == PW_DGRAD)) return out0 + (long long)s_row[r] * p.nout;
-    else return out0 + (unsigned)(r * p.nout);
+  const long long o_rows = UP || (STRIDED && MODE == PW_DGRAD) ? p.M_out - o_base : p.M - m0;
+  const EpiBuffers eb(p, o_base, o_rows * p.nout * 2);
+  const unsigned col = n < nv ? (unsigned)((up_tap * p.nout + up_n) * 2) : DMA_OOB;
+  auto out_off = [&](int r) -> unsigned {
+    if constexpr (UP || (STRIDED && MODE == PW_DGRAD)) return m0 + r < p.M ? col + s_row[r] * (unsigned)(p.nout * 2) : DMA_OOB;
+    else return col + (unsigned)(r * p.nout * 2);                 // rows beyond the last lie beyond the buffer
   };
   constexpr int EV = TM * T::QV;
   uint4 pre_add[EV], pre_mask[EV];
 #pragma unroll
   for (int q = 0; q < EV; ++q) {
-    pre_add[q] = make_uint4(0, 0, 0, 0);
-    pre_mask[q] = make_uint4(0, 0, 0, 0);
-    const int r = er + (q / T::QV) * 32 + (q % T::QV) * T::RPI;
-    if (m0 + r < p.M && n < nv) {
-      if (p.add) pre_add[q] = *reinterpret_cast<const uint4*>(p.add + out_off(r));
-      if (p.mask) pre_mask[q] = *reinterpret_cast<const uint4*>(p.mask + out_off(r));
-    }
+    const unsigned o = out_off(er + (q / T::QV) * 32 + (q % T::QV) * T::RPI);
+    pre_add[q] = EpiBuffers::get(eb.add, o);
+    pre_mask[q] = EpiBuffers::get(eb.mask, o);
   }
 
   // ---- loads: vector v of a stage's tile goes to LDS bytes [16 v, 16 v + 16); which channels it holds is permuted within
   // a row so that the reads below fall into different banks ----
   const long long a_row0 = STRIDED && MODE == PW_FWD ? pw_strided_row(m0, p.osp, p.asp, p.stride) : m0;
   const long long a_rows = STRIDED && MODE == PW_FWD ? p.M_in - a_row0 : p.M - m0;
-  const v4u rs_a = pw_rsrc(p.A + a_row0 * p.red, a_rows * p.red * 2), rs_b = pw_rsrc(p.B, (long long)nv * p.red * 2);
+  const v4u rs_a = buffer_rsrc(p.A + a_row0 * p.red, a_rows * p.red * 2), rs_b = buffer_rsrc(p.B, (long long)nv * p.red * 2);
   const unsigned lds0 = (unsigned)(uintptr_t)pw_smem;             // LDS address: the low half of the generic one
   unsigned a_off[AV], b_off[BV];
   int a_k[AV], b_k[BV];                                           // reduction channel of the vector within the stage
@@ -176,7 +149,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
     a_k[j] = ((v % SL) ^ pw_swz(row)) * 8;
     long long src = row;
     if constexpr (STRIDED && MODE == PW_FWD) src = pw_strided_row(m0 + row < p.M ? m0 + row : m0, p.osp, p.asp, p.stride) - a_row0;
-    a_off[j] = m0 + row < p.M ? (unsigned)((src * p.red + a_k[j]) * 2) : PW_OOB;
+    a_off[j] = m0 + row < p.M ? (unsigned)((src * p.red + a_k[j]) * 2) : DMA_OOB;
   }
 #pragma unroll
   for (int j = 0; j < BV; ++j) {
@@ -184,14 +157,14 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
     if constexpr (MODE == PW_DGRAD) {                             // rows n of 32 reduction channels
       const int row = v / SL;
       b_k[j] = ((v % SL) ^ pw_swz(row)) * 8;
-      b_off[j] = n0 + row < nv ? (unsigned)(((n0 + row) * p.red + b_k[j]) * 2) : PW_OOB;
+      b_off[j] = n0 + row < nv ? (unsigned)(((n0 + row) * p.red + b_k[j]) * 2) : DMA_OOB;
     } else {                                                      // rows r of BN columns
       const int r = v / (BN / 8), slot = v % (BN / 8);
       const int blk = (slot >> 2) ^ (BN == 128 ? r & 3 : (r >> 1) & 1);
       const int col = n0 + blk * 32 + (slot & 3) * 8;
       b_k[j] = r;
       const int t = UP ? col / p.nout : 0;
-      b_off[j] = col < nv ? (unsigned)(((t * p.red + r) * p.nout + col - t * p.nout) * 2) : PW_OOB;
+      b_off[j] = col < nv ? (unsigned)(((t * p.red + r) * p.nout + col - t * p.nout) * 2) : DMA_OOB;
     }
   }
   const unsigned a_step = PK * 2, b_step = MODE == PW_DGRAD ? PK * 2 : (unsigned)(PK * p.nout * 2);
@@ -201,10 +174,10 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
     const bool whole = (it + 1) * PK <= p.red;                    // the last stage may be partial: zeros, whatever lies behind
 #pragma unroll
     for (int j = 0; j < AV; ++j)
-      pw_load_lds(rs_a, a + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : PW_OOB, it * a_step);
+      load_lds16(rs_a, a + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : DMA_OOB, it * a_step);
 #pragma unroll
     for (int j = 0; j < BV; ++j)
-      pw_load_lds(rs_b, a + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : PW_OOB, it * b_step);
+      load_lds16(rs_b, a + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : DMA_OOB, it * b_step);
   };
 
   // ---- LDS read addresses ----
@@ -244,9 +217,9 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
     constexpr int buf = decltype(buf_c)::value;
     // stage `it` has landed once at most the loads of the (up to two) stages after it are in flight; the barrier says so
     // for every wave, and that every wave is done with the buffer that the next request writes
-    if (NBUF > 3 && it + 2 < niter) pw_wait_barrier<(NBUF > 3 ? 2 : 0) * LD>();
-    else if (NBUF > 2 && it + 1 < niter) pw_wait_barrier<(NBUF > 2 ? 1 : 0) * LD>();
-    else pw_wait_barrier<0>();
+    if (NBUF > 3 && it + 2 < niter) wait_barrier<(NBUF > 3 ? 2 : 0) * LD>();
+    else if (NBUF > 2 && it + 1 < niter) wait_barrier<(NBUF > 2 ? 1 : 0) * LD>();
+    else wait_barrier<0>();
     if (it + NBUF - 1 < niter) fetch(it + NBUF - 1, (buf + NBUF - 1) % NBUF);
     const unsigned char* a = pw_smem + buf * T::STAGE;
     const unsigned char* b = a + T::A_BYTES;
@@ -286,32 +259,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   }
   __syncthreads();                                                // the ring is free for the epilogue
 
-  // ---- epilogue.  Lane l of a transposed 32 x 32 accumulator holds position l % 32, channels 8 * (v / 4) + 4 * (l / 32) + v % 4 ----
-  float* sC = reinterpret_cast<float*>(pw_smem + wave * T::EPI_WAVE);
-  EpiCoef coef;
-  if (n < nv) epilogue_coef(p, UP ? up_n : n, 8, coef);
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        *reinterpret_cast<float4*>(sC + (lane & 31) * T::LDC + j * 32 + 8 * v + 4 * half) =
-            make_float4(acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]);
-    uint4 outw[T::QV];
-#pragma unroll
-    for (int q = 0; q < T::QV; ++q) {                             // this wave's own writes: in order, no barrier
-      const float* row = sC + (lane / T::LPR + q * T::RPI) * T::LDC + cg;
-      const float4 lo = *reinterpret_cast<const float4*>(row), hi = *reinterpret_cast<const float4*>(row + 4);
-      const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-      outw[q] = epilogue_pack8(p, coef, v, pre_add[i * T::QV + q], pre_mask[i * T::QV + q]);
-    }
-#pragma unroll
-    for (int q = 0; q < T::QV; ++q) {
-      const int r = er + i * 32 + q * T::RPI;
-      if (m0 + r < p.M && n < nv) put_vec(p.out + out_off(r), outw[q]);
-    }
-  }
+  wave_epilogue<T::WTN, TM, TN>(p, eb, acc, pw_smem + wave * T::EPI_WAVE, pre_add, pre_mask, UP ? up_n : n, n < nv, er, out_off);
 }
 
 // Data gradient of a strided pointwise layer, the positions no dy row lies under: the epilogue of zero.  A pure stream
@@ -330,7 +278,7 @@ __global__ __launch_bounds__(NTHREADS) void strided_rest_kernel(IgemmP p, long l
     if (p.mask) maskq = *reinterpret_cast<const uint4*>(p.mask + i * 8);
     EpiCoef none;
     const float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    put_vec(p.out + i * 8, epilogue_pack8(p, none, v, addq, maskq));
+    __builtin_nontemporal_store(__builtin_bit_cast(v4u, epilogue_pack8(p, none, v, addq, maskq)), reinterpret_cast<v4u*>(p.out + i * 8));
   }
 }
 
@@ -405,11 +353,16 @@ bool pw_up_eligible(const IgemmP& p) {
   if (off) return false;
   for (int i = 0; i < 3; ++i)
     if (p.up[i] < 1 || p.up[i] > 2 || p.osp[i] != p.asp[i] * p.up[i]) return false;
-  return pw_channels(p, 8LL * p.nout);
+  // output rows that a tile may span: 32-bit offsets from its first one
+  const long long rows = 4LL * 256 * 8 + 4LL * p.osp[2] + 4LL * p.osp[1] * p.osp[2];
+  return pw_channels(p, 8LL * p.nout) && rows * p.nout < 0x3fffffffLL;
 }
 
 hipError_t launch_pw(IgemmP& p, hipStream_t s) {
-  if (p.up[0] > 0) return launch_pw_shape<PW_UP, false>(p, s);
+  if (p.up[0] > 0) {
+    p.M_out = p.M * p.up[0] * p.up[1] * p.up[2];
+    return launch_pw_shape<PW_UP, false>(p, s);
+  }
   const bool strided = p.stride[0] != 1 || p.stride[1] != 1 || p.stride[2] != 1;
   if (p.mode == 0) {
     p.M_in = p.M / ((long long)p.osp[0] * p.osp[1] * p.osp[2]) * p.asp[0] * p.asp[1] * p.asp[2];
@@ -417,7 +370,7 @@ hipError_t launch_pw(IgemmP& p, hipStream_t s) {
     return launch_pw_shape<PW_FWD, false>(p, s);
   }
   if (!strided) return launch_pw_shape<PW_DGRAD, false>(p, s);
-  const long long rows = p.M;                               // dx rows; the product runs over the dy rows
+  const long long rows = p.M_out = p.M;                     // dx rows; the product runs over the dy rows
   if (rows >= 0x7fffffffLL) return hipErrorInvalidValue;
   p.M = rows / ((long long)p.osp[0] * p.osp[1] * p.osp[2]) * p.asp[0] * p.asp[1] * p.asp[2];
   const int vpr = p.nout / 8;
