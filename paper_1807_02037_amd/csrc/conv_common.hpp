@@ -60,6 +60,15 @@ constexpr int NTHREADS = 256;
 
 
 
+// Work-groups are dealt round-robin to the 8 XCDs, each with an L2 of its own: number `total` work-groups so that each XCD
+// gets a contiguous run of them (-1: none, the grid is a multiple of 8), and neighbours share what they read.
+__device__ __forceinline__ int xcd_order(int total) {
+  const int per_xcd = (total + 7) / 8;
+  const int i = ((int)blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8;
+  return (int)blockIdx.x / 8 < per_xcd && i < total ? i : -1;
+}
+inline long long xcd_grid(long long total) { return (total + 7) / 8 * 8; }
+
 // Epilogue of 8-channel vectors of output rows: v = acc*scale + shift + add; ReLU; ReLU mask; bf16.  It comes in
 // three pieces so that a kernel can load the per-channel coefficients once, do the arithmetic of all its vectors,
 // and only then issue all stores together: a wait for a load placed between two stores would also wait for the
@@ -165,7 +174,7 @@ hipError_t launch_pw(IgemmP& p, hipStream_t s);
 
 // Weight gradient of a transposed convolution with window = stride on the pointwise weight-gradient kernel
 // (wgrad_rows.hip): partial results [split][cx][taps * kk], splits = wgrad_rows_splits(rows, cx, taps * kk).
-bool wgrad_rows_tconv_eligible(int cx, int kk, const int* filt, const int* stride);
+bool wgrad_rows_tconv_eligible(int cx, int kk, const int* osp, const int* filt, const int* stride);
 hipError_t launch_wgrad_rows_tconv(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int kk, const int* asp,
                                    const int* osp, const int* stride, hipStream_t s);
 
@@ -181,7 +190,7 @@ hipError_t launch_wgrad_small(const uint16_t* X, const uint16_t* DY, float* part
                               const int* osp, const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s);
 
 // Streaming weight gradient for 1x1 filters without padding (wgrad_rows.hip): per-split partial filters [split][cx][ky].
-bool wgrad_rows_eligible(int cx, int ky, const int* filt, const int* stride, const int* pad);
+bool wgrad_rows_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride, const int* pad);
 int wgrad_rows_splits(long long rows, int cx, int ky);
 // cs_part (or null): partial column sums of dy [split][ky] on the side.
 hipError_t launch_wgrad_rows(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp,

@@ -914,7 +914,7 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
     colsum_done = cs != nullptr;
     return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
   }
-  if (!transpose && wgrad_rows_eligible(cx, ky, filt, stride, pad)) {
+  if (!transpose && wgrad_rows_eligible(cx, ky, asp, filt, stride, pad)) {
     const long long per = (long long)cx * ky;
     const int splits = wgrad_rows_splits(rows, cx, ky);
     float* cs = side ? colsum_part(ws, splits, per) : nullptr;
@@ -976,7 +976,7 @@ uint64_t conv_wgrad_ws(const ConvGeom& g, bool with_colsum) {
     const uint64_t ss = (uint64_t)wgrad_small_splits(g.out_rows(), g.out_sp);
     if (ss > splits) splits = ss;
   }
-  if (wgrad_rows_eligible(g.c, g.k, g.filt, g.stride, g.pad)) {
+  if (wgrad_rows_eligible(g.c, g.k, g.in_sp, g.filt, g.stride, g.pad)) {
     const uint64_t rs = (uint64_t)wgrad_rows_splits(g.out_rows(), g.c, g.k);
     if (rs > splits) splits = rs;
   }
@@ -995,7 +995,7 @@ uint64_t tconv_fwd_ws(const ConvGeom& g) { return (uint64_t)g.taps() * g.c * g.k
 uint64_t tconv_wgrad_ws(const ConvGeom& g) {
   WgradSplit w = wgrad_split(g.in_rows(), g.taps(), g.k, g.c);
   uint64_t splits = (uint64_t)w.splits;
-  if (wgrad_rows_tconv_eligible(g.c, g.k, g.filt, g.stride)) {
+  if (wgrad_rows_tconv_eligible(g.c, g.k, g.out_sp, g.filt, g.stride)) {
     const uint64_t rs = (uint64_t)wgrad_rows_splits(g.in_rows(), g.c, g.taps() * g.k);
     if (rs > splits) splits = rs;
   }
@@ -1213,7 +1213,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_taps_kernel(const float4* pa
 hipError_t tconv_wgrad(const ConvGeom& g, const void* x, const void* dy, float* dw, void* ws, hipStream_t s) {
   bool exact = true;                                     // the output grid is the input grid times the stride
   for (int i = 0; i < 3; ++i) exact = exact && g.out_sp[i] == g.in_sp[i] * g.stride[i];
-  if (exact && wgrad_rows_tconv_eligible(g.c, g.k, g.filt, g.stride)) {
+  if (exact && wgrad_rows_tconv_eligible(g.c, g.k, g.out_sp, g.filt, g.stride)) {
     // window = stride: a pointwise weight gradient over the positions of x against taps * k gathered channels of dy
     hipError_t e = launch_wgrad_rows_tconv((const uint16_t*)x, (const uint16_t*)dy, reinterpret_cast<float*>(ws), g.in_rows(), g.c, g.k,
                                            g.in_sp, g.out_sp, g.stride, s);

@@ -1,19 +1,27 @@
 // Weight gradient of 1x1 (1x1x1) convolutions: dw[c][k] = sum over output positions of x[pos * stride][c] * dy[pos][k].
 //
-// Both operands lie position-major with channels contiguous (with a stride, the rows of x are gathered), and the reduction runs over positions, so a
-// work-group streams blocks of 64 positions of both tensors through LDS exactly as they lie in memory and
-// reads the MFMA operands (8 consecutive positions per lane) with the gfx950 LDS transpose read.  The kernel
-// is bound by the one pass over x and dy, so a work-group keeps a wide filter tile (256 x 64, 64 x 256 or
-// 128 x 128 channels): with the tile covering all channels of the narrower tensor each operand is read once.
-// Eight waves share a tile (two per SIMD), two register sets keep the loads of two position blocks in flight
-// and LDS is double-buffered, so one barrier per block remains.  Each work-group reduces a contiguous range
-// of positions and writes one partial filter; the caller sums the partials in a fixed order.
+// Both operands lie position-major with channels contiguous (with a stride, the rows of x are gathered), and the reduction
+// runs over positions: blocks of PB positions of both tensors go from memory straight to LDS as they lie (buffer loads that
+// write LDS; rows and channels beyond the last read zeros), and the MFMA operands (8 consecutive positions per lane) are
+// read with the gfx950 LDS transpose read.  A wave owns 64 x 64 filter entries, so a product needs one 16-byte LDS read.
+// A work-group of eight waves, one per compute unit, covers TC x TK entries of the filter with G = 8 / (tiles of a wave)
+// groups of waves: each group reduces its own blocks of positions (group g the blocks g, g + G, ...) through its own
+// pair of LDS buffers, one barrier per round, and the groups' sums meet in LDS at the end.  So the partial filters that
+// have to be written and read again number one per work-group and not one per group, and narrow filters (64 x 64: eight
+// groups) keep all waves at work.  The partials of the work-groups are summed in a fixed order by the caller.
+//
+// Measured with the sums that follow, us (MI355X, ResNet-50 layers, three sets of tensors in turn; before: eight waves on one
+// tile, blocks staged through two register sets, of which the compiler waited for both, tiles of a split on all XCDs):
+//   1024 x 256 at 14 x 14, batch 256 53 -> 42; 256 x 512 stride 2 at 56 x 56, batch 128 69 -> 53; 512 x 2048 at 7 x 7, batch 256
+//   51 -> 43; 64 x 256 at 56 x 56, batch 128 52 (257 MB: bound by memory); U-Net up-convolutions 64 -> 32 at 64^3 12 -> 8.
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "conv_common.hpp"
+#include "conv_dma.hpp"
 
 namespace lms {
 
@@ -23,7 +31,6 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 
 constexpr int RT = 512;      // threads per work-group
-constexpr int PB = 64;       // positions per block
 
 struct WRowsP {
   const uint16_t* X;
@@ -32,7 +39,7 @@ struct WRowsP {
   long long rows;
   int cx, ky;
   int ctiles, ktiles, splits;
-  int rows_per_split;        // multiple of PB
+  int rows_per_split;        // multiple of the positions of a round
   int asp[3], osp[3], stride[3];   // strided variant: x is gathered at output position * stride
   // gathered-dy variant (weight gradient of a transposed convolution with window = stride): rows run over the
   // positions of x (extents asp), column j of the virtual dy is channel j % kk of tap j / kk, read at the output
@@ -45,284 +52,333 @@ struct WRowsP {
 
 enum { ROWS_PLAIN = 0, ROWS_STRIDED_X = 1, ROWS_GATHERED_DY = 2 };
 
-__device__ __forceinline__ bf16x8 tr_frag8(const uint16_t* p0, const uint16_t* p1) {
+template <int TC_, int TK_, int PB_>
+struct RowsTile {
+  static constexpr int TC = TC_, TK = TK_, PB = PB_;         // PB: positions of a block
+  static constexpr int WPG = (TC / 64) * (TK / 64);          // waves of a group
+  static constexpr int G = 8 / WPG;
+  static constexpr int GT = 64 * WPG;                        // threads of a group
+  static constexpr int X_BYTES = PB * TC * 2, Y_BYTES = PB * TK * 2;
+  static constexpr int XV = X_BYTES / (16 * GT), YV = Y_BYTES / (16 * GT);   // loads per thread and block
+  static constexpr int BUF = X_BYTES + Y_BYTES;
+  static constexpr int RING = G * 2 * BUF;
+  static constexpr int SUMS = (G - 1) * TC * TK * 4;         // the groups' sums on their way to group 0
+  static constexpr int LDS_BYTES = RING > SUMS ? RING : SUMS;
+  static_assert(WPG * G == 8 && LDS_BYTES <= 163840, "eight waves, the LDS of a compute unit");
+};
+
+__device__ __forceinline__ bf16x8 tr_frag8(const unsigned char* p0, const unsigned char* p1) {
   const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p0);
   const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p1);
   const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   return __builtin_bit_cast(bf16x8, r);
 }
 
-template <int TC, int TK>
-struct RowsTile {
-  // a wave owns SC x SK channels of the tile: 2048 filter entries, two 32 x 32 MFMA tiles
-  static constexpr int SC = TC >= 256 ? 32 : (TC == 128 ? 32 : 64);
-  static constexpr int SK = 2048 / SC;
-  static_assert((TC / SC) * (TK / SK) == 8, "eight waves");
-  // row pitch: a 64-byte shift per row spreads the four rows of a transpose read over all banks
-  static constexpr int LA = TC + 32, LB = TK + 32;
-  static constexpr int XV = PB * (TC / 8) / RT, YV = PB * (TK / 8) / RT;
-  static constexpr int BUF = PB * (LA + LB);                 // elements per LDS buffer
-  static constexpr int LDS_BYTES = 2 * BUF * 2;
-};
+// 64-byte blocks of row r of an LDS tile of T channels are permuted by this, so that the four rows of a transpose read
+// fall into different quarters of the banks.
+template <int T>
+__device__ __forceinline__ int rows_swz(int r) { return T >= 128 ? r & 3 : (r >> 1) & 1; }
 
-// Sum of the eight bf16 values of a vector into eight fp32 accumulators.
-__device__ __forceinline__ void add_bf16x8(float (&acc)[8], const uint4& q) {
-  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] += __uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
+// Position of a row in a grid, stepped by a constant number of rows without divisions.
+struct RowPos {
+  int n, d, h, w;
+};
+__device__ __forceinline__ RowPos row_pos(unsigned m, const int* sp) {
+  RowPos q;
+  q.w = m % (unsigned)sp[2]; m /= (unsigned)sp[2];
+  q.h = m % (unsigned)sp[1]; m /= (unsigned)sp[1];
+  q.d = m % (unsigned)sp[0];
+  q.n = m / (unsigned)sp[0];
+  return q;
+}
+__device__ __forceinline__ void row_step(RowPos& q, const RowPos& by, const int* sp) {
+  q.w += by.w; q.h += by.h; q.d += by.d; q.n += by.n;
+  if (q.w >= sp[2]) { q.w -= sp[2]; ++q.h; }
+  if (q.h >= sp[1]) { q.h -= sp[1]; ++q.d; }
+  if (q.d >= sp[0]) { q.d -= sp[0]; ++q.n; }
 }
 
-// CS: the work-groups of channel tile 0 of x also add up the rows of dy they stage (every row of dy passes through
-// exactly one of them per column tile): the bias / shift gradient without another pass over dy.
-template <int TC, int TK, int MODE, bool CS>
-__global__ __launch_bounds__(RT, 1) void wgrad_rows_kernel(WRowsP p) {
-  constexpr bool STRIDED = MODE == ROWS_STRIDED_X;
+// CS: the work-groups of channel tile 0 of x also add up the rows of dy (every row of dy passes through exactly one of them
+// per column tile): the bias / shift gradient as products of dy with a fragment of ones.
+template <typename T, int MODE, bool CS>
+__global__ __launch_bounds__(RT, 2) void wgrad_rows_kernel(WRowsP p) {
   static_assert(!CS || MODE != ROWS_GATHERED_DY, "column sums are kept for the plain and strided variants only");
-  typedef RowsTile<TC, TK> T;
-  constexpr int XV = T::XV, YV = T::YV, LA = T::LA, LB = T::LB;
-  constexpr int FA = T::SC / 32, FB = T::SK / 32;
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds_rows[];
+  constexpr int TC = T::TC, TK = T::TK, PB = T::PB, G = T::G, XV = T::XV, YV = T::YV;
+  constexpr int XVR = TC / 8, YVR = TK / 8;                  // vectors of a row
+  constexpr int XRS = T::GT / XVR, YRS = T::GT / YVR;        // rows between a thread's vectors
+  static_assert(XRS % 4 == 0 && YRS % 4 == 0, "a thread's rows have the same permutation");
+  extern __shared__ __attribute__((aligned(256))) unsigned char lds_rows[];
 
-  int b = blockIdx.x;
+  // the tiles of one split read the same rows: on one XCD they share them in its L2
+  int b = p.ctiles * p.ktiles > 1 ? xcd_order(p.ctiles * p.ktiles * p.splits) : (int)blockIdx.x;
+  if (b < 0 || b >= p.ctiles * p.ktiles * p.splits) return;
   const int ct = b % p.ctiles; b /= p.ctiles;
   const int kt = b % p.ktiles; b /= p.ktiles;
   const int split = b;
   const int c0 = ct * TC, k0 = kt * TK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wc = (wave % (TC / T::SC)) * T::SC, wk = (wave / (TC / T::SC)) * T::SK;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = wave / T::WPG, wq = wave % T::WPG, gt = tid - g * T::GT;
+  const int wc = (wq % (TC / 64)) * 64, wk = (wq / (TC / 64)) * 64;
   const int li = lane & 15, lg = lane >> 4;
-  const int half = lg >> 1;
-  const int src_a = (8 * half + (li >> 2)) * LA + wc + 16 * (lg & 1) + 4 * (li & 3);
-  const int src_b = (8 * half + (li >> 2)) * LB + wk + 16 * (lg & 1) + 4 * (li & 3);
 
   const long long lo = (long long)split * p.rows_per_split;
   const long long hi = lo + p.rows_per_split < p.rows ? lo + p.rows_per_split : p.rows;
-  const int nblk = hi > lo ? (int)((hi - lo + PB - 1) / PB) : 0;
+  const int rounds = hi > lo ? (int)((hi - lo + G * PB - 1) / (G * PB)) : 0;
 
-  // this thread's vectors of a block: row and channel of each
-  int xr[XV], xoff[XV], yr[YV], yoff[YV];
-  bool xok[XV], yok[YV];
-#pragma unroll
-  for (int j = 0; j < XV; ++j) {
-    const int v = tid + j * RT;
-    xr[j] = v / (TC / 8);
-    const int ch = (v % (TC / 8)) * 8;
-    xok[j] = c0 + ch < p.cx;
-    xoff[j] = xr[j] * p.cx + c0 + ch;
+  // ---- this thread's vectors of a block: LDS vector v of the tile (16 bytes) holds row v / XVR, permuted 64-byte block ----
+  const int xr = gt / XVR, yr = gt % T::GT / YVR;
+  auto column = [](int slot, int swz) { return ((slot >> 2) ^ swz) * 32 + (slot & 3) * 8; };
+  const int xc = column(gt % XVR, rows_swz<TC>(xr)), yc = column(gt % YVR, rows_swz<TK>(yr));
+  const bool x_ok = c0 + xc < p.cx, y_ok = k0 + yc < p.ky;
+  unsigned x_off = x_ok ? (unsigned)((xr * p.cx + c0 + xc) * 2) : DMA_OOB;
+  unsigned y_off = y_ok ? (unsigned)((yr * p.ky + k0 + yc) * 2) : DMA_OOB;
+  // strided / gathered variants: where the thread's rows are, and the first row of the block (uniform), which 32-bit
+  // offsets count from
+  constexpr int XP = MODE == ROWS_STRIDED_X ? XV : 1, YP = MODE == ROWS_GATHERED_DY ? YV : 1;
+  RowPos xpos[XP], ypos[YP], step{}, first{};
+  const int* small = MODE == ROWS_GATHERED_DY ? p.asp : p.osp;
+  const int* big = MODE == ROWS_GATHERED_DY ? p.osp : p.asp;
+  auto big_row = [&](const RowPos& q) {
+    return (((long long)q.n * big[0] + q.d * p.stride[0]) * big[1] + q.h * p.stride[1]) * (long long)big[2] + q.w * p.stride[2];
+  };
+  unsigned y_tap = 0;
+  if constexpr (MODE != ROWS_PLAIN) {
+    step = row_pos(G * PB, small);
+    first = row_pos((unsigned)(lo + g * PB), small);
   }
+  if constexpr (MODE == ROWS_STRIDED_X) {
 #pragma unroll
-  for (int j = 0; j < YV; ++j) {
-    const int v = tid + j * RT;
-    yr[j] = v / (TK / 8);
-    const int ch = (v % (TK / 8)) * 8;
-    yok[j] = k0 + ch < p.ky;
-    yoff[j] = yr[j] * p.ky + k0 + ch;
-    if (MODE == ROWS_GATHERED_DY) {
-      // the column lies in one tap (kk is a multiple of 8): offset of the tap within the output grid, in elements
-      const int col = k0 + ch;
-      int t = yok[j] ? col / p.kk : 0;
-      const int cc = yok[j] ? col - t * p.kk : 0;
-      const int tw = t % p.stride[2]; t /= p.stride[2];
-      const int th = t % p.stride[1];
-      const int td = t / p.stride[1];
-      yoff[j] = ((td * p.osp[1] + th) * p.osp[2] + tw) * p.kk + cc;
+    for (int j = 0; j < XV; ++j) xpos[j] = row_pos((unsigned)(lo + g * PB + xr + j * XRS), small);
+  }
+  if constexpr (MODE == ROWS_GATHERED_DY) {
+#pragma unroll
+    for (int j = 0; j < YV; ++j) ypos[j] = row_pos((unsigned)(lo + g * PB + yr + j * YRS), small);
+    // the column lies in one tap (kk is a multiple of 8): offset of the tap within the output grid
+    int t = y_ok ? (k0 + yc) / p.kk : 0;
+    const int cc = y_ok ? k0 + yc - t * p.kk : 0;
+    const int tw = t % p.stride[2]; t /= p.stride[2];
+    const int th = t % p.stride[1];
+    y_tap = (unsigned)(((((t / p.stride[1]) * p.osp[1] + th) * p.osp[2] + tw) * p.kk + cc) * 2);
+  }
+
+  const unsigned lds0 = (unsigned)(uintptr_t)lds_rows + g * 2 * T::BUF;          // this group's pair of buffers
+  const unsigned lds_w = __builtin_amdgcn_readfirstlane(lds0 + wq * 1024);
+  // block `r * G + g` of the split into buffer `buf`; rows from hi on lie beyond the buffers
+  auto fetch = [&](int r, int buf) {
+    const long long r0 = lo + (long long)(r * G + g) * PB;
+    const long long left = r0 < hi ? hi - r0 : 0;
+    const unsigned dst = lds_w + buf * T::BUF;
+    long long big0 = 0;
+    if constexpr (MODE != ROWS_PLAIN) {
+      big0 = big_row(first);
+      row_step(first, step, small);
+    }
+    if constexpr (MODE == ROWS_STRIDED_X) {
+      const v4u rs = buffer_rsrc(p.X + big0 * p.cx, 0x7fffffff);
+#pragma unroll
+      for (int j = 0; j < XV; ++j) {
+        const unsigned o = (unsigned)((big_row(xpos[j]) - big0) * p.cx * 2) + (unsigned)((c0 + xc) * 2);
+        load_lds16(rs, dst + j * T::GT * 16, x_ok && xr + j * XRS < left ? o : DMA_OOB, 0);
+        row_step(xpos[j], step, small);
+      }
+    } else {
+      const v4u rs = buffer_rsrc(p.X + r0 * p.cx, left * p.cx * 2);
+#pragma unroll
+      for (int j = 0; j < XV; ++j) load_lds16(rs, dst + j * T::GT * 16, x_off + (unsigned)(j * XRS * p.cx * 2), 0);
+    }
+    if constexpr (MODE == ROWS_GATHERED_DY) {
+      const v4u rs = buffer_rsrc(p.DY + big0 * p.kk, 0x7fffffff);
+#pragma unroll
+      for (int j = 0; j < YV; ++j) {
+        const unsigned o = (unsigned)((big_row(ypos[j]) - big0) * p.kk * 2) + y_tap;
+        load_lds16(rs, dst + T::X_BYTES + j * T::GT * 16, y_ok && yr + j * YRS < left ? o : DMA_OOB, 0);
+        row_step(ypos[j], step, small);
+      }
+    } else {
+      const v4u rs = buffer_rsrc(p.DY + r0 * p.ky, left * p.ky * 2);
+#pragma unroll
+      for (int j = 0; j < YV; ++j) load_lds16(rs, dst + T::X_BYTES + j * T::GT * 16, y_off + (unsigned)(j * YRS * p.ky * 2), 0);
+    }
+  };
+
+  // ---- LDS read addresses: lane's row of a transpose read and its 8 bytes of a 64-byte block ----
+  const int rd_row = 8 * (lg >> 1) + (li >> 2), rd_in = 32 * (lg & 1) + 8 * (li & 3);
+  int x_rd[2], y_rd[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    x_rd[i] = rd_row * TC * 2 + (((wc / 32 + i) ^ rows_swz<TC>(rd_row)) << 6) + rd_in;
+    y_rd[i] = T::X_BYTES + rd_row * TK * 2 + (((wk / 32 + i) ^ rows_swz<TK>(rd_row)) << 6) + rd_in;
+  }
+
+  f32x16 acc[2][2], cs[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { acc[i][0][v] = 0.f; acc[i][1][v] = 0.f; cs[i][v] = 0.f; }
+  const bool cs_on = CS && ct == 0 && wc == 0;                // uniform over the wave
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
+
+  auto multiply = [&](const unsigned char* t) {
+    constexpr int NKS = PB / 16;
+    bf16x8 af[2][2], bfr[2][2];
+    auto load = [&](int ks) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const unsigned char* a = t + x_rd[i] + ks * 16 * TC * 2;
+        const unsigned char* q = t + y_rd[i] + ks * 16 * TK * 2;
+        af[ks & 1][i] = tr_frag8(a, a + 4 * TC * 2);
+        bfr[ks & 1][i] = tr_frag8(q, q + 4 * TK * 2);
+      }
+    };
+    load(0);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      if (ks + 1 < NKS) load(ks + 1);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][i], bfr[ks & 1][j], acc[i][j], 0, 0, 0);
+      if (cs_on) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) cs[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr[ks & 1][j], cs[j], 0, 0, 0);
+      }
+    }
+  };
+
+  if (rounds > 0) fetch(0, 0);
+  const unsigned char* ring = lds_rows + g * 2 * T::BUF;
+  for (int r = 0; r < rounds; r += 2) {
+    wait_barrier<0>();                                        // the block of this round has landed, the other buffer is free
+    if (r + 1 < rounds) fetch(r + 1, 1);
+    multiply(ring);
+    if (r + 1 < rounds) {
+      wait_barrier<0>();
+      if (r + 2 < rounds) fetch(r + 2, 0);
+      multiply(ring + T::BUF);
     }
   }
 
-  auto fetch = [&](int blk, uint4 (&rx)[XV], uint4 (&ry)[YV]) {
-    const long long r0 = lo + (long long)blk * PB;
-    const uint16_t* xb = p.X + r0 * p.cx;
-    const uint16_t* yb = p.DY + r0 * p.ky;
+  // ---- the groups' sums: 1 .. G - 1 leave theirs in LDS, group 0 adds them in order ----
+  float* sums = reinterpret_cast<float*>(lds_rows);
+  auto slot = [&](int grp, int q) { return reinterpret_cast<float4*>(sums + (grp - 1) * (TC * TK) + (wq * 16 + q) * 256 + lane * 4); };
+  __syncthreads();
+  if (g > 0) {
 #pragma unroll
-    for (int j = 0; j < XV; ++j) {
-      rx[j] = make_uint4(0, 0, 0, 0);
-      if (xok[j] && r0 + xr[j] < hi) {
-        if (STRIDED) {
-          unsigned t = (unsigned)(r0 + xr[j]);                 // host guarantees rows < 2^31
-          const unsigned ow = t % (unsigned)p.osp[2]; t /= (unsigned)p.osp[2];
-          const unsigned oh = t % (unsigned)p.osp[1]; t /= (unsigned)p.osp[1];
-          const unsigned od = t % (unsigned)p.osp[0]; t /= (unsigned)p.osp[0];
-          const long long src = (((long long)t * p.asp[0] + od * p.stride[0]) * p.asp[1] + oh * p.stride[1]) * p.asp[2] + ow * p.stride[2];
-          rx[j] = *reinterpret_cast<const uint4*>(p.X + src * p.cx + (xoff[j] - xr[j] * p.cx));
-        } else {
-          rx[j] = *reinterpret_cast<const uint4*>(xb + xoff[j]);
-        }
-      }
+    for (int q = 0; q < 16; ++q) {
+      const f32x16& a = acc[q >> 3][(q >> 2) & 1];
+      *slot(g, q) = make_float4(a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]);
     }
-#pragma unroll
-    for (int j = 0; j < YV; ++j) {
-      ry[j] = make_uint4(0, 0, 0, 0);
-      if (yok[j] && r0 + yr[j] < hi) {
-        if (MODE == ROWS_GATHERED_DY) {
-          unsigned t = (unsigned)(r0 + yr[j]);                 // host guarantees rows < 2^31
-          const unsigned w = t % (unsigned)p.asp[2]; t /= (unsigned)p.asp[2];
-          const unsigned h = t % (unsigned)p.asp[1]; t /= (unsigned)p.asp[1];
-          const unsigned d = t % (unsigned)p.asp[0]; t /= (unsigned)p.asp[0];
-          const long long row = (((long long)t * p.osp[0] + d * p.stride[0]) * p.osp[1] + h * p.stride[1]) * p.osp[2] + w * p.stride[2];
-          ry[j] = *reinterpret_cast<const uint4*>(p.DY + row * p.kk + yoff[j]);
-        } else {
-          ry[j] = *reinterpret_cast<const uint4*>(yb + yoff[j]);
-        }
-      }
-    }
-  };
-  // every vector of this thread lies in the same 8 channels (the thread count is a multiple of the vectors per row)
-  float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const bool cs_on = CS && ct == 0;
-  auto stage = [&](uint16_t* sX, const uint4 (&rx)[XV], const uint4 (&ry)[YV]) {
-    uint16_t* sY = sX + PB * LA;
-    if (cs_on) {
-#pragma unroll
-      for (int j = 0; j < YV; ++j) add_bf16x8(csum, ry[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < XV; ++j) {
-      const int v = tid + j * RT;
-      *reinterpret_cast<uint4*>(sX + (v / (TC / 8)) * LA + (v % (TC / 8)) * 8) = rx[j];
-    }
-#pragma unroll
-    for (int j = 0; j < YV; ++j) {
-      const int v = tid + j * RT;
-      *reinterpret_cast<uint4*>(sY + (v / (TK / 8)) * LB + (v % (TK / 8)) * 8) = ry[j];
-    }
-  };
-
-  f32x16 acc[FA][FB];
-#pragma unroll
-  for (int i = 0; i < FA; ++i)
-#pragma unroll
-    for (int j = 0; j < FB; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  auto multiply = [&](const uint16_t* sX) {
-    const uint16_t* sY = sX + PB * LA;
-#pragma unroll
-    for (int ks = 0; ks < PB / 16; ++ks) {
-      bf16x8 af[FA], bfr[FB];
-#pragma unroll
-      for (int i = 0; i < FA; ++i) {
-        const uint16_t* a = sX + ks * 16 * LA + src_a + 32 * i;
-        af[i] = tr_frag8(a, a + 4 * LA);
-      }
-#pragma unroll
-      for (int j = 0; j < FB; ++j) {
-        const uint16_t* q = sY + ks * 16 * LB + src_b + 32 * j;
-        bfr[j] = tr_frag8(q, q + 4 * LB);
-      }
-#pragma unroll
-      for (int i = 0; i < FA; ++i)
-#pragma unroll
-        for (int j = 0; j < FB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-  };
-
-  uint4 rxa[XV], rya[YV], rxb[XV], ryb[YV];
-  uint16_t* buf0 = lds_rows;
-  uint16_t* buf1 = lds_rows + T::BUF;
-  if (nblk > 0) {
-    fetch(0, rxa, rya);
-    if (nblk > 1) fetch(1, rxb, ryb);
-    stage(buf0, rxa, rya);
-    if (nblk > 2) fetch(2, rxa, rya);
   }
   __syncthreads();
-  for (int blk = 0; blk < nblk; blk += 2) {
-    // buf0 holds block blk; set b holds block blk + 1, set a block blk + 2
-    if (blk + 1 < nblk) {
-      stage(buf1, rxb, ryb);
-      if (blk + 3 < nblk) fetch(blk + 3, rxb, ryb);
-    }
-    multiply(buf0);
-    __syncthreads();
-    if (blk + 1 < nblk) {
-      if (blk + 2 < nblk) {
-        stage(buf0, rxa, rya);
-        if (blk + 4 < nblk) fetch(blk + 4, rxa, rya);
-      }
-      multiply(buf1);
-      __syncthreads();
-    }
-  }
-
   float* out = p.part + (long long)split * p.cx * p.ky;
+  if (g == 0) {
+#pragma unroll 1
+    for (int grp = 1; grp < G; ++grp) {
 #pragma unroll
-  for (int i = 0; i < FA; ++i)
-#pragma unroll
-    for (int j = 0; j < FB; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int c = c0 + wc + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int k = k0 + wk + 32 * j + (lane & 31);
-        if (c < p.cx && k < p.ky) out[(long long)c * p.ky + k] = acc[i][j][v];
+      for (int q = 0; q < 16; ++q) {
+        f32x16& a = acc[q >> 3][(q >> 2) & 1];
+        const float4 t = *slot(grp, q);
+        a[4 * (q & 3)] += t.x; a[4 * (q & 3) + 1] += t.y; a[4 * (q & 3) + 2] += t.z; a[4 * (q & 3) + 3] += t.w;
       }
-  if (cs_on) {
-    // the threads tid, tid + TK / 8, ... hold the same channels: add them in a fixed order (LDS is free: the
-    // loop ended with a barrier, or never ran)
-    static_assert(RT * 9 * 4 <= T::LDS_BYTES, "the column sums fit the tile buffers");
-    float* sh = reinterpret_cast<float*>(lds_rows);
+    }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sh[tid * 9 + e] = csum[e];
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int c = c0 + wc + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+          const int k = k0 + wk + 32 * j + (lane & 31);
+          if (c < p.cx && k < p.ky) out[(long long)c * p.ky + k] = acc[i][j][v];
+        }
+  }
+  if (CS && ct == 0) {
+    __syncthreads();                                          // the sums above have been read
+    if (wc == 0 && lane < 32) {                               // every row of the product with ones is the sum: row 0
+#pragma unroll
+      for (int j = 0; j < 2; ++j) sums[g * TK + wk + 32 * j + lane] = cs[j][0];
+    }
     __syncthreads();
     if (tid < TK && k0 + tid < p.ky) {
-      constexpr int G = TK / 8;
       float t = 0.f;
-      for (int i = 0; i < RT / G; ++i) t += sh[((tid >> 3) + i * G) * 9 + (tid & 7)];
+#pragma unroll
+      for (int i = 0; i < G; ++i) t += sums[i * TK + tid];
       p.cs_part[(long long)split * p.ky + k0 + tid] = t;
     }
   }
 }
 
-struct RowsPlan { int tc, tk, ctiles, ktiles, splits, rows_per_split; };
+typedef RowsTile<128, 128, 64> Rows128;
+typedef RowsTile<256, 64, 64> Rows256x64;
+typedef RowsTile<64, 256, 64> Rows64x256;
+typedef RowsTile<64, 128, 32> Rows64x128;
+typedef RowsTile<128, 64, 32> Rows128x64;
+typedef RowsTile<64, 64, 32> Rows64;
+
+struct RowsPlan { int shape, ctiles, ktiles, splits, rows_per_split; };
 
 RowsPlan rows_plan(long long rows, int cx, int ky) {
-  // tile shape with the least traffic: x is read once per k-tile, dy once per c-tile
-  static const int shapes[3][2] = {{128, 128}, {256, 64}, {64, 256}};
+  // tile shape with the least traffic: x is read once per k-tile, dy once per c-tile; of equals the one with the fewest
+  // products (a smaller tile has more groups of waves)
+  static const int shapes[6][3] = {{64, 64, 256}, {64, 128, 128}, {128, 64, 128}, {128, 128, 128}, {256, 64, 128}, {64, 256, 128}};   // third: positions of a round
   RowsPlan best{};
   long long best_cost = -1;
-  for (const auto& sh : shapes) {
-    const int ct = (cx + sh[0] - 1) / sh[0], kt = (ky + sh[1] - 1) / sh[1];
+  for (int i = 0; i < 6; ++i) {
+    const int ct = (cx + shapes[i][0] - 1) / shapes[i][0], kt = (ky + shapes[i][1] - 1) / shapes[i][1];
     const long long cost = (long long)cx * kt + (long long)ky * ct;
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = RowsPlan{sh[0], sh[1], ct, kt, 0, 0}; }
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = RowsPlan{i, ct, kt, 0, 0}; }
   }
-  long long target = 256;                                    // one work-group of eight waves per CU
-  if (const char* e = getenv("LMS_WGRAD_ROWS_WGS")) target = atoll(e);
-  const long long tiles = (long long)best.ctiles * best.ktiles;
-  long long splits = (target + tiles - 1) / tiles;
-  const long long blocks = (rows + PB - 1) / PB;
+  const long long tiles = (long long)best.ctiles * best.ktiles, round = shapes[best.shape][2];
+  long long splits = (256 + tiles - 1) / tiles;              // one work-group of eight waves per CU
+  const long long blocks = (rows + round - 1) / round;
   if (splits > blocks) splits = blocks;
   if (splits < 1) splits = 1;
-  const long long per = ((blocks + splits - 1) / splits) * PB;
+  const long long per = ((blocks + splits - 1) / splits) * round;
   best.rows_per_split = (int)per;
   best.splits = (int)((rows + per - 1) / per);
   if (best.splits < 1) best.splits = 1;
   return best;
 }
 
-template <int TC, int TK, int MODE, bool CS>
+template <typename T, int MODE, bool CS>
 hipError_t launch_rows_t(const WRowsP& p, hipStream_t s) {
-  typedef RowsTile<TC, TK> T;
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_rows_kernel<TC, TK, MODE, CS>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_rows_kernel<T, MODE, CS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((wgrad_rows_kernel<TC, TK, MODE, CS>), dim3((unsigned)(p.ctiles * p.ktiles * p.splits)), dim3(RT), T::LDS_BYTES, s, p);
+  hipLaunchKernelGGL((wgrad_rows_kernel<T, MODE, CS>), dim3((unsigned)xcd_grid((long long)p.ctiles * p.ktiles * p.splits)), dim3(RT), T::LDS_BYTES, s, p);
   return hipGetLastError();
 }
-template <int TC, int TK>
+template <typename T>
 hipError_t launch_rows(const WRowsP& p, int mode, hipStream_t s) {
-  if (mode == ROWS_GATHERED_DY) return launch_rows_t<TC, TK, ROWS_GATHERED_DY, false>(p, s);
-  if (p.cs_part)
-    return mode == ROWS_STRIDED_X ? launch_rows_t<TC, TK, ROWS_STRIDED_X, true>(p, s) : launch_rows_t<TC, TK, ROWS_PLAIN, true>(p, s);
-  return mode == ROWS_STRIDED_X ? launch_rows_t<TC, TK, ROWS_STRIDED_X, false>(p, s) : launch_rows_t<TC, TK, ROWS_PLAIN, false>(p, s);
+  if (mode == ROWS_GATHERED_DY) return launch_rows_t<T, ROWS_GATHERED_DY, false>(p, s);
+  if (p.cs_part) return mode == ROWS_STRIDED_X ? launch_rows_t<T, ROWS_STRIDED_X, true>(p, s) : launch_rows_t<T, ROWS_PLAIN, true>(p, s);
+  return mode == ROWS_STRIDED_X ? launch_rows_t<T, ROWS_STRIDED_X, false>(p, s) : launch_rows_t<T, ROWS_PLAIN, false>(p, s);
+}
+hipError_t launch_rows_shape(const WRowsP& p, int shape, int mode, hipStream_t s) {
+  switch (shape) {
+    case 0: return launch_rows<Rows64>(p, mode, s);
+    case 1: return launch_rows<Rows64x128>(p, mode, s);
+    case 2: return launch_rows<Rows128x64>(p, mode, s);
+    case 3: return launch_rows<Rows128>(p, mode, s);
+    case 4: return launch_rows<Rows256x64>(p, mode, s);
+    default: return launch_rows<Rows64x256>(p, mode, s);
+  }
 }
 
 }  // namespace
 
-bool wgrad_rows_eligible(int cx, int ky, const int* filt, const int* stride, const int* pad) {
+// Rows of the wider grid that a block of 64 positions may span, times the channels: 32-bit offsets from its first one.
+static bool rows_span_ok(const int* big, const int* stride, long long channels) {
+  return (64LL * stride[0] * stride[1] * stride[2] + 2LL * stride[0] * big[1] * big[2] + 2LL * stride[1] * big[2]) * channels < 0x3fffffffLL;
+}
+
+bool wgrad_rows_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride, const int* pad) {
   if (getenv("LMS_NO_WGRAD_ROWS")) return false;
   for (int i = 0; i < 3; ++i)
     if (filt[i] != 1 || stride[i] < 1 || pad[i] != 0) return false;
-  return (cx & 7) == 0 && (ky & 7) == 0 && cx >= 48 && ky >= 48;
+  return (cx & 7) == 0 && (ky & 7) == 0 && cx >= 48 && ky >= 48 && rows_span_ok(asp, stride, cx);
 }
 
 int wgrad_rows_splits(long long rows, int cx, int ky) { return rows_plan(rows, cx, ky).splits; }
@@ -331,7 +387,6 @@ hipError_t launch_wgrad_rows(const uint16_t* X, const uint16_t* DY, float* part,
                              const int* osp, const int* stride, float* cs_part, hipStream_t s) {
   const RowsPlan pl = rows_plan(rows, cx, ky);
   if ((long long)pl.ctiles * pl.ktiles * pl.splits > 0x7fffff00LL || rows >= 0x7fffff00LL) return hipErrorInvalidValue;
-  if ((long long)PB * (cx > ky ? cx : ky) > 0x7fffffffLL) return hipErrorInvalidValue;     // 32-bit offsets within a block
   WRowsP p{};
   p.X = X; p.DY = DY; p.part = part; p.rows = rows; p.cx = cx; p.ky = ky; p.cs_part = cs_part;
   p.ctiles = pl.ctiles; p.ktiles = pl.ktiles; p.splits = pl.splits; p.rows_per_split = pl.rows_per_split;
@@ -340,24 +395,21 @@ hipError_t launch_wgrad_rows(const uint16_t* X, const uint16_t* DY, float* part,
     p.asp[i] = asp[i]; p.osp[i] = osp[i]; p.stride[i] = stride[i];
     strided = strided || stride[i] != 1;
   }
-  const int mode = strided ? ROWS_STRIDED_X : ROWS_PLAIN;
-  if (pl.tc == 256) return launch_rows<256, 64>(p, mode, s);
-  if (pl.tc == 64) return launch_rows<64, 256>(p, mode, s);
-  return launch_rows<128, 128>(p, mode, s);
+  return launch_rows_shape(p, pl.shape, strided ? ROWS_STRIDED_X : ROWS_PLAIN, s);
 }
 
 // Weight gradient of a transposed convolution whose window equals its stride (1 or 2 per axis): every output
 // position belongs to one tap, so dw[t][c][k] = sum over x-positions m of x[m][c] * dy[stride * m + t][k] is a
 // pointwise weight gradient whose second operand has taps * kk virtual channels.  Partial results are
 // [split][c][taps * kk]; the caller sums them into [t][c][k].
-bool wgrad_rows_tconv_eligible(int cx, int kk, const int* filt, const int* stride) {
+bool wgrad_rows_tconv_eligible(int cx, int kk, const int* osp, const int* filt, const int* stride) {
   if (getenv("LMS_NO_WGRAD_ROWS")) return false;
   long long taps = 1;
   for (int i = 0; i < 3; ++i) {
     if (filt[i] != stride[i] || stride[i] < 1 || stride[i] > 2) return false;
     taps *= filt[i];
   }
-  return (cx & 7) == 0 && (kk & 7) == 0 && cx >= 48 && taps * kk >= 48;
+  return (cx & 7) == 0 && (kk & 7) == 0 && cx >= 48 && taps * kk >= 48 && rows_span_ok(osp, stride, kk);
 }
 
 hipError_t launch_wgrad_rows_tconv(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int kk, const int* asp,
@@ -365,15 +417,11 @@ hipError_t launch_wgrad_rows_tconv(const uint16_t* X, const uint16_t* DY, float*
   const int ky = stride[0] * stride[1] * stride[2] * kk;
   const RowsPlan pl = rows_plan(rows, cx, ky);
   if ((long long)pl.ctiles * pl.ktiles * pl.splits > 0x7fffff00LL || rows >= 0x7fffff00LL) return hipErrorInvalidValue;
-  if ((long long)PB * (cx > ky ? cx : ky) > 0x7fffffffLL) return hipErrorInvalidValue;     // 32-bit offsets within a block
-  if ((long long)osp[1] * osp[2] * 2 * kk > 0x7fffffffLL) return hipErrorInvalidValue;      // 32-bit tap offsets
   WRowsP p{};
   p.X = X; p.DY = DY; p.part = part; p.rows = rows; p.cx = cx; p.ky = ky; p.kk = kk;
   p.ctiles = pl.ctiles; p.ktiles = pl.ktiles; p.splits = pl.splits; p.rows_per_split = pl.rows_per_split;
   for (int i = 0; i < 3; ++i) { p.asp[i] = asp[i]; p.osp[i] = osp[i]; p.stride[i] = stride[i]; }
-  if (pl.tc == 256) return launch_rows<256, 64>(p, ROWS_GATHERED_DY, s);
-  if (pl.tc == 64) return launch_rows<64, 256>(p, ROWS_GATHERED_DY, s);
-  return launch_rows<128, 128>(p, ROWS_GATHERED_DY, s);
+  return launch_rows_shape(p, pl.shape, ROWS_GATHERED_DY, s);
 }
 
 }  // namespace lms
