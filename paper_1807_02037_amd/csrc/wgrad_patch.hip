@@ -13,9 +13,11 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "conv_common.hpp"
+#include "conv_dma.hpp"
 
 namespace lms {
 
@@ -60,9 +62,10 @@ __device__ __forceinline__ bf16x8 tr_frag(const uint16_t* p0, const uint16_t* p1
 // Wave w owns the contiguous taps [TAPS*w/4, TAPS*(w+1)/4).  The taps kw = 0, 1, 2 of one filter row (kd, kh) read
 // the positions p .. p+9 of one halo row: where a wave has several of them, the 12 positions p .. p+11 are fetched
 // once (three transpose reads) and the fragments of the three taps are cut out in registers.
-template <int P3D, int W>
+// CS: also ones x dy, the column sums (wave 0, which has one tap less than the others).
+template <int P3D, int W, bool CS = false>
 __device__ __forceinline__ void wgrad_patch_mma(const uint16_t* sX, const uint16_t* sY, f32x16 (&acc)[WPatch<P3D>::MAXT], int src_off,
-                                                int half) {
+                                                int half, f32x16* cs = nullptr) {
   typedef WPatch<P3D> PT;
   constexpr int TAPS = P3D ? 27 : 9;
   constexpr int LO = TAPS * W / 4, HI = TAPS * (W + 1) / 4;
@@ -74,6 +77,11 @@ __device__ __forceinline__ void wgrad_patch_mma(const uint16_t* sX, const uint16
     const uint16_t* xb = sX + ((pd * PT::HH + ph) * PT::HW + pw) * LDX + src_off;
     const uint16_t* yb = sY + q0 * LDX + src_off;
     const bf16x8 bfr = tr_frag(yb, yb + 4 * LDX);
+    if constexpr (CS) {
+      const __bf16 o = (__bf16)1.f;
+      const bf16x8 ones = {o, o, o, o, o, o, o, o};
+      *cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr, *cs, 0, 0, 0);
+    }
 #pragma unroll
     for (int row = LO / 3; row <= (HI - 1) / 3; ++row) {
       const int k_lo = (LO > row * 3 ? LO : row * 3) - row * 3, k_hi = (HI < row * 3 + 3 ? HI : row * 3 + 3) - row * 3;   // kw range
@@ -293,6 +301,163 @@ __global__ __launch_bounds__(NTHREADS, 2) void wgrad_patch_kernel(WPatchP p) {
 }
 
 
+// The same tile (32 x 32 channels, all taps) for input channel counts that are multiples of 8, eight waves: two groups of
+// four that take every second patch each, into sums of their own that meet in LDS at the end.  Patches go from memory
+// straight to LDS (buffer loads that write LDS, outside the tensors zeros), one patch ahead in a pair of buffers per group.
+// What bounds the small layers is not the products but the partial filters, written by every work-group and read
+// again: with the groups' sums added first there is one per compute unit instead of two (27 x 32 x 32 filters: 28 MB each
+// way instead of 56).  Both parameter gradients, us: 64 -> 64 at 64^3 77 -> 74, 32 -> 32 38 -> 33,
+// 128 -> 128 at 32^3 52 -> 46, 256 -> 256 at 16^3 37 -> 33.
+constexpr int GP_NT = 512;
+template <int P3D>
+struct GPatch {
+  typedef WPatch<P3D> PT;
+  static constexpr int XV = (PT::MAXPIX + 4 + 63) / 64;           // input loads per thread of a group and patch
+  static constexpr int YV = 2;
+  static constexpr int X_BYTES = XV * 64 * 64, Y_BYTES = 128 * 64, BUF = X_BYTES + Y_BYTES;
+  static constexpr int TAPS = P3D ? 27 : 9;
+  static constexpr int SUMS = TAPS * 4096;
+  static constexpr int LDS_BYTES = 4 * BUF > SUMS ? 4 * BUF : SUMS;
+};
+
+template <int P3D, bool CS>
+__global__ __launch_bounds__(GP_NT, 2) void wgrad_patch_group_kernel(WPatchP p) {
+  typedef WPatch<P3D> PT;
+  typedef GPatch<P3D> GP;
+  constexpr int XV = GP::XV, YV = GP::YV;
+  extern __shared__ __attribute__((aligned(256))) unsigned char lds_gp[];
+  int b = blockIdx.x;
+  const int cc = b % p.cchunks; b /= p.cchunks;
+  const int kt = b % p.ktiles; b /= p.ktiles;
+  const int split = b;
+  const int c0 = cc * 32, k0 = kt * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = wave8 >> 2, wave = wave8 & 3, gt = tid & 255;
+  const int hd = PT::TD + p.filt[0] - 1;
+  const int halo_pix = hd * PT::HH * PT::HW;
+  const int li = lane & 15, lg = lane >> 4;
+  const int src_off = (li >> 2) * LDX + 16 * (lg & 1) + 4 * (li & 3);
+  const int half = lg >> 1;
+
+  // this thread's vectors of a patch: position relative to the patch origin (input: origin - pad), byte offset from it
+  const int vch = (gt & 3) * 8;
+  const bool xc_ok = c0 + vch < p.cx, yc_ok = k0 + vch < p.ky;
+  int xj[XV], yj[YV];                                             // coordinates, 8 bits each
+  unsigned x_off[XV], y_off[YV];
+#pragma unroll
+  for (int j = 0; j < XV; ++j) {
+    const int pix = (gt >> 2) + j * 64;
+    const int w = pix % PT::HW, h = (pix / PT::HW) % PT::HH, d = pix / (PT::HW * PT::HH);
+    xj[j] = w | h << 8 | d << 16;
+    x_off[j] = pix < halo_pix && xc_ok ? (unsigned)((((d * p.asp[1] + h) * p.asp[2] + w) * p.cx + c0 + vch) * 2) : DMA_OOB;
+  }
+#pragma unroll
+  for (int j = 0; j < YV; ++j) {
+    const int q = (gt >> 2) + j * 64;
+    const int w = q % PT::TW, h = (q / PT::TW) % PT::TH, d = q / (PT::TW * PT::TH);
+    yj[j] = w | h << 8 | d << 16;
+    y_off[j] = yc_ok ? (unsigned)((((d * p.osp[1] + h) * p.osp[2] + w) * p.ky + k0 + vch) * 2) : DMA_OOB;
+  }
+
+  const int pbegin = split * p.patches_per_split;
+  const int pend = (pbegin + p.patches_per_split < p.patches) ? pbegin + p.patches_per_split : p.patches;
+  const int rounds = pend > pbegin ? (pend - pbegin + 1) / 2 : 0;
+  int tw, th, td, nb;                                             // the group's next patch (uniform)
+  {
+    unsigned t = (unsigned)(pbegin + g);
+    tw = (int)(t % (unsigned)p.tiles[2]); t /= (unsigned)p.tiles[2];
+    th = (int)(t % (unsigned)p.tiles[1]); t /= (unsigned)p.tiles[1];
+    td = (int)(t % (unsigned)p.tiles[0]);
+    nb = (int)(t / (unsigned)p.tiles[0]);
+  }
+  auto advance = [&]() {
+    if (++tw == p.tiles[2]) { tw = 0; if (++th == p.tiles[1]) { th = 0; if (++td == p.tiles[0]) { td = 0; ++nb; } } }
+  };
+  const unsigned lds_w = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_gp + g * 2 * GP::BUF + wave * 1024);
+  auto fetch = [&](int round, int buf) {
+    const bool in = pbegin + 2 * round + g < pend;
+    const int o0[3] = {td * PT::TD, th * PT::TH, tw * PT::TW};
+    const int i0[3] = {o0[0] - p.pad[0], o0[1] - p.pad[1], o0[2] - p.pad[2]};
+    const v4u rx = buffer_rsrc(p.X + (((long long)nb * p.asp[0] + i0[0]) * p.asp[1] + i0[1]) * (long long)p.asp[2] * p.cx + (long long)i0[2] * p.cx, in ? 0x7fffffff : 0);
+    const v4u ry = buffer_rsrc(p.DY + (((long long)nb * p.osp[0] + o0[0]) * p.osp[1] + o0[1]) * (long long)p.osp[2] * p.ky + (long long)o0[2] * p.ky, in ? 0x7fffffff : 0);
+#pragma unroll
+    for (int j = 0; j < XV; ++j) {
+      const bool ok = (unsigned)(i0[0] + (xj[j] >> 16)) < (unsigned)p.asp[0] && (unsigned)(i0[1] + ((xj[j] >> 8) & 255)) < (unsigned)p.asp[1] &&
+                      (unsigned)(i0[2] + (xj[j] & 255)) < (unsigned)p.asp[2];
+      load_lds16(rx, lds_w + buf * GP::BUF + j * 4096, ok ? x_off[j] : DMA_OOB, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < YV; ++j) {
+      const bool ok = o0[0] + (yj[j] >> 16) < p.osp[0] && o0[1] + ((yj[j] >> 8) & 255) < p.osp[1] && o0[2] + (yj[j] & 255) < p.osp[2];
+      load_lds16(ry, lds_w + buf * GP::BUF + GP::X_BYTES + j * 4096, ok ? y_off[j] : DMA_OOB, 0);
+    }
+    advance();
+    advance();
+  };
+
+  // Everything from the sums on is written once per wave of a group: with one loop around a switch over the waves, the
+  // sums of its four branches had to be moved into the same registers (250 of them, and spills).
+  auto run = [&](auto wave_c) {
+    constexpr int W = decltype(wave_c)::value;
+    constexpr int TAP_LO = GP::TAPS * W / 4, TAP_N = GP::TAPS * (W + 1) / 4 - TAP_LO;
+    f32x16 acc[PT::MAXT], cs;
+#pragma unroll
+    for (int j = 0; j < PT::MAXT; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) cs[v] = 0.f;
+    if (rounds > 0) fetch(0, 0);
+#pragma unroll 1
+    for (int r = 0; r < rounds; ++r) {
+      wait_barrier<0>();                                          // this round's patches have landed, the other buffers are free
+      if (r + 1 < rounds) fetch(r + 1, (r + 1) & 1);
+      const uint16_t* sX = reinterpret_cast<const uint16_t*>(lds_gp + (g * 2 + (r & 1)) * GP::BUF);
+      wgrad_patch_mma<P3D, W, CS && W == 0>(sX, sX + GP::X_BYTES / 2, acc, src_off, half, &cs);
+    }
+    // ---- group 1 leaves its sums in LDS, group 0 adds them and writes ----
+    float4* sums = reinterpret_cast<float4*>(lds_gp);
+    __syncthreads();
+    if (g == 1) {
+#pragma unroll
+      for (int j = 0; j < TAP_N; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          sums[((TAP_LO + j) * 4 + q) * 64 + lane] = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
+    }
+    __syncthreads();
+    if (g == 0) {
+#pragma unroll
+      for (int j = 0; j < TAP_N; ++j) {
+        float* out = p.part + ((long long)split * p.taps + TAP_LO + j) * p.cx * p.ky;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 t = sums[((TAP_LO + j) * 4 + q) * 64 + lane];
+          const float v[4] = {acc[j][4 * q] + t.x, acc[j][4 * q + 1] + t.y, acc[j][4 * q + 2] + t.z, acc[j][4 * q + 3] + t.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int c = c0 + 8 * q + 4 * (lane >> 5) + e, k = k0 + (lane & 31);
+            if (c < p.cx && k < p.ky) out[(long long)c * p.ky + k] = v[e];
+          }
+        }
+      }
+    }
+    if (CS && cc == 0) {
+      float* sh = reinterpret_cast<float*>(lds_gp);
+      __syncthreads();                                            // the sums above have been read
+      if (W == 0 && lane < 32) sh[g * 32 + lane] = cs[0];         // every row of the product with ones is the sum
+      __syncthreads();
+      if (tid < 32 && k0 + tid < p.ky) p.cs_part[(long long)split * p.ky + k0 + tid] = sh[tid] + sh[32 + tid];
+    }
+  };
+  switch (wave) {
+    case 0: run(std::integral_constant<int, 0>{}); break;
+    case 1: run(std::integral_constant<int, 1>{}); break;
+    case 2: run(std::integral_constant<int, 2>{}); break;
+    default: run(std::integral_constant<int, 3>{}); break;
+  }
+}
+
 // 2-D variant with a 64 x 64 channel tile per work-group: every wave owns one 32 x 32 quadrant with all nine
 // taps (nine accumulators), so an input patch and a gradient patch are read from memory once for 64 x 64
 // filter entries instead of once per 32 x 32.
@@ -488,6 +653,22 @@ bool pair_packed(const int* asp, const int* osp, const int* filt, const int* pad
   return wide_tile(filt, cx, ky) && osp[2] <= 7 && osp[1] <= 8 && asp[1] == osp[1] && asp[2] == osp[2] && pad[2] == 1;
 }
 
+// Channel counts whose rows are 16-byte vectors take the kernel with two groups of waves; it addresses a patch (six input
+// planes at most) with 31 bits.
+bool grouped(const int* asp, const int* osp, int cx, int ky) {
+  return (cx & 7) == 0 && 12LL * asp[1] * asp[2] * cx < 0x7fffffffLL && 8LL * osp[1] * osp[2] * ky < 0x7fffffffLL;
+}
+
+template <int P3D, bool CS>
+hipError_t launch_grouped(const WPatchP& p, hipStream_t s) {
+  constexpr int LDS = GPatch<P3D>::LDS_BYTES;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_patch_group_kernel<P3D, CS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((wgrad_patch_group_kernel<P3D, CS>), dim3((unsigned)(p.cchunks * p.ktiles * p.splits)), dim3(GP_NT), LDS, s, p);
+  return hipGetLastError();
+}
+
 struct PatchGrid { int tiles[3]; long long patches; int splits, per_split; bool pairs; };
 PatchGrid patch_grid(long long batch, const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky) {
   PatchGrid g;
@@ -502,8 +683,8 @@ PatchGrid patch_grid(long long batch, const int* asp, const int* osp, const int*
   const int tile = wide_tile(filt, cx, ky) ? 64 : 32;
   const long long wg = (long long)((cx + tile - 1) / tile) * ((ky + tile - 1) / tile);
   // partial sums cost 4 bytes x filter size per work-group, written and read again: two work-groups per compute unit
-  // (32 x 32 tiles) measured 5 % faster on the 3D U-Net step than four
-  long long target = tile == 64 ? 256 : 512;
+  // (32 x 32 tiles) measured 5 % faster on the 3D U-Net step than four; with two groups of waves in one that is one
+  long long target = tile == 64 || grouped(asp, osp, cx, ky) ? 256 : 512;
   if (const char* e = getenv("LMS_WGRAD_PATCH_WGS")) target = atoll(e);
   long long splits = (target + wg - 1) / wg;
   if (splits > g.patches) splits = g.patches;
@@ -554,6 +735,10 @@ hipError_t launch_wgrad_patch(const uint16_t* X, const uint16_t* DY, float* part
     return cs_part ? run(wgrad_patch64_kernel<true, false>) : run(wgrad_patch64_kernel<false, false>);
   }
   const long long blocks = (long long)p.cchunks * p.ktiles * p.splits;
+  if (grouped(asp, osp, cx, ky)) {
+    if (filt[0] == 3) return cs_part ? launch_grouped<1, true>(p, s) : launch_grouped<1, false>(p, s);
+    return cs_part ? launch_grouped<0, true>(p, s) : launch_grouped<0, false>(p, s);
+  }
   auto run = [&](auto kernel) -> hipError_t {
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NTHREADS), 0, s, p);
     return hipGetLastError();
