@@ -1,4 +1,4 @@
-// 3x3 stride-1 convolutions that keep the extents (padding 1), 2-D, forward and data gradient.
+// 3x3 and 3x3x3 stride-1 convolutions that keep the extents (padding 1), forward and data gradient.
 //
 // A tile is BM consecutive positions of the batch in memory order, whatever rows and images they belong to, so no
 // tile is padded: patches of 8 x 16 positions are 77 % full on the 14 x 14, 28 x 28 and 7 x 7 maps of ResNet-50 and fill worse
@@ -30,16 +30,17 @@ __device__ __forceinline__ void unrolled(F&& f) {
   }
 }
 
-template <int BM_, int BN_, int WM_, int WN_, int AVS_>
+template <int BM_, int BN_, int WM_, int WN_, int AV_, int NB_, int G_ = 1>
 struct FlatTile {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-  static constexpr int AVS = AVS_;                                // input loads per thread in each of two stages of a channel block
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, G = G_;
+  static constexpr int NT = NTHREADS * G;                         // threads of the work-group
+  static constexpr int AV = AV_;                                  // input loads per thread and block
   static constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
-  static_assert(WM * WN == 4, "four waves");
+  static_assert(WM * WN == 4, "four waves a group");
   static constexpr int BV = (3 * BN * 4 + NTHREADS - 1) / NTHREADS;       // filter loads per thread and stage
   static constexpr int B_STAGE = BV * NTHREADS * 16;
-  static constexpr int NB = 2;                                    // filter ring
-  static constexpr int MAXPIX = 2 * AVS * NTHREADS / 4;           // input pixels at most
+  static constexpr int NB = NB_;                                  // filter ring, 2 or 3 stages
+  static constexpr int MAXPIX = AV * NTHREADS / 4;                // input pixels at most
   static constexpr int LPR = WTN / 8, RPI = 64 / LPR, QV = 32 / RPI;
 };
 
@@ -47,9 +48,13 @@ struct FlatTile {
 __host__ __device__ inline int flat_pixels(int bm, int w) { return (bm + 2 * w + 2 + 15) / 16 * 16; }
 __host__ __device__ inline int flat_abuf(int bm, int w) { return flat_pixels(bm, w) * 64 + 256; }
 
-template <typename T, bool FLIP>
-__global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
-  constexpr int TM = T::TM, TN = T::TN, BV = T::BV, AVS = T::AVS, NB = T::NB;
+// LDS of a group: filter ring, two input buffers, a place for loads that nobody needs.
+template <typename T>
+__host__ __device__ inline int flat_group_lds(int w) { return T::NB * T::B_STAGE + 2 * flat_abuf(T::BM, w) + 1024; }
+
+template <typename T, bool P3D, bool FLIP>
+__global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
+  constexpr int TM = T::TM, TN = T::TN, BV = T::BV, AV = T::AV, NB = T::NB, G = T::G, KD = P3D ? 3 : 1;
   extern __shared__ __attribute__((aligned(256))) unsigned char flat_smem[];
   const int per_xcd = (p.ntiles + 7) / 8;
   const int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
@@ -58,21 +63,22 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
   const long long m0 = (long long)(tile / p.ntiles_n) * T::BM;
   const int W = p.osp[2], H = p.osp[1];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x & (NTHREADS - 1), lane = tid & 63, wave = tid >> 6;      // within the group
+  const int grp = G > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NTHREADS) : 0;
   const int wm = wave / T::WN, wn = wave % T::WN, half = lane >> 5;
 
-  // ---- LDS: filter ring, two input buffers (pixels, then zeros), a place for loads that nobody needs ----
+  // ---- LDS of the group ----
   const int npix = flat_pixels(T::BM, W), abuf = flat_abuf(T::BM, W);
-  unsigned char* sB = flat_smem;
-  unsigned char* sA = flat_smem + NB * T::B_STAGE;
-  const unsigned lds0 = (unsigned)(uintptr_t)flat_smem;           // LDS address: the low half of the generic one
+  unsigned char* sB = flat_smem + grp * flat_group_lds<T>(W);
+  unsigned char* sA = sB + NB * T::B_STAGE;
+  const unsigned lds0 = (unsigned)(uintptr_t)sB;                  // LDS address: the low half of the generic one
   const unsigned ldsA = lds0 + NB * T::B_STAGE, ldsX = ldsA + 2 * abuf;
   if (tid < 32) *reinterpret_cast<uint4*>(sA + (tid >> 4) * abuf + npix * 64 + (tid & 15) * 16) = make_uint4(0, 0, 0, 0);
 
   // ---- operands of the epilogue, fetched ahead ----
   const int cg = (lane % T::LPR) * 8, n = n0 + wn * T::WTN + cg;
   const int er = wm * T::WTM + lane / T::LPR;
-  const EpiBuffers eb(p, m0, (p.M - m0) * p.nout * 2);
+  const EpiBuffers eb(p, m0, grp == 0 ? (p.M - m0) * p.nout * 2 : 0);                 // group 0 writes
   const unsigned col = n < p.nout ? (unsigned)(n * 2) : DMA_OOB;
   auto out_off = [&](int r) -> unsigned { return col + (unsigned)(r * p.nout * 2); };   // rows beyond the last lie beyond the buffer
   constexpr int EV = TM * T::QV;
@@ -86,29 +92,38 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
 
   // ---- input loads: pixel j of the buffer is row m0 - W - 1 + j of the tensor, channel slot g sits at g ^ ((j >> 2) & 3) ----
   const int apix = tid >> 2, ag = (tid & 3) ^ ((apix >> 2) & 3);
-  const long long arow0 = m0 - W - 1;
+  const long long plane = (long long)H * W, arow0 = m0 - W - 1 - (P3D ? plane : 0);
   const v4u rs_a = buffer_rsrc(p.A + arow0 * p.red, 0x7fffffff);  // rows outside the tensor are never asked for
-  const unsigned a_off = (unsigned)((apix * p.red + ag * 8) * 2);
-  unsigned a_in = 0;                                              // bit j: pixel apix + 64 j is a row of the tensor
+  const unsigned a_off = (unsigned)((apix * p.red + ag * 8) * 2), a_plane = (unsigned)(plane * p.red * 2);
+  unsigned a_in[KD];                                              // bit j: pixel apix + 64 j of this plane's run is a row of the tensor
 #pragma unroll
-  for (int j = 0; j < 2 * AVS; ++j) {
-    const int pix = apix + j * (NTHREADS / 4);
-    const long long row = arow0 + pix;
-    if (pix < npix && row >= 0 && row < p.M) a_in |= 1u << j;
+  for (int kd = 0; kd < KD; ++kd) {
+    a_in[kd] = 0;
+#pragma unroll
+    for (int j = 0; j < AV; ++j) {
+      const int pix = apix + j * (NTHREADS / 4);
+      const long long row = arow0 + kd * plane + pix;
+      if (pix < npix && row >= 0 && row < p.M) a_in[kd] |= 1u << j;
+    }
   }
   const unsigned ldsA_w = __builtin_amdgcn_readfirstlane(ldsA + wave * 1024), ldsX_u = __builtin_amdgcn_readfirstlane(ldsX);
   const int wpix = __builtin_amdgcn_readfirstlane(wave * 16);
-  auto fetch_a = [&](int chunk, int part) {                       // part 0 or 1: AVS loads per thread each
-    const bool ok = chunk * BK + ag * 8 < p.red;
+  // block vb of the layer: channel block vb / KD, input plane vb % KD; the group takes vb = grp, grp + G, ...
+  const int nblocks = ((p.red + BK - 1) / BK) * KD, nlocal = (nblocks + G - 1) / G;
+  auto fetch_a = [&](int lb) {
+    const int vb = lb * G + grp, chunk = vb / KD, kd = vb % KD;
+    const bool ok = vb < nblocks && chunk * BK + ag * 8 < p.red;
+    unsigned in = a_in[0];
+    if constexpr (P3D) in = kd == 0 ? a_in[0] : (kd == 1 ? a_in[1] : a_in[2]);
+    const unsigned so = (P3D ? kd * a_plane : 0) + chunk * (BK * 2);
 #pragma unroll
-    for (int jj = 0; jj < AVS; ++jj) {
-      const int j = part * AVS + jj;
-      const unsigned dst = j * (NTHREADS / 4) + wpix < npix ? ldsA_w + (chunk & 1) * abuf + j * NTHREADS * 16 : ldsX_u;   // uniform
-      load_lds16(rs_a, dst, ok && ((a_in >> j) & 1) ? a_off : DMA_OOB, (unsigned)(j * (NTHREADS / 4) * p.red * 2 + chunk * (BK * 2)));
+    for (int j = 0; j < AV; ++j) {
+      const unsigned dst = j * (NTHREADS / 4) + wpix < npix ? ldsA_w + (lb & 1) * abuf + j * NTHREADS * 16 : ldsX_u;   // uniform
+      load_lds16(rs_a, dst, ok && ((in >> j) & 1) ? a_off : DMA_OOB, (unsigned)(j * (NTHREADS / 4) * p.red * 2) + so);
     }
   };
   // ---- filter loads: row (tap of the filter row, output channel), channel slot g at g ^ ((n >> 2) & 3) ----
-  const v4u rs_b = buffer_rsrc(p.B, (long long)9 * p.nout * p.red * 2);
+  const v4u rs_b = buffer_rsrc(p.B, (long long)(9 * KD) * p.nout * p.red * 2);
   unsigned b_off[BV];
   int b_k[BV];
 #pragma unroll
@@ -118,27 +133,30 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
     b_off[j] = tl < 3 && n0 + nr < p.nout ? (unsigned)(((tl * p.nout + n0 + nr) * p.red + b_k[j]) * 2) : DMA_OOB;
   }
   const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
-  auto fetch_b = [&](int chunk, int u, int buf) {
-    const unsigned so = (unsigned)u * 3 * p.nout * p.red * 2 + chunk * (BK * 2);
+  auto fetch_b = [&](int lb, int u, int buf) {
+    const int vb = lb * G + grp, chunk = vb / KD, kd = FLIP ? KD - 1 - vb % KD : vb % KD;
+    const unsigned so = (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * (BK * 2);
 #pragma unroll
     for (int j = 0; j < BV; ++j)
-      load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, chunk * BK + b_k[j] < p.red ? b_off[j] : DMA_OOB, so);
+      load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, vb < nblocks && chunk * BK + b_k[j] < p.red ? b_off[j] : DMA_OOB, so);
   };
 
   // ---- LDS read addresses: per 32-position group and tap the pixel, or the zeros ----
-  int a_rd[TM][9];
+  int a_rd[TM][9], a_d[TM];                                       // a_d: depth of the lane's position
+  const int a_zero = npix * 64 + (lane & 3) * 64;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int r = wm * T::WTM + i * 32 + (lane & 31);
-    const unsigned t = (unsigned)(m0 + r < p.M ? m0 + r : 0);     // host guarantees M < 2^31
+    const unsigned t = (unsigned)(m0 + r < p.M ? m0 + r : 0);     // M < 2^31: flat_eligible
     const int w = (int)(t % (unsigned)W), h = (int)((t / (unsigned)W) % (unsigned)H);
+    a_d[i] = P3D ? (int)((t / (unsigned)W / (unsigned)H) % (unsigned)p.osp[0]) : 0;
 #pragma unroll
     for (int kh = 0; kh < 3; ++kh)
 #pragma unroll
       for (int kw = 0; kw < 3; ++kw) {
         const int pix = r + kh * W + kw;
         const bool in = (unsigned)(h + kh - 1) < (unsigned)H && (unsigned)(w + kw - 1) < (unsigned)W;
-        a_rd[i][kh * 3 + kw] = in ? pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4) : npix * 64 + (lane & 3) * 64;
+        a_rd[i][kh * 3 + kw] = in ? pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4) : a_zero;
       }
   }
   int b_rd[TN][2];
@@ -157,22 +175,42 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int nchunks = (p.red + BK - 1) / BK;
-  fetch_b(0, 0, 0);
-  fetch_a(0, 0);
-  fetch_a(0, 1);
-  // Filter row u of channel block `chunk`, the buffers of both as compile-time parities of the stage.  Order of the loads:
-  // every stage asks for the next stage's filter row, then the first two stages of a block for half of the next
-  // block's input each; so what the next stage needs is older than those AVS input loads.
-  auto stage = [&](int chunk, auto u_c, auto bbuf_c, bool last) {
+  // Stage st = 3 lb + u multiplies filter row u of the group's block lb.  It asks for the input of block lb + 1 (at u = 0,
+  // into the buffer of block lb - 1), then for the filter row NB - 1 stages on; so when stage st begins, what it needs is
+  // older than the filter rows asked for in the NB - 2 stages before it, and than the next input among them.
+  const int nstages = 3 * nlocal;
+  fetch_a(0);
+#pragma unroll
+  for (int st = 0; st < NB - 1; ++st)
+    if (st < nstages) fetch_b(st / 3, st % 3, st);
+  int a_cur[TM][9];                                               // addresses of the block: zeros where its plane is outside
+  auto stage = [&](int lb, auto u_c, auto bbuf_c) {
     constexpr int u = decltype(u_c)::value, bbuf = decltype(bbuf_c)::value;
-    if (u == 0 || chunk + 1 >= nchunks) wait_barrier<0>();
-    else wait_barrier<AVS>();
-    if (!last) fetch_b(u == 2 ? chunk + 1 : chunk, (u + 1) % 3, bbuf ^ 1);
-    if (u < 2 && chunk + 1 < nchunks) fetch_a(chunk + 1, u);
+    const int left = nstages - 1 - (3 * lb + u);                  // stages after this one
+    const bool more = lb + 1 < nlocal;
+    constexpr bool a_newer = u > 0 && u <= NB - 2;                // the next input was asked for in the last NB - 2 stages
+    if (left == 0) wait_barrier<0>();
+    else if (a_newer && more) wait_barrier<(NB - 2) * BV + AV>();
+    else wait_barrier<(NB - 2) * BV>();
+    if (u == 0 && more) fetch_a(lb + 1);
+    if (left >= NB - 1) {
+      constexpr int fu = (u + NB - 1) % 3;
+      fetch_b(lb + (u + NB - 1) / 3, fu, (bbuf + NB - 1) % NB);
+    }
+    if constexpr (P3D && u == 0) {
+      const int kd = (lb * G + grp) % KD;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const bool in = (unsigned)(a_d[i] + kd - 1) < (unsigned)p.osp[0];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) a_cur[i][q] = in ? a_rd[i][q] : a_zero;
+      }
+    }
+    const int (&ar)[TM][9] = P3D ? a_cur : a_rd;
     const unsigned char* b = sB + bbuf * T::B_STAGE;
-    const unsigned char* a = sA + (chunk & 1) * abuf;
-    constexpr int NSTEP = 6, DEPTH = 1;
+    const unsigned char* a = sA + (lb & 1) * abuf;
+    // operands are read this many steps ahead of their products: with one product a step the LDS latency shows
+    constexpr int NSTEP = 6, DEPTH = TM * TN == 1 ? 3 : 1;
     bf16x8 af[DEPTH + 1][TM], bfr[DEPTH + 1][TN];
     auto load = [&](int st) {
       const int tl = st / 2, ks = st % 2;
@@ -180,7 +218,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) bfr[st % (DEPTH + 1)][j] = *reinterpret_cast<const bf16x8*>(b + b_rd[j][ks] + tl * T::BN * 64);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[st % (DEPTH + 1)][i] = *reinterpret_cast<const bf16x8*>(a + (a_rd[i][tap] ^ (ks * 32)));
+      for (int i = 0; i < TM; ++i) af[st % (DEPTH + 1)][i] = *reinterpret_cast<const bf16x8*>(a + (ar[i][tap] ^ (ks * 32)));
     };
 #pragma unroll
     for (int st = 0; st < DEPTH; ++st) load(st);
@@ -200,53 +238,116 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_flat_kernel(IgemmP p) {
       __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
     }
   };
-  // three stages a block: the filter buffer's parity alternates from block to block
-  for (int chunk = 0; chunk < nchunks; chunk += 2) {
-    unrolled<3>([&](auto u) { stage(chunk, u, std::integral_constant<int, decltype(u)::value & 1>{}, chunk + 1 >= nchunks && decltype(u)::value == 2); });
-    if (chunk + 1 < nchunks)
-      unrolled<3>([&](auto u) { stage(chunk + 1, u, std::integral_constant<int, (decltype(u)::value + 1) & 1>{}, chunk + 2 >= nchunks && decltype(u)::value == 2); });
+  // three stages a block: the ring is where it was after NB blocks (three buffers: after each)
+  constexpr int PERIOD = NB == 3 ? 1 : NB;
+  for (int lb0 = 0; lb0 < nlocal; lb0 += PERIOD)
+    unrolled<PERIOD>([&](auto b_c) {
+      constexpr int bi = decltype(b_c)::value;
+      if (lb0 + bi < nlocal) unrolled<3>([&](auto u) { stage(lb0 + bi, u, std::integral_constant<int, (3 * bi + decltype(u)::value) % NB>{}); });
+    });
+  __syncthreads();                                                // LDS is free
+  if constexpr (G > 1) {
+    float4* sums = reinterpret_cast<float4*>(flat_smem);
+    auto slot = [&](int g, int i, int j, int q) -> float4& { return sums[((((g - 1) * 4 + wave) * TM + i) * TN + j) * 256 + q * 64 + lane]; };
+    if (grp > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            slot(grp, i, j, q) = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int g = 1; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const float4 t = slot(g, i, j, q);
+              acc[i][j][4 * q] += t.x; acc[i][j][4 * q + 1] += t.y; acc[i][j][4 * q + 2] += t.z; acc[i][j][4 * q + 3] += t.w;
+            }
+    }
+    __syncthreads();
+    if (grp > 0) return;
   }
-  __syncthreads();                                                // LDS is free for the epilogue
   wave_epilogue<T::WTN, TM, TN>(p, eb, acc, flat_smem + wave * epi_wave_bytes(T::WTN), pre_add, pre_mask, n, n < p.nout, er, out_off);
 }
 
-template <typename T, bool FLIP>
+template <typename T, bool P3D, bool FLIP>
 hipError_t launch_flat_t(IgemmP& p, hipStream_t s) {
-  const int ring = T::NB * T::B_STAGE + 2 * flat_abuf(T::BM, p.osp[2]) + 1024, epi = 4 * epi_wave_bytes(T::WTN);
-  const int lds = ring > epi ? ring : epi;
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_flat_kernel<T, FLIP>),
+  const int ring = T::G * flat_group_lds<T>(p.osp[2]), epi = 4 * epi_wave_bytes(T::WTN), sums = (T::G - 1) * T::BM * T::BN * 4;
+  int lds = ring > epi ? ring : epi;
+  if (sums > lds) lds = sums;
+  if (lds > 163840) return hipErrorInvalidValue;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_flat_kernel<T, P3D, FLIP>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
   if (attr != hipSuccess) return attr;
   p.ntiles_n = (p.nout + T::BN - 1) / T::BN;
   const long long mt = (p.M + T::BM - 1) / T::BM;
-  if (mt * p.ntiles_n > 0x7fffff00LL || p.M >= 0x7fffffffLL) return hipErrorInvalidValue;
+  if (mt * p.ntiles_n > 0x7fffff00LL) return hipErrorInvalidValue;
   p.ntiles = (int)(mt * p.ntiles_n);
-  hipLaunchKernelGGL((conv_flat_kernel<T, FLIP>), dim3(8 * ((p.ntiles + 7) / 8)), dim3(NTHREADS), lds, s, p);
+  hipLaunchKernelGGL((conv_flat_kernel<T, P3D, FLIP>), dim3(8 * ((p.ntiles + 7) / 8)), dim3(T::NT), lds, s, p);
   return hipGetLastError();
 }
 
-template <bool FLIP>
+typedef FlatTile<256, 64, 4, 1, 8, 2> Flat256x64;
+typedef FlatTile<128, 64, 2, 2, 6, 2> Flat128x64;
+typedef FlatTile<64, 64, 2, 2, 6, 3> Flat64;
+typedef FlatTile<64, 64, 2, 2, 5, 3, 2> Flat64g2;
+typedef FlatTile<256, 32, 4, 1, 8, 2> Flat256x32;
+typedef FlatTile<128, 32, 4, 1, 6, 3> Flat128x32;
+
+// The widest tile leaves room for a second work-group on a compute unit up to 87 positions a row.
+bool wide_fits(int w) { return flat_group_lds<Flat256x64>(w) <= 81920; }
+
+long long flat_tiles(const IgemmP& p, int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.nout + bn - 1) / bn); }
+
+template <bool P3D, bool FLIP>
 hipError_t launch_flat_f(IgemmP& p, hipStream_t s) {
-  auto tiles = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.nout + bn - 1) / bn); };
-  // the widest tile leaves room for a second work-group on a compute unit up to 87 positions a row
-  const bool wide = 2 * FlatTile<256, 64, 4, 1, 4>::B_STAGE + 2 * flat_abuf(256, p.osp[2]) + 1024 <= 81920;
-  if (p.nout <= 32) return tiles(256, 32) >= 256 ? launch_flat_t<FlatTile<256, 32, 4, 1, 4>, FLIP>(p, s) : launch_flat_t<FlatTile<128, 32, 4, 1, 3>, FLIP>(p, s);
-  if (wide && tiles(256, 64) >= 256) return launch_flat_t<FlatTile<256, 64, 4, 1, 4>, FLIP>(p, s);
-  if (tiles(128, 64) >= 256) return launch_flat_t<FlatTile<128, 64, 2, 2, 3>, FLIP>(p, s);
-  return launch_flat_t<FlatTile<64, 64, 2, 2, 3>, FLIP>(p, s);
+  // us, forward / data gradient; before: patches of 8 x 16 or 4 x 4 x 8 positions, or the general kernel where they fill badly.
+  //                                                     before         256 x 64     128 x 64    64 x 64     64 x 64, two groups
+  //   2-D 256 -> 256, 14 x 14, batch 256                81 / 85        65 / 68      69 / 73     89 / 93     107 / 118
+  //   2-D 512 -> 512, 7 x 7, batch 256                  81 / 88        62 / 67      77 / 84     98 / 105    108 / 116
+  //   2-D 96 -> 160, 23 x 21, batch 16                  15.4 / 17.6    17.0 / 20.6  15.0 / 17.5 14.4 / 14.6 18.6 / 15.3
+  //   2-D 72 -> 40, 45 x 37, batch 3                    14.8 / 10.0    16.5 / 11.5  14.2 / 9.2  12.6 / 8.6  13.3 / 8.1
+  //   3-D 128 -> 128, 32^3                              40 / 37        37 / 33      38 / 35     50 / 47     54 / 51
+  //   3-D 256 -> 256, 16^3                              40 / 37        56 / 52      45 / 41     35 / 31     31 / 27
+  //   3-D 96 -> 144, 13 x 13 x 12                       67 / 94        29 / 36      24 / 29     20 / 21     19 / 20
+  //   2-D 512 -> 512, 7 x 7, batch 32                                                       25 / 30     23 / 27
+  // So the widest tile of which there is one per compute unit; below that, the reduction is shared by two groups of
+  // waves where it is long enough (8 blocks) to pay for adding their sums.
+  const bool wide = wide_fits(p.osp[2]);
+  if (p.nout <= 32) return flat_tiles(p, 256, 32) >= 256 ? launch_flat_t<Flat256x32, P3D, FLIP>(p, s) : launch_flat_t<Flat128x32, P3D, FLIP>(p, s);
+  if (wide && flat_tiles(p, 256, 64) >= 256) return launch_flat_t<Flat256x64, P3D, FLIP>(p, s);
+  if (flat_tiles(p, 128, 64) >= 256) return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
+  const int blocks = (p.red + BK - 1) / BK * (P3D ? 3 : 1);
+  if (blocks >= 8 && flat_tiles(p, 64, 64) <= 512) return launch_flat_t<Flat64g2, P3D, FLIP>(p, s);
+  return launch_flat_t<Flat64, P3D, FLIP>(p, s);
 }
 
 }  // namespace
 
 bool flat_eligible(const IgemmP& p) {
   static const bool off = getenv("LMS_NO_FLAT") != nullptr;   // tuning aid
-  if (off || p.small || p.filt[0] != 1 || p.filt[1] != 3 || p.filt[2] != 3 || p.pad[0] != 0 || p.pad[1] != 1 || p.pad[2] != 1) return false;
+  const bool p3d = p.filt[0] == 3;
+  if (off || p.small || (p.filt[0] != 1 && !p3d) || p.filt[1] != 3 || p.filt[2] != 3 || p.pad[0] != (p3d ? 1 : 0) || p.pad[1] != 1 || p.pad[2] != 1) return false;
   for (int i = 0; i < 3; ++i)
     if (p.stride[i] != 1 || p.asp[i] != p.osp[i]) return false;
-  if ((p.red & 7) != 0 || (p.nout & 7) != 0 || p.osp[2] > 120) return false;
-  return (long long)9 * p.nout * p.red < 0x3fffffffLL && 600LL * p.red < 0x3fffffffLL;
+  if ((p.red & 7) != 0 || (p.nout & 7) != 0 || p.osp[2] > 120 || p.M >= 0x7fffffffLL) return false;
+  // Volumes of wider rows stay with patches: 64 -> 64 at 48 x 96 x 96 took 130 us with the 128 x 64 tile and 107 there, while
+  // 64^3 took 61 with the 256 x 64 tile and 66 there.
+  if (p3d && (!wide_fits(p.osp[2]) || 4LL * p.osp[1] * p.osp[2] * p.red >= 0x3fffffffLL)) return false;
+  return (long long)27 * p.nout * p.red < 0x3fffffffLL && 600LL * p.red < 0x3fffffffLL;
 }
 
-hipError_t launch_flat(IgemmP& p, hipStream_t s) { return p.mode == 1 ? launch_flat_f<true>(p, s) : launch_flat_f<false>(p, s); }
+hipError_t launch_flat(IgemmP& p, hipStream_t s) {
+  if (p.filt[0] == 3) return p.mode == 1 ? launch_flat_f<true, true>(p, s) : launch_flat_f<true, false>(p, s);
+  return p.mode == 1 ? launch_flat_f<false, true>(p, s) : launch_flat_f<false, false>(p, s);
+}
 
 }  // namespace lms

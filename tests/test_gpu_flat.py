@@ -1,0 +1,60 @@
+"""Stride-1 3x3 and 3x3x3 convolutions that keep the extents, at the edges of the tiles of consecutive positions: fewer positions
+than one tile, a last tile with few rows, images that begin inside a tile, channel counts that fill no block or tile, one and
+two groups of waves, rows too wide for the widest tile.  Reference: float64 over the GPU's own bf16 inputs; bound: bf16
+rounding of the result plus fp32 sums.  The two parameter gradients of the same layers: 2e-6 of the norm."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# n, extents, c, k
+CASES = [
+    (1, (1, 1), 8, 8), (1, (3, 2), 40, 24), (3, (5, 7), 264, 72), (2, (9, 120), 16, 40), (2, (9, 121), 16, 40), (5, (13, 88), 24, 200),
+    (70, (14, 14), 136, 256), (131, (23, 21), 40, 32), (9, (7, 7), 264, 264), (1, (40, 87), 96, 96),
+    (1, (1, 1, 1), 8, 8), (2, (2, 1, 3), 88, 48), (1, (5, 6, 7), 96, 24), (3, (3, 11, 13), 40, 104), (1, (33, 31, 30), 72, 64),
+    (2, (3, 4, 87), 24, 16), (2, (3, 4, 88), 24, 16), (1, (41, 40, 39), 8, 40),
+]
+
+
+@pytest.mark.parametrize("n,sp,c,k", CASES)
+def test_all_directions(n, sp, c, k):
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    nd = len(sp)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k + n)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    filt = (3,) * nd
+    x, dy, addend = rnd(n, *sp, c), rnd(n, *sp, k), rnd(n, *sp, c)
+    w = (rnd(*filt, c, k).float() / (c * 3 ** nd) ** 0.5).to(torch.bfloat16)
+    d = L.conv_desc(n, sp, c, k, filt, 1, 1, 0)
+    s = torch.cuda.current_stream().cuda_stream
+    y, dx = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    dw, db = torch.full(filt + (c, k), float("nan"), device="cuda"), torch.full((k,), float("nan"), device="cuda")
+    ws = torch.full((max(L.conv_workspace_bytes(d, q) for q in (A.CONV_FWD, A.CONV_DGRAD, A.CONV_WGRAD_BIAS)) + 256,), 255, dtype=torch.uint8,
+                    device="cuda")
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), s)
+    L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), None, addend.data_ptr(), None, dx.data_ptr(), ws.data_ptr(), s)
+    L.conv_wgrad_bias(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws.data_ptr(), s)
+    torch.cuda.synchronize()
+
+    # tap by tap over a padded copy, float64 on the device
+    pad = [0, 0] + [1, 1] * nd
+    xp, dyp = torch.nn.functional.pad(x.double(), pad), torch.nn.functional.pad(dy.double(), pad)
+    wd, dyd = w.double(), dy.double().reshape(-1, k)
+    ry, rdx, rdw = torch.zeros_like(dyd), addend.double().reshape(-1, c), torch.zeros_like(dw, dtype=torch.float64)
+    ay, adx = ry.clone(), rdx.abs()
+    for tap in torch.cartesian_prod(*[torch.arange(3)] * nd).tolist():
+        cut = (slice(None),) + tuple(slice(t, t + e) for t, e in zip(tap, sp))
+        back = (slice(None),) + tuple(slice(2 - t, 2 - t + e) for t, e in zip(tap, sp))
+        xt, dt, wt = xp[cut].reshape(-1, c), dyp[back].reshape(-1, k), wd[tuple(tap)]
+        ry += xt @ wt
+        ay += xt.abs() @ wt.abs()
+        rdx += dt @ wt.t()
+        adx += dt.abs() @ wt.abs().t()
+        rdw[tuple(tap)] = xt.t() @ dyd
+    # one bf16 rounding (2^-9), and fp32 sums of exact products: 2^-18 of the sum of magnitudes covers 27 * 264 terms in any order
+    for got, ref, mag in ((y, ry, ay), (dx, rdx, adx)):
+        assert bool(((got.double().reshape(ref.shape) - ref).abs() <= ref.abs() * 2.0 ** -8 + mag * 2.0 ** -18).all())
+    assert float((dw.double() - rdw).norm() / rdw.norm().clamp_min(1e-30)) <= 2e-6
+    assert float((db.double() - dyd.sum(0)).norm() / dyd.sum(0).norm()) <= 2e-6
