@@ -357,9 +357,9 @@ lms_status lms_conv_wgrad(const lms_conv_desc* d, const void* x, const void* dy,
                           void* workspace, void* stream);
 /* The two parameter gradients of a convolution layer that the chain rule takes from dy (Section 2.1: every
  * backward operation of a layer reads the layer's output gradient): dw as lms_conv_wgrad, and dbias[k] (fp32,
- * d->k values) = sum of dy over batch and positions, the gradient of a per-channel bias or shift.  Where the
- * weight-gradient kernel stages dy through registers (1x1 filters, 2-D 3x3 filters with at least 48 channels on both
- * sides) the sums come out of the same pass over dy; otherwise a separate pass follows.  Deterministic.
+ * d->k values) = sum of dy over batch and positions, the gradient of a per-channel bias or shift.  Where one
+ * of the specialised weight-gradient kernels applies (1x1 filters, stride-1 3x3 and 3x3x3 filters, first layers) the
+ * sums come out of the same pass over dy; otherwise a separate pass follows.  Deterministic.
  * workspace: lms_conv_workspace_bytes(d, LMS_CONV_WGRAD_BIAS_K) bytes.  All pointers device memory, caller-owned. */
 lms_status lms_conv_wgrad_bias(const lms_conv_desc* d, const void* x, const void* dy, float* dw, float* dbias,
                                void* workspace, void* stream);
