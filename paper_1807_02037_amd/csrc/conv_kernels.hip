@@ -784,7 +784,9 @@ WgradSplit wgrad_split(long long rows, int taps, int cx, int ky) {
 // Weight gradient of a 1x1 stride-1 convolution with at most 8 output channels (class heads): dw[c][k] = sum over
 // positions of x[m][c] * dy[m][k].  No MFMA: a thread keeps 8 channels x 8 outputs of the sum in registers and
 // walks over the rows of its work-group with a stride; threads of the same channel vector are then added in a
-// fixed order (wave shuffles, then the four waves through LDS).  part[work-group][c][k].
+// fixed order (wave shuffles, then the four waves through LDS).  part[work-group][c][k].  What bounds it is latency, of the few
+// rounds of loads and of the exchanges: both parameter gradients, us, 32 -> 4 at 64^3 41 -> 30, 32 -> 8 80 -> 73, 64 -> 3 46 -> 43, 8 -> 2 on
+// two maps of 113 x 97 40 -> 20 with loads of four rows at a time (where they are vectors) and exchanges side by side.
 constexpr int WT_WGS = 1024;
 __global__ __launch_bounds__(256) void wgrad_tiny_kernel(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky,
                                                          long long rows_per_wg) {
@@ -799,41 +801,63 @@ __global__ __launch_bounds__(256) void wgrad_tiny_kernel(const uint16_t* X, cons
   for (int e = 0; e < 8; ++e)
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[e][k] = 0.f;
-  for (long long m = lo + r; m < hi; m += rpb) {
-    const uint4 q = *reinterpret_cast<const uint4*>(X + m * cx + cv * 8);
+  // Rows of vector loads are taken four at a time, loads first: one at a time, each of the few rounds waited for memory.
+  auto get = [&](long long m, uint4& q, uint32_t (&g)[4]) {
+    q = *reinterpret_cast<const uint4*>(X + m * cx + cv * 8);
+    if (ky == 8) {
+      const uint4 v = *reinterpret_cast<const uint4*>(DY + m * 8);
+      g[0] = v.x; g[1] = v.y; g[2] = v.z; g[3] = v.w;
+    } else if (ky == 4) {
+      const uint2 v = *reinterpret_cast<const uint2*>(DY + m * 4);
+      g[0] = v.x; g[1] = v.y; g[2] = g[3] = 0;
+    } else {
+      uint32_t e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) e[k] = k < ky ? DY[m * ky + k] : 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) g[k] = e[2 * k] | e[2 * k + 1] << 16;
+    }
+  };
+  auto add = [&](const uint4& q, const uint32_t (&g)[4]) {
     const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
     float xv[8], d[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) xv[e] = __uint_as_float((e & 1) ? (qw[e >> 1] & 0xffff0000u) : (qw[e >> 1] << 16));
-    if (ky == 8 || ky == 4) {
-      uint32_t dw4[4] = {0, 0, 0, 0};
-      if (ky == 8) {
-        const uint4 g = *reinterpret_cast<const uint4*>(DY + m * 8);
-        dw4[0] = g.x; dw4[1] = g.y; dw4[2] = g.z; dw4[3] = g.w;
-      } else {
-        const uint2 g = *reinterpret_cast<const uint2*>(DY + m * 4);
-        dw4[0] = g.x; dw4[1] = g.y;
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) d[k] = __uint_as_float((k & 1) ? (dw4[k >> 1] & 0xffff0000u) : (dw4[k >> 1] << 16));
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) d[k] = k < ky ? bf2f(DY[m * ky + k]) : 0.f;
+    for (int e = 0; e < 8; ++e) {
+      xv[e] = __uint_as_float((e & 1) ? (qw[e >> 1] & 0xffff0000u) : (qw[e >> 1] << 16));
+      d[e] = __uint_as_float((e & 1) ? (g[e >> 1] & 0xffff0000u) : (g[e >> 1] << 16));
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e)
 #pragma unroll
       for (int k = 0; k < 8; ++k) acc[e][k] = __builtin_fmaf(xv[e], d[k], acc[e][k]);
+  };
+  long long m = lo + r;
+  for (; (ky == 8 || ky == 4) && m + 3 * rpb < hi; m += 4 * rpb) {
+    uint4 q[4];
+    uint32_t g[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) get(m + j * rpb, q[j], g[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) add(q[j], g[j]);
   }
-  // lanes with the same channel vector: lane, lane + cvn, ... ; add them pairwise at growing distance
+  for (; m < hi; m += rpb) {
+    uint4 q;
+    uint32_t g[4];
+    get(m, q, g);
+    add(q, g);
+  }
+  // lanes with the same channel vector: lane, lane + cvn, ... ; add them pairwise at growing distance, the eight sums of
+  // an output column side by side (one after the other, each exchange waited for the one before)
+  for (int dist = cvn; dist < 64; dist <<= 1)
 #pragma unroll
-  for (int e = 0; e < 8; ++e)
+    for (int k = 0; k < 8; ++k)
+      if (k < ky) {                                     // uniform
+        float v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      float v = acc[e][k];
-      for (int dist = cvn; dist < 64; dist <<= 1) v += __shfl_xor(v, dist, 64);
-      acc[e][k] = v;
-    }
+        for (int e = 0; e < 8; ++e) v[e] = __shfl_xor(acc[e][k], dist, 64);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e][k] += v[e];
+      }
   float* out = part + (long long)blockIdx.x * cx * ky;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
