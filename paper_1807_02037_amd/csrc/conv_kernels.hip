@@ -896,6 +896,25 @@ bool wgrad_use_small(int cx, int ky, const int* asp, const int* osp, const int* 
   return osp[2] >= 64 || !wgrad_patch_eligible(cx, ky, filt, stride);
 }
 
+// The kernel that a weight gradient runs on and the number of partial filters it leaves: the launch and the workspace size
+// both follow this one choice.
+enum WgradRoute { WGRAD_TINY, WGRAD_SMALL, WGRAD_ROWS, WGRAD_PATCH, WGRAD_GENERAL };
+struct WgradPlan { WgradRoute route; int splits; };
+WgradPlan wgrad_plan(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad,
+                     int transpose) {
+  static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;   // tuning aid
+  if (!transpose) {
+    if (wgrad_tiny_eligible(cx, ky, filt, stride, pad)) return {WGRAD_TINY, wgrad_tiny_wgs(rows, cx)};
+    if (wgrad_use_small(cx, ky, asp, osp, filt, stride)) return {WGRAD_SMALL, wgrad_small_splits(rows, osp)};
+    if (wgrad_rows_eligible(cx, ky, asp, filt, stride, pad)) return {WGRAD_ROWS, wgrad_rows_splits(rows, cx, ky)};
+    if (!no_patch && wgrad_patch_eligible(cx, ky, filt, stride)) {
+      const long long batch = rows / ((long long)osp[0] * osp[1] * osp[2]);
+      return {WGRAD_PATCH, wgrad_patch_splits(batch, asp, osp, filt, pad, cx, ky)};
+    }
+  }
+  return {WGRAD_GENERAL, wgrad_split(rows, filt[0] * filt[1] * filt[2], cx, ky).splits};
+}
+
 // The part of the workspace behind the partial filters: partial column sums of dy, [splits][ky].
 float* colsum_part(void* ws, long long splits, long long per) { return reinterpret_cast<float*>(ws) + splits * per; }
 
@@ -920,40 +939,23 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
                            int transpose, float* colsum_out, bool& colsum_done, hipStream_t s) {
   static const bool no_side = getenv("LMS_NO_WGRAD_COLSUM") != nullptr;   // tuning aid: always the separate pass
   const bool side = colsum_out && !no_side;
-  if (!transpose && wgrad_tiny_eligible(cx, ky, filt, stride, pad)) {
-    const int wgs = wgrad_tiny_wgs(rows, cx);
-    const long long per_wg = (rows + wgs - 1) / wgs;
-    hipLaunchKernelGGL(wgrad_tiny_kernel, dim3(wgs), dim3(256), 0, s, X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, per_wg);
+  const WgradPlan plan = wgrad_plan(rows, cx, ky, asp, osp, filt, stride, pad, transpose);
+  const int splits = plan.splits;
+  const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
+  if (plan.route == WGRAD_TINY) {
+    const long long per_wg = (rows + splits - 1) / splits;
+    hipLaunchKernelGGL(wgrad_tiny_kernel, dim3(splits), dim3(256), 0, s, X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, per_wg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long long per = (long long)cx * ky;
-    return launch_wgrad_reduce(ws, dw, per, wgs, s);
+    return launch_wgrad_reduce(ws, dw, per, splits, s);
   }
-  if (!transpose && wgrad_use_small(cx, ky, asp, osp, filt, stride)) {
-    const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
-    const int splits = wgrad_small_splits(rows, osp);
+  if (plan.route != WGRAD_GENERAL) {
+    float* part = reinterpret_cast<float*>(ws);
     float* cs = side ? colsum_part(ws, splits, per) : nullptr;
-    hipError_t e = launch_wgrad_small(X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
-    if (e != hipSuccess) return e;
-    colsum_done = cs != nullptr;
-    return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
-  }
-  if (!transpose && wgrad_rows_eligible(cx, ky, asp, filt, stride, pad)) {
-    const long long per = (long long)cx * ky;
-    const int splits = wgrad_rows_splits(rows, cx, ky);
-    float* cs = side ? colsum_part(ws, splits, per) : nullptr;
-    hipError_t e = launch_wgrad_rows(X, DY, reinterpret_cast<float*>(ws), rows, cx, ky, asp, osp, stride, cs, s);
-    if (e != hipSuccess) return e;
-    colsum_done = cs != nullptr;
-    return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
-  }
-  static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;   // tuning aid
-  if (!transpose && !no_patch && wgrad_patch_eligible(cx, ky, filt, stride)) {
-    const long long batch = rows / ((long long)osp[0] * osp[1] * osp[2]);
-    const int splits = wgrad_patch_splits(batch, asp, osp, filt, pad, cx, ky);
-    const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
-    float* cs = side ? colsum_part(ws, splits, per) : nullptr;
-    hipError_t e = launch_wgrad_patch(X, DY, reinterpret_cast<float*>(ws), batch, asp, osp, filt, pad, cx, ky, cs, s);
+    hipError_t e;
+    if (plan.route == WGRAD_SMALL) e = launch_wgrad_small(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
+    else if (plan.route == WGRAD_ROWS) e = launch_wgrad_rows(X, DY, part, rows, cx, ky, asp, osp, stride, cs, s);
+    else e = launch_wgrad_patch(X, DY, part, rows / ((long long)osp[0] * osp[1] * osp[2]), asp, osp, filt, pad, cx, ky, cs, s);
     if (e != hipSuccess) return e;
     colsum_done = cs != nullptr;
     return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
@@ -971,7 +973,6 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
   hipLaunchKernelGGL(wgrad_kernel, dim3((unsigned)blocks), dim3(NTHREADS), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long per = (long long)p.taps * cx * ky;
   if (!transpose && (per & 3) == 0)
     return launch_wgrad_reduce(p.part, dw, per, w.splits, s);
   else
@@ -990,24 +991,13 @@ uint64_t conv_dgrad_ws(const ConvGeom& g, bool scaled) {
   return scaled ? (uint64_t)g.taps() * g.c * g.k * 2 : 0;
 }
 uint64_t conv_wgrad_ws(const ConvGeom& g, bool with_colsum) {
-  WgradSplit w = wgrad_split(g.out_rows(), g.taps(), g.c, g.k);
-  uint64_t splits = (uint64_t)w.splits;
-  if (wgrad_tiny_eligible(g.c, g.k, g.filt, g.stride, g.pad)) {
-    const uint64_t ts = (uint64_t)wgrad_tiny_wgs(g.out_rows(), g.c);
-    if (ts > splits) splits = ts;
-  }
-  if (wgrad_use_small(g.c, g.k, g.in_sp, g.out_sp, g.filt, g.stride)) {
-    const uint64_t ss = (uint64_t)wgrad_small_splits(g.out_rows(), g.out_sp);
-    if (ss > splits) splits = ss;
-  }
-  if (wgrad_rows_eligible(g.c, g.k, g.in_sp, g.filt, g.stride, g.pad)) {
-    const uint64_t rs = (uint64_t)wgrad_rows_splits(g.out_rows(), g.c, g.k);
-    if (rs > splits) splits = rs;
-  }
-  if (wgrad_patch_eligible(g.c, g.k, g.filt, g.stride)) {
-    const uint64_t ps = (uint64_t)wgrad_patch_splits(g.n, g.in_sp, g.out_sp, g.filt, g.pad, g.c, g.k);
-    static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;
-    splits = no_patch ? (ps > splits ? ps : splits) : ps;
+  const WgradPlan plan = wgrad_plan(g.out_rows(), g.c, g.k, g.in_sp, g.out_sp, g.filt, g.stride, g.pad, 0);
+  uint64_t splits = (uint64_t)plan.splits;
+  // the other specialised kernels keep room for the general one's partial filters as well: which geometries fit the static
+  // scratch array is known to callers
+  if (plan.route != WGRAD_PATCH) {
+    const uint64_t gs = (uint64_t)wgrad_split(g.out_rows(), g.taps(), g.c, g.k).splits;
+    if (gs > splits) splits = gs;
   }
   const uint64_t dw_part = splits * g.taps() * g.c * g.k * 4;
   if (!with_colsum) return dw_part;

@@ -1,0 +1,107 @@
+"""Workspace of the weight gradients: the partial filters and column sums that the kernel of a geometry writes fit the bytes that
+lms_conv_workspace_bytes returns.  On the host from the library's own sizes, over random geometries of every kernel; on the GPU
+with a guard region behind the exact size."""
+import ctypes
+import random
+
+import pytest
+
+import paper_1807_02037_amd as L
+
+A = L.abi
+
+
+def ints(v):
+    return (ctypes.c_int * 3)(*v)
+
+
+def host(name, ret, *args):
+    f = getattr(ctypes.CDLL(A.lib()._name), name)     # functions of the kernel files, by their C++ names
+    f.restype = ret
+    return f(*args)
+
+
+def written(n, sp, c, k, filt, stride, pad):
+    """Splits of the kernel that the launch takes, in its order of choice (the general kernel: at least one)."""
+    ext = lambda v: (1,) * (3 - len(v)) + tuple(v)
+    nd = len(sp)
+    osp = ext([(e + 2 * pad - f) // stride + 1 for e, f in zip(sp, filt)])
+    rows, i32, i64 = n * osp[0] * osp[1] * osp[2], ctypes.c_int, ctypes.c_longlong
+    f3, s3, p3 = ints(ext(filt)), ints(ext([stride] * nd)), ints((0,) * (3 - nd) + (pad,) * nd)
+    a3, o3 = ints(ext(sp)), ints(osp)
+    taps = f3[0] * f3[1] * f3[2]
+    if taps == 1 and stride == 1 and pad == 0 and k <= 8 and c % 8 == 0 and c <= 256 and (c & (c - 1)) == 0:
+        return max(1, min(1024, rows // (256 // (c // 8) * 8)))
+    patch = host("_ZN3lms20wgrad_patch_eligibleEiiPKiS1_", ctypes.c_bool, i32(c), i32(k), f3, s3)
+    if host("_ZN3lms20wgrad_small_eligibleEiiPKiS1_S1_", ctypes.c_bool, i32(c), i32(k), a3, f3, s3) and (osp[2] >= 64 or not patch):
+        return host("_ZN3lms18wgrad_small_splitsExPKi", i32, i64(rows), o3)
+    if host("_ZN3lms19wgrad_rows_eligibleEiiPKiS1_S1_S1_", ctypes.c_bool, i32(c), i32(k), a3, f3, s3, p3):
+        return host("_ZN3lms17wgrad_rows_splitsExii", i32, i64(rows), i32(c), i32(k))
+    if patch:
+        return host("_ZN3lms18wgrad_patch_splitsExPKiS1_S1_S1_ii", i32, i64(n), a3, o3, f3, p3, i32(c), i32(k))
+    return 1
+
+
+def test_partials_fit_the_workspace():
+    rng = random.Random(5)
+    for _ in range(20000):
+        nd = rng.choice((2, 2, 3))
+        filt = (rng.choice((1, 3, 3, 7 if nd == 2 else 2)),) * nd
+        stride, pad = rng.choice((1, 1, 2)), rng.choice((0, filt[0] // 2))
+        sp = tuple(rng.randint(max(1, filt[0] - 2 * pad), 230 if nd == 2 else 100) for _ in range(nd))
+        c = rng.choice((1, 2, 3, 4, 8, rng.randint(1, 80), 8 * rng.randint(1, 64)))
+        k = rng.choice((1, 8, 32, 64, rng.randint(1, 80), 8 * rng.randint(1, 64)))
+        n = rng.randint(1, 9)
+        d = L.conv_desc(n, sp, c, k, filt, stride, pad, 0)
+        splits = written(n, sp, c, k, filt, stride, pad)
+        per = c * k * filt[0] ** nd
+        what = (n, sp, c, k, filt, stride, pad, splits)
+        assert splits * per * 4 <= L.conv_workspace_bytes(d, A.CONV_WGRAD), what
+        assert splits * (per + k) * 4 <= L.conv_workspace_bytes(d, A.CONV_WGRAD_BIAS) or (filt[0] == 1 and k <= 8), what
+
+
+# first layers whose rows are and are not shorter than a segment, and one geometry of every other kernel; n, extents, c, k, filter, stride, pad
+GUARDED = [
+    (1, (80, 80, 80), 1, 32, 3, 1, 1), (8, (100, 100), 1, 32, 3, 1, 1), (2, (224, 224), 3, 64, 3, 1, 1), (1, (40, 40, 72), 1, 32, 3, 1, 1),
+    (2, (40, 40), 3, 16, 3, 1, 1), (1, (9, 70), 4, 8, 3, 1, 0), (1, (66, 90), 3, 64, 7, 2, 3), (3, (33, 31), 3, 24, 5, 1, 2),
+    (2, (20, 21), 64, 72, 1, 1, 0), (1, (33, 35), 16, 8, 1, 1, 0), (2, (17, 19), 64, 64, 1, 2, 0), (1, (15, 14), 64, 80, 3, 1, 1),
+    (1, (9, 10, 11), 24, 40, 3, 1, 1), (2, (15, 15), 32, 64, 3, 2, 1), (1, (12, 13), 20, 12, 3, 1, 1), (3, (7, 7), 64, 64, 3, 1, 1),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,sp,c,k,filt,stride,pad", GUARDED)
+def test_nothing_behind_the_workspace_is_written(n, sp, c, k, filt, stride, pad):
+    import torch
+    nd = len(sp)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k)
+    osp = tuple((e + 2 * pad - filt) // stride + 1 for e in sp)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    x, dy, w = rnd(n, *sp, c), rnd(n, *osp, k), rnd(*(filt,) * nd, c, k)
+    d = L.conv_desc(n, sp, c, k, (filt,) * nd, stride, pad, 0)
+    s = torch.cuda.current_stream().cuda_stream
+    scale = torch.ones(k, device="cuda")
+    y, dx = torch.empty_like(dy), torch.empty_like(x)
+    dw, dw2, db = torch.full((filt ** nd, c, k), float("nan"), device="cuda"), torch.empty((filt ** nd, c, k), device="cuda"), torch.empty(k, device="cuda")
+    calls = ((A.CONV_WGRAD, lambda ws: L.conv_wgrad(d, x.data_ptr(), dy.data_ptr(), dw2.data_ptr(), ws, s)),
+             (A.CONV_WGRAD_BIAS, lambda ws: L.conv_wgrad_bias(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws, s)),
+             (A.CONV_FWD, lambda ws: L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws, s)),
+             (A.CONV_DGRAD, lambda ws: L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), scale.data_ptr(), None, None, dx.data_ptr(), ws, s)))
+    for which, call in calls:
+        need = L.conv_workspace_bytes(d, which)
+        buf = torch.full((need + (8 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+        call(buf.data_ptr())
+        torch.cuda.synchronize()
+        assert bool((buf[need:] == 0xA5).all()), which
+    # float64, tap by tap
+    xp = torch.nn.functional.pad(x.double(), [0, 0] + [pad, pad] * nd)
+    dyd = dy.double().reshape(-1, k)
+    for t, tap in enumerate(torch.cartesian_prod(*[torch.arange(filt)] * nd).reshape(-1, nd).tolist()):
+        cut = (slice(None),) + tuple(slice(a, a + (o - 1) * stride + 1, stride) for a, o in zip(tap, osp))
+        ref = xp[cut].reshape(-1, c).t() @ dyd
+        # fp32 sums of exact products: 1e-6 of the norm of the sums of magnitudes
+        mag = float((xp[cut].reshape(-1, c).abs().t() @ dyd.abs()).norm())
+        assert float((dw[t].double() - ref).norm()) <= 1e-6 * mag, tap
+    assert torch.equal(dw, dw2)
+    assert float((db.double() - dyd.sum(0)).norm()) <= 1e-6 * float(dyd.abs().sum(0).norm())
