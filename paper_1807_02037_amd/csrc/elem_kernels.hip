@@ -631,56 +631,80 @@ __global__ __launch_bounds__(TB) void mse_grad_vec_kernel(const uint4* y, const 
   dy[i] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Global average pooling, y[b][c] = mean over the positions of image b.  A work-group owns one image and `vb` neighbouring
-// vectors of E channels; its TB / vb row lanes stride over the positions and are then added in a fixed order (lanes of a
-// wave by shuffles, the four waves through LDS).  One thread per (image, channel) walked all positions alone, with too
+// Global average pooling, y[b][c] = mean over the positions of image b.  A work-group owns vb = 2^lvb neighbouring vectors of E
+// channels of TB / (vb * nrl) images: nrl = 2^lrl row lanes of a vector stride over the positions and are then added in a fixed
+// order (lanes of a wave by shuffles, waves through LDS).  One thread per (image, channel) walked all positions alone, with too
 // few waves to hide its loads: (64, 28, 28, 512) 195 us, now 14 us (51 MB); (2, 32, 32, 16) 106 us, now 4 us.
 template <int E>
-__global__ __launch_bounds__(TB) void gap_fwd_kernel(const uint16_t* x, uint16_t* y, int positions, int c, int vb, int chunks) {
-  __shared__ float sh[4][TB / 4 * E];
-  const int b = blockIdx.x / chunks, v = threadIdx.x & (vb - 1), rl = threadIdx.x / vb, nrl = TB / vb;
-  const int ch = ((blockIdx.x % chunks) * vb + v) * E;
+__global__ __launch_bounds__(TB) void gap_fwd_kernel(const uint16_t* x, uint16_t* y, long long n, long long positions, float denom, int c, int lvb,
+                                                     int lrl, int chunks) {
+  __shared__ float sh[4][64 * E];
+  const int vb = 1 << lvb, lpi = lvb + lrl, per_image = 1 << lpi;
+  const int v = threadIdx.x & (vb - 1), rl = (threadIdx.x & (per_image - 1)) >> lvb;
+  const unsigned group = blockIdx.x / (unsigned)chunks, chunk = blockIdx.x - group * (unsigned)chunks;
+  const long long b0 = (long long)group * (TB >> lpi), b = b0 + (threadIdx.x >> lpi);
+  const int c0 = (int)chunk * vb * E, ch = c0 + v * E;
   float s[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) s[e] = 0.f;
-  if (ch < c) {
-    const uint16_t* xb = x + (long long)b * positions * c + ch;
+  if (ch < c && b < n) {
+    const uint16_t* p = x + (b * positions + rl) * c + ch;
+    const long long step = (long long)c << lrl;
+    const unsigned rows = (unsigned)((positions - rl + (1 << lrl) - 1) >> lrl);   // the host keeps it below 2^32
 #pragma unroll 4
-    for (int q = rl; q < positions; q += nrl) {
+    for (unsigned q = 0; q < rows; ++q, p += step) {
       if constexpr (E == 8) {
         float f[8];
-        unpack8(*reinterpret_cast<const uint4*>(xb + (long long)q * c), f);
+        unpack8(*reinterpret_cast<const uint4*>(p), f);
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[e] += f[e];
       } else {
-        s[0] += bf2f(xb[(long long)q * c]);
+        s[0] += bf2f(*p);
       }
     }
   }
+  for (int dist = vb; dist < 64 && dist < per_image; dist <<= 1) {
 #pragma unroll
-  for (int e = 0; e < E; ++e)
-    for (int dist = vb; dist < 64; dist <<= 1) s[e] += __shfl_xor(s[e], dist, 64);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane < vb) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) sh[wave][lane * E + e] = s[e];
+    for (int e = 0; e < E; ++e) s[e] += __shfl_xor(s[e], dist, 64);
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < vb * E; i += TB) {
-    const int o = (blockIdx.x % chunks) * vb * E + i;
-    if (o < c) y[(long long)b * c + o] = f2bf(((sh[0][i] + sh[1][i]) + (sh[2][i] + sh[3][i])) / (float)positions);
+  if (per_image > 64) {                                         // an image's sums lie in two or four waves
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < vb) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) sh[wave][lane * E + e] = s[e];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < (TB >> lpi) * vb * E; i += TB) {
+      const int o = i & (vb * E - 1), w = i >= vb * E ? 2 : 0;  // second image: waves 2 and 3
+      float t = sh[w][o] + sh[w + 1][o];
+      if (per_image == TB) t += sh[2][o] + sh[3][o];
+      if (c0 + o < c && b0 + (w >> 1) < n) y[(b0 + (w >> 1)) * c + c0 + o] = f2bf(t / denom);
+    }
+  } else if (rl == 0 && ch < c && b < n) {
+    uint16_t o[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = f2bf(s[e] / denom);
+    if constexpr (E == 8)
+      *reinterpret_cast<uint4*>(y + b * c + ch) = make_uint4(o[0] | (uint32_t)o[1] << 16, o[2] | (uint32_t)o[3] << 16, o[4] | (uint32_t)o[5] << 16, o[6] | (uint32_t)o[7] << 16);
+    else
+      y[b * c + ch] = o[0];
   }
 }
-// Its gradient: every position of an image gets dy / positions.  `per` work-groups per image, E channels per thread: the
-// element-wise form spent its time on three 64-bit divisions per element ((64, 28, 28, 512) with mask 61 us, now 21 us).
-template <int E>
-__global__ __launch_bounds__(TB) void gap_bwd_kernel(const uint16_t* dy, const uint16_t* mask, uint16_t* dx, int per, long long vecs, int positions,
-                                                     int cv) {
-  const long long b = blockIdx.x / per;
-  const float denom = (float)positions;
-  for (long long i = (long long)(blockIdx.x % per) * TB + threadIdx.x; i < vecs; i += (long long)per * TB) {
+// Its gradient: every position of an image gets dy / positions.  E channels per thread.  FLAT: one vector per thread over the whole
+// batch (n * vecs < 2^31).  Else `per` work-groups per image, which walk over its `vecs` vectors: the element-wise form
+// spent its time on three 64-bit divisions per element ((64, 28, 28, 512) with mask 61 us, now 21 us).
+template <int E, bool FLAT>
+__global__ __launch_bounds__(TB) void gap_bwd_kernel(const uint16_t* dy, const uint16_t* mask, uint16_t* dx, int per, long long vecs, unsigned total,
+                                                     float denom, int cv) {
+  long long b = FLAT ? 0 : blockIdx.x / per, i = (long long)(FLAT ? blockIdx.x : blockIdx.x % per) * TB + threadIdx.x;
+  if constexpr (FLAT) {
+    if ((unsigned)i >= total) return;
+    b = (unsigned)i / (unsigned)vecs;
+    i = (unsigned)i - (unsigned)b * (unsigned)vecs;
+  }
+  for (; i < vecs; i += (long long)per * TB) {
     const long long off = (b * vecs + i) * E;
-    const uint16_t* d = dy + (b * cv + (vecs <= 0x7fffffff ? (unsigned)i % (unsigned)cv : i % cv)) * E;
+    const uint16_t* d = dy + (b * cv + (FLAT || vecs <= 0x7fffffff ? (unsigned)i % (unsigned)cv : i % cv)) * E;
     if constexpr (E == 8) {
       float f[8], m[8];
       unpack8(*reinterpret_cast<const uint4*>(d), f);
@@ -697,6 +721,7 @@ __global__ __launch_bounds__(TB) void gap_bwd_kernel(const uint16_t* dy, const u
       if (mask && !(bf2f(mask[off]) > 0.f)) g = 0.f;
       dx[off] = f2bf(g);
     }
+    if constexpr (FLAT) break;
   }
 }
 
@@ -1345,34 +1370,63 @@ hipError_t maxpool_bwd(const ConvGeom& g, const void* dy, const void* x, int mas
                      mask_relu, (uint16_t*)dx, total);
   return hipGetLastError();
 }
-// Eight channels per thread where rows and pointers are 16-byte aligned, else one.
+// Eight channels per thread where rows and pointers are 16-byte aligned, else one.  Batches beyond 2^23 work-groups (a grid
+// holds less than 2^32 threads) go in several launches.
+constexpr int64_t GAP_WGS = 1 << 23;
 hipError_t gap_fwd(int64_t n, int64_t positions, int c, const void* x, void* y, hipStream_t s) {
-  const bool vec = (c & 7) == 0 && ((uintptr_t)x & 15) == 0;
+  const bool vec = (c & 7) == 0 && (((uintptr_t)x | (uintptr_t)y) & 15) == 0;
   const int cv = vec ? c / 8 : c, cap = vec ? 32 : 64;      // widest row of a work-group: 512 / 128 bytes
-  int vb = 1;
+  int lvb = 0, lrl = 0;
   // one wave of vectors at most, and fewer where that leaves compute units without a work-group (but 64 bytes a row)
-  while (vb < cv && vb < cap && (vb < (vec ? 4 : 32) || n * ((cv + 2 * vb - 1) / (2 * vb)) >= 1024)) vb *= 2;
-  const int64_t chunks = (cv + vb - 1) / vb;
-  if (positions > 0x7fffffff || n * chunks > 0x7fffff00LL) return hipErrorInvalidValue;
-  if (vec)
-    hipLaunchKernelGGL(gap_fwd_kernel<8>, dim3((unsigned)(n * chunks)), dim3(TB), 0, s, (const uint16_t*)x, (uint16_t*)y, (int)positions, c, vb, (int)chunks);
-  else
-    hipLaunchKernelGGL(gap_fwd_kernel<1>, dim3((unsigned)(n * chunks)), dim3(TB), 0, s, (const uint16_t*)x, (uint16_t*)y, (int)positions, c, vb, (int)chunks);
-  return hipGetLastError();
+  while ((1 << lvb) < cv && (1 << lvb) < cap && ((1 << lvb) < (vec ? 4 : 32) || n * ((cv + (2 << lvb) - 1) / (2 << lvb)) >= 1024)) ++lvb;
+  const int64_t chunks = (cv + (1 << lvb) - 1) >> lvb;
+  // all the work-group's lanes on one image, unless there are more lanes than positions, or less than eight positions each
+  // and work-groups in plenty: then several images share a work-group.  us, one image a work-group / this rule:
+  // (65536, 2, 2, 16) 125 / 3.9, (4096, 1, 1, 2048) 33 / 7.6, (16384, 4, 4, 24) 29 / 3.5
+  while (TB >> (lvb + lrl + 1)) ++lrl;
+  while (lrl > 0 && ((1LL << (lrl - 1)) >= positions || (positions < (8LL << lrl) && n * chunks / (TB >> (lvb + lrl)) > 512))) --lrl;
+  if ((positions >> lrl) >= 0xffffffffLL) return hipErrorInvalidValue;
+  const int images = TB >> (lvb + lrl);
+  for (int64_t b = 0; b < n;) {
+    const int64_t most = GAP_WGS / chunks > 0 ? GAP_WGS / chunks * images : images, take = n - b < most ? n - b : most;
+    const dim3 grid((unsigned)((take + images - 1) / images * chunks));
+    const uint16_t* xb = (const uint16_t*)x + b * positions * c;
+    uint16_t* yb = (uint16_t*)y + b * c;
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(TB), 0, s, xb, yb, (long long)take, (long long)positions, (float)positions, c, lvb, lrl, (int)chunks);
+      return hipGetLastError();
+    };
+    const hipError_t e = vec ? run(gap_fwd_kernel<8>) : run(gap_fwd_kernel<1>);
+    if (e != hipSuccess) return e;
+    b += take;
+  }
+  return hipSuccess;
 }
 hipError_t gap_bwd(int64_t n, int64_t positions, int c, const void* dy, const void* mask, void* dx, hipStream_t s) {
   const bool vec = (c & 7) == 0 && (((uintptr_t)dy | (uintptr_t)mask | (uintptr_t)dx) & 15) == 0;
-  const int cv = vec ? c / 8 : c;
+  const int cv = vec ? c / 8 : c, E = vec ? 8 : 1;
   const int64_t vecs = positions * cv;
+  // small images: no work-group of their own.  us, one image a work-group / this rule: (65536, 2, 2, 16) 29 / 5.3, (65536, 1, 1, 10) 18 / 3.6
+  const bool flat = vecs < 4 * TB || (!vec && vecs <= 0x7fffffff);
   int64_t per = (vecs + TB - 1) / TB;
   const int64_t most = n < 16384 ? 16384 / n : 1;             // about 64 work-groups per compute unit, then several rounds each
   if (per > most) per = most;
-  if (positions > 0x7fffffff || n * per > 0x7fffff00LL) return hipErrorInvalidValue;
-  if (vec)
-    hipLaunchKernelGGL(gap_bwd_kernel<8>, dim3((unsigned)(n * per)), dim3(TB), 0, s, (const uint16_t*)dy, (const uint16_t*)mask, (uint16_t*)dx, (int)per, (long long)vecs, (int)positions, cv);
-  else
-    hipLaunchKernelGGL(gap_bwd_kernel<1>, dim3((unsigned)(n * per)), dim3(TB), 0, s, (const uint16_t*)dy, (const uint16_t*)mask, (uint16_t*)dx, (int)per, (long long)vecs, (int)positions, cv);
-  return hipGetLastError();
+  for (int64_t b = 0; b < n;) {
+    const int64_t fit = flat ? 0x7fffffff / vecs : GAP_WGS, take = n - b < fit ? n - b : fit;
+    const unsigned total = flat ? (unsigned)(take * vecs) : 0;
+    const dim3 grid((unsigned)(flat ? (take * vecs + TB - 1) / TB : take * per));
+    const uint16_t *d = (const uint16_t*)dy + b * c, *m = mask ? (const uint16_t*)mask + b * vecs * E : nullptr;
+    uint16_t* o = (uint16_t*)dx + b * vecs * E;
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(TB), 0, s, d, m, o, (int)per, (long long)vecs, total, (float)positions, cv);
+      return hipGetLastError();
+    };
+    const hipError_t e = vec ? (flat ? run(gap_bwd_kernel<8, true>) : run(gap_bwd_kernel<8, false>))
+                             : (flat ? run(gap_bwd_kernel<1, true>) : run(gap_bwd_kernel<1, false>));
+    if (e != hipSuccess) return e;
+    b += take;
+  }
+  return hipSuccess;
 }
 hipError_t copy_channels(int64_t rows, const void* src, int src_c, int src_begin, void* dst, int dst_c, int dst_begin, int count,
                          const void* mask, hipStream_t s) {
