@@ -146,6 +146,13 @@ __device__ __forceinline__ void epilogue_put8(const IgemmP& p, const uint4& w, i
 
 }  // namespace
 
+// Loads that write LDS and buffer stores of 16 bytes are for pointers of that alignment.  Arena blocks have it; a caller's slice of
+// a packed buffer may not, and takes the kernels that load through registers.
+inline bool aligned16(const void* a, const void* b, const void* c = nullptr, const void* d = nullptr, const void* e = nullptr) {
+  return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d | (uintptr_t)e) & 15) == 0;
+}
+inline bool aligned16(const IgemmP& p) { return aligned16(p.A, p.B, p.out, p.add, p.mask); }
+
 // Patch-tiled kernel for 3x3 / 3x3x3 stride-1 filters (conv_halo.hip).
 bool halo_eligible(const IgemmP& p);
 hipError_t launch_halo(IgemmP& p, hipStream_t s);

@@ -335,7 +335,7 @@ hipError_t launch_flat_f(IgemmP& p, hipStream_t s) {
 bool flat_eligible(const IgemmP& p) {
   static const bool off = getenv("LMS_NO_FLAT") != nullptr;   // tuning aid
   const bool p3d = p.filt[0] == 3;
-  if (off || p.small || (p.filt[0] != 1 && !p3d) || p.filt[1] != 3 || p.filt[2] != 3 || p.pad[0] != (p3d ? 1 : 0) || p.pad[1] != 1 || p.pad[2] != 1) return false;
+  if (off || p.small || !aligned16(p) || (p.filt[0] != 1 && !p3d) || p.filt[1] != 3 || p.filt[2] != 3 || p.pad[0] != (p3d ? 1 : 0) || p.pad[1] != 1 || p.pad[2] != 1) return false;
   for (int i = 0; i < 3; ++i)
     if (p.stride[i] != 1 || p.asp[i] != p.osp[i]) return false;
   if ((p.red & 7) != 0 || (p.nout & 7) != 0 || p.osp[2] > 120 || p.M >= 0x7fffffffLL) return false;

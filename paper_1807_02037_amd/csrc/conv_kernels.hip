@@ -939,7 +939,8 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
                            int transpose, float* colsum_out, bool& colsum_done, hipStream_t s) {
   static const bool no_side = getenv("LMS_NO_WGRAD_COLSUM") != nullptr;   // tuning aid: always the separate pass
   const bool side = colsum_out && !no_side;
-  const WgradPlan plan = wgrad_plan(rows, cx, ky, asp, osp, filt, stride, pad, transpose);
+  WgradPlan plan = wgrad_plan(rows, cx, ky, asp, osp, filt, stride, pad, transpose);
+  if (plan.route == WGRAD_ROWS && !aligned16(X, DY)) plan.route = WGRAD_GENERAL;     // the workspace has room for its partial filters
   const int splits = plan.splits;
   const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
   if (plan.route == WGRAD_TINY) {
@@ -1019,24 +1020,18 @@ uint64_t tconv_wgrad_ws(const ConvGeom& g) {
 hipError_t conv_fwd(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, void* y, void* ws, hipStream_t s) {
   IgemmP p{};
   p.small = (g.c % 8) != 0;
-  p.A = (const uint16_t*)x; p.B = (const uint16_t*)ws; p.out = (uint16_t*)y;
+  p.A = (const uint16_t*)x; p.B = (const uint16_t*)w; p.out = (uint16_t*)y;
   p.scale = ep.scale; p.shift = ep.shift; p.add = (const uint16_t*)ep.add; p.mask = (const uint16_t*)ep.mask; p.relu = ep.relu;
   p.M = g.out_rows(); p.nout = g.k; p.red = g.c;
   fill_geom(g, p.asp, p.osp, p.filt, p.stride, p.pad);
   p.mode = 0;
   p.taps = g.taps();
-  if (pw_eligible(p)) {        // pointwise: the filter is read as stored
-    p.B = (const uint16_t*)w;
-    return launch_pw(p, s);
-  }
-  if (rf_eligible(p)) {        // filter resident in registers: read as stored as well
-    p.B = (const uint16_t*)w;
-    return launch_rf(p, s);
-  }
-  if (conv_small_eligible(p)) {   // first layers with 1 to 4 channels: filter read as stored, patch matrix gathered in LDS
-    p.B = (const uint16_t*)w;
-    return launch_conv_small(p, s);
-  }
+  // kernels that read the filter as stored: pointwise; filter resident in registers; first layers with 1 to 4 channels,
+  // patch matrix gathered in LDS
+  if (pw_eligible(p)) return launch_pw(p, s);
+  if (rf_eligible(p)) return launch_rf(p, s);
+  if (conv_small_eligible(p)) return launch_conv_small(p, s);
+  p.B = (const uint16_t*)ws;
   if (p.small) {
     p.jpad = small_jpad(g);
     const long long n = (long long)g.k * p.jpad;
@@ -1227,7 +1222,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_taps_kernel(const float4* pa
 hipError_t tconv_wgrad(const ConvGeom& g, const void* x, const void* dy, float* dw, void* ws, hipStream_t s) {
   bool exact = true;                                     // the output grid is the input grid times the stride
   for (int i = 0; i < 3; ++i) exact = exact && g.out_sp[i] == g.in_sp[i] * g.stride[i];
-  if (exact && wgrad_rows_tconv_eligible(g.c, g.k, g.out_sp, g.filt, g.stride)) {
+  if (exact && aligned16(x, dy) && wgrad_rows_tconv_eligible(g.c, g.k, g.out_sp, g.filt, g.stride)) {
     // window = stride: a pointwise weight gradient over the positions of x against taps * k gathered channels of dy
     hipError_t e = launch_wgrad_rows_tconv((const uint16_t*)x, (const uint16_t*)dy, reinterpret_cast<float*>(ws), g.in_rows(), g.c, g.k,
                                            g.in_sp, g.out_sp, g.stride, s);

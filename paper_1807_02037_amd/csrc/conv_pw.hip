@@ -327,7 +327,7 @@ hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
 
 bool pw_channels(const IgemmP& p, long long columns) {
   // 16-byte vectors of both operands, 32-bit filter offsets, tiles not mostly padding
-  return !p.small && (p.red & 7) == 0 && (p.nout & 7) == 0 && p.nout >= 32 && p.red >= 32 && columns * p.red < 0x3fffffffLL;
+  return !p.small && aligned16(p) && (p.red & 7) == 0 && (p.nout & 7) == 0 && p.nout >= 32 && p.red >= 32 && columns * p.red < 0x3fffffffLL;
 }
 
 }  // namespace

@@ -735,7 +735,7 @@ hipError_t launch_wgrad_patch(const uint16_t* X, const uint16_t* DY, float* part
     return cs_part ? run(wgrad_patch64_kernel<true, false>) : run(wgrad_patch64_kernel<false, false>);
   }
   const long long blocks = (long long)p.cchunks * p.ktiles * p.splits;
-  if (grouped(asp, osp, cx, ky)) {
+  if (grouped(asp, osp, cx, ky) && aligned16(X, DY)) {
     if (filt[0] == 3) return cs_part ? launch_grouped<1, true>(p, s) : launch_grouped<1, false>(p, s);
     return cs_part ? launch_grouped<0, true>(p, s) : launch_grouped<0, false>(p, s);
   }
