@@ -360,6 +360,7 @@ lms_status lms_conv_wgrad(const lms_conv_desc* d, const void* x, const void* dy,
  * d->k values) = sum of dy over batch and positions, the gradient of a per-channel bias or shift.  Where one
  * of the specialised weight-gradient kernels applies (1x1 filters, stride-1 3x3 and 3x3x3 filters, first layers) the
  * sums come out of the same pass over dy; otherwise a separate pass follows.  Deterministic.
+ * dbias needs the alignment of a float only (a slice of a packed gradient buffer); dw is written 16 bytes at a time.
  * workspace: lms_conv_workspace_bytes(d, LMS_CONV_WGRAD_BIAS_K) bytes.  All pointers device memory, caller-owned. */
 lms_status lms_conv_wgrad_bias(const lms_conv_desc* d, const void* x, const void* dy, float* dw, float* dbias,
                                void* workspace, void* stream);

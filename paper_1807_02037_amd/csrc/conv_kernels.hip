@@ -569,11 +569,11 @@ __global__ void wgrad_reduce_kernel(const float* part, float* dw, long long per_
 // the same pass left behind: one launch for both parameter gradients instead of two (a launch of its own cost the column
 // sums 2.5 to 4.5 us a layer, whatever their size).
 __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* part, float4* dw, long long per4, int splits, int blocks,
-                                                               const float4* cs_part, float4* cs_out, int cs_per4) {
+                                                               const float4* cs_part, float* cs_out, int cs_per4) {
   __shared__ float4 sh[8][32];
   const int o = threadIdx.x & 31, g = threadIdx.x >> 5;
   const bool cs = (int)blockIdx.x >= blocks;                // uniform
-  if (cs) { part = cs_part; dw = cs_out; per4 = cs_per4; }
+  if (cs) { part = cs_part; per4 = cs_per4; }
   const long long idx = (long long)((int)blockIdx.x - (cs ? blocks : 0)) * 32 + o;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (idx < per4) {
@@ -597,7 +597,11 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* par
     float4 t = sh[0][o];
 #pragma unroll
     for (int j = 1; j < 8; ++j) { t.x += sh[j][o].x; t.y += sh[j][o].y; t.z += sh[j][o].z; t.w += sh[j][o].w; }
-    dw[idx] = t;
+    if (cs) {                                               // one gradient among others in a caller's buffer: aligned as a float
+      cs_out[idx * 4] = t.x; cs_out[idx * 4 + 1] = t.y; cs_out[idx * 4 + 2] = t.z; cs_out[idx * 4 + 3] = t.w;
+    } else {
+      dw[idx] = t;
+    }
   }
 }
 
@@ -606,7 +610,7 @@ static hipError_t launch_wgrad_reduce(const void* part, float* dw, long long per
                                       float* cs_out = nullptr, int ky = 0) {
   const int blocks = (int)((per / 4 + 31) / 32), cs_blocks = cs_part ? (ky / 4 + 31) / 32 : 0;
   hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(blocks + cs_blocks), dim3(256), 0, s, (const float4*)part, (float4*)dw, per / 4, splits, blocks,
-                     (const float4*)cs_part, (float4*)cs_out, ky / 4);
+                     (const float4*)cs_part, cs_out, ky / 4);
   return hipGetLastError();
 }
 
