@@ -342,7 +342,7 @@ bool flat_eligible(const IgemmP& p) {
   // Volumes of wider rows stay with patches: 64 -> 64 at 48 x 96 x 96 took 130 us with the 128 x 64 tile and 107 there, while
   // 64^3 took 61 with the 256 x 64 tile and 66 there.
   if (p3d && (!wide_fits(p.osp[2]) || 4LL * p.osp[1] * p.osp[2] * p.red >= 0x3fffffffLL)) return false;
-  return (long long)27 * p.nout * p.red < 0x3fffffffLL && 600LL * p.red < 0x3fffffffLL;
+  return (long long)27 * p.nout * p.red < 0x3fffffffLL && 600LL * (p.red > p.nout ? p.red : p.nout) < 0x3fffffffLL;
 }
 
 hipError_t launch_flat(IgemmP& p, hipStream_t s) {

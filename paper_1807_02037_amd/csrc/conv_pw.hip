@@ -326,7 +326,8 @@ hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
 }
 
 bool pw_channels(const IgemmP& p, long long columns) {
-  // 16-byte vectors of both operands, 32-bit filter offsets, tiles not mostly padding
+  // 16-byte vectors of both operands, 32-bit offsets into the filter and into the 128 rows of a tile, tiles not mostly padding
+  if (128LL * (p.red > p.nout ? p.red : p.nout) >= 0x3fffffffLL) return false;
   return !p.small && aligned16(p) && (p.red & 7) == 0 && (p.nout & 7) == 0 && p.nout >= 32 && p.red >= 32 && columns * p.red < 0x3fffffffLL;
 }
 

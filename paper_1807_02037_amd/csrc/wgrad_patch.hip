@@ -654,9 +654,9 @@ bool pair_packed(const int* asp, const int* osp, const int* filt, const int* pad
 }
 
 // Channel counts whose rows are 16-byte vectors take the kernel with two groups of waves; it addresses a patch (six input
-// planes at most) with 31 bits.
+// planes of ten rows at most, four of dy and eight rows) with 31 bits.
 bool grouped(const int* asp, const int* osp, int cx, int ky) {
-  return (cx & 7) == 0 && 12LL * asp[1] * asp[2] * cx < 0x7fffffffLL && 8LL * osp[1] * osp[2] * ky < 0x7fffffffLL;
+  return (cx & 7) == 0 && 2LL * ((5LL * asp[1] + 10) * asp[2] + 18) * cx < 0x7fffffffLL && 2LL * ((3LL * osp[1] + 8) * osp[2] + 16) * ky < 0x7fffffffLL;
 }
 
 template <int P3D, bool CS>

@@ -369,16 +369,17 @@ hipError_t launch_rows_shape(const WRowsP& p, int shape, int mode, hipStream_t s
 
 }  // namespace
 
-// Rows of the wider grid that a block of 64 positions may span, times the channels: 32-bit offsets from its first one.
-static bool rows_span_ok(const int* big, const int* stride, long long channels) {
-  return (64LL * stride[0] * stride[1] * stride[2] + 2LL * stride[0] * big[1] * big[2] + 2LL * stride[1] * big[2]) * channels < 0x3fffffffLL;
+// Rows of the wider grid that a block of 64 positions may span, times its channels, and the 64 rows of the other operand: 32-bit
+// offsets from the first one.
+static bool rows_span_ok(const int* big, const int* stride, long long channels, long long other) {
+  return 64 * other < 0x3fffffffLL && (64LL * stride[0] * stride[1] * stride[2] + 2LL * stride[0] * big[1] * big[2] + 2LL * stride[1] * big[2]) * channels < 0x3fffffffLL;
 }
 
 bool wgrad_rows_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride, const int* pad) {
   if (getenv("LMS_NO_WGRAD_ROWS")) return false;
   for (int i = 0; i < 3; ++i)
     if (filt[i] != 1 || stride[i] < 1 || pad[i] != 0) return false;
-  return (cx & 7) == 0 && (ky & 7) == 0 && cx >= 48 && ky >= 48 && rows_span_ok(asp, stride, cx);
+  return (cx & 7) == 0 && (ky & 7) == 0 && cx >= 48 && ky >= 48 && rows_span_ok(asp, stride, cx, ky);
 }
 
 int wgrad_rows_splits(long long rows, int cx, int ky) { return rows_plan(rows, cx, ky).splits; }
@@ -409,7 +410,7 @@ bool wgrad_rows_tconv_eligible(int cx, int kk, const int* osp, const int* filt, 
     if (filt[i] != stride[i] || stride[i] < 1 || stride[i] > 2) return false;
     taps *= filt[i];
   }
-  return (cx & 7) == 0 && (kk & 7) == 0 && cx >= 48 && taps * kk >= 48 && rows_span_ok(osp, stride, kk);
+  return (cx & 7) == 0 && (kk & 7) == 0 && cx >= 48 && taps * kk >= 48 && rows_span_ok(osp, stride, kk, cx);
 }
 
 hipError_t launch_wgrad_rows_tconv(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int kk, const int* asp,

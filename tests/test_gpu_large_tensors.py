@@ -109,3 +109,56 @@ def test_entry_points_on_tensors_of_2gib_and_more(case):
         for tap in taps:
             ref = S.conv_wgrad_tap(x, dy, stride, pad, tap)
             assert np.abs(got[tap] - ref).max() <= 1e-4 * scale_ref, (name, "wgrad", tap)
+
+
+# One tile, millions of channels: its rows lie more than 2^31 bytes apart, beyond the 32-bit offsets of the kernels that load whole
+# tiles from one descriptor.  Compared on the last position (the largest offsets) or on the last filter columns.
+@pytest.mark.parametrize("what", ["pw_fwd", "pw_dgrad", "3x3_fwd", "pw_wgrad", "3x3x3_wgrad"])
+def test_rows_of_a_tile_beyond_31_bits(what):
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(31)
+    s = torch.cuda.current_stream().cuda_stream
+    n, sp, c, k, filt, pad = {
+        "pw_fwd": (1, (8, 8), 17825792, 32, 1, 0), "pw_dgrad": (1, (8, 16), 8519680, 32, 1, 0), "3x3_fwd": (1, (16, 16), 8, 4400000, 3, 1),
+        "pw_wgrad": (1, (8, 8), 48, 17825792, 1, 0), "3x3x3_wgrad": (1, (8, 1, 10400000), 16, 8, 3, 2)}[what]
+    nd = len(sp)
+    osp = tuple(e + 2 * pad - filt + 1 for e in sp)
+    d = L.conv_desc(n, sp, c, k, (filt,) * nd, 1, pad, 0)
+    which = A.CONV_FWD if "fwd" in what else A.CONV_DGRAD if "dgrad" in what else A.CONV_WGRAD
+    ws = torch.empty(max(256, L.conv_workspace_bytes(d, which) if which != A.CONV_DGRAD else 0), dtype=torch.uint8, device="cuda")
+
+    def close(got, ref):                               # one bf16 rounding at most, and fp32 sums of up to 10^8 products in any order
+        assert float((got.double() - ref).norm() / ref.norm()) <= 4e-3
+
+    if which == A.CONV_WGRAD:
+        x, dy = _rand(gen, (n,) + sp + (c,)), _rand(gen, (n,) + osp + (k,))
+        dw = torch.full((filt ** nd, c, k), float("nan"), device="cuda")
+        L.conv_wgrad(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws.data_ptr(), s)
+        torch.cuda.synchronize()
+        if filt == 1:
+            close(dw[0, :, -4096:], x.reshape(-1, c).double().t() @ dy.reshape(-1, k)[:, -4096:].double())
+        else:                                          # input position + pad - tap, the one row of the input under the tap's row
+            for kd, kh, kw in ((2, 2, 2), (0, 1, 0)):
+                at = [slice(pad - t, pad - t + e) for t, e in zip((kd, kh, kw), sp)]
+                close(dw[(kd * 3 + kh) * 3 + kw], x.reshape(-1, c).double().t() @ dy[0, at[0], at[1], at[2]].reshape(-1, k).double())
+        return
+    w = _rand(gen, (filt,) * nd + (c, k))
+    if which == A.CONV_DGRAD:
+        dy, dx = _rand(gen, (n,) + osp + (k,)), torch.full((n,) + sp + (c,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), None, None, None, dx.data_ptr(), ws.data_ptr(), s)
+        torch.cuda.synchronize()
+        close(dx.reshape(-1, c)[-1], w.reshape(c, k).double() @ dy.reshape(-1, k)[-1].double())
+        return
+    x, y = _rand(gen, (n,) + sp + (c,)), torch.full((n,) + osp + (k,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), s)
+    torch.cuda.synchronize()
+    ref = torch.zeros(k, dtype=torch.float64, device="cuda")
+    for i in range(filt if pad else 1):                # the last position: taps beyond the corner lie outside
+        for j in range(filt if pad else 1):
+            h, v = sp[0] - 1 + i - pad, sp[1] - 1 + j - pad
+            if h < sp[0] and v < sp[1]:
+                ref += x[0, h, v].double() @ w[i, j].double()
+    close(y.reshape(-1, k)[-1], ref)
