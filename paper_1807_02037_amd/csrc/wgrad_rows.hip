@@ -32,6 +32,25 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 
 constexpr int RT = 512;      // threads per work-group
 
+// Position of a row in a grid, stepped by a constant number of rows without divisions.
+struct RowPos {
+  int n, d, h, w;
+};
+__host__ __device__ __forceinline__ RowPos row_pos(unsigned m, const int* sp) {
+  RowPos q;
+  q.w = m % (unsigned)sp[2]; m /= (unsigned)sp[2];
+  q.h = m % (unsigned)sp[1]; m /= (unsigned)sp[1];
+  q.d = m % (unsigned)sp[0];
+  q.n = m / (unsigned)sp[0];
+  return q;
+}
+__device__ __forceinline__ void row_step(RowPos& q, const RowPos& by, const int* sp) {
+  q.w += by.w; q.h += by.h; q.d += by.d; q.n += by.n;
+  if (q.w >= sp[2]) { q.w -= sp[2]; ++q.h; }
+  if (q.h >= sp[1]) { q.h -= sp[1]; ++q.d; }
+  if (q.d >= sp[0]) { q.d -= sp[0]; ++q.n; }
+}
+
 struct WRowsP {
   const uint16_t* X;
   const uint16_t* DY;
@@ -45,6 +64,7 @@ struct WRowsP {
   // positions of x (extents asp), column j of the virtual dy is channel j % kk of tap j / kk, read at the output
   // position (extents osp) x-position * stride + tap
   int kk;
+  RowPos step, vstep;        // both gathering variants: the rows of a round, and those between a thread's vectors, in extents
   // column sums of dy on the side (plain and strided variants): partial sums [split][ky], written by the
   // work-groups of the first channel tile of x; the caller adds them over the splits
   float* cs_part;
@@ -62,7 +82,7 @@ struct RowsTile {
   static constexpr int XV = X_BYTES / (16 * GT), YV = Y_BYTES / (16 * GT);   // loads per thread and block
   static constexpr int BUF = X_BYTES + Y_BYTES;
   static constexpr int RING = G * 2 * BUF;
-  static constexpr int SUMS = (G - 1) * TC * TK * 4;         // the groups' sums on their way to group 0
+  static constexpr int SUMS = G * TC * TK * 4;               // the groups' sums
   static constexpr int LDS_BYTES = RING > SUMS ? RING : SUMS;
   static_assert(WPG * G == 8 && LDS_BYTES <= 163840, "eight waves, the LDS of a compute unit");
 };
@@ -78,25 +98,6 @@ __device__ __forceinline__ bf16x8 tr_frag8(const unsigned char* p0, const unsign
 // fall into different quarters of the banks.
 template <int T>
 __device__ __forceinline__ int rows_swz(int r) { return T >= 128 ? r & 3 : (r >> 1) & 1; }
-
-// Position of a row in a grid, stepped by a constant number of rows without divisions.
-struct RowPos {
-  int n, d, h, w;
-};
-__device__ __forceinline__ RowPos row_pos(unsigned m, const int* sp) {
-  RowPos q;
-  q.w = m % (unsigned)sp[2]; m /= (unsigned)sp[2];
-  q.h = m % (unsigned)sp[1]; m /= (unsigned)sp[1];
-  q.d = m % (unsigned)sp[0];
-  q.n = m / (unsigned)sp[0];
-  return q;
-}
-__device__ __forceinline__ void row_step(RowPos& q, const RowPos& by, const int* sp) {
-  q.w += by.w; q.h += by.h; q.d += by.d; q.n += by.n;
-  if (q.w >= sp[2]) { q.w -= sp[2]; ++q.h; }
-  if (q.h >= sp[1]) { q.h -= sp[1]; ++q.d; }
-  if (q.d >= sp[0]) { q.d -= sp[0]; ++q.n; }
-}
 
 // CS: the work-groups of channel tile 0 of x also add up the rows of dy (every row of dy passes through exactly one of them
 // per column tile): the bias / shift gradient as products of dy with a fragment of ones.
@@ -132,27 +133,30 @@ __global__ __launch_bounds__(RT, 2) void wgrad_rows_kernel(WRowsP p) {
   const bool x_ok = c0 + xc < p.cx, y_ok = k0 + yc < p.ky;
   unsigned x_off = x_ok ? (unsigned)((xr * p.cx + c0 + xc) * 2) : DMA_OOB;
   unsigned y_off = y_ok ? (unsigned)((yr * p.ky + k0 + yc) * 2) : DMA_OOB;
-  // strided / gathered variants: where the thread's rows are, and the first row of the block (uniform), which 32-bit
-  // offsets count from
+  // strided / gathered variants: where the thread's rows are, and the first of them in the wave (uniform; lane 0 has it), which
+  // 32-bit offsets count from.  One division per extent finds a thread's first row, the others are stepped to: with
+  // six positions found by division a small layer spent a third of its time on them ((2, 7, 9) 128 -> 64 10.1 us, now 9.6).
   constexpr int XP = MODE == ROWS_STRIDED_X ? XV : 1, YP = MODE == ROWS_GATHERED_DY ? YV : 1;
-  RowPos xpos[XP], ypos[YP], step{}, first{};
+  RowPos xpos[XP], ypos[YP], first{};
   const int* small = MODE == ROWS_GATHERED_DY ? p.asp : p.osp;
   const int* big = MODE == ROWS_GATHERED_DY ? p.osp : p.asp;
   auto big_row = [&](const RowPos& q) {
     return (((long long)q.n * big[0] + q.d * p.stride[0]) * big[1] + q.h * p.stride[1]) * (long long)big[2] + q.w * p.stride[2];
   };
   unsigned y_tap = 0;
-  if constexpr (MODE != ROWS_PLAIN) {
-    step = row_pos(G * PB, small);
-    first = row_pos((unsigned)(lo + g * PB), small);
-  }
-  if constexpr (MODE == ROWS_STRIDED_X) {
+  auto positions = [&](RowPos* pos, int count, int row) {
+    pos[0] = row_pos((unsigned)(lo + g * PB + row), small);
 #pragma unroll
-    for (int j = 0; j < XV; ++j) xpos[j] = row_pos((unsigned)(lo + g * PB + xr + j * XRS), small);
-  }
+    for (int j = 1; j < count; ++j) {
+      pos[j] = pos[j - 1];
+      row_step(pos[j], p.vstep, small);
+    }
+    auto lane0 = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    first = RowPos{lane0(pos[0].n), lane0(pos[0].d), lane0(pos[0].h), lane0(pos[0].w)};
+  };
+  if constexpr (MODE == ROWS_STRIDED_X) positions(xpos, XV, xr);
   if constexpr (MODE == ROWS_GATHERED_DY) {
-#pragma unroll
-    for (int j = 0; j < YV; ++j) ypos[j] = row_pos((unsigned)(lo + g * PB + yr + j * YRS), small);
+    positions(ypos, YV, yr);
     // the column lies in one tap (kk is a multiple of 8): offset of the tap within the output grid
     int t = y_ok ? (k0 + yc) / p.kk : 0;
     const int cc = y_ok ? k0 + yc - t * p.kk : 0;
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(RT, 2) void wgrad_rows_kernel(WRowsP p) {
     long long big0 = 0;
     if constexpr (MODE != ROWS_PLAIN) {
       big0 = big_row(first);
-      row_step(first, step, small);
+      row_step(first, p.step, small);
     }
     if constexpr (MODE == ROWS_STRIDED_X) {
       const v4u rs = buffer_rsrc(p.X + big0 * p.cx, 0x7fffffff);
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(RT, 2) void wgrad_rows_kernel(WRowsP p) {
       for (int j = 0; j < XV; ++j) {
         const unsigned o = (unsigned)((big_row(xpos[j]) - big0) * p.cx * 2) + (unsigned)((c0 + xc) * 2);
         load_lds16(rs, dst + j * T::GT * 16, x_ok && xr + j * XRS < left ? o : DMA_OOB, 0);
-        row_step(xpos[j], step, small);
+        row_step(xpos[j], p.step, small);
       }
     } else {
       const v4u rs = buffer_rsrc(p.X + r0 * p.cx, left * p.cx * 2);
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(RT, 2) void wgrad_rows_kernel(WRowsP p) {
       for (int j = 0; j < YV; ++j) {
         const unsigned o = (unsigned)((big_row(ypos[j]) - big0) * p.kk * 2) + y_tap;
         load_lds16(rs, dst + T::X_BYTES + j * T::GT * 16, y_ok && yr + j * YRS < left ? o : DMA_OOB, 0);
-        row_step(ypos[j], step, small);
+        row_step(ypos[j], p.step, small);
       }
     } else {
       const v4u rs = buffer_rsrc(p.DY + r0 * p.ky, left * p.ky * 2);
@@ -260,39 +264,45 @@ __global__ __launch_bounds__(RT, 2) void wgrad_rows_kernel(WRowsP p) {
     }
   }
 
-  // ---- the groups' sums: 1 .. G - 1 leave theirs in LDS, group 0 adds them in order ----
+  // ---- the groups' sums meet in LDS; every group adds its share of the entries, in the order of the groups, and stores it (group 0
+  // alone adding and storing all of them cost small layers 1.5 us) ----
+  constexpr int SHARE = 16 / G;
   float* sums = reinterpret_cast<float*>(lds_rows);
-  auto slot = [&](int grp, int q) { return reinterpret_cast<float4*>(sums + (grp - 1) * (TC * TK) + (wq * 16 + q) * 256 + lane * 4); };
-  __syncthreads();
-  if (g > 0) {
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const f32x16& a = acc[q >> 3][(q >> 2) & 1];
-      *slot(g, q) = make_float4(a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]);
-    }
-  }
-  __syncthreads();
   float* out = p.part + (long long)split * p.cx * p.ky;
-  if (g == 0) {
-#pragma unroll 1
-    for (int grp = 1; grp < G; ++grp) {
+  auto own = [&](int q) {
+    const f32x16& a = acc[q >> 3][(q >> 2) & 1];
+    return make_float4(a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]);
+  };
+  auto slot = [&](int grp, int q) { return reinterpret_cast<float4*>(sums + grp * (TC * TK) + (wq * 16 + q) * 256 + lane * 4); };
+  auto put = [&](int q, const float4& t) {
+    const int c = c0 + wc + 32 * (q >> 3) + 8 * (q & 3) + 4 * (lane >> 5), k = k0 + wk + 32 * ((q >> 2) & 1) + (lane & 31);
+    const float v[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        f32x16& a = acc[q >> 3][(q >> 2) & 1];
-        const float4 t = *slot(grp, q);
-        a[4 * (q & 3)] += t.x; a[4 * (q & 3) + 1] += t.y; a[4 * (q & 3) + 2] += t.z; a[4 * (q & 3) + 3] += t.w;
-      }
+    for (int e = 0; e < 4; ++e)
+      if (c + e < p.cx && k < p.ky) out[(long long)(c + e) * p.ky + k] = v[e];
+  };
+  auto plus = [](const float4& t, const float4& u) { return make_float4(t.x + u.x, t.y + u.y, t.z + u.z, t.w + u.w); };
+  __syncthreads();
+  if constexpr (G == 2) {                                     // a group keeps its own half
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      if (g != q / SHARE) *slot(g, q) = own(q);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      if (g == q / SHARE) put(q, plus(q < SHARE ? own(q) : *slot(0, q), q < SHARE ? *slot(1, q) : own(q)));
+  } else {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) *slot(g, q) = own(q);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < SHARE; ++r) {
+      const int q = g * SHARE + r;
+      float4 t = *slot(0, q);
+#pragma unroll
+      for (int grp = 1; grp < G; ++grp) t = plus(t, *slot(grp, q));
+      put(q, t);
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int c = c0 + wc + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          const int k = k0 + wk + 32 * j + (lane & 31);
-          if (c < p.cx && k < p.ky) out[(long long)c * p.ky + k] = acc[i][j][v];
-        }
   }
   if (CS && ct == 0) {
     __syncthreads();                                          // the sums above have been read
@@ -331,7 +341,9 @@ RowsPlan rows_plan(long long rows, int cx, int ky) {
     if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = RowsPlan{i, ct, kt, 0, 0}; }
   }
   const long long tiles = (long long)best.ctiles * best.ktiles, round = shapes[best.shape][2];
-  long long splits = (256 + tiles - 1) / tiles;              // one work-group of eight waves per CU
+  // at most one work-group of eight waves per CU, all that its LDS holds: 260 of them (432 x 616 at 10920 rows) took
+  // 31 us, 240 20
+  long long splits = 256 / tiles;
   const long long blocks = (rows + round - 1) / round;
   if (splits > blocks) splits = blocks;
   if (splits < 1) splits = 1;
@@ -343,7 +355,10 @@ RowsPlan rows_plan(long long rows, int cx, int ky) {
 }
 
 template <typename T, int MODE, bool CS>
-hipError_t launch_rows_t(const WRowsP& p, hipStream_t s) {
+hipError_t launch_rows_t(WRowsP p, hipStream_t s) {
+  const int* small = MODE == ROWS_GATHERED_DY ? p.asp : p.osp;
+  p.step = row_pos(T::G * T::PB, small);
+  p.vstep = row_pos(T::GT / ((MODE == ROWS_GATHERED_DY ? T::TK : T::TC) / 8), small);
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_rows_kernel<T, MODE, CS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
   if (attr != hipSuccess) return attr;
