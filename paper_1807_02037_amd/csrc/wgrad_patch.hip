@@ -683,10 +683,12 @@ PatchGrid patch_grid(long long batch, const int* asp, const int* osp, const int*
   const int tile = wide_tile(filt, cx, ky) ? 64 : 32;
   const long long wg = (long long)((cx + tile - 1) / tile) * ((ky + tile - 1) / tile);
   // partial sums cost 4 bytes x filter size per work-group, written and read again: two work-groups per compute unit
-  // (32 x 32 tiles) measured 5 % faster on the 3D U-Net step than four; with two groups of waves in one that is one
-  long long target = tile == 64 || grouped(asp, osp, cx, ky) ? 256 : 512;
+  // (32 x 32 tiles) measured 5 % faster on the 3D U-Net step than four; with two groups of waves in one that is one, and
+  // no more than one, which is what its LDS leaves room for (240 x 80 at 29 x 25 x 27: 264 of them 65 us, 240 47)
+  const bool one = tile == 32 && grouped(asp, osp, cx, ky);
+  long long target = tile == 64 || one ? 256 : 512;
   if (const char* e = getenv("LMS_WGRAD_PATCH_WGS")) target = atoll(e);
-  long long splits = (target + wg - 1) / wg;
+  long long splits = one ? target / wg : (target + wg - 1) / wg;
   if (splits > g.patches) splits = g.patches;
   if (splits < 1) splits = 1;
   g.per_split = (int)((g.patches + splits - 1) / splits);
