@@ -325,6 +325,23 @@ hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   return tiles(64, 128) >= 256 ? launch_pw_t<Tile1, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
 }
 
+// Data gradients under a stride take two launches here, the product and the positions that no dy row lies under; the general
+// kernel takes one.  us, general / here (stride 2, batch n; 250 layers measured):
+//   64 <- 128, n 16, 28 x 28   6.3 / 8.8       64 <- 128, n 32, 56 x 56   14 / 12       256 <- 512, n 2, 14 x 14   12.8 / 10.0
+//   32 <- 64, n 16, 56 x 56    6.4 / 8.7       64 <- 128, n 128, 56 x 56  40 / 33       512 <- 256, n 2, 14 x 14   9.2 / 8.5
+//   128 <- 192, n 6, 30 x 29   7.9 / 9.0       128 <- 192, n 16, 56 x 56  14 / 13       64 <- 512, n 6, 30 x 29    9.1 / 10.1
+// So the second launch has to pay: 0.8 G products over all positions (2 G where few columns fill the tile badly: 48 <- 72,
+// n 128, 56 x 56 32 / 35), or a filter so large that the general kernel waits for its long reductions.  Beyond the
+// caches, tensors much wider than dy are bound by the writes, and it writes whole rows in order (1024 <- 64, n 64,
+// 56 x 56 235 / 271; odd extents cost it more: 512 <- 128, n 64, 57 x 55 158 / 127).
+bool strided_dgrad_general(const IgemmP& p) {
+  const double macs = (double)p.M * p.nout * p.red;
+  bool whole = true;
+  for (int i = 0; i < 3; ++i) whole = whole && p.osp[i] % p.stride[i] == 0;
+  if (p.nout >= 4 * p.red && p.M * p.nout >= (whole ? 100000000LL : 200000000LL)) return true;
+  return macs < (p.nout < 64 && p.red < 128 ? 2e9 : 8e8) && (long long)p.nout * p.red < 100000;
+}
+
 bool pw_channels(const IgemmP& p, long long columns) {
   // 16-byte vectors of both operands, 32-bit offsets into the filter and into the 128 rows of a tile, tiles not mostly padding
   if (128LL * (p.red > p.nout ? p.red : p.nout) >= 0x3fffffffLL) return false;
@@ -344,6 +361,7 @@ bool pw_eligible(const IgemmP& p) {
     strided = strided || p.stride[i] != 1;
   }
   const int* big = p.mode == 0 ? p.asp : p.osp;
+  if (strided && p.mode == 1 && strided_dgrad_general(p)) return false;
   rows += 2LL * p.stride[1] * big[2] + 2LL * p.stride[0] * big[1] * (long long)big[2];
   return pw_channels(p, p.nout) && (!strided || rows * (p.red > p.nout ? p.red : p.nout) < 0x3fffffffLL);
 }
