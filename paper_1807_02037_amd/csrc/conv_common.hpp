@@ -155,9 +155,10 @@ inline bool aligned16(const IgemmP& p) { return aligned16(p.A, p.B, p.out, p.add
 
 // Patch-tiled kernel for 3x3 / 3x3x3 stride-1 filters (conv_halo.hip).
 bool halo_eligible(const IgemmP& p);
+double patch_use(const IgemmP& p, int td, int th, int tw);   // fraction of the patch grid that covers real output positions
 hipError_t launch_halo(IgemmP& p, hipStream_t s);
 
-// 2-D 3x3 stride-1 convolutions with padding 1, tiles of consecutive positions (conv_flat.hip).
+// 3x3 and 3x3x3 stride-1 convolutions with padding 1, tiles of consecutive positions (conv_flat.hip).
 bool flat_eligible(const IgemmP& p);
 hipError_t launch_flat(IgemmP& p, hipStream_t s);
 

@@ -305,7 +305,39 @@ typedef FlatTile<128, 32, 4, 1, 6, 3> Flat128x32;
 // The widest tile leaves room for a second work-group on a compute unit up to 87 positions a row.
 bool wide_fits(int w) { return flat_group_lds<Flat256x64>(w) <= 81920; }
 
+bool long_fits(int w) { return flat_group_lds<Flat256x32>(w) <= 81920; }    // 256 x 32: up to 119
+
 long long flat_tiles(const IgemmP& p, int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.nout + bn - 1) / bn); }
+
+// At most 32 output channels: tiles of 256 positions where two of their work-groups share a compute unit, unless tiles of 128
+// all run at once (us, 256 / 128 positions: 2-D 16 -> 16, 62 x 31, batch 46 8.2 / 7.4; 32 <- 64, 96 x 96, batch 8 8.1 / 8.9;
+// 64 -> 32, 120 x 120, batch 12 18.4 / 17.3).
+bool narrow_256(const IgemmP& p) {
+  const int w = p.osp[2];
+  return long_fits(w) && flat_tiles(p, 256, 32) >= 256 && flat_tiles(p, 128, 32) > 256LL * (163840 / flat_group_lds<Flat128x32>(w));
+}
+
+// Layers that patches (conv_halo.hip) are faster on, us, this kernel / patches:
+//   3-D, at most 32 outputs, up to 64 Ki positions: data gradients (24 <- 40, 16^3 9.4 / 8.3; 16 <- 208, 16^3 24 / 18) and, but for
+//   short reductions on less than one tile per compute unit, forward passes (128 -> 16, 24 x 40 x 36 21 / 18; but
+//   32 -> 32, 16^3 8.3 / 9.2); beyond one round of tiles where patches are full (64 -> 16, 80^3 64 / 59; but 48^3, 432 tiles, 18.7 / 22.3)
+//   3-D, more outputs: long reductions on full patches of large volumes (192 -> 192, 80^3 855 / 811; but 64 -> 64 108 / 109)
+//   2-D data gradients of one short block (16 <- 16, 112 x 112, batch 8 6.7 / 6.4); long reductions on full patches where rows
+//   are too long for 256 x 64 (256 -> 256, 112 x 112, batch 16 248 / 240; but 104 x 104, 93 % full, 114 / 118); rows of 120
+//   positions, where 256 x 32 does not fit either (256 -> 256, batch 12 227 / 215; 32 <- 64 19 / 18)
+bool patches_win(const IgemmP& p) {
+  if (!halo_eligible(p)) return false;
+  const bool p3d = p.filt[0] == 3, dgrad = p.mode == 1;
+  const double full = p3d ? patch_use(p, 4, 4, 8) : patch_use(p, 1, 8, 16);
+  if (!p3d) {
+    const int w = p.osp[2];
+    if (!long_fits(w) && (p.red >= 192 || p.nout <= 32) && full >= 0.9) return true;
+    return full >= 0.95 && ((dgrad && p.nout <= 32 && p.red <= 16 && p.M >= 65536) || (!wide_fits(w) && p.nout > 32 && p.red >= 192));
+  }
+  if (p.nout > 32) return p.red >= 128 && p.M >= 262144 && full >= 0.95;
+  if (p.M <= 65536) return dgrad || p.red > 64 || p.M > 32768;
+  return flat_tiles(p, 256, 32) > 512 && full >= 0.95;
+}
 
 template <bool P3D, bool FLIP>
 hipError_t launch_flat_f(IgemmP& p, hipStream_t s) {
@@ -320,13 +352,21 @@ hipError_t launch_flat_f(IgemmP& p, hipStream_t s) {
   //   3-D 96 -> 144, 13 x 13 x 12                       67 / 94        29 / 36      24 / 29     20 / 21     19 / 20
   //   2-D 512 -> 512, 7 x 7, batch 32                                                       25 / 30     23 / 27
   // So the widest tile of which there is one per compute unit; below that, the reduction is shared by two groups of
-  // waves where it is long enough (8 blocks) to pay for adding their sums.
+  // waves where it is long enough (8 blocks) to pay for adding their sums and one such work-group, all that a compute
+  // unit holds, is enough for each (2-D 256 -> 256, 45 x 37, batch 3, 316 tiles: 21 / 17 us, with 128 x 64 18 / 13).
+  // Where rows are too long for the widest tile, 256 x 32 has the shorter runs of filter and twice the tiles (us, 128 x 64 /
+  // 256 x 32 / patches: 2-D 256 -> 256, 96 x 96, batch 24 284 / 268 / 263; 128 -> 128, 112 x 112, batch 16 76 / 73 / 73;
+  // 96 -> 96, 112 x 112, batch 16 59 / 48 / 57).
   const bool wide = wide_fits(p.osp[2]);
-  if (p.nout <= 32) return flat_tiles(p, 256, 32) >= 256 ? launch_flat_t<Flat256x32, P3D, FLIP>(p, s) : launch_flat_t<Flat128x32, P3D, FLIP>(p, s);
+  if (p.nout <= 32) return narrow_256(p) ? launch_flat_t<Flat256x32, P3D, FLIP>(p, s) : launch_flat_t<Flat128x32, P3D, FLIP>(p, s);
+  if (!wide && long_fits(p.osp[2]) && flat_tiles(p, 256, 32) >= 512) return launch_flat_t<Flat256x32, P3D, FLIP>(p, s);
   if (wide && flat_tiles(p, 256, 64) >= 256) return launch_flat_t<Flat256x64, P3D, FLIP>(p, s);
   if (flat_tiles(p, 128, 64) >= 256) return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
   const int blocks = (p.red + BK - 1) / BK * (P3D ? 3 : 1);
-  if (blocks >= 8 && flat_tiles(p, 64, 64) <= 512) return launch_flat_t<Flat64g2, P3D, FLIP>(p, s);
+  if (blocks >= 8) {
+    if (flat_tiles(p, 64, 64) <= 256) return launch_flat_t<Flat64g2, P3D, FLIP>(p, s);
+    if (flat_tiles(p, 64, 64) <= 512) return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
+  }
   return launch_flat_t<Flat64, P3D, FLIP>(p, s);
 }
 
@@ -342,6 +382,7 @@ bool flat_eligible(const IgemmP& p) {
   // Volumes of wider rows stay with patches: 64 -> 64 at 48 x 96 x 96 took 130 us with the 128 x 64 tile and 107 there, while
   // 64^3 took 61 with the 256 x 64 tile and 66 there.
   if (p3d && (!wide_fits(p.osp[2]) || 4LL * p.osp[1] * p.osp[2] * p.red >= 0x3fffffffLL)) return false;
+  if (patches_win(p)) return false;
   return (long long)27 * p.nout * p.red < 0x3fffffffLL && 600LL * (p.red > p.nout ? p.red : p.nout) < 0x3fffffffLL;
 }
 

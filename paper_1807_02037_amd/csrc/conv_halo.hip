@@ -386,8 +386,7 @@ hipError_t launch_halo_t(HaloP& hp, hipStream_t s) {
 
 }  // namespace
 
-// Fraction of the patch grid that covers real output positions.
-static double patch_use(const IgemmP& p, int td, int th, int tw) {
+double patch_use(const IgemmP& p, int td, int th, int tw) {
   double u = 1.0;
   const int t[3] = {td, th, tw};
   for (int i = 0; i < 3; ++i) u *= (double)p.osp[i] / (double)(((p.osp[i] + t[i] - 1) / t[i]) * t[i]);

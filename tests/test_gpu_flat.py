@@ -12,6 +12,12 @@ CASES = [
     (70, (14, 14), 136, 256), (131, (23, 21), 40, 32), (9, (7, 7), 264, 264), (1, (40, 87), 96, 96),
     (1, (1, 1, 1), 8, 8), (2, (2, 1, 3), 88, 48), (1, (5, 6, 7), 96, 24), (3, (3, 11, 13), 40, 104), (1, (33, 31, 30), 72, 64),
     (2, (3, 4, 87), 24, 16), (2, (3, 4, 88), 24, 16), (1, (41, 40, 39), 8, 40),
+    # tiles of 256 positions, the last one partly filled: 256 x 64 up to rows of 87, 256 x 32 up to 119 (narrow outputs, or any
+    # where 256 x 64 does not fit); rows of 88, 119, 120 and 121 beside them
+    (9, (87, 87), 40, 72), (13, (77, 71), 72, 64), (9, (88, 88), 72, 64), (13, (89, 119), 40, 32), (10, (99, 119), 24, 72), (9, (75, 120), 40, 32),
+    (9, (75, 120), 200, 72), (8, (76, 121), 40, 64), (1, (40, 43, 41), 40, 32), (1, (42, 40, 41), 40, 72), (2, (20, 41, 87), 24, 72),
+    # between one and two of the 64 x 64 tiles for a compute unit, long reduction: 128 x 64; one at most: two groups
+    (3, (45, 37), 256, 256), (2, (23, 21), 264, 136),
 ]
 
 
