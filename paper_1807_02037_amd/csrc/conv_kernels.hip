@@ -927,8 +927,9 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
                            int transpose, float* colsum_out, bool& colsum_done, hipStream_t s);
 
 // colsum_out (or null): the sums of dy over all positions, per channel (the bias / shift gradient of the same
-// layer).  The kernels that stage dy through registers add it up on the side; the others are followed by the plain
-// column-sum pass, which reuses the workspace.
+// layer).  The specialised kernels but the one for class heads leave it on the side, from the vectors of dy on their way
+// through registers or as products of dy with ones; the others are followed by the plain column-sum pass, which reuses
+// the workspace.
 hipError_t launch_wgrad(const uint16_t* X, const uint16_t* DY, float* dw, void* ws, long long rows, int cx, int ky,
                         const int* asp, const int* osp, const int* filt, const int* stride, const int* pad,
                         int transpose, float* colsum_out, hipStream_t s) {

@@ -40,9 +40,9 @@ __device__ __forceinline__ int pw_swz(int row) { return (row >> 1) & 7; }
 
 enum { PW_FWD = 0, PW_DGRAD = 1, PW_UP = 2 };
 
-template <int BM_, int BN_, int WM_, int WN_, int NBUF_>
+template <int BM_, int BN_, int WM_, int WN_>
 struct PwTile {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NBUF = NBUF_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int NT = 64 * WM * WN;                         // threads
   static constexpr int WTM = BM / WM, WTN = BN / WN;              // outputs of a wave
   static constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -50,7 +50,7 @@ struct PwTile {
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int AV = A_BYTES / (16 * NT), BV = B_BYTES / (16 * NT);   // loads per thread and stage
   static constexpr int EPI_WAVE = epi_wave_bytes(WTN);
-  static constexpr int LDS_BYTES = NBUF * STAGE > WM * WN * EPI_WAVE ? NBUF * STAGE : WM * WN * EPI_WAVE;
+  static constexpr int LDS_BYTES = 2 * STAGE > WM * WN * EPI_WAVE ? 2 * STAGE : WM * WN * EPI_WAVE;
   static constexpr int LPR = WTN / 8;                             // lanes per output row in the epilogue
   static constexpr int RPI = 64 / LPR;                            // rows per instruction
   static constexpr int QV = 32 / RPI;                             // vectors per lane and 32 positions
@@ -83,7 +83,7 @@ __device__ __forceinline__ long long pw_strided_row(long long m, const int* smal
 template <typename T, int MODE, bool STRIDED>
 __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   constexpr bool UP = MODE == PW_UP;
-  constexpr int BN = T::BN, PM = T::BM, NBUF = T::NBUF, TM = T::TM, TN = T::TN, AV = T::AV, BV = T::BV;
+  constexpr int BN = T::BN, PM = T::BM, TM = T::TM, TN = T::TN, AV = T::AV, BV = T::BV;
   constexpr int ROWB = BN * 2;                                    // bytes of a filter row of the [r][n] tile
   extern __shared__ __attribute__((aligned(16))) unsigned char pw_smem[];
 
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
 #pragma unroll
   for (int j = 0; j < BV; ++j) {
     const int v = tid + j * T::NT;
-    if constexpr (MODE == PW_DGRAD) {                             // rows n of 32 reduction channels
+    if constexpr (MODE == PW_DGRAD) {                             // rows n of PK reduction channels
       const int row = v / SL;
       b_k[j] = ((v % SL) ^ pw_swz(row)) * 8;
       b_off[j] = n0 + row < nv ? (unsigned)(((n0 + row) * p.red + b_k[j]) * 2) : DMA_OOB;
@@ -209,18 +209,13 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  constexpr int LD = AV + BV;
-#pragma unroll
-  for (int s = 0; s < NBUF - 1; ++s)
-    if (s < niter) fetch(s, s);
+  fetch(0, 0);                                                    // red >= 32: pw_channels
   auto stage = [&](int it, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
-    // stage `it` has landed once at most the loads of the (up to two) stages after it are in flight; the barrier says so
-    // for every wave, and that every wave is done with the buffer that the next request writes
-    if (NBUF > 3 && it + 2 < niter) wait_barrier<(NBUF > 3 ? 2 : 0) * LD>();
-    else if (NBUF > 2 && it + 1 < niter) wait_barrier<(NBUF > 2 ? 1 : 0) * LD>();
-    else wait_barrier<0>();
-    if (it + NBUF - 1 < niter) fetch(it + NBUF - 1, (buf + NBUF - 1) % NBUF);
+    // stage `it` has landed; the barrier says so for every wave, and that every wave is done with the buffer that the
+    // next request writes
+    wait_barrier<0>();
+    if (it + 1 < niter) fetch(it + 1, buf ^ 1);
     const unsigned char* a = pw_smem + buf * T::STAGE;
     const unsigned char* b = a + T::A_BYTES;
     constexpr int NKS = PK / 16;
@@ -251,11 +246,9 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
       __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
     }
   };
-  for (int it = 0; it < niter; it += NBUF) {
+  for (int it = 0; it < niter; it += 2) {
     stage(it, std::integral_constant<int, 0>{});
     if (it + 1 < niter) stage(it + 1, std::integral_constant<int, 1>{});
-    if constexpr (NBUF > 2) { if (it + 2 < niter) stage(it + 2, std::integral_constant<int, 2>{}); }
-    if constexpr (NBUF > 3) { if (it + 3 < niter) stage(it + 3, std::integral_constant<int, 3>{}); }
   }
   __syncthreads();                                                // the ring is free for the epilogue
 
@@ -293,15 +286,15 @@ hipError_t launch_pw_t(IgemmP& p, hipStream_t s) {
   if (mt * p.ntiles_n > 0x7fffff00LL || p.M >= 0x7fffffffLL) return hipErrorInvalidValue;
   p.ntiles = (int)(mt * p.ntiles_n);
   const int grid = 8 * ((p.ntiles + 7) / 8);
-  const int ring = p.red > PK ? T::NBUF * T::STAGE : T::STAGE, epi = T::WM * T::WN * T::EPI_WAVE;
+  const int ring = p.red > PK ? 2 * T::STAGE : T::STAGE, epi = T::WM * T::WN * T::EPI_WAVE;
   hipLaunchKernelGGL((pw_kernel<T, MODE, STRIDED>), dim3(grid), dim3(T::NT), ring > epi ? ring : epi, s, p);
   return hipGetLastError();
 }
 
-typedef PwTile<128, 128, 2, 2, 2> Tile0;
-typedef PwTile<64, 128, 2, 2, 2> Tile1;
-typedef PwTile<128, 64, 2, 2, 2> Tile2;
-typedef PwTile<64, 64, 2, 2, 2> Tile3;
+typedef PwTile<128, 128, 2, 2> Tile0;
+typedef PwTile<64, 128, 2, 2> Tile1;
+typedef PwTile<128, 64, 2, 2> Tile2;
+typedef PwTile<64, 64, 2, 2> Tile3;
 
 // Tile by shape (us on ResNet-50 layers, three sets of tensors in turn so that nothing stays cached; batch 128 at 56 x 56 and
 // 28 x 28, 256 below; before: 128-position tiles staged through registers, data gradients of narrowing layers on the general
