@@ -330,27 +330,31 @@ typedef RowsTile<64, 64, 32> Rows64;
 struct RowsPlan { int shape, ctiles, ktiles, splits, rows_per_split; };
 
 RowsPlan rows_plan(long long rows, int cx, int ky) {
-  // tile shape with the least traffic: x is read once per k-tile, dy once per c-tile; of equals the one with the fewest
-  // products (a smaller tile has more groups of waves)
+  // The shape with the least traffic: x is read once per k-tile, dy once per c-tile, mostly out of the L2 (counted at 0.7 of a
+  // byte; 0.4 and 0.55 lose up to 10 % on long reductions), and every split writes a partial filter that is read again.
+  // Long reductions take wide tiles, short ones under large filters narrow tiles with more groups of waves and fewer
+  // splits (both gradients, us, by operand reads alone / this rule: 256 x 256 at 7680 rows 16.2 / 10.8, 1024 x 256 at 3136 16.0 / 13.3,
+  // transposed convolution 256 -> 128 at 16^3 19.3 / 16.6 and 64 -> 32 at 32^3 22.3 / 13.9; 48 x 72 at 4096 8.8 / 9.5).
   static const int shapes[6][3] = {{64, 64, 256}, {64, 128, 128}, {128, 64, 128}, {128, 128, 128}, {256, 64, 128}, {64, 256, 128}};   // third: positions of a round
   RowsPlan best{};
-  long long best_cost = -1;
+  double best_cost = -1;
   for (int i = 0; i < 6; ++i) {
     const int ct = (cx + shapes[i][0] - 1) / shapes[i][0], kt = (ky + shapes[i][1] - 1) / shapes[i][1];
-    const long long cost = (long long)cx * kt + (long long)ky * ct;
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = RowsPlan{i, ct, kt, 0, 0}; }
+    const long long tiles = (long long)ct * kt, round = shapes[i][2];
+    // at most one work-group of eight waves per CU, all that its LDS holds: 260 of them (432 x 616 at 10920 rows) took
+    // 31 us, 240 20
+    long long splits = 256 / tiles;
+    const long long blocks = (rows + round - 1) / round;
+    if (splits > blocks) splits = blocks;
+    if (splits < 1) splits = 1;
+    const long long per = ((blocks + splits - 1) / splits) * round;
+    splits = (rows + per - 1) / per;
+    if (splits < 1) splits = 1;
+    // more tiles than compute units: whole rounds of them
+    const double rounds = tiles > 256 ? (double)((tiles + 255) / 256) * 256. / (double)tiles : 1.;
+    const double cost = 0.7 * rounds * 2. * (double)rows * ((double)cx * kt + (double)ky * ct) + 8. * (double)splits * cx * ky;
+    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = RowsPlan{i, ct, kt, (int)splits, (int)per}; }
   }
-  const long long tiles = (long long)best.ctiles * best.ktiles, round = shapes[best.shape][2];
-  // at most one work-group of eight waves per CU, all that its LDS holds: 260 of them (432 x 616 at 10920 rows) took
-  // 31 us, 240 20
-  long long splits = 256 / tiles;
-  const long long blocks = (rows + round - 1) / round;
-  if (splits > blocks) splits = blocks;
-  if (splits < 1) splits = 1;
-  const long long per = ((blocks + splits - 1) / splits) * round;
-  best.rows_per_split = (int)per;
-  best.splits = (int)((rows + per - 1) / per);
-  if (best.splits < 1) best.splits = 1;
   return best;
 }
 
