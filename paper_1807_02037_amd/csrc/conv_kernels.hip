@@ -1001,7 +1001,9 @@ uint64_t conv_wgrad_ws(const ConvGeom& g, bool with_colsum) {
   uint64_t splits = (uint64_t)plan.splits;
   // the other specialised kernels keep room for the general one's partial filters as well: which geometries fit the static
   // scratch array is known to callers
-  if (plan.route != WGRAD_PATCH) {
+  if (plan.route == WGRAD_PATCH) {
+    if (wgrad_run_eligible(g.n, g.in_sp, g.out_sp, g.filt, g.pad, g.c, g.k)) splits = (uint64_t)wgrad_patch_room(g.n, g.out_sp[1], g.out_sp[2], g.c, g.k);
+  } else {
     const uint64_t gs = (uint64_t)wgrad_split(g.out_rows(), g.taps(), g.c, g.k).splits;
     if (gs > splits) splits = gs;
   }

@@ -1,0 +1,46 @@
+"""Weight gradient of 3x3 layers on runs of positions with a zero column and row: maps of one pixel, row and column, rows as long
+as the kernel takes and one more, runs that end on and beside a step of 128 positions, the ring's wrap, many small images in a
+step, channel counts that fill no tile, both tile widths, tensors that do not start on 16 bytes.  Reference: float64 sums of the
+GPU's own bf16 inputs; bound: 2e-6 of the norm (fp32 sums of at most 10^5 exact products)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# n, extents, c, k, elements before the tensors' first
+CASES = [
+    (1, (1, 1), 48, 48, 0), (17, (1, 5), 64, 64, 0), (9, (5, 1), 64, 56, 0), (70, (3, 3), 64, 64, 0), (1, (7, 15), 64, 64, 0), (1, (15, 7), 64, 72, 0),
+    (2, (5, 126), 56, 128, 0), (1, (3, 127), 64, 64, 0), (3, (63, 63), 64, 64, 0), (1, (126, 126), 48, 200, 0), (40, (7, 7), 512, 72, 0),
+    (60, (14, 14), 256, 256, 0), (8, (56, 56), 64, 64, 0), (12, (30, 31), 192, 320, 0), (3, (14, 14), 64, 64, 1), (2, (20, 30), 128, 72, 3),
+]
+
+
+@pytest.mark.parametrize("n,sp,c,k,off", CASES)
+def test_weight_and_bias_gradient(n, sp, c, k, off):
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k + sp[0])
+
+    def tensor(channels, mean):
+        flat = torch.empty(n * sp[0] * sp[1] * channels + 8, dtype=torch.bfloat16, device="cuda")
+        t = flat[off:off + n * sp[0] * sp[1] * channels].view(n, *sp, channels)
+        return t.copy_(torch.randn(t.shape, generator=g, device="cuda") + mean)
+
+    x, dy = tensor(c, 0.0), tensor(k, 0.5)
+    d = L.conv_desc(n, sp, c, k, (3, 3), 1, 1, 0)
+    need = L.conv_workspace_bytes(d, A.CONV_WGRAD_BIAS)
+    ws = torch.full((need + 4096,), 255, dtype=torch.uint8, device="cuda")
+    dw, db, dw2 = torch.full((3, 3, c, k), float("nan"), device="cuda"), torch.full((k,), float("nan"), device="cuda"), torch.full((3, 3, c, k), float("nan"), device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    L.conv_wgrad_bias(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws.data_ptr(), s)
+    L.conv_wgrad(d, x.data_ptr(), dy.data_ptr(), dw2.data_ptr(), ws.data_ptr(), s)
+    torch.cuda.synchronize()
+    assert bool((ws[need:] == 255).all())
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    dyd = dy.double().reshape(-1, k)
+    ref = torch.stack([xp[:, r:r + sp[0], q:q + sp[1]].reshape(-1, c).t() @ dyd for r in range(3) for q in range(3)]).view(3, 3, c, k)
+    refb = dyd.sum(dim=0)
+    assert float((dw.double() - ref).norm()) <= 2e-6 * float(ref.norm())
+    assert float((db.double() - refb).norm()) <= 2e-6 * float(refb.norm())
+    assert torch.equal(dw, dw2)
