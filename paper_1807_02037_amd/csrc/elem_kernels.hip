@@ -592,43 +592,51 @@ __global__ __launch_bounds__(TB) void grad_sum_vec_kernel(Ptrs4v in, int n_in, c
   out[i] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Vector forms of the squared-error kernels (8 elements per load); same partial layout as the scalar ones.
-__global__ __launch_bounds__(TB) void mse_partial_vec_kernel(const uint4* y, const uint4* t, long long n8, float* part) {
+// Vector form of the squared error (8 elements per load): the sum for the loss (part: one per work-group, or null) and the gradient
+// (dy, or null) in one pass, which reads y and t once.  The same grid and order of sums with and without the gradient, so that
+// the loss has the same bits.  25.7 M elements with the ReLU mask of y: loss 36 us and gradient 48 us apart, 55 us in one pass (308 MB:
+// 53 us at the rate of a large copy).
+template <bool LOSS, bool GRAD>
+__global__ __launch_bounds__(TB) void mse_vec_kernel(const uint4* y, const uint4* t, const uint4* mask, long long n8, float coef, float* part,
+                                                     uint4* dy) {
   __shared__ float sh[TB];
   float s = 0.f;
-  for (long long i = (long long)blockIdx.x * TB + threadIdx.x; i < n8; i += (long long)gridDim.x * TB) {
+  const long long step = (long long)gridDim.x * TB;
+  auto one = [&](long long i, const uint4& yq, const uint4& tq, const uint4& mq) {
     float a[8], b[8];
-    unpack8(y[i], a);
-    unpack8(t[i], b);
+    unpack8(yq, a);
+    unpack8(tq, b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float d = a[e] - b[e];
-      s += d * d;
+      a[e] -= b[e];
+      if (LOSS) s += a[e] * a[e];
     }
+    if (GRAD) {
+      unpack8(mq, b);
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] = mask && !(b[e] > 0.f) ? 0.f : coef * a[e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = (uint32_t)f2bf(a[2 * e]) | ((uint32_t)f2bf(a[2 * e + 1]) << 16);
+      dy[i] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+  };
+  const bool other = GRAD && mask && mask != y;          // the ReLU behind the loss usually is y itself
+  long long i = (long long)blockIdx.x * TB + threadIdx.x;
+  for (; i + step < n8; i += 2 * step) {                 // two elements' loads at a time
+    const uint4 y0 = y[i], t0 = t[i], y1 = y[i + step], t1 = t[i + step];
+    const uint4 m0 = other ? mask[i] : y0, m1 = other ? mask[i + step] : y1;
+    one(i, y0, t0, m0);
+    one(i + step, y1, t1, m1);
   }
-  const float tot = block_sum(s, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(TB) void mse_grad_vec_kernel(const uint4* y, const uint4* t, const uint4* mask, long long n8, float coef,
-                                                          uint4* dy) {
-  const long long i = (long long)blockIdx.x * TB + threadIdx.x;
-  if (i >= n8) return;
-  float a[8], b[8];
-  unpack8(y[i], a);
-  unpack8(t[i], b);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = coef * (a[e] - b[e]);
-  if (mask) {
-    unpack8(mask[i], b);
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (!(b[e] > 0.f)) a[e] = 0.f;
+  if (i < n8) {
+    const uint4 y0 = y[i];
+    one(i, y0, t[i], other ? mask[i] : y0);
   }
-  uint32_t w[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) w[e] = (uint32_t)f2bf(a[2 * e]) | ((uint32_t)f2bf(a[2 * e + 1]) << 16);
-  dy[i] = make_uint4(w[0], w[1], w[2], w[3]);
+  if (LOSS) {
+    const float tot = block_sum(s, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = tot;
+  }
 }
 
 // Global average pooling, y[b][c] = mean over the positions of image b.  A work-group owns vb = 2^lvb neighbouring vectors of E
@@ -1126,45 +1134,62 @@ uint64_t reduce_ws(int64_t rows, int cols) {
 hipError_t mse_loss(int64_t numel, const void* y, const void* t, float* loss, void* ws, hipStream_t s) {
   const int parts = parts_for(numel);
   if ((numel & 7) == 0 && (((uintptr_t)y | (uintptr_t)t) & 15) == 0)
-    hipLaunchKernelGGL(mse_partial_vec_kernel, dim3(parts), dim3(TB), 0, s, (const uint4*)y, (const uint4*)t, (long long)(numel / 8), (float*)ws);
+    hipLaunchKernelGGL((mse_vec_kernel<true, false>), dim3(parts), dim3(TB), 0, s, (const uint4*)y, (const uint4*)t, (const uint4*)nullptr,
+                       (long long)(numel / 8), 0.f, (float*)ws, (uint4*)nullptr);
   else
-  hipLaunchKernelGGL(mse_partial_kernel, dim3(parts), dim3(TB), 0, s, (const uint16_t*)y, (const uint16_t*)t, (long long)numel, (float*)ws);
+    hipLaunchKernelGGL(mse_partial_kernel, dim3(parts), dim3(TB), 0, s, (const uint16_t*)y, (const uint16_t*)t, (long long)numel, (float*)ws);
   hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(TB), 0, s, (const float*)ws, parts, (float)numel, loss);
   return hipGetLastError();
 }
 hipError_t mse_grad(int64_t numel, const void* y, const void* t, const void* mask, void* dy, hipStream_t s) {
   if ((numel & 7) == 0 && (((uintptr_t)y | (uintptr_t)t | (uintptr_t)mask | (uintptr_t)dy) & 15) == 0) {
-    hipLaunchKernelGGL(mse_grad_vec_kernel, dim3(cdiv(numel / 8, TB)), dim3(TB), 0, s, (const uint4*)y, (const uint4*)t,
-                       (const uint4*)mask, (long long)(numel / 8), 2.0f / (float)numel, (uint4*)dy);
+    hipLaunchKernelGGL((mse_vec_kernel<false, true>), dim3(cdiv(numel / 8, TB)), dim3(TB), 0, s, (const uint4*)y, (const uint4*)t,
+                       (const uint4*)mask, (long long)(numel / 8), 2.0f / (float)numel, (float*)nullptr, (uint4*)dy);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(mse_grad_kernel, dim3(cdiv(numel, TB)), dim3(TB), 0, s, (const uint16_t*)y, (const uint16_t*)t,
                      (const uint16_t*)mask, (long long)numel, 2.0f / (float)numel, (uint16_t*)dy);
   return hipGetLastError();
 }
-hipError_t softmax_ce_loss(int64_t rows, int classes, const void* z, const int32_t* labels, float* loss, void* ws, hipStream_t s) {
-  int parts;
-  if (classes <= 64) {
-    parts = parts_for(rows);
-    hipLaunchKernelGGL(ce_rows_kernel, dim3(parts), dim3(TB), 0, s, (const uint16_t*)z, labels, (long long)rows, classes, (float*)ws,
-                       (const uint16_t*)nullptr, (uint16_t*)nullptr, 0.f);
-  } else {
-    parts = (int)rows;
-    hipLaunchKernelGGL(ce_wide_kernel, dim3((unsigned)rows), dim3(TB), 0, s, (const uint16_t*)z, labels, classes, (float*)ws,
-                       (const uint16_t*)nullptr, (uint16_t*)nullptr, 0.f);
+hipError_t mse_loss_grad(int64_t numel, const void* y, const void* t, const void* mask, void* dy, float* loss, void* ws, hipStream_t s) {
+  if ((numel & 7) != 0 || (((uintptr_t)y | (uintptr_t)t | (uintptr_t)mask | (uintptr_t)dy) & 15) != 0) {
+    const hipError_t e = mse_loss(numel, y, t, loss, ws, s);
+    return e == hipSuccess ? mse_grad(numel, y, t, mask, dy, s) : e;
   }
-  hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(TB), 0, s, (const float*)ws, parts, (float)rows, loss);
+  const int parts = parts_for(numel);
+  hipLaunchKernelGGL((mse_vec_kernel<true, true>), dim3(parts), dim3(TB), 0, s, (const uint4*)y, (const uint4*)t, (const uint4*)mask,
+                     (long long)(numel / 8), 2.0f / (float)numel, (float*)ws, (uint4*)dy);
+  hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(TB), 0, s, (const float*)ws, parts, (float)numel, loss);
   return hipGetLastError();
 }
-hipError_t softmax_ce_grad(int64_t rows, int classes, const void* z, const int32_t* labels, const void* mask, void* dz, hipStream_t s) {
+
+// Loss and / or gradient of softmax cross-entropy; with few classes the partial sums of the loss come from the same work-groups
+// with and without the gradient (64^3 rows of 4 classes: 128 work-groups took 14 us for the loss and 7 for the gradient, 6 together now).
+static hipError_t softmax_ce(int64_t rows, int classes, const void* z, const int32_t* labels, const void* mask, void* dz, float* loss, void* ws, hipStream_t s) {
   const float inv = 1.0f / (float)rows;
-  if (classes <= 64)
-    hipLaunchKernelGGL(ce_rows_kernel, dim3(cdiv(rows, TB)), dim3(TB), 0, s, (const uint16_t*)z, labels, (long long)rows, classes,
-                       (float*)nullptr, (const uint16_t*)mask, (uint16_t*)dz, inv);
-  else
-    hipLaunchKernelGGL(ce_wide_kernel, dim3((unsigned)rows), dim3(TB), 0, s, (const uint16_t*)z, labels, classes, (float*)nullptr,
+  int parts;
+  if (classes <= 64) {
+    const unsigned full = cdiv(rows, TB);
+    parts = loss && full > (unsigned)MAX_PARTS ? MAX_PARTS : (int)full;
+    hipLaunchKernelGGL(ce_rows_kernel, dim3(parts), dim3(TB), 0, s, (const uint16_t*)z, labels, (long long)rows, classes,
+                       loss ? (float*)ws : nullptr, (const uint16_t*)mask, (uint16_t*)dz, inv);
+  } else {
+    parts = (int)rows;
+    hipLaunchKernelGGL(ce_wide_kernel, dim3((unsigned)rows), dim3(TB), 0, s, (const uint16_t*)z, labels, classes, loss ? (float*)ws : nullptr,
                        (const uint16_t*)mask, (uint16_t*)dz, inv);
+  }
+  if (loss) hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(TB), 0, s, (const float*)ws, parts, (float)rows, loss);
   return hipGetLastError();
+}
+hipError_t softmax_ce_loss(int64_t rows, int classes, const void* z, const int32_t* labels, float* loss, void* ws, hipStream_t s) {
+  return softmax_ce(rows, classes, z, labels, nullptr, nullptr, loss, ws, s);
+}
+hipError_t softmax_ce_grad(int64_t rows, int classes, const void* z, const int32_t* labels, const void* mask, void* dz, hipStream_t s) {
+  return softmax_ce(rows, classes, z, labels, mask, dz, nullptr, nullptr, s);
+}
+hipError_t softmax_ce_loss_grad(int64_t rows, int classes, const void* z, const int32_t* labels, const void* mask, void* dz, float* loss, void* ws,
+                                hipStream_t s) {
+  return softmax_ce(rows, classes, z, labels, mask, dz, loss, ws, s);
 }
 hipError_t grad_sum(int64_t numel, int n, const void* const* g, const void* mask, void* out, hipStream_t s) {
   if (n < 1 || n > 4) return hipErrorInvalidValue;

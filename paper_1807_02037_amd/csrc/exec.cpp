@@ -141,6 +141,12 @@ struct Exec {
   hipEvent_t stage_start[2] = {nullptr, nullptr};   // per direction: the node's stream has waited for its dependencies
   hipEvent_t stage_done[2] = {nullptr, nullptr};    // the second lane has finished its chunks
 
+  // A loss whose gradient follows comes out of the gradient's pass over the same tensors: per node, the loss that the gradient
+  // operation also computes (or -1), and on the loss itself a mark to skip it.
+  std::vector<int> side_loss;
+  std::vector<char> loss_later;
+  void* loss_ws = nullptr;
+
   hipStream_t stream_of(const Node& n) const {
     if (n.op == LMS_OP_SWAP_OUT) return s_d2h;
     if (n.op == LMS_OP_SWAP_IN) return s_h2d;
@@ -295,6 +301,37 @@ void build_sync(Exec& e) {
   e.ev.assign(n, nullptr);
   for (int v = 0; v < n; ++v)
     if (need[v] && hipEventCreateWithFlags(&e.ev[v], hipEventDisableTiming) != hipSuccess) { e.ev[v] = nullptr; e.events_ok = false; }
+}
+
+// Pairs a loss with its gradient operation where the gradient reads the same two tensors and nobody reads, or is ordered by, the
+// loss before.  The partial sums of the loss go to a few kilobytes of the executor's own: in the plan the gradient's block may
+// lie where the loss has its workspace.
+void pair_losses(Exec& e) {
+  const Graph& g = e.g;
+  const int n = (int)g.nodes.size();
+  e.side_loss.assign(n, -1);
+  e.loss_later.assign(n, 0);
+  std::vector<std::vector<int>> readers, outs;
+  adjacency(g, readers, outs);
+  uint64_t bytes = 0;
+  for (const Node& v : g.nodes) {
+    if (v.op != LMS_OP_MSE_GRAD && v.op != LMS_OP_SOFTMAX_CE_GRAD) continue;
+    const int op = v.op == LMS_OP_MSE_GRAD ? LMS_OP_MSE : LMS_OP_SOFTMAX_CE;
+    for (const Node& l : g.nodes) {
+      if (l.op != op || l.in[0] != v.in[0] || l.in[1] != v.in[1] || g.nodes[l.in[0]].dtype != LMS_BF16) continue;
+      if (e.plan.pos[l.id] > e.plan.pos[v.id] || e.ev[l.id] || !outs[l.id].empty() || e.loss_later[l.id]) continue;
+      e.side_loss[v.id] = l.id;
+      e.loss_later[l.id] = 1;
+      bytes = std::max(bytes, workspace_bytes(g, l));
+      break;
+    }
+  }
+  if (bytes && hipMalloc(&e.loss_ws, bytes) != hipSuccess) {
+    (void)hipGetLastError();                                   // without it loss and gradient run apart
+    e.loss_ws = nullptr;
+    e.side_loss.assign(n, -1);
+    e.loss_later.assign(n, 0);
+  }
 }
 
 // fp32 check mode: the operation's activations are fp32 (the graph was built on an fp32 input batch and fp32 filters).
@@ -488,22 +525,32 @@ lms_status run_node(Exec& e, const Node& n) {
       e.n_kernels += 1;
       break;
     case LMS_OP_MSE:
+      if (e.loss_later[n.id]) break;
       err = mse_loss(IN(0).numel(), P(0), P(1), (float*)out, e.ws(n.id), s);
       e.n_kernels += 2;
       break;
-    case LMS_OP_MSE_GRAD:
-      err = mse_grad(IN(0).numel(), P(0), P(1), (f & LMS_F_MASK) ? P(2) : nullptr, out, s);
-      e.n_kernels += 1;
+    case LMS_OP_MSE_GRAD: {
+      const int l = e.side_loss[n.id];
+      const void* mask = (f & LMS_F_MASK) ? P(2) : nullptr;
+      if (l >= 0) err = mse_loss_grad(IN(0).numel(), P(0), P(1), mask, out, (float*)e.ptr(l), e.loss_ws, s);
+      else err = mse_grad(IN(0).numel(), P(0), P(1), mask, out, s);
+      e.n_kernels += l >= 0 ? 2 : 1;
       break;
+    }
     case LMS_OP_SOFTMAX_CE:
+      if (e.loss_later[n.id]) break;
       err = softmax_ce_loss(IN(0).numel() / IN(0).channels(), (int)IN(0).channels(), P(0), (const int32_t*)P(1), (float*)out, e.ws(n.id), s);
       e.n_kernels += 2;
       break;
-    case LMS_OP_SOFTMAX_CE_GRAD:
-      err = softmax_ce_grad(IN(0).numel() / IN(0).channels(), (int)IN(0).channels(), P(0), (const int32_t*)P(1),
-                            (f & LMS_F_MASK) ? P(2) : nullptr, out, s);
-      e.n_kernels += 1;
+    case LMS_OP_SOFTMAX_CE_GRAD: {
+      const int l = e.side_loss[n.id];
+      const int64_t rows = IN(0).numel() / IN(0).channels();
+      const void* mask = (f & LMS_F_MASK) ? P(2) : nullptr;
+      if (l >= 0) err = softmax_ce_loss_grad(rows, (int)IN(0).channels(), P(0), (const int32_t*)P(1), mask, out, (float*)e.ptr(l), e.loss_ws, s);
+      else err = softmax_ce_grad(rows, (int)IN(0).channels(), P(0), (const int32_t*)P(1), mask, out, s);
+      e.n_kernels += l >= 0 ? 2 : 1;
       break;
+    }
     case LMS_OP_GRAD_SUM: {
       const int ng = (int)n.in.size() - ((f & LMS_F_MASK) ? 1 : 0);
       const void* gp[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -615,6 +662,7 @@ lms_status exec_create(const Graph& g, void* arena, uint64_t arena_bytes, void* 
   if (const char* cb = getenv("LMS_ENCODE_BLOCKS")) { const int v = atoi(cb); if (v > 0 && v <= 4096) e->encode_blocks = v; }
   if (const char* cb = getenv("LMS_DECODE_BLOCKS")) { const int v = atoi(cb); if (v > 0 && v <= 4096) e->decode_blocks = v; }
   build_sync(*e);
+  pair_losses(*e);
   if (flags & LMS_X_TIMING) {
     const int n = (int)g.nodes.size();
     e->wait_span.assign(n, Exec::WaitSpan());
@@ -685,6 +733,7 @@ lms_status exec_destroy(Exec* e) {
     if (ev) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : e->copy_end)
     if (ev) (void)hipEventDestroy(ev);
+  if (e->loss_ws) (void)hipFree(e->loss_ws);
   if (e->step_begin) (void)hipEventDestroy(e->step_begin);
   if (e->step_end) (void)hipEventDestroy(e->step_end);
   if (e->join_d2h) (void)hipEventDestroy(e->join_d2h);

@@ -71,6 +71,11 @@ hipError_t mse_grad(int64_t numel, const void* y, const void* t, const void* mas
 hipError_t softmax_ce_loss(int64_t rows, int classes, const void* z, const int32_t* labels, float* loss, void* ws, hipStream_t s);
 hipError_t softmax_ce_grad(int64_t rows, int classes, const void* z, const int32_t* labels, const void* mask, void* dz, hipStream_t s);
 
+// Loss and gradient in one pass over the inputs; the same bits as apart.  dy may be y.
+hipError_t mse_loss_grad(int64_t numel, const void* y, const void* t, const void* mask, void* dy, float* loss, void* ws, hipStream_t s);
+hipError_t softmax_ce_loss_grad(int64_t rows, int classes, const void* z, const int32_t* labels, const void* mask, void* dz, float* loss, void* ws,
+                                hipStream_t s);
+
 // out = (g0 + .. + g{n-1}) * [mask > 0]
 hipError_t grad_sum(int64_t numel, int n, const void* const* g, const void* mask, void* out, hipStream_t s);
 // out[c] (fp32) = sum over rows of dy[row][c]; ws: reduce_ws(rows, c) bytes
