@@ -200,12 +200,22 @@ hipError_t launch_wgrad_rows_tconv(const uint16_t* X, const uint16_t* DY, float*
 bool conv_small_eligible(const IgemmP& p);
 hipError_t launch_conv_small(IgemmP& p, hipStream_t s);
 
+// The same for 2-D layers whose stride times channels is even: filter rows read straight from the staged input rows (conv_stem.hip).
+bool conv_stem_eligible(const IgemmP& p);
+hipError_t launch_conv_stem(IgemmP& p, hipStream_t s);
+
 // Weight gradient for convolutions with at most 4 input channels (wgrad_small.hip): per-split partial filters [split][tap][cx][ky].
 // cs_part (or null): partial column sums of dy [split][ky] on the side.
 bool wgrad_small_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride);
 int wgrad_small_splits(long long rows, const int* osp);
 hipError_t launch_wgrad_small(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp,
                               const int* osp, const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s);
+
+// The same for 2-D layers whose stride times channels is six (wgrad_stem.hip); at most as many splits as wgrad_small.hip.
+bool wgrad_stem_eligible(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad);
+int wgrad_stem_splits(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad);
+hipError_t launch_wgrad_stem(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp, const int* osp,
+                             const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s);
 
 // Streaming weight gradient for 1x1 filters without padding (wgrad_rows.hip): per-split partial filters [split][cx][ky].
 bool wgrad_rows_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride, const int* pad);

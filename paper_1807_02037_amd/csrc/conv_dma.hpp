@@ -1,13 +1,10 @@
-// Pieces of the convolution kernels whose operands go from memory straight to LDS (conv_pw.hip, conv_flat.hip; internal).
+// Loads from memory straight to LDS, for the convolution kernels built on them (internal).
 #pragma once
-#include "conv_common.hpp"
+#include "conv_tile.hpp"
 
 namespace lms {
 namespace {
 
-constexpr unsigned DMA_OOB = 0x80000000u;        // a buffer offset outside every buffer
-
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // 16 bytes per lane from buffer offset voff + soff to LDS bytes lds + 16 * lane (lds: the same for the whole wave; offsets
 // outside the buffer write zeros).  Written in assembly because the compiler, seeing such a load, waits for all of
 // them before any LDS transpose read; it has no register output, and wait_barrier does the waiting.  The compiler does not
@@ -24,69 +21,6 @@ __device__ __forceinline__ void load_lds16(v4u rsrc, unsigned lds, unsigned voff
 __device__ __forceinline__ v4u buffer_rsrc(const void* base, long long bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
   return v4u{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, (unsigned)(bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000u};
-}
-
-// At most N of this wave's memory loads may still be in flight, and its LDS reads have come back; then every wave of the
-// work-group has got here.
-template <int N>
-__device__ __forceinline__ void wait_barrier() {
-  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-// LDS bytes that wave_epilogue needs per wave: 32 positions x WTN channels of fp32, rows 16 bytes apart modulo 256.
-constexpr int epi_wave_bytes(int wtn) { return 32 * (wtn + 4) * 4; }
-
-// The tensors of the epilogue as the rows of one tile see them: buffers that start at the tile's first row, so that offsets
-// have 32 bits and everything beyond them (rows past the last, columns past the last, a tensor that is not there) reads
-// zeros and drops writes.  No branch: behind one the compiler waits for every older load before the next, and
-// the 16 vectors of a thread came one latency after the other.
-struct EpiBuffers {
-  __amdgpu_buffer_rsrc_t add, mask, out;
-  __device__ __forceinline__ EpiBuffers(const IgemmP& p, long long row0, long long bytes) {
-    const int n = (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff);
-    const long long at = row0 * p.nout;
-    add = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.add ? p.add + at : p.out), 0, p.add ? n : 0, 0x00020000);
-    mask = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.mask ? p.mask + at : p.out), 0, p.mask ? n : 0, 0x00020000);
-    out = __builtin_amdgcn_make_buffer_rsrc(p.out + at, 0, n, 0x00020000);
-  }
-  __device__ __forceinline__ static uint4 get(__amdgpu_buffer_rsrc_t rs, unsigned off) {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
-  }
-  __device__ __forceinline__ void put(unsigned off, const uint4& d) const {            // 2: nontemporal, around the L2s
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, d), out, (int)off, 0, 2);
-  }
-};
-
-// Epilogue of a wave's TM x TN transposed accumulators (lane l of a 32 x 32 one holds position l % 32, channels
-// 8 * (v / 4) + 4 * (l / 32) + v % 4): 32 positions at a time go through the wave's own LDS (in order: no barrier) and leave
-// as 8-channel vectors, WTN / 8 lanes to a position.  n: this lane's first channel (n_ok: it exists); er: tile row of the
-// lane's first vector; add / mask: the vectors of those rows, fetched ahead; off(r): byte offset of the lane's vector in
-// row r of the tile.
-template <int WTN, int TM, int TN, typename Off>
-__device__ __forceinline__ void wave_epilogue(const IgemmP& p, const EpiBuffers& eb, const f32x16 (&acc)[TM][TN], unsigned char* lds, const uint4* add,
-                                              const uint4* mask, int n, bool n_ok, int er, Off&& off) {
-  constexpr int LDC = WTN + 4, LPR = WTN / 8, RPI = 64 / LPR, QV = 32 / RPI;
-  const int lane = threadIdx.x & 63, half = lane >> 5, cg = (lane % LPR) * 8;
-  float* sC = reinterpret_cast<float*>(lds);
-  EpiCoef coef;
-  if (n_ok) epilogue_coef(p, n, 8, coef);
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        *reinterpret_cast<float4*>(sC + (lane & 31) * LDC + j * 32 + 8 * v + 4 * half) =
-            make_float4(acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]);
-#pragma unroll
-    for (int q = 0; q < QV; ++q) {
-      const float* row = sC + (lane / LPR + q * RPI) * LDC + cg;
-      const float4 lo = *reinterpret_cast<const float4*>(row), hi = *reinterpret_cast<const float4*>(row + 4);
-      const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-      eb.put(off(er + i * 32 + q * RPI), epilogue_pack8(p, coef, v, add[i * QV + q], mask[i * QV + q]));
-    }
-  }
 }
 
 }  // namespace

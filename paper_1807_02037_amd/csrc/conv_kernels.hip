@@ -563,14 +563,15 @@ __global__ void wgrad_reduce_kernel(const float* part, float* dw, long long per_
   }
 }
 
-// Same sum for the common case (no transpose, element count a multiple of 4): every thread adds one eighth
-// of the splits for four neighbouring elements, the eight partial sums are then added in a fixed order.  The
+// Same sum for the common case (no transpose, element count a multiple of 4): a work-group of 32 G threads adds 32 vectors of four
+// neighbouring elements, a thread every G-th of the splits, the G partial sums then in a fixed order.  The
 // work-groups from `blocks` on do the same for the column sums of dy (cs_per4 vectors of four, the same splits), which
 // the same pass left behind: one launch for both parameter gradients instead of two (a launch of its own cost the column
 // sums 2.5 to 4.5 us a layer, whatever their size).
-__global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* part, float4* dw, long long per4, int splits, int blocks,
-                                                               const float4* cs_part, float* cs_out, int cs_per4) {
-  __shared__ float4 sh[8][32];
+template <int G>
+__global__ __launch_bounds__(32 * G) void wgrad_reduce_vec_kernel(const float4* part, float4* dw, long long per4, int splits, int blocks,
+                                                                  const float4* cs_part, float* cs_out, int cs_per4) {
+  __shared__ float4 sh[G][32];
   const int o = threadIdx.x & 31, g = threadIdx.x >> 5;
   const bool cs = (int)blockIdx.x >= blocks;                // uniform
   if (cs) { part = cs_part; per4 = cs_per4; }
@@ -578,21 +579,32 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* par
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (idx < per4) {
     int i = g;
-    for (; i + 24 < splits; i += 32) {
-      const float4 a = part[(long long)i * per4 + idx], b = part[(long long)(i + 8) * per4 + idx];
-      const float4 c = part[(long long)(i + 16) * per4 + idx], d = part[(long long)(i + 24) * per4 + idx];
+    for (; i + 3 * G < splits; i += 4 * G) {
+      const float4 a = part[(long long)i * per4 + idx], b = part[(long long)(i + G) * per4 + idx];
+      const float4 c = part[(long long)(i + 2 * G) * per4 + idx], d = part[(long long)(i + 3 * G) * per4 + idx];
       s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
       s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
       s.x += c.x; s.y += c.y; s.z += c.z; s.w += c.w;
       s.x += d.x; s.y += d.y; s.z += d.z; s.w += d.w;
     }
-    for (; i < splits; i += 8) {
+    for (; i < splits; i += G) {
       const float4 a = part[(long long)i * per4 + idx];
       s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
     }
   }
   sh[g][o] = s;
   __syncthreads();
+  if (G == 32) {                                            // eight partial sums of four, then those
+    if (g < 8) {
+      float4 t = sh[4 * g][o];
+#pragma unroll
+      for (int j = 1; j < 4; ++j) { t.x += sh[4 * g + j][o].x; t.y += sh[4 * g + j][o].y; t.z += sh[4 * g + j][o].z; t.w += sh[4 * g + j][o].w; }
+      s = t;
+    }
+    __syncthreads();
+    if (g < 8) sh[g][o] = s;
+    __syncthreads();
+  }
   if (g == 0 && idx < per4) {
     float4 t = sh[0][o];
 #pragma unroll
@@ -605,13 +617,19 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float4* par
   }
 }
 
-// cs_part / cs_out (or null): the partial column sums of dy of the same splits, ky of them (a multiple of 4).
+// cs_part / cs_out (or null): the partial column sums of dy of the same splits, ky of them (a multiple of 4).  Few elements of many
+// splits leave most compute units without work and each thread with a long chain of loads: 32 threads then share a sum's splits
+// (both parameter gradients, us, 8 / 32: 27 x 1 x 32 of 512 splits 21.6 / 19.3, 32 x 4 of 1024 27.5 / 24.9, 64 x 64 of 100 16.6 / 16.2; but
+// 64 x 256 of 112, 128 work-groups, 35.3 / 35.6, 9 x 64 x 64 of 128 31.5 / 31.9).
 static hipError_t launch_wgrad_reduce(const void* part, float* dw, long long per, int splits, hipStream_t s, const float* cs_part = nullptr,
                                       float* cs_out = nullptr, int ky = 0) {
   const int blocks = (int)((per / 4 + 31) / 32), cs_blocks = cs_part ? (ky / 4 + 31) / 32 : 0;
-  hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(blocks + cs_blocks), dim3(256), 0, s, (const float4*)part, (float4*)dw, per / 4, splits, blocks,
-                     (const float4*)cs_part, cs_out, ky / 4);
-  return hipGetLastError();
+  auto run = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(blocks + cs_blocks), dim3(threads), 0, s, (const float4*)part, (float4*)dw, per / 4, splits, blocks,
+                       (const float4*)cs_part, cs_out, ky / 4);
+    return hipGetLastError();
+  };
+  return blocks < 128 && splits >= 32 ? run(wgrad_reduce_vec_kernel<32>, 1024) : run(wgrad_reduce_vec_kernel<8>, 256);
 }
 
 // Filter packing: dst[tap][k][c] = w[tap][c][k] (transpose == 1) or dst = w (transpose == 0), times scale[k].
@@ -902,14 +920,17 @@ bool wgrad_use_small(int cx, int ky, const int* asp, const int* osp, const int* 
 
 // The kernel that a weight gradient runs on and the number of partial filters it leaves: the launch and the workspace size
 // both follow this one choice.
-enum WgradRoute { WGRAD_TINY, WGRAD_SMALL, WGRAD_ROWS, WGRAD_PATCH, WGRAD_GENERAL };
+enum WgradRoute { WGRAD_TINY, WGRAD_STEM, WGRAD_SMALL, WGRAD_ROWS, WGRAD_PATCH, WGRAD_GENERAL };
 struct WgradPlan { WgradRoute route; int splits; };
 WgradPlan wgrad_plan(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad,
                      int transpose) {
   static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;   // tuning aid
   if (!transpose) {
     if (wgrad_tiny_eligible(cx, ky, filt, stride, pad)) return {WGRAD_TINY, wgrad_tiny_wgs(rows, cx)};
-    if (wgrad_use_small(cx, ky, asp, osp, filt, stride)) return {WGRAD_SMALL, wgrad_small_splits(rows, osp)};
+    if (wgrad_use_small(cx, ky, asp, osp, filt, stride)) {
+      if (wgrad_stem_eligible(rows, cx, ky, asp, osp, filt, stride, pad)) return {WGRAD_STEM, wgrad_stem_splits(rows, cx, ky, asp, osp, filt, stride, pad)};
+      return {WGRAD_SMALL, wgrad_small_splits(rows, osp)};
+    }
     if (wgrad_rows_eligible(cx, ky, asp, filt, stride, pad)) return {WGRAD_ROWS, wgrad_rows_splits(rows, cx, ky)};
     if (!no_patch && wgrad_patch_eligible(cx, ky, filt, stride)) {
       const long long batch = rows / ((long long)osp[0] * osp[1] * osp[2]);
@@ -946,6 +967,7 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
   const bool side = colsum_out && !no_side;
   WgradPlan plan = wgrad_plan(rows, cx, ky, asp, osp, filt, stride, pad, transpose);
   if (plan.route == WGRAD_ROWS && !aligned16(X, DY)) plan.route = WGRAD_GENERAL;     // the workspace has room for its partial filters
+  if (plan.route == WGRAD_STEM && (((uintptr_t)X & 3) != 0 || !aligned16(nullptr, DY))) plan = {WGRAD_SMALL, wgrad_small_splits(rows, osp)};
   const int splits = plan.splits;
   const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
   if (plan.route == WGRAD_TINY) {
@@ -959,7 +981,8 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
     float* part = reinterpret_cast<float*>(ws);
     float* cs = side ? colsum_part(ws, splits, per) : nullptr;
     hipError_t e;
-    if (plan.route == WGRAD_SMALL) e = launch_wgrad_small(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
+    if (plan.route == WGRAD_STEM) e = launch_wgrad_stem(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
+    else if (plan.route == WGRAD_SMALL) e = launch_wgrad_small(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
     else if (plan.route == WGRAD_ROWS) e = launch_wgrad_rows(X, DY, part, rows, cx, ky, asp, osp, stride, cs, s);
     else e = launch_wgrad_patch(X, DY, part, rows / ((long long)osp[0] * osp[1] * osp[2]), asp, osp, filt, pad, cx, ky, cs, s);
     if (e != hipSuccess) return e;
@@ -1004,6 +1027,7 @@ uint64_t conv_wgrad_ws(const ConvGeom& g, bool with_colsum) {
   if (plan.route == WGRAD_PATCH) {
     if (wgrad_run_eligible(g.n, g.in_sp, g.out_sp, g.filt, g.pad, g.c, g.k)) splits = (uint64_t)wgrad_patch_room(g.n, g.out_sp[1], g.out_sp[2], g.c, g.k);
   } else {
+    if (plan.route == WGRAD_STEM) splits = (uint64_t)wgrad_small_splits(g.out_rows(), g.out_sp);
     const uint64_t gs = (uint64_t)wgrad_split(g.out_rows(), g.taps(), g.c, g.k).splits;
     if (gs > splits) splits = gs;
   }
@@ -1037,6 +1061,7 @@ hipError_t conv_fwd(const ConvGeom& g, const void* x, const void* w, const Epilo
   // patch matrix gathered in LDS
   if (pw_eligible(p)) return launch_pw(p, s);
   if (rf_eligible(p)) return launch_rf(p, s);
+  if (conv_stem_eligible(p)) return launch_conv_stem(p, s);
   if (conv_small_eligible(p)) return launch_conv_small(p, s);
   p.B = (const uint16_t*)ws;
   if (p.small) {
