@@ -7,7 +7,9 @@
 // multiplied, and a tap is a shift by kh * W + kw pixels.  Where a tap leaves the image, the lane reads a pixel of zeros
 // instead: its nine addresses are worked out once per tile.  The filter streams through a ring of LDS buffers one
 // filter row (three taps x BN x 32 channels) a stage, one barrier each.  Products are taken transposed and leave through
-// wave_epilogue.
+// wave_epilogue.  The forward pass reads the filter as it is stored, through the LDS transpose read: packing it first was a launch of
+// 3 to 5 us (us, packed / as stored: 72 -> 40 at 45 x 37, batch 3 12.5 / 8.8; 256 -> 256 at 14 x 14, batch 256 64.8 / 61.7, 16^3 30.6 /
+// 25.8; 64 -> 64 at 64^3 60.3 / 55.9; 100 random layers 0.82 of the time, none slower by more than 2 %).
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
@@ -28,6 +30,14 @@ __device__ __forceinline__ void unrolled(F&& f) {
     f(std::integral_constant<int, I>{});
     unrolled<N, I + 1>(f);
   }
+}
+
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ bf16x8 flat_tr_frag(const unsigned char* q0, const unsigned char* q1) {
+  const v2u a = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q0));
+  const v2u b = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q1));
+  return __builtin_bit_cast(bf16x8, v4u{a[0], a[1], b[0], b[1]});
 }
 
 template <int BM_, int BN_, int WM_, int WN_, int AV_, int NB_, int G_ = 1>
@@ -122,20 +132,31 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       load_lds16(rs_a, dst, ok && ((in >> j) & 1) ? a_off : DMA_OOB, (unsigned)(j * (NTHREADS / 4) * p.red * 2) + so);
     }
   };
-  // ---- filter loads: row (tap of the filter row, output channel), channel slot g at g ^ ((n >> 2) & 3) ----
+  // ---- filter loads.  Data gradient: row (tap of the filter row, output channel), channel slot g at g ^ ((n >> 2) & 3).  Forward: the
+  // filter as stored, row (tap, input channel) of BN output channels for the transpose read; of 64, pairs of slots are permuted
+  // by the row so that the four rows of a read fall into different banks ----
   const v4u rs_b = buffer_rsrc(p.B, (long long)(9 * KD) * p.nout * p.red * 2);
   unsigned b_off[BV];
   int b_k[BV];
 #pragma unroll
   for (int j = 0; j < BV; ++j) {
-    const int v = tid + j * NTHREADS, row = v >> 2, nr = row % T::BN, tl = row / T::BN;
-    b_k[j] = ((v & 3) ^ ((nr >> 2) & 3)) * 8;
-    b_off[j] = tl < 3 && n0 + nr < p.nout ? (unsigned)(((tl * p.nout + n0 + nr) * p.red + b_k[j]) * 2) : DMA_OOB;
+    const int v = tid + j * NTHREADS;
+    if constexpr (FLIP) {
+      const int row = v >> 2, nr = row % T::BN, tl = row / T::BN;
+      b_k[j] = ((v & 3) ^ ((nr >> 2) & 3)) * 8;
+      b_off[j] = tl < 3 && n0 + nr < p.nout ? (unsigned)(((tl * p.nout + n0 + nr) * p.red + b_k[j]) * 2) : DMA_OOB;
+    } else {
+      constexpr int SPR = T::BN / 8;
+      const int row = v / SPR, g = v % SPR, tl = row / BK, ch = (T::BN == 64 ? ((g >> 1) ^ ((row >> 1) & 3)) << 1 | (g & 1) : g) * 8;
+      b_k[j] = row % BK;
+      b_off[j] = tl < 3 && n0 + ch < p.nout ? (unsigned)(((tl * p.red + b_k[j]) * p.nout + n0 + ch) * 2) : DMA_OOB;
+    }
   }
+  const unsigned b_chunk = (unsigned)(FLIP ? BK * 2 : BK * 2 * p.nout);
   const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
   auto fetch_b = [&](int lb, int u, int buf) {
     const int vb = lb * G + grp, chunk = vb / KD, kd = FLIP ? KD - 1 - vb % KD : vb % KD;
-    const unsigned so = (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * (BK * 2);
+    const unsigned so = (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk;
 #pragma unroll
     for (int j = 0; j < BV; ++j)
       load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, vb < nblocks && chunk * BK + b_k[j] < p.red ? b_off[j] : DMA_OOB, so);
@@ -159,12 +180,20 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
         a_rd[i][kh * 3 + kw] = in ? pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4) : a_zero;
       }
   }
+  // data gradient: per 16 channels of the reduction; forward: their first four rows of the lane's half, and the next four
   int b_rd[TN][2];
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int nr = wn * T::WTN + j * 32 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) b_rd[j][ks] = nr * 64 + (((ks * 2 + half) ^ ((nr >> 2) & 3)) << 4);
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (FLIP) {
+        b_rd[j][i] = nr * 64 + (((i * 2 + half) ^ ((nr >> 2) & 3)) << 4);
+      } else {
+        const int li = lane & 15, lg = lane >> 4, row = (lg >> 1) * 8 + (li >> 2) + 4 * i, pair = wn * (T::WTN / 16) + j * 2 + (lg & 1);
+        b_rd[j][i] = row * T::BN * 2 + ((T::BN == 64 ? pair ^ ((row >> 1) & 3) : pair) << 5) + (li & 3) * 8;
+      }
+    }
   }
 
   f32x16 acc[TM][TN];
@@ -216,7 +245,10 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       const int tl = st / 2, ks = st % 2;
       const int tap = (FLIP ? 2 - u : u) * 3 + (FLIP ? 2 - tl : tl);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) bfr[st % (DEPTH + 1)][j] = *reinterpret_cast<const bf16x8*>(b + b_rd[j][ks] + tl * T::BN * 64);
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (FLIP) bfr[st % (DEPTH + 1)][j] = *reinterpret_cast<const bf16x8*>(b + b_rd[j][ks] + tl * T::BN * 64);
+        else bfr[st % (DEPTH + 1)][j] = flat_tr_frag(b + b_rd[j][0] + (tl * BK + ks * 16) * T::BN * 2, b + b_rd[j][1] + (tl * BK + ks * 16) * T::BN * 2);
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i) af[st % (DEPTH + 1)][i] = *reinterpret_cast<const bf16x8*>(a + (ar[i][tap] ^ (ks * 32)));
     };
@@ -231,10 +263,11 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[st % (DEPTH + 1)][j], af[st % (DEPTH + 1)][i], acc[i][j], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x100, (TM + TN) * DEPTH, 0);
+    constexpr int READS = TM + (FLIP ? TN : 2 * TN);
+    __builtin_amdgcn_sched_group_barrier(0x100, READS * DEPTH, 0);
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st) {
-      if (st + DEPTH < NSTEP) __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
+      if (st + DEPTH < NSTEP) __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
       __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
     }
   };
@@ -317,7 +350,7 @@ bool narrow_256(const IgemmP& p) {
   return long_fits(w) && flat_tiles(p, 256, 32) >= 256 && flat_tiles(p, 128, 32) > 256LL * (163840 / flat_group_lds<Flat128x32>(w));
 }
 
-// Layers that patches (conv_halo.hip) are faster on, us, this kernel / patches:
+// Layers that patches (conv_halo.hip) are faster on, us, this kernel (forward: with the filter packed first) / patches:
 //   3-D, at most 32 outputs, up to 64 Ki positions: data gradients (24 <- 40, 16^3 9.4 / 8.3; 16 <- 208, 16^3 24 / 18) and, but for
 //   short reductions on less than one tile per compute unit, forward passes (128 -> 16, 24 x 40 x 36 21 / 18; but
 //   32 -> 32, 16^3 8.3 / 9.2); beyond one round of tiles where patches are full (64 -> 16, 80^3 64 / 59; but 48^3, 432 tiles, 18.7 / 22.3)

@@ -774,7 +774,7 @@ hipError_t launch_igemm_g(IgemmP& p, hipStream_t s) {
 hipError_t launch_igemm(IgemmP& p, hipStream_t s) {
   static const bool no_halo = getenv("LMS_NO_HALO") != nullptr;   // tuning aid: force the per-tap gather kernel
   if (!no_halo && p.mode == 1 && rf_eligible(p)) return launch_rf(p, s);   // the forward pass takes this path before packing
-  if (!no_halo && flat_eligible(p)) return launch_flat(p, s);
+  if (!no_halo && p.mode == 1 && flat_eligible(p)) return launch_flat(p, s);      // forward: before packing, too
   if (!no_halo && halo_eligible(p)) return launch_halo(p, s);
   if (p.small) return launch_igemm_g<GM_SMALL>(p, s);
   if (p.mode == 0) return launch_igemm_g<GM_FWD>(p, s);
@@ -1057,10 +1057,12 @@ hipError_t conv_fwd(const ConvGeom& g, const void* x, const void* w, const Epilo
   fill_geom(g, p.asp, p.osp, p.filt, p.stride, p.pad);
   p.mode = 0;
   p.taps = g.taps();
-  // kernels that read the filter as stored: pointwise; filter resident in registers; first layers with 1 to 4 channels,
+  // kernels that read the filter as stored: pointwise; filter resident in registers; 3x3 on runs of positions; first layers with 1 to 4 channels,
   // patch matrix gathered in LDS
   if (pw_eligible(p)) return launch_pw(p, s);
   if (rf_eligible(p)) return launch_rf(p, s);
+  static const bool no_halo = getenv("LMS_NO_HALO") != nullptr;   // tuning aid, as in launch_igemm
+  if (!no_halo && flat_eligible(p)) return launch_flat(p, s);
   if (conv_stem_eligible(p)) return launch_conv_stem(p, s);
   if (conv_small_eligible(p)) return launch_conv_small(p, s);
   p.B = (const uint16_t*)ws;

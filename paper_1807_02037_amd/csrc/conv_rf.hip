@@ -450,6 +450,10 @@ bool rf_eligible(const IgemmP& p) {
   const long long batch = p.M / ((long long)p.osp[0] * p.osp[1] * p.osp[2]);
   const long long a_bytes = batch * p.asp[0] * p.asp[1] * p.asp[2] * p.red * 2, o_bytes = p.M * p.nout * 2;
   if (a_bytes >= 0x7fffff00LL || o_bytes >= 0x7fffff00LL) return false;             // 32-bit buffer offsets
+  // 2-D rows of at most 87 positions: the kernel of conv_flat.hip, whose widest tile fits, is faster (us, this one / that, forward and
+  // data gradient: 56 x 56, batch 64 27.2 / 26.1 and 34.3 / 30.5; 39 x 38, batch 195 46.6 / 35.6 and 50 / 38; but 95 x 96, batch 82
+  // 91 / 102; 128 x 128, batch 17 38 / 47)
+  if (!p3d && p.osp[2] <= 87 && flat_eligible(p)) return false;
   const int cus = rf_compute_units();
   if (cus < 8) return false;
   int tiles[3];
