@@ -3,6 +3,8 @@
 // summation order, so results are bit-identical from run to run.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace lms {
@@ -253,6 +255,62 @@ __global__ __launch_bounds__(TB) void colsum_partial_kernel(const uint16_t* dy, 
 __global__ void scale_cols_kernel(const float* raw, const float* scale, float* out, long long total, int k) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < total) out[i] = raw[i] * scale[i % k];
+}
+
+// Both gradients an affine layer takes from its raw filter gradient, in one pass over it: out = raw * scale and dot[k] = sum
+// over rows of w * raw, four columns a thread and Q such quads a work-group, which owns its columns.
+// Bound by the latency of the rows a thread reads one behind the other, so a work-group has 1024 / Q rows in flight and four times
+// that in its unrolled loop; the sums of the threads meet in a fixed order.
+template <int Q>
+__global__ __launch_bounds__(1024) void scale_dot_kernel(const float4* raw, const uint2* w, const float4* scale, float4* out, float4* dot,
+                                                         long long rows, int cq) {
+  constexpr int R = 1024 / Q;
+  __shared__ float4 sh[16][Q];
+  const int q = threadIdx.x % Q, col = blockIdx.x * Q + q;
+  float4 acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (col < cq) {
+    const float4 sc = scale[col];
+    auto row = [&](float4 a, uint2 b, long long i, float4& t) {
+      out[i] = make_float4(a.x * sc.x, a.y * sc.y, a.z * sc.z, a.w * sc.w);
+      t.x += a.x * __uint_as_float(b.x << 16);
+      t.y += a.y * __uint_as_float(b.x & 0xffff0000u);
+      t.z += a.z * __uint_as_float(b.y << 16);
+      t.w += a.w * __uint_as_float(b.y & 0xffff0000u);
+    };
+    long long r = threadIdx.x / Q;
+    for (; r + 3 * R < rows; r += 4 * R) {
+      float4 a[4];
+      uint2 b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        a[u] = raw[(r + u * R) * cq + col];
+        b[u] = w[(r + u * R) * cq + col];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) row(a[u], b[u], (r + u * R) * cq + col, acc[u]);
+    }
+    for (; r < rows; r += R) row(raw[r * cq + col], w[r * cq + col], r * cq + col, acc[0]);
+  }
+  float t[4] = {(acc[0].x + acc[1].x) + (acc[2].x + acc[3].x), (acc[0].y + acc[1].y) + (acc[2].y + acc[3].y),
+                (acc[0].z + acc[1].z) + (acc[2].z + acc[3].z), (acc[0].w + acc[1].w) + (acc[2].w + acc[3].w)};
+#pragma unroll
+  for (int off = Q; off < 64; off <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] += __shfl_xor(t[e], off);
+  if ((threadIdx.x & 63) < Q) sh[threadIdx.x >> 6][q] = make_float4(t[0], t[1], t[2], t[3]);
+  __syncthreads();
+  if (threadIdx.x < Q && col < cq) {
+    float4 v = sh[0][q];
+    for (int j = 1; j < 16; ++j) {
+      v.x += sh[j][q].x;
+      v.y += sh[j][q].y;
+      v.z += sh[j][q].z;
+      v.w += sh[j][q].w;
+    }
+    dot[col] = v;
+  }
 }
 __global__ void fill16_kernel(uint16_t* p, long long n, uint16_t v) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1276,6 +1334,24 @@ hipError_t scale_cols(int64_t j, int k, const float* raw, const float* scale, fl
 }
 hipError_t dot_cols(int64_t j, int k, const float* raw, const void* w, float* out, hipStream_t s) {
   hipLaunchKernelGGL(col_reduce_kernel, dim3(cdiv(k, 32)), dim3(1024), 0, s, raw, (const uint16_t*)w, (long long)j, k, out);
+  return hipGetLastError();
+}
+// Four quads (64-byte pieces of a row) a work-group, eight (whole lines) for filters beyond the caches' comfort.  us, two launches
+// / four / eight quads: 64 x 256 6.7 / 2.8 / 2.8, 1152 x 128 6.5 / 4.3 / 5.7, 2304 x 256 8.7 / 6.8 / 9.3, 2048 x 512
+// 8.8 / 6.5 / 8.5; 1024 x 2048 8.6 / 8.3 / 6.0, 4608 x 512 17.1 / 23.7 / 16.3.
+hipError_t scale_dot_cols(int64_t j, int k, const float* raw, const float* scale, const void* w, float* out, float* dot, hipStream_t s) {
+  const uintptr_t a16 = (uintptr_t)raw | (uintptr_t)scale | (uintptr_t)out | (uintptr_t)dot;
+  if (k % 4 || (a16 & 15) || ((uintptr_t)w & 7)) {
+    const hipError_t err = scale_cols(j, k, raw, scale, out, s);
+    return err == hipSuccess ? dot_cols(j, k, raw, w, dot, s) : err;
+  }
+  auto launch = [&](auto q) {
+    constexpr int Q = decltype(q)::value;
+    hipLaunchKernelGGL((scale_dot_kernel<Q>), dim3(cdiv(k / 4, Q)), dim3(1024), 0, s, (const float4*)raw, (const uint2*)w,
+                       (const float4*)scale, (float4*)out, (float4*)dot, (long long)j, k / 4);
+  };
+  if ((long long)j * k > 3 << 19) launch(std::integral_constant<int, 8>{});
+  else launch(std::integral_constant<int, 4>{});
   return hipGetLastError();
 }
 hipError_t fill16(void* p, uint64_t bytes, uint16_t pattern, hipStream_t s) {

@@ -145,6 +145,10 @@ struct Exec {
   // operation also computes (or -1), and on the loss itself a mark to skip it.
   std::vector<int> side_loss;
   std::vector<char> loss_later;
+  // The filter and the scale gradient of an affine layer read the same raw filter gradient: per node, the partner that is
+  // computed with it (or -1), and on the partner a mark to skip it.
+  std::vector<int> side_grad;
+  std::vector<char> grad_done;
   void* loss_ws = nullptr;
 
   hipStream_t stream_of(const Node& n) const {
@@ -331,6 +335,33 @@ void pair_losses(Exec& e) {
     e.loss_ws = nullptr;
     e.side_loss.assign(n, -1);
     e.loss_later.assign(n, 0);
+  }
+}
+
+// Pairs the SCALE_COLS and the DOT_COLS operation of one raw filter gradient where the plan runs them next to each other (but for
+// copies and for column sums that other operations compute) and the second one's result goes to caller memory, which is there
+// when the first one runs.
+void pair_affine_grads(Exec& e) {
+  const Graph& g = e.g;
+  const int n = (int)g.nodes.size();
+  e.side_grad.assign(n, -1);
+  e.grad_done.assign(n, 0);
+  auto kind = [&](int v) { return g.nodes[v].op == LMS_OP_SCALE_COLS || g.nodes[v].op == LMS_OP_DOT_COLS; };
+  const std::vector<int>& order = e.plan.order;
+  for (size_t i = 0; i < order.size(); ++i) {
+    const int a = order[i];
+    if (!kind(a) || e.grad_done[a]) continue;
+    for (size_t j = i + 1; j < order.size(); ++j) {
+      const Node& b = g.nodes[order[j]];
+      if (b.is_var || b.op == LMS_OP_SWAP_IN || b.op == LMS_OP_SWAP_OUT || (b.op == LMS_OP_COLSUM && colsum_host_wgrad(g, b.id) >= 0)) continue;
+      const Node& dot = b.op == LMS_OP_DOT_COLS ? b : g.nodes[a];
+      if (kind(b.id) && b.op != g.nodes[a].op && b.in[0] == g.nodes[a].in[0] && b.external && g.nodes[dot.in[1]].dtype == LMS_BF16 &&
+          e.waits[b.id].empty()) {
+        e.side_grad[a] = b.id;
+        e.grad_done[b.id] = 1;
+      }
+      break;
+    }
   }
 }
 
@@ -565,13 +596,23 @@ lms_status run_node(Exec& e, const Node& n) {
       e.n_kernels += 2;
       break;
     case LMS_OP_SCALE_COLS:
-      err = scale_cols(n.numel() / n.channels(), (int)n.channels(), (const float*)P(0), (const float*)P(1), (float*)out, s);
+    case LMS_OP_DOT_COLS: {
+      if (e.grad_done[n.id]) break;
+      const int64_t rows = IN(0).numel() / IN(0).channels();
+      const int k = (int)IN(0).channels();
+      const bool is_scale = n.op == LMS_OP_SCALE_COLS;
+      if (const int o = e.side_grad[n.id]; o >= 0) {
+        const void* other = e.ptr(g.nodes[o].in[1]);
+        err = scale_dot_cols(rows, k, (const float*)P(0), (const float*)(is_scale ? P(1) : other), is_scale ? other : P(1),
+                             (float*)(is_scale ? out : e.ptr(o)), (float*)(is_scale ? e.ptr(o) : out), s);
+      } else if (is_scale) {
+        err = scale_cols(rows, k, (const float*)P(0), (const float*)P(1), (float*)out, s);
+      } else {
+        err = dot_cols(rows, k, (const float*)P(0), P(1), (float*)out, s);
+      }
       e.n_kernels += 1;
       break;
-    case LMS_OP_DOT_COLS:
-      err = dot_cols(IN(0).numel() / IN(0).channels(), (int)IN(0).channels(), (const float*)P(0), P(1), (float*)out, s);
-      e.n_kernels += 1;
-      break;
+    }
     case LMS_OP_SWAP_OUT:
       if (e.flags & LMS_X_DMA_COPY) err = hipMemcpyAsync(out, P(0), n.bytes(), hipMemcpyDeviceToHost, s);
       // no trailer kernel on the swap stream: the step's statistics count the bytes on the host afterwards
@@ -663,6 +704,7 @@ lms_status exec_create(const Graph& g, void* arena, uint64_t arena_bytes, void* 
   if (const char* cb = getenv("LMS_DECODE_BLOCKS")) { const int v = atoi(cb); if (v > 0 && v <= 4096) e->decode_blocks = v; }
   build_sync(*e);
   pair_losses(*e);
+  pair_affine_grads(*e);
   if (flags & LMS_X_TIMING) {
     const int n = (int)g.nodes.size();
     e->wait_span.assign(n, Exec::WaitSpan());
