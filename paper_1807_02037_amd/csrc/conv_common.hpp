@@ -25,6 +25,7 @@ struct IgemmP {
   int jpad;     // small mode: row pitch of B, multiple of BK
   int ntiles_n;
   int ntiles;   // total tiles
+  int rest;     // pointwise data gradient under a stride: the kernel also writes the positions that no dy row lies under
   int up[3];    // pointwise kernel as a transposed convolution with window = stride: upsampling factor per axis (0: off)
   // strided transposed gather tiled by residue class: positions per class and axis, rows per class, tiles per class
   int qsp[3];

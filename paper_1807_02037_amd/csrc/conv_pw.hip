@@ -78,8 +78,9 @@ __device__ __forceinline__ long long pw_strided_row(long long m, const int* smal
 // n % k of tap n / k, filter element w[tap][c][n % k], written to the output position stride * input position + tap.
 // The input tile is read once for all taps of a column tile, and the taps that differ in the last coordinate only are
 // neighbours in memory, so their channels leave as one contiguous run.
-// STRIDED: rows are gathered (forward) or scattered (data gradient: only the positions a stride leaves under a dy row;
-// the others are strided_rest_kernel's).
+// STRIDED: rows are gathered (forward) or scattered (data gradient: the positions a stride leaves under a dy row; the others, up
+// to the next one along each axis, get the epilogue of zero from the same work-group behind the product, or from
+// strided_rest_kernel).
 template <typename T, int MODE, bool STRIDED>
 __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   constexpr bool UP = MODE == PW_UP;
@@ -102,12 +103,23 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   const int cg = (lane % T::LPR) * 8, n = n0 + wn * T::WTN + cg;
   const int er = wm * T::WTM + lane / T::LPR;                     // tile row of vector (0, 0)
   __shared__ unsigned s_row[UP || (STRIDED && MODE == PW_DGRAD) ? PM : 1];
+  __shared__ unsigned s_left[STRIDED && MODE == PW_DGRAD ? PM : 1];   // rest: positions along each axis, 8 bits each
   long long o_base = m0;                                          // output row that s_row counts from
   if constexpr (UP || (STRIDED && MODE == PW_DGRAD)) {
     const int* big = p.osp;
     const int* st = UP ? p.up : p.stride;
     o_base = pw_strided_row(m0, p.asp, big, st);
     if (tid < PM) s_row[tid] = (unsigned)(pw_strided_row(m0 + tid < p.M ? m0 + tid : m0, p.asp, big, st) - o_base);
+    if (STRIDED && MODE == PW_DGRAD && tid < PM) {
+      unsigned t = (unsigned)(m0 + tid), left = 0;
+#pragma unroll
+      for (int i = 2; i >= 0; --i) {
+        const int at = (int)(t % (unsigned)p.asp[i]) * st[i];
+        t /= (unsigned)p.asp[i];
+        left = left << 8 | (unsigned)(big[i] - at < st[i] ? big[i] - at : st[i]);
+      }
+      s_left[tid] = m0 + tid < p.M ? left : 0;
+    }
     __syncthreads();
   }
   long long up_tap = 0;                                           // UP: this lane's columns lie in one tap
@@ -139,7 +151,13 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   // a row so that the reads below fall into different banks ----
   const long long a_row0 = STRIDED && MODE == PW_FWD ? pw_strided_row(m0, p.osp, p.asp, p.stride) : m0;
   const long long a_rows = STRIDED && MODE == PW_FWD ? p.M_in - a_row0 : p.M - m0;
-  const v4u rs_a = buffer_rsrc(p.A + a_row0 * p.red, a_rows * p.red * 2), rs_b = buffer_rsrc(p.B, (long long)nv * p.red * 2);
+  v4u rs_a = buffer_rsrc(p.A + a_row0 * p.red, a_rows * p.red * 2), rs_b = buffer_rsrc(p.B, (long long)nv * p.red * 2);
+  if constexpr (STRIDED && MODE == PW_DGRAD)                      // the same for all lanes, which the compiler loses sight of here
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      rs_a[i] = __builtin_amdgcn_readfirstlane(rs_a[i]);
+      rs_b[i] = __builtin_amdgcn_readfirstlane(rs_b[i]);
+    }
   const unsigned lds0 = (unsigned)(uintptr_t)pw_smem;             // LDS address: the low half of the generic one
   unsigned a_off[AV], b_off[BV];
   int a_k[AV], b_k[BV];                                           // reduction channel of the vector within the stage
@@ -253,6 +271,34 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   __syncthreads();                                                // the ring is free for the epilogue
 
   wave_epilogue<T::WTN, TM, TN>(p, eb, acc, pw_smem + wave * T::EPI_WAVE, pre_add, pre_mask, UP ? up_n : n, n < nv, er, out_off);
+
+  if constexpr (STRIDED && MODE == PW_DGRAD) {
+    if (!p.rest) return;
+    constexpr int VPR = BN / 8, RL = T::NT / VPR, RV = PM / RL < 4 ? PM / RL : 4;   // vectors of a row, rows side by side, rows at a time
+    const int rn = n0 + tid % VPR * 8;
+    const EpiCoef none = {};
+    const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int ad = 0; ad < p.stride[0]; ++ad)
+      for (int ah = 0; ah < p.stride[1]; ++ah)
+        for (int aw = 0; aw < p.stride[2]; ++aw) {
+          if ((ad | ah | aw) == 0) continue;
+          const unsigned delta = (unsigned)((ad * p.osp[1] + ah) * p.osp[2] + aw);
+          for (int r0 = tid / VPR; r0 < PM; r0 += RV * RL) {
+            unsigned o[RV];
+            uint4 a[RV], m[RV];
+#pragma unroll
+            for (int v = 0; v < RV; ++v) {
+              const unsigned left = s_left[r0 + v * RL];
+              const bool ok = rn < p.nout && ad < (int)(left & 255) && ah < (int)(left >> 8 & 255) && aw < (int)(left >> 16 & 255);
+              o[v] = ok ? ((s_row[r0 + v * RL] + delta) * (unsigned)p.nout + (unsigned)rn) * 2u : DMA_OOB;
+              a[v] = EpiBuffers::get(eb.add, o[v]);
+              m[v] = EpiBuffers::get(eb.mask, o[v]);
+            }
+#pragma unroll
+            for (int v = 0; v < RV; ++v) eb.put(o[v], epilogue_pack8(p, none, zero, a[v], m[v]));
+          }
+        }
+  }
 }
 
 // Data gradient of a strided pointwise layer, the positions no dy row lies under: the epilogue of zero.  A pure stream
@@ -318,20 +364,35 @@ hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   return tiles(64, 128) >= 256 ? launch_pw_t<Tile1, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
 }
 
-// Data gradients under a stride take two launches here, the product and the positions that no dy row lies under; the general
-// kernel takes one.  us, general / here (stride 2, batch n; 250 layers measured):
+// Where the product's work-groups also write the positions between the strides, instead of a launch of its own: one launch
+// less, and both halves of a row pair are in flight together.  us, apart / inside (stride 2, addend and mask): 256 <- 512, n 128,
+// 56 x 56 169 / 149; 64 <- 128, n 32, 56 x 56 13.1 / 8.9; 256 <- 512, n 2, 14 x 14 10.8 / 7.8; 512 <- 128, n 64, 57 x 55 130 / 123.
+// Beyond the caches the separate kernel's whole rows in memory order win where a tile's piece of a row is not whole
+// lines (648 <- 400, n 32, 95 x 46 144 / 170; 440 <- 184, n 16, 68 x 100 73 / 86), and its streaming beside long reductions
+// (512 <- 1024, n 128, 28 x 28 92.8 / 95.5).  Strides of more than 8 positions leave too few work-groups for the stream.
+bool pw_rest_inside(const IgemmP& p) {
+  if (p.stride[0] * (long long)p.stride[1] * p.stride[2] > 8) return false;
+  const double bytes = 2.0 * (double)p.M * p.nout * (1 + (p.add != nullptr) + (p.mask != nullptr));
+  return bytes <= 100e6 || ((p.nout & 63) == 0 && p.red <= 512);
+}
+
+// Data gradients under a stride: the general kernel or the product here.  Where the positions that no dy row lies under take a
+// second launch, us, general / here (stride 2, batch n; 250 layers measured):
 //   64 <- 128, n 16, 28 x 28   6.3 / 8.8       64 <- 128, n 32, 56 x 56   14 / 12       256 <- 512, n 2, 14 x 14   12.8 / 10.0
 //   32 <- 64, n 16, 56 x 56    6.4 / 8.7       64 <- 128, n 128, 56 x 56  40 / 33       512 <- 256, n 2, 14 x 14   9.2 / 8.5
 //   128 <- 192, n 6, 30 x 29   7.9 / 9.0       128 <- 192, n 16, 56 x 56  14 / 13       64 <- 512, n 6, 30 x 29    9.1 / 10.1
 // So the second launch has to pay: 0.8 G products over all positions (2 G where few columns fill the tile badly: 48 <- 72,
 // n 128, 56 x 56 32 / 35), or a filter so large that the general kernel waits for its long reductions.  Beyond the
 // caches, tensors much wider than dy are bound by the writes, and it writes whole rows in order (1024 <- 64, n 64,
-// 56 x 56 235 / 271; odd extents cost it more: 512 <- 128, n 64, 57 x 55 158 / 127).
+// 56 x 56 235 / 271; odd extents cost it more: 512 <- 128, n 64, 57 x 55 158 / 127).  With one launch in two dimensions the
+// line is at 0.12 G: 176 <- 192, n 6, 40 x 41 9.1 / 6.7; 168 <- 296, n 4, 34 x 88 11.4 / 7.3; 128 <- 192, n 6, 30 x 29 8.2 / 7.6;
+// 72 <- 64, n 1, 22 x 107 (0.01 G) 6.6 / 7.0.
 bool strided_dgrad_general(const IgemmP& p) {
   const double macs = (double)p.M * p.nout * p.red;
   bool whole = true;
   for (int i = 0; i < 3; ++i) whole = whole && p.osp[i] % p.stride[i] == 0;
   if (p.nout >= 4 * p.red && p.M * p.nout >= (whole ? 100000000LL : 200000000LL)) return true;
+  if ((long long)p.stride[0] * p.stride[1] * p.stride[2] <= 4 && pw_rest_inside(p)) return macs < 1.2e8 && (long long)p.nout * p.red < 100000;
   return macs < (p.nout < 64 && p.red < 128 ? 2e9 : 8e8) && (long long)p.nout * p.red < 100000;
 }
 
@@ -383,8 +444,10 @@ hipError_t launch_pw(IgemmP& p, hipStream_t s) {
   }
   if (!strided) return launch_pw_shape<PW_DGRAD, false>(p, s);
   const long long rows = p.M_out = p.M;                     // dx rows; the product runs over the dy rows
+  p.rest = pw_rest_inside(p);
   if (rows >= 0x7fffffffLL) return hipErrorInvalidValue;
   p.M = rows / ((long long)p.osp[0] * p.osp[1] * p.osp[2]) * p.asp[0] * p.asp[1] * p.asp[2];
+  if (p.rest) return launch_pw_shape<PW_DGRAD, true>(p, s);
   const int vpr = p.nout / 8;
   const long long blocks = (rows * vpr + NTHREADS * 4 - 1) / (NTHREADS * 4);
   hipLaunchKernelGGL(strided_rest_kernel, dim3((unsigned)(blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks))), dim3(NTHREADS), 0, s, p, rows, vpr);

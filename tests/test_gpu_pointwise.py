@@ -27,6 +27,15 @@ CASES = [
     (1, (20, 22), 512, 256, 3),
     (9, (57, 55), 128, 256, 2),        # and many products: 128 x 128 / 64 x 128 tiles
     (8, (66, 71), 64, 392, 2),         # 128 x 64 tiles
+    # strided data gradients whose work-groups also write the positions between the strides, and sizes beyond which they do not
+    (1, (57, 59), 152, 360, 2),        # odd extents: the last positions have no neighbours
+    (3, (60, 58), 72, 520, 2),
+    (1, (15, 13, 11), 256, 400, 2),    # seven positions to each row
+    (2, (40, 1), 256, 400, 2),         # one extent without neighbours
+    (1, (25, 26), 320, 328, 3),        # nine positions: a launch of their own
+    (2, (15, 16), 1032, 1024, 2),
+    (32, (56, 57), 296, 72, 2),        # beyond the caches, rows in whole lines and not
+    (32, (56, 57), 320, 72, 2),
 ]
 
 
