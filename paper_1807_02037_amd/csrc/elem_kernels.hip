@@ -762,7 +762,7 @@ __global__ __launch_bounds__(TB) void gap_fwd_kernel(const uint16_t* x, uint16_t
     const uint16_t* p = x + (b * positions + rl) * c + ch;
     const long long step = (long long)c << lrl;
     const unsigned rows = (unsigned)((positions - rl + (1 << lrl) - 1) >> lrl);   // the host keeps it below 2^32
-#pragma unroll 4
+#pragma unroll 8
     for (unsigned q = 0; q < rows; ++q, p += step) {
       if constexpr (E == 8) {
         float f[8];
@@ -1549,8 +1549,12 @@ hipError_t gap_fwd(int64_t n, int64_t positions, int c, const void* x, void* y, 
   const bool vec = (c & 7) == 0 && (((uintptr_t)x | (uintptr_t)y) & 15) == 0;
   const int cv = vec ? c / 8 : c, cap = vec ? 32 : 64;      // widest row of a work-group: 512 / 128 bytes
   int lvb = 0, lrl = 0;
-  // one wave of vectors at most, and fewer where that leaves compute units without a work-group (but 64 bytes a row)
-  while ((1 << lvb) < cv && (1 << lvb) < cap && ((1 << lvb) < (vec ? 4 : 32) || n * ((cv + (2 << lvb) - 1) / (2 << lvb)) >= 1024)) ++lvb;
+  // one wave of vectors at most, and fewer where that leaves compute units without a work-group (but 64 bytes a row; whole lines
+  // from two work-groups per compute unit on: with half lines two work-groups fetch each, (64, 28, 28, 512) in a training step
+  // 5 us longer)
+  while ((1 << lvb) < cv && (1 << lvb) < cap &&
+         ((1 << lvb) < (vec ? 4 : 32) || n * ((cv + (2 << lvb) - 1) / (2 << lvb)) >= (vec && (1 << lvb) < 8 ? 512 : 1024)))
+    ++lvb;
   const int64_t chunks = (cv + (1 << lvb) - 1) >> lvb;
   // all the work-group's lanes on one image, unless there are more lanes than positions, or less than eight positions each
   // and work-groups in plenty: then several images share a work-group.  us, one image a work-group / this rule:
