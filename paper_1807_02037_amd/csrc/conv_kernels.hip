@@ -1048,6 +1048,84 @@ uint64_t tconv_wgrad_ws(const ConvGeom& g) {
   return splits * g.taps() * g.c * g.k * 4;
 }
 
+// Forward pass of a 1x1 stride-1 convolution with at most 4 output channels (class heads).  Bound by reading x once: four lanes share
+// a position, a 16-byte vector of channels each, with their slices of the filter in registers; they load four positions before
+// they multiply, and two exchanges within the quad (no LDS) leave each lane with the sums of one of the four.  The general kernel
+// packed the filter in a launch before and filled a 32-column tile with 4 columns.  us, general /
+// this kernel: 32 -> 4 at 64^3 11.9 / 9.1, at 128^3 68 / 38 (151 MB); 16 -> 3 at 96^3 27.3 / 13.4; 8 -> 2, two maps of 113 x 97 6.9 / 4.3.
+// With 8 outputs or 64 inputs the arithmetic costs more than that saves (32 -> 8 at 64^3 10.6 / 13.5, 64 -> 4 14.4 / 15.5).
+template <int CTRL>
+__device__ __forceinline__ float quad_swap(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__global__ __launch_bounds__(256) void head_fwd_kernel(IgemmP p, int iters) {
+  constexpr int K = 4;                                            // output channels, absent ones zero
+  const int j = threadIdx.x & 3, cvn = p.red >> 3;
+  float wv[8][K];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int k = 0; k < K; ++k) wv[e][k] = j < cvn && k < p.nout ? bf2f(p.B[(j * 8 + e) * p.nout + k]) : 0.f;
+  EpiCoef coef;
+  epilogue_coef(p, 0, p.nout, coef);
+  const long long m0 = (long long)blockIdx.x * 64 * iters + (threadIdx.x >> 2);
+  for (int it = 0; it < iters; it += 4) {
+    uint4 q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long long m = m0 + (it + u) * 64;
+      q[u] = j < cvn && m < p.M ? *reinterpret_cast<const uint4*>(p.A + m * p.red + j * 8) : make_uint4(0, 0, 0, 0);
+    }
+    float v[4][K], r[2][K], t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[u][k] = 0.f;
+      const uint32_t qw[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float f = __uint_as_float((e & 1) ? (qw[e >> 1] & 0xffff0000u) : (qw[e >> 1] << 16));
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[u][k] = __builtin_fmaf(f, wv[e][k], v[u][k]);
+      }
+    }
+    // lanes 0, 1 of a quad keep positions 0, 1, lanes 2, 3 the others; then each its own
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) r[u][k] = ((j & 2) ? v[u + 2][k] : v[u][k]) + quad_swap<0x4e>((j & 2) ? v[u][k] : v[u + 2][k]);
+      t[k] = ((j & 1) ? r[1][k] : r[0][k]) + quad_swap<0xb1>((j & 1) ? r[0][k] : r[1][k]);
+    }
+    const long long m = m0 + (it + j) * 64;
+    if (m >= p.M) continue;
+    const long long off = m * p.nout;
+    uint32_t a[4] = {0, 0, 0, 0}, b[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (k < p.nout) {
+        if (p.add) a[k >> 1] |= (uint32_t)p.add[off + k] << (16 * (k & 1));
+        if (p.mask) b[k >> 1] |= (uint32_t)p.mask[off + k] << (16 * (k & 1));
+      }
+    const uint4 o = epilogue_pack8(p, coef, t, make_uint4(a[0], a[1], a[2], a[3]), make_uint4(b[0], b[1], b[2], b[3]));
+    if (p.nout == 4 && ((uintptr_t)p.out & 7) == 0) *reinterpret_cast<uint2*>(p.out + off) = make_uint2(o.x, o.y);
+    else epilogue_put8(p, o, p.nout, off, false);
+  }
+}
+
+bool head_eligible(const IgemmP& p) {
+  for (int i = 0; i < 3; ++i)
+    if (p.filt[i] != 1 || p.stride[i] != 1 || p.pad[i] != 0) return false;
+  return p.nout <= 4 && (p.red & 7) == 0 && p.red <= 32 && ((uintptr_t)p.A & 15) == 0 && p.M < 0x7fffffffLL;
+}
+
+hipError_t launch_head_fwd(IgemmP& p, hipStream_t s) {
+  // four rounds of positions or more where that leaves four work-groups to a compute unit
+  long long iters = p.M / (64 * 1024LL) / 4 * 4;
+  iters = iters < 4 ? 4 : (iters > 32 ? 32 : iters);
+  hipLaunchKernelGGL(head_fwd_kernel, dim3((unsigned)((p.M + 64 * iters - 1) / (64 * iters))), dim3(256), 0, s, p, (int)iters);
+  return hipGetLastError();
+}
+
 hipError_t conv_fwd(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, void* y, void* ws, hipStream_t s) {
   IgemmP p{};
   p.small = (g.c % 8) != 0;
@@ -1057,9 +1135,10 @@ hipError_t conv_fwd(const ConvGeom& g, const void* x, const void* w, const Epilo
   fill_geom(g, p.asp, p.osp, p.filt, p.stride, p.pad);
   p.mode = 0;
   p.taps = g.taps();
-  // kernels that read the filter as stored: pointwise; filter resident in registers; 3x3 on runs of positions; first layers with 1 to 4 channels,
+  // kernels that read the filter as stored: pointwise; class heads; filter resident in registers; 3x3 on runs of positions; first layers with 1 to 4 channels,
   // patch matrix gathered in LDS
   if (pw_eligible(p)) return launch_pw(p, s);
+  if (head_eligible(p)) return launch_head_fwd(p, s);
   if (rf_eligible(p)) return launch_rf(p, s);
   static const bool no_halo = getenv("LMS_NO_HALO") != nullptr;   // tuning aid, as in launch_igemm
   if (!no_halo && flat_eligible(p)) return launch_flat(p, s);

@@ -23,3 +23,32 @@ def test_weight_gradient(n, sp, c, k):
     torch.cuda.synchronize()
     ref = x.double().reshape(-1, c).t() @ dy.double().reshape(-1, k)
     assert float((dw.double() - ref).norm() / ref.norm()) <= 2e-6
+
+
+@pytest.mark.parametrize("epi", ["plain", "all"])
+@pytest.mark.parametrize("n,sp,c,k", CASES + [(1, (7, 9), 24, 3), (2, (65, 130), 40, 7), (1, (31, 30), 512, 8), (1, (3, 3), 504, 2), (1, (64, 64, 70), 16, 4), (1, (80, 81, 82), 64, 8),
+                                              (2, (15, 17), 520, 4)])
+def test_forward(n, sp, c, k, epi):
+    """Lanes without channels, positions that fill no work-group, several rounds of positions, the widest reduction and ones beyond
+    it.  Bound: 2^-8 of the value (one rounding to bf16) and 1e-5 of the root mean square (fp32 sums)."""
+    import torch
+    import paper_1807_02037_amd as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k)
+
+    def rnd(shape, std=1.0):
+        return (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    x, w, res = rnd((n,) + sp + (c,)), rnd((c, k), c ** -0.5), rnd((n,) + sp + (k,))
+    scale, shift = 1 + 0.1 * torch.randn(k, generator=g, device="cuda"), torch.randn(k, generator=g, device="cuda")
+    full = epi == "all"
+    d = L.conv_desc(n, sp, c, k, (1,) * len(sp), 1, 0, L.abi.F_RELU if full else 0)
+    ws = torch.full((max(L.conv_workspace_bytes(d, L.abi.CONV_FWD), 256),), 255, dtype=torch.uint8, device="cuda")
+    y = torch.full((n,) + sp + (k,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    p = lambda t: t.data_ptr() if full else None
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), p(scale), p(shift), p(res), y.data_ptr(), ws.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    ref = x.double() @ w.double()
+    if full:
+        ref = torch.relu(ref * scale.double() + shift.double() + res.double())
+    rms = float(ref.square().mean().sqrt()) + 1.0
+    assert bool(((y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * rms).all())
