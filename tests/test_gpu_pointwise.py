@@ -22,7 +22,7 @@ CASES = [
     (1, (7, 6, 9), 48, 40, 2),         # 3-D, strided
     (1, (10, 11), 32, 64, 3),
     (2, (5, 6, 7), 64, 200, 1),
-    (2, (15, 17), 320, 328, 2),        # data gradient in two launches: large filter
+    (2, (15, 17), 320, 328, 2),        # data gradient here and not in the general kernel: large filter
     (1, (9, 8, 7), 264, 512, 2),
     (1, (20, 22), 512, 256, 3),
     (9, (57, 55), 128, 256, 2),        # and many products: 128 x 128 / 64 x 128 tiles
