@@ -196,6 +196,7 @@ bool stem_plan(const IgemmP& p, StemP& sp) {
   sp.tw = (p.osp[2] + sp.tiles_w - 1) / sp.tiles_w;
   const long long images = p.M / ((long long)p.osp[1] * p.osp[2]);
   while (sp.th > 1 && images * ((p.osp[1] + sp.th - 1) / sp.th) * sp.tiles_w < 192) sp.th = (sp.th + 1) / 2;
+  while (sp.th > 1 && 2LL * sp.th * p.osp[2] * p.nout >= 0x7fffffffLL) --sp.th;      // 31-bit offsets within the output rows of a tile
   sp.tiles_h = (p.osp[1] + sp.th - 1) / sp.th;
   sp.rows = (sp.th - 1) * p.stride[1] + p.filt[1];
   sp.pd = ((sp.tw - 1) * sc + sp.rc * 8 + 1) / 2;

@@ -53,3 +53,37 @@ def test_forward_and_weight_gradient(n, sp, c, k, f, stride, pad, off):
     assert bool(((y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all())
     assert float((dw.double() - refw).norm()) <= 2e-6 * float(refw.norm())
     assert float((db.double() - dyd.sum(0)).norm()) <= 2e-6 * float(dyd.sum(0).norm())
+
+
+# extents, c, k, filter, stride, padding: two, three and four output rows of 64 channels that span more than 2^31 and 2^32 bytes
+WIDE = [((4, 6000000), 2, 64, 3, 1, 1), ((5, 17000002), 1, 64, 3, 2, 1), ((4, 12000000), 2, 64, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("sp,c,k,f,stride,pad", WIDE)
+def test_forward_on_rows_of_gigabytes(sp, c, k, f, stride, pad):
+    """Every output row of images so wide that four of their rows leave 32-bit offsets, at the ends and in the middle."""
+    import torch
+    import paper_1807_02037_amd as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(sp[1])
+    x = torch.empty((1,) + sp + (c,), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    w = torch.empty((f, f, c, k), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    oh, ow = [(e + 2 * pad - f) // stride + 1 for e in sp]
+    assert oh * ow * k * 2 >= 1 << 31
+    d = L.conv_desc(1, sp, c, k, (f, f), stride, pad, 0)
+    ws = torch.empty(max(L.conv_workspace_bytes(d, L.abi.CONV_FWD), 256), dtype=torch.uint8, device="cuda")
+    y = torch.full((oh, ow, k), float("nan"), dtype=torch.bfloat16, device="cuda")
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert not any(bool(torch.isnan(part).any()) for row in y for part in row.split(1 << 20))
+    wd = w.double().cpu()
+    for b in (0, 4194000, ow // 2, ow - 1500):
+        e = min(ow, b + 1500)
+        lo, hi = b * stride - pad, (e - 1) * stride - pad + f                    # input columns
+        cols = x[0, :, max(lo, 0):min(hi, sp[1])].double().cpu()
+        cols = torch.nn.functional.pad(cols, (0, 0, max(-lo, 0), max(hi - sp[1], 0), pad, pad))
+        ref = torch.zeros((oh, e - b, k), dtype=torch.float64)
+        for r in range(f):
+            for q in range(f):
+                ref += cols[r:r + (oh - 1) * stride + 1:stride, q:q + (e - b - 1) * stride + 1:stride] @ wd[r, q]
+        assert bool(((y[:, b:e].double().cpu() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all()), b
