@@ -307,6 +307,23 @@ void build_sync(Exec& e) {
     if (need[v] && hipEventCreateWithFlags(&e.ev[v], hipEventDisableTiming) != hipSuccess) { e.ev[v] = nullptr; e.events_ok = false; }
 }
 
+// Schedule positions (first, last): is a variable that the inputs of v name written by an update operation in between, or is one of
+// the inputs such an operation's result?  An operation must not be moved across that; an update may also be held back beyond its
+// position (flush_updates), until an operation that is run where it stands reads what it writes.
+bool updates_inputs(const Exec& e, const Node& v, int first, int last) {
+  const Graph& g = e.g;
+  auto between = [&](int u) { return e.plan.pos[u] > first && e.plan.pos[u] < last; };
+  auto is_update = [&](int u) { return g.nodes[u].op == LMS_OP_SGD || g.nodes[u].op == LMS_OP_MOMENTUM; };
+  for (int u : v.in) {
+    if (is_update(u) && between(u)) return true;
+    for (const auto& up : g.updates)
+      if (up.second == u && between(up.first)) return true;
+    for (const Node& w : g.nodes)                                // bound to the variable's memory without an update edge
+      if (is_update(w.id) && w.in[0] == u && between(w.id)) return true;
+  }
+  return false;
+}
+
 // Pairs a loss with its gradient operation where the gradient reads the same two tensors and nobody reads, or is ordered by, the
 // loss before.  The partial sums of the loss go to a few kilobytes of the executor's own: in the plan the gradient's block may
 // lie where the loss has its workspace.
@@ -324,6 +341,7 @@ void pair_losses(Exec& e) {
     for (const Node& l : g.nodes) {
       if (l.op != op || l.in[0] != v.in[0] || l.in[1] != v.in[1] || g.nodes[l.in[0]].dtype != LMS_BF16) continue;
       if (e.plan.pos[l.id] > e.plan.pos[v.id] || e.ev[l.id] || !outs[l.id].empty() || e.loss_later[l.id]) continue;
+      if (updates_inputs(e, l, e.plan.pos[l.id], e.plan.pos[v.id])) continue;
       e.side_loss[v.id] = l.id;
       e.loss_later[l.id] = 1;
       bytes = std::max(bytes, workspace_bytes(g, l));
@@ -339,8 +357,8 @@ void pair_losses(Exec& e) {
 }
 
 // Pairs the SCALE_COLS and the DOT_COLS operation of one raw filter gradient where the plan runs them next to each other (but for
-// copies and for column sums that other operations compute) and the second one's result goes to caller memory, which is there
-// when the first one runs.
+// copies and for column sums that other operations compute), the second one's result goes to caller memory, which is there
+// when the first one runs, and so is everything that the second one reads or waits for.
 void pair_affine_grads(Exec& e) {
   const Graph& g = e.g;
   const int n = (int)g.nodes.size();
@@ -351,12 +369,13 @@ void pair_affine_grads(Exec& e) {
   for (size_t i = 0; i < order.size(); ++i) {
     const int a = order[i];
     if (!kind(a) || e.grad_done[a]) continue;
+    auto done = [&](int u) { return g.nodes[u].is_var || e.plan.pos[u] < (int)i; };
     for (size_t j = i + 1; j < order.size(); ++j) {
       const Node& b = g.nodes[order[j]];
       if (b.is_var || b.op == LMS_OP_SWAP_IN || b.op == LMS_OP_SWAP_OUT || (b.op == LMS_OP_COLSUM && colsum_host_wgrad(g, b.id) >= 0)) continue;
       const Node& dot = b.op == LMS_OP_DOT_COLS ? b : g.nodes[a];
       if (kind(b.id) && b.op != g.nodes[a].op && b.in[0] == g.nodes[a].in[0] && b.external && g.nodes[dot.in[1]].dtype == LMS_BF16 &&
-          e.waits[b.id].empty()) {
+          e.waits[b.id].empty() && done(b.in[1]) && std::all_of(b.ctrl_in.begin(), b.ctrl_in.end(), done) && !updates_inputs(e, b, -1, (int)j)) {
         e.side_grad[a] = b.id;
         e.grad_done[b.id] = 1;
       }

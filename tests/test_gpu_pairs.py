@@ -1,0 +1,123 @@
+"""Operations that the executor computes together with a neighbour (a loss with its gradient, the filter gradient of an affine
+layer with its scale gradient) in graphs built by hand, where they may be and where something between them forbids it."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class Built:
+    """A graph whose variables and results are all bound to tensors of the caller."""
+
+    def __init__(self, flags=0):
+        import paper_1807_02037_amd as L
+        self.L, self.A, self.g, self.flags = L, L.abi, L.Graph(), flags
+        self.dev, self.ex = {}, None
+
+    def var(self, name, tensor, kind):
+        import torch
+        dtype = {torch.bfloat16: self.A.BF16, torch.float32: self.A.F32, torch.int32: self.A.I32}[tensor.dtype]
+        node = self.g.add_variable(name, dtype, tuple(tensor.shape), kind)
+        self.dev[node] = tensor
+        return node
+
+    def op(self, name, op, inputs, phase=None, out=None, **attr):
+        node = self.g.add_op(name, op, inputs, self.A.BWD if phase is None else phase, **attr)
+        if out is not None:
+            self.g.set_external(node)
+            self.dev[node] = out
+        return node
+
+    def step(self):
+        import torch
+        if self.ex is None:
+            need = self.g.memory_need()[1]
+            self.arena = torch.zeros(max(need, 256), dtype=torch.uint8, device="cuda")
+            self.streams = [torch.cuda.Stream() for _ in range(3)]
+            torch.cuda.synchronize()
+            self.pool = self.L.api.PinnedPool(1 << 20)
+            self.ex = self.L.Executor(self.g, self.arena.data_ptr(), need, self.pool.ptr, 1 << 20, *[s.cuda_stream for s in self.streams], self.flags)
+            for node, t in self.dev.items():
+                self.ex.bind(node, t.data_ptr())
+        return self.ex.step()
+
+
+def rnd(seed, shape, dtype=None):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.randn(shape, generator=g, device="cuda").to(dtype or torch.bfloat16)
+
+
+@pytest.mark.parametrize("first", ["scale", "dot"])
+@pytest.mark.parametrize("update", [None, "filter", "scale"])
+def test_affine_gradients_read_the_updated_variable(first, update):
+    """An operation created after an update reads the updated value, also where the update is held back (everything bound)."""
+    import torch
+    rows, k, lr = 96, 40, 0.5
+    f32 = torch.float32
+    b = Built()
+    A = b.A
+    raw, w, scale = rnd(1, (1, 1, rows, k), f32), rnd(2, (1, 1, rows, k)), rnd(3, (k,), f32)
+    vraw, vw, vs = b.var("raw", raw, A.VAR_CONST), b.var("w", w, A.VAR_PARAM), b.var("s", scale, A.VAR_PARAM)
+    if update:
+        var, t = (vw, w) if update == "filter" else (vs, scale)
+        grad = rnd(4, tuple(t.shape), f32)
+        ref = (t.float() - lr * grad).to(t.dtype)
+        u = b.op("upd", A.OP_SGD, [var, b.var("g", grad, A.VAR_CONST)], phase=A.UPD, out=t, lr=lr)
+        b.g.add_update_edge(u, var)
+    dw, ds = torch.full_like(raw, float("nan")), torch.full_like(scale, float("nan"))
+    ops = [("dw", A.OP_SCALE_COLS, [vraw, vs], dw), ("ds", A.OP_DOT_COLS, [vraw, vw], ds)]
+    for name, op, inputs, out in (ops if first == "scale" else ops[::-1]):
+        b.op(name, op, inputs, out=out)
+    _, st = b.step()
+    torch.cuda.synchronize()
+    if update:
+        assert float((t.float() - ref.float()).abs().max()) <= 2.0 ** -7 * float(ref.float().abs().max())
+    assert torch.equal(dw, raw * scale)
+    terms = raw.double() * w.double()
+    assert bool(((ds.double() - terms.sum((0, 1, 2))).abs() <= 1e-5 * terms.abs().sum((0, 1, 2))).all())
+    if not update:
+        assert st.n_kernels == 1
+
+
+@pytest.mark.parametrize("kind", ["mse", "ce"])
+@pytest.mark.parametrize("update", [None, "before", "between"])
+def test_loss_reads_what_it_was_created_on(kind, update):
+    """A target (or the logits) updated between the loss and its gradient: the loss is of the old values, the gradient of the new ones."""
+    import torch
+    n, c, lr = 300, 16, 0.5
+    f32 = torch.float32
+    b = Built()
+    A = b.A
+    y = rnd(5, (n, c))
+    t = rnd(6, (n, c)) if kind == "mse" else torch.arange(n, dtype=torch.int32, device="cuda") % c
+    vy, vt = b.var("y", y, A.VAR_PARAM), b.var("t", t, A.VAR_TARGET)
+    grad = rnd(7, (n, c), f32)
+    old = y.clone()
+    upd = None
+
+    def add_update():
+        u = b.op("upd", A.OP_SGD, [vy, b.var("g", grad, A.VAR_CONST)], phase=A.UPD, out=y, lr=lr)
+        b.g.add_update_edge(u, vy)
+
+    if update == "before":
+        add_update()
+    b.op("loss", A.OP_MSE if kind == "mse" else A.OP_SOFTMAX_CE, [vy, vt], phase=A.FWD)
+    if update == "between":
+        add_update()
+    dy = torch.full_like(y, float("nan"))
+    b.op("dy", A.OP_MSE_GRAD if kind == "mse" else A.OP_SOFTMAX_CE_GRAD, [vy, vt], out=dy)
+    loss, st = b.step()
+    torch.cuda.synchronize()
+    new = (old.float() - lr * grad).to(torch.bfloat16) if update else old
+    assert float((y.float() - new.float()).abs().max()) <= 2.0 ** -7 * float(new.float().abs().max())
+    at_loss = (old if update == "between" else y).double()
+    if kind == "mse":
+        ref, g = float(((at_loss - t.double()) ** 2).mean()), 2.0 / y.numel() * (y.double() - t.double())
+    else:
+        lab = t.long()
+        ref = float(torch.nn.functional.cross_entropy(at_loss, lab))
+        g = (torch.softmax(y.double(), -1) - torch.nn.functional.one_hot(lab, c)) / n
+    assert abs(loss - ref) <= 1e-5 * abs(ref)
+    assert bool(((dy.double() - g).abs() <= 2.0 ** -8 * g.abs() + 1e-6 / n).all())
+    assert st.n_kernels == (2 if update is None else 3 if update == "before" else 4), st.n_kernels
