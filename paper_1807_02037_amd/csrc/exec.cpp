@@ -141,15 +141,12 @@ struct Exec {
   hipEvent_t stage_start[2] = {nullptr, nullptr};   // per direction: the node's stream has waited for its dependencies
   hipEvent_t stage_done[2] = {nullptr, nullptr};    // the second lane has finished its chunks
 
-  // A loss whose gradient follows comes out of the gradient's pass over the same tensors: per node, the loss that the gradient
-  // operation also computes (or -1), and on the loss itself a mark to skip it.
-  std::vector<int> side_loss;
+  // A loss that its gradient operation also computes (plan.side_loss) is skipped.
   std::vector<char> loss_later;
   // The filter and the scale gradient of an affine layer read the same raw filter gradient: per node, the partner that is
   // computed with it (or -1), and on the partner a mark to skip it.
   std::vector<int> side_grad;
   std::vector<char> grad_done;
-  void* loss_ws = nullptr;
 
   hipStream_t stream_of(const Node& n) const {
     if (n.op == LMS_OP_SWAP_OUT) return s_d2h;
@@ -307,55 +304,6 @@ void build_sync(Exec& e) {
     if (need[v] && hipEventCreateWithFlags(&e.ev[v], hipEventDisableTiming) != hipSuccess) { e.ev[v] = nullptr; e.events_ok = false; }
 }
 
-// Schedule positions (first, last): is a variable that the inputs of v name written by an update operation in between, or is one of
-// the inputs such an operation's result?  An operation must not be moved across that; an update may also be held back beyond its
-// position (flush_updates), until an operation that is run where it stands reads what it writes.
-bool updates_inputs(const Exec& e, const Node& v, int first, int last) {
-  const Graph& g = e.g;
-  auto between = [&](int u) { return e.plan.pos[u] > first && e.plan.pos[u] < last; };
-  auto is_update = [&](int u) { return g.nodes[u].op == LMS_OP_SGD || g.nodes[u].op == LMS_OP_MOMENTUM; };
-  for (int u : v.in) {
-    if (is_update(u) && between(u)) return true;
-    for (const auto& up : g.updates)
-      if (up.second == u && between(up.first)) return true;
-    for (const Node& w : g.nodes)                                // bound to the variable's memory without an update edge
-      if (is_update(w.id) && w.in[0] == u && between(w.id)) return true;
-  }
-  return false;
-}
-
-// Pairs a loss with its gradient operation where the gradient reads the same two tensors and nobody reads, or is ordered by, the
-// loss before.  The partial sums of the loss go to a few kilobytes of the executor's own: in the plan the gradient's block may
-// lie where the loss has its workspace.
-void pair_losses(Exec& e) {
-  const Graph& g = e.g;
-  const int n = (int)g.nodes.size();
-  e.side_loss.assign(n, -1);
-  e.loss_later.assign(n, 0);
-  std::vector<std::vector<int>> readers, outs;
-  adjacency(g, readers, outs);
-  uint64_t bytes = 0;
-  for (const Node& v : g.nodes) {
-    if (v.op != LMS_OP_MSE_GRAD && v.op != LMS_OP_SOFTMAX_CE_GRAD) continue;
-    const int op = v.op == LMS_OP_MSE_GRAD ? LMS_OP_MSE : LMS_OP_SOFTMAX_CE;
-    for (const Node& l : g.nodes) {
-      if (l.op != op || l.in[0] != v.in[0] || l.in[1] != v.in[1] || g.nodes[l.in[0]].dtype != LMS_BF16) continue;
-      if (e.plan.pos[l.id] > e.plan.pos[v.id] || e.ev[l.id] || !outs[l.id].empty() || e.loss_later[l.id]) continue;
-      if (updates_inputs(e, l, e.plan.pos[l.id], e.plan.pos[v.id])) continue;
-      e.side_loss[v.id] = l.id;
-      e.loss_later[l.id] = 1;
-      bytes = std::max(bytes, workspace_bytes(g, l));
-      break;
-    }
-  }
-  if (bytes && hipMalloc(&e.loss_ws, bytes) != hipSuccess) {
-    (void)hipGetLastError();                                   // without it loss and gradient run apart
-    e.loss_ws = nullptr;
-    e.side_loss.assign(n, -1);
-    e.loss_later.assign(n, 0);
-  }
-}
-
 // Pairs the SCALE_COLS and the DOT_COLS operation of one raw filter gradient where the plan runs them next to each other (but for
 // copies and for column sums that other operations compute), the second one's result goes to caller memory, which is there
 // when the first one runs, and so is everything that the second one reads or waits for.
@@ -375,7 +323,7 @@ void pair_affine_grads(Exec& e) {
       if (b.is_var || b.op == LMS_OP_SWAP_IN || b.op == LMS_OP_SWAP_OUT || (b.op == LMS_OP_COLSUM && colsum_host_wgrad(g, b.id) >= 0)) continue;
       const Node& dot = b.op == LMS_OP_DOT_COLS ? b : g.nodes[a];
       if (kind(b.id) && b.op != g.nodes[a].op && b.in[0] == g.nodes[a].in[0] && b.external && g.nodes[dot.in[1]].dtype == LMS_BF16 &&
-          e.waits[b.id].empty() && done(b.in[1]) && std::all_of(b.ctrl_in.begin(), b.ctrl_in.end(), done) && !updates_inputs(e, b, -1, (int)j)) {
+          e.waits[b.id].empty() && done(b.in[1]) && std::all_of(b.ctrl_in.begin(), b.ctrl_in.end(), done) && !updates_inputs(g, e.plan.pos, b, -1, (int)j)) {
         e.side_grad[a] = b.id;
         e.grad_done[b.id] = 1;
       }
@@ -580,9 +528,9 @@ lms_status run_node(Exec& e, const Node& n) {
       e.n_kernels += 2;
       break;
     case LMS_OP_MSE_GRAD: {
-      const int l = e.side_loss[n.id];
+      const int l = e.plan.side_loss[n.id];
       const void* mask = (f & LMS_F_MASK) ? P(2) : nullptr;
-      if (l >= 0) err = mse_loss_grad(IN(0).numel(), P(0), P(1), mask, out, (float*)e.ptr(l), e.loss_ws, s);
+      if (l >= 0) err = mse_loss_grad(IN(0).numel(), P(0), P(1), mask, out, (float*)e.ptr(l), e.ws(n.id), s);
       else err = mse_grad(IN(0).numel(), P(0), P(1), mask, out, s);
       e.n_kernels += l >= 0 ? 2 : 1;
       break;
@@ -593,10 +541,10 @@ lms_status run_node(Exec& e, const Node& n) {
       e.n_kernels += 2;
       break;
     case LMS_OP_SOFTMAX_CE_GRAD: {
-      const int l = e.side_loss[n.id];
+      const int l = e.plan.side_loss[n.id];
       const int64_t rows = IN(0).numel() / IN(0).channels();
       const void* mask = (f & LMS_F_MASK) ? P(2) : nullptr;
-      if (l >= 0) err = softmax_ce_loss_grad(rows, (int)IN(0).channels(), P(0), (const int32_t*)P(1), mask, out, (float*)e.ptr(l), e.loss_ws, s);
+      if (l >= 0) err = softmax_ce_loss_grad(rows, (int)IN(0).channels(), P(0), (const int32_t*)P(1), mask, out, (float*)e.ptr(l), e.ws(n.id), s);
       else err = softmax_ce_grad(rows, (int)IN(0).channels(), P(0), (const int32_t*)P(1), mask, out, s);
       e.n_kernels += l >= 0 ? 2 : 1;
       break;
@@ -722,7 +670,9 @@ lms_status exec_create(const Graph& g, void* arena, uint64_t arena_bytes, void* 
   if (const char* cb = getenv("LMS_ENCODE_BLOCKS")) { const int v = atoi(cb); if (v > 0 && v <= 4096) e->encode_blocks = v; }
   if (const char* cb = getenv("LMS_DECODE_BLOCKS")) { const int v = atoi(cb); if (v > 0 && v <= 4096) e->decode_blocks = v; }
   build_sync(*e);
-  pair_losses(*e);
+  e->loss_later.assign(g.nodes.size(), 0);
+  for (int l : e->plan.side_loss)
+    if (l >= 0) e->loss_later[l] = 1;
   pair_affine_grads(*e);
   if (flags & LMS_X_TIMING) {
     const int n = (int)g.nodes.size();
@@ -794,7 +744,6 @@ lms_status exec_destroy(Exec* e) {
     if (ev) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : e->copy_end)
     if (ev) (void)hipEventDestroy(ev);
-  if (e->loss_ws) (void)hipFree(e->loss_ws);
   if (e->step_begin) (void)hipEventDestroy(e->step_begin);
   if (e->step_end) (void)hipEventDestroy(e->step_end);
   if (e->join_d2h) (void)hipEventDestroy(e->join_d2h);

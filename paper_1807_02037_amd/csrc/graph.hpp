@@ -76,6 +76,9 @@ struct PlanResult {
   std::vector<std::vector<int>> ws_prev_tenants;
   std::vector<uint64_t> host_off;         // per swap-out node: offset in the pinned pool
   std::vector<char> moved;                // block handed on to an in-place consumer instead of being released
+  // per gradient operation of a loss: the loss that it also computes, in the same pass over the same tensors (or -1; the loss's own
+  // turn is then skipped).  wspace holds the loss's workspace for either place
+  std::vector<int> side_loss;
   uint64_t arena_needed = 0, peak_live = 0, pinned_needed = 0;
   bool fits = true;
 };
@@ -91,6 +94,10 @@ bool schedule(const Graph& g, std::vector<int>& order);
 // placement alone, which is what decides whether a graph fits.
 void plan_memory(const Graph& g, uint64_t arena_limit, bool keep_all, const std::vector<char>* external,
                  PlanResult& out, bool encode_swaps = false, bool hold_swapped = true);
+// Schedule positions (first, last): is a variable among the inputs of v written by an update operation in between, or is one of the
+// inputs such an operation's result?  v must not be moved across that; an update may also be held back beyond its
+// position, until an operation that is run where it stands reads what it writes.
+bool updates_inputs(const Graph& g, const std::vector<int>& pos, const Node& v, int first, int last);
 // true if a swap of this node's tensor can use the lossless encoding: 16-bit elements, count a multiple of 8
 bool swap_is_encodable(const Node& n);
 // Bytes a swap of this node's tensor is expected to put on the host link: all of them for a plain copy; encoded,

@@ -107,6 +107,19 @@ int inplace_source(const Graph& g, const Node& n) {
 
 }  // namespace
 
+bool updates_inputs(const Graph& g, const std::vector<int>& pos, const Node& v, int first, int last) {
+  auto between = [&](int u) { return pos[u] > first && pos[u] < last; };
+  auto is_update = [&](int u) { return g.nodes[u].op == LMS_OP_SGD || g.nodes[u].op == LMS_OP_MOMENTUM; };
+  for (int u : v.in) {
+    if (is_update(u) && between(u)) return true;
+    for (const auto& up : g.updates)
+      if (up.second == u && between(up.first)) return true;
+    for (const Node& w : g.nodes)                                // bound to the variable's memory without an update edge
+      if (is_update(w.id) && w.in[0] == u && between(w.id)) return true;
+  }
+  return false;
+}
+
 // Lifetimes are known before the step runs, so offsets are assigned off line: buffers are placed
 // largest first, each at the lowest offset that is free during its whole lifetime.
 bool swap_is_encodable(const Node& n) { return n.dtype == LMS_BF16 && n.numel() % 8 == 0 && n.numel() > 0; }
@@ -231,6 +244,7 @@ void plan_memory(const Graph& g, uint64_t arena_limit, bool keep_all, const std:
   // (the compact placement).  Offsets depend on sizes and positions only, so the
   // plan stays reproducible.
   bool relaxed = false;
+  std::vector<int> held = until;
   if (arena_limit && !keep_all && hold_swapped) {
     std::vector<double> clock(n + 1, 0.0);            // clock[i]: start of position i
     for (int i = 0; i < n; ++i) {
@@ -243,7 +257,6 @@ void plan_memory(const Graph& g, uint64_t arena_limit, bool keep_all, const std:
       clock[i + 1] = clock[i] + bytes / 2e12;
     }
     const double link = 52e9;
-    std::vector<int> held = until;
     std::vector<int> longer;                          // buffers whose block would be held beyond its last reader
     double link_free = 0.0;                           // the copies leave one after the other
     for (int i = 0; i < n; ++i) {
@@ -280,8 +293,10 @@ void plan_memory(const Graph& g, uint64_t arena_limit, bool keep_all, const std:
       }
     }
   }
-  if (!relaxed) out.arena_needed = place(until);
-  else {
+  if (!relaxed) {
+    held = until;
+    out.arena_needed = place(until);
+  } else {
     out.arena_needed = 0;
     for (const Buf& bb : bufs) out.arena_needed = std::max(out.arena_needed, bb.off + bb.size);
   }
@@ -290,18 +305,20 @@ void plan_memory(const Graph& g, uint64_t arena_limit, bool keep_all, const std:
     if (buf_of[v] >= 0) out.block[v] = Block{bufs[buf_of[v]].off, bufs[buf_of[v]].size};
     if (ws_of[v] >= 0) out.wspace[v] = Block{bufs[ws_of[v]].off, bufs[ws_of[v]].size};
   }
-  // earlier tenants of every buffer's address range: per sub-range only the most recent one matters
-  std::vector<int> by_end(bufs.size());
-  for (size_t i = 0; i < bufs.size(); ++i) by_end[i] = (int)i;
-  std::sort(by_end.begin(), by_end.end(), [&](int a, int b) { return bufs[a].end > bufs[b].end; });
-  for (size_t bi = 0; bi < bufs.size(); ++bi) {
-    const Buf& b = bufs[bi];
-    std::vector<std::pair<uint64_t, uint64_t>> open{{b.off, b.off + b.size}};   // parts without a known tenant yet
-    std::vector<int>& prev = b.ws ? out.ws_prev_tenants[b.members[0]] : out.prev_tenants[b.members[0]];
+  // earlier tenants of an address range at position `start`: per sub-range only the most recent one matters
+  std::vector<int> by_end;
+  auto sort_by_end = [&] {
+    by_end.resize(bufs.size());
+    for (size_t i = 0; i < bufs.size(); ++i) by_end[i] = (int)i;
+    std::sort(by_end.begin(), by_end.end(), [&](int a, int b) { return bufs[a].end > bufs[b].end; });
+  };
+  auto earlier_tenants = [&](uint64_t off, uint64_t size, int start) {
+    std::vector<int> found;
+    std::vector<std::pair<uint64_t, uint64_t>> open{{off, off + size}};   // parts without a known tenant yet
     for (int aj : by_end) {
       if (open.empty()) break;
       const Buf& a = bufs[aj];
-      if (a.end >= b.start) continue;
+      if (a.end >= start) continue;
       const uint64_t lo = a.off, hi = a.off + a.size;
       bool hit = false;
       std::vector<std::pair<uint64_t, uint64_t>> rest;
@@ -312,11 +329,66 @@ void plan_memory(const Graph& g, uint64_t arena_limit, bool keep_all, const std:
         if (iv.second > hi) rest.emplace_back(hi, iv.second);
       }
       if (hit) {
-        // a workspace was touched by its operation alone, an output block by its producer and every reader
-        for (int m : a.members) prev.push_back(a.ws ? ~m : m);
+        found.push_back(aj);
         open.swap(rest);
       }
     }
+    return found;
+  };
+  sort_by_end();
+  // A loss comes out of its gradient's pass where the gradient reads the same two tensors, nobody reads, or is ordered by, the loss
+  // before, and nothing updates what it reads in between.  Its workspace is then needed at the gradient's turn: where it is, or in
+  // another part of the arena that is free then and that no copy to the host may still be reading, what a larger arena has behind the
+  // need last.  The need itself does not grow for it; without such a part loss and gradient run apart.
+  out.side_loss.assign(n, -1);
+  std::vector<char> paired(n, 0);
+  for (const Node& v : g.nodes) {
+    if (v.op != LMS_OP_MSE_GRAD && v.op != LMS_OP_SOFTMAX_CE_GRAD) continue;
+    for (const Node& l : g.nodes) {
+      if (l.op != (v.op == LMS_OP_MSE_GRAD ? LMS_OP_MSE : LMS_OP_SOFTMAX_CE) || l.in[0] != v.in[0] || l.in[1] != v.in[1]) continue;
+      const int at = out.pos[v.id];
+      if (paired[l.id] || out.pos[l.id] > at || out.last_use[l.id] >= 0 || ws_of[l.id] < 0 || ws_of[v.id] >= 0) continue;
+      if (g.nodes[l.in[0]].dtype != LMS_BF16 || updates_inputs(g, out.pos, l, out.pos[l.id], at)) continue;
+      bool ordered = false;
+      for (const Node& w : g.nodes) ordered = ordered || std::find(w.ctrl_in.begin(), w.ctrl_in.end(), l.id) != w.ctrl_in.end();
+      if (ordered) continue;
+      Buf b = bufs[ws_of[l.id]];
+      std::vector<std::pair<uint64_t, uint64_t>> taken;
+      for (int i = 0; i < (int)bufs.size(); ++i)
+        if (i != ws_of[l.id] && bufs[i].start <= at && held[i] >= at) taken.emplace_back(bufs[i].off, bufs[i].off + bufs[i].size);
+      std::vector<uint64_t> offsets{b.off, 0};
+      for (const auto& t : taken)
+        if (t.second < out.arena_needed) offsets.push_back(t.second);
+      offsets.push_back(out.arena_needed);
+      for (uint64_t off : offsets) {
+        bool free = off + b.size <= (off < out.arena_needed ? out.arena_needed : arena_limit);
+        for (const auto& t : taken) free = free && (off + b.size <= t.first || off >= t.second);
+        if (!free) continue;
+        for (int a : earlier_tenants(off, b.size, at))
+          for (int m : bufs[a].members)
+            for (const Node& r : g.nodes) free = free && (bufs[a].ws || r.op != LMS_OP_SWAP_OUT || r.in[0] != m);
+        if (!free) continue;
+        b.off = off;
+        b.start = b.end = at;
+        b.members.assign(1, v.id);
+        ws_of[v.id] = (int)bufs.size();
+        bufs.push_back(b);
+        held.push_back(at);
+        out.wspace[v.id] = Block{b.off, b.size};
+        out.arena_needed = std::max(out.arena_needed, off + b.size);
+        out.side_loss[v.id] = l.id;
+        paired[l.id] = 1;
+        sort_by_end();
+        break;
+      }
+      if (paired[l.id]) break;
+    }
+  }
+  for (const Buf& b : bufs) {
+    std::vector<int>& prev = b.ws ? out.ws_prev_tenants[b.members[0]] : out.prev_tenants[b.members[0]];
+    // a workspace was touched by its operation alone, an output block by its producer and every reader
+    for (int aj : earlier_tenants(b.off, b.size, b.start))
+      for (int m : bufs[aj].members) prev.push_back(bufs[aj].ws ? ~m : m);
   }
 }
 

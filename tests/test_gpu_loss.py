@@ -46,4 +46,11 @@ def test_loss_and_gradient(name):
     if relu:
         g = torch.where(y > 0, g, torch.zeros_like(g))
     assert abs(loss - ref) <= 1e-5 * abs(ref)
+    # without keep-all the gradient may be written over y while the same pass sums the loss: the same bits of the loss and of every
+    # parameter gradient
+    packed = Session(spec, W.make_tensors(spec), lr=0.0)
+    loss2, _ = packed.step()
+    assert loss2 == loss
+    kept, bits = s.grad_bits(), packed.grad_bits()
+    assert kept.keys() == bits.keys() and all(np.array_equal(kept[k], bits[k]) for k in kept)
     assert np.isfinite(loss) and bool(((dy - g).abs() <= 2.0 ** -8 * g.abs() + 1e-6 / y.numel()).all())

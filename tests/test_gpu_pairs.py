@@ -5,6 +5,9 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+GUARD = 1 << 20          # bytes behind the arena that the executor was given
+
+
 class Built:
     """A graph whose variables and results are all bound to tensors of the caller."""
 
@@ -31,14 +34,18 @@ class Built:
         import torch
         if self.ex is None:
             need = self.g.memory_need()[1]
-            self.arena = torch.zeros(max(need, 256), dtype=torch.uint8, device="cuda")
+            self.arena = torch.full((need + GUARD,), 0xa5, dtype=torch.uint8, device="cuda")
+            self.need = need
             self.streams = [torch.cuda.Stream() for _ in range(3)]
             torch.cuda.synchronize()
             self.pool = self.L.api.PinnedPool(1 << 20)
             self.ex = self.L.Executor(self.g, self.arena.data_ptr(), need, self.pool.ptr, 1 << 20, *[s.cuda_stream for s in self.streams], self.flags)
             for node, t in self.dev.items():
                 self.ex.bind(node, t.data_ptr())
-        return self.ex.step()
+        out = self.ex.step()
+        torch.cuda.synchronize()
+        assert bool((self.arena[self.need:] == 0xa5).all())
+        return out
 
 
 def rnd(seed, shape, dtype=None):
@@ -121,3 +128,56 @@ def test_loss_reads_what_it_was_created_on(kind, update):
     assert abs(loss - ref) <= 1e-5 * abs(ref)
     assert bool(((dy.double() - g).abs() <= 2.0 ** -8 * g.abs() + 1e-6 / n).all())
     assert st.n_kernels == (2 if update is None else 3 if update == "before" else 4), st.n_kernels
+
+
+@pytest.mark.parametrize("kind,n,c", [("mse", 300, 16), ("mse", 7, 9), ("mse", 50000, 128), ("ce", 300, 16), ("ce", 300000, 4), ("ce", 70, 1000), ("ce", 5000, 65)])
+def test_loss_has_the_same_bits_apart(kind, n, c):
+    """The same loss and gradient with a control edge between them, which keeps them apart, and without; the arena holds what the plan
+    asks for and nothing else is written."""
+    import torch
+    got = []
+    for apart in (False, True):
+        b = Built()
+        A = b.A
+        y = rnd(8, (n, c))
+        t = rnd(9, (n, c)) if kind == "mse" else torch.arange(n, dtype=torch.int32, device="cuda") % c
+        vy, vt = b.var("y", y, A.VAR_PARAM), b.var("t", t, A.VAR_TARGET)
+        loss = b.op("loss", A.OP_MSE if kind == "mse" else A.OP_SOFTMAX_CE, [vy, vt], phase=A.FWD)
+        dy = torch.full_like(y, float("nan"))
+        grad = b.op("dy", A.OP_MSE_GRAD if kind == "mse" else A.OP_SOFTMAX_CE_GRAD, [vy, vt], out=dy)
+        if apart:
+            b.g.add_control_edge(loss, grad)
+        value, st = b.step()
+        assert st.n_kernels == (3 if apart else 2)
+        got.append((value, dy))
+    assert got[0][0] == got[1][0]
+    assert torch.equal(got[0][1], got[1][1])
+
+
+def test_executor_allocates_no_device_memory():
+    """A head of 72 classes over a million positions keeps one partial sum a position: 4 MB, which come out of the arena."""
+    import torch
+
+    def build(rows):
+        b = Built()
+        A = b.A
+        z, t = rnd(10, (rows, 72)), torch.zeros(rows, dtype=torch.int32, device="cuda")
+        vz, vt = b.var("z", z, A.VAR_PARAM), b.var("t", t, A.VAR_TARGET)
+        b.op("loss", A.OP_SOFTMAX_CE, [vz, vt], phase=A.FWD)
+        b.op("dz", A.OP_SOFTMAX_CE_GRAD, [vz, vt], out=torch.empty_like(z))
+        return b
+
+    build(16).step()                                            # code objects are loaded
+    b = build(1 << 20)
+    need = b.g.memory_need()[1]
+    assert need >= 4 << 20
+    arena, pool = torch.empty(need, dtype=torch.uint8, device="cuda"), b.L.api.PinnedPool(256)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    b.ex = b.L.Executor(b.g, arena.data_ptr(), need, pool.ptr, 256, *[s.cuda_stream for s in streams], 0)
+    for node, t in b.dev.items():
+        b.ex.bind(node, t.data_ptr())
+    loss, st = b.ex.step()
+    assert torch.cuda.mem_get_info()[0] == before
+    assert st.n_kernels == 2 and abs(loss - 4.28) < 1.0
