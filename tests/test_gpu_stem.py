@@ -55,6 +55,46 @@ def test_forward_and_weight_gradient(n, sp, c, k, f, stride, pad, off):
     assert float((db.double() - dyd.sum(0)).norm()) <= 2e-6 * float(dyd.sum(0).norm())
 
 
+def sprinkle(x, g, every):
+    """Infinities of both signs and NaN in place of one element in `every`, the corners of the first image among them."""
+    import torch
+    u = torch.rand(x.shape, generator=g, device="cuda") * every
+    for i, v in enumerate((float("inf"), float("-inf"), float("nan"))):
+        x[(u >= i / 3) & (u < (i + 1) / 3)] = v
+    x[0, 0, 0, 0], x[0, -1, -1, -1], x[0, 0, -1, 0] = float("inf"), float("-inf"), float("inf")
+    return x
+
+
+@pytest.mark.parametrize("n,sp,c,k,f,stride,pad,off", [case for case in CASES if case[1] != (1, 2)] + [(1, (40, 52), 2, 64, 20, 2, 9, 0), (1, (9, 90), 4, 16, 1, 1, 0, 0)])
+def test_forward_of_infinities_and_nan(n, sp, c, k, f, stride, pad, off):
+    """They reach the outputs whose window contains them, and the others have the values that they have without them."""
+    import torch
+    import paper_1807_02037_amd as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k + f)
+    osp = tuple((e + 2 * pad - f) // stride + 1 for e in sp)
+    x = sprinkle(torch.randn((n,) + sp + (c,), generator=g, device="cuda"), g, 6 * f * f * c).to(torch.bfloat16)
+    x = torch.empty(x.numel() + 8, dtype=torch.bfloat16, device="cuda")[off:off + x.numel()].view(x.shape).copy_(x)
+    w = torch.randn((f, f, c, k), generator=g, device="cuda").to(torch.bfloat16)
+    d = L.conv_desc(n, sp, c, k, (f, f), stride, pad, 0)
+    ws = torch.empty(max(L.conv_workspace_bytes(d, L.abi.CONV_FWD), 256), dtype=torch.uint8, device="cuda")
+    y = torch.empty((n,) + osp + (k,), dtype=torch.bfloat16, device="cuda")
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    xp, wd = torch.nn.functional.pad(x.double(), (0, 0, pad, pad, pad, pad)), w.double()
+    ref = torch.zeros(y.shape, dtype=torch.float64, device="cuda")
+    for r in range(f):
+        for q in range(f):
+            cut = xp[:, r:r + (osp[0] - 1) * stride + 1:stride, q:q + (osp[1] - 1) * stride + 1:stride]
+            for e in range(c):                                  # element by element: a product of matrices may mix what is not finite
+                ref += cut[..., e:e + 1] * wd[r, q, e]
+    fin = torch.isfinite(ref)
+    assert bool(fin.any()) and not bool(fin.all())
+    yd = y.double()
+    assert torch.equal(torch.nan_to_num(yd[~fin], 0.5, 1.0, -1.0), torch.nan_to_num(ref[~fin], 0.5, 1.0, -1.0))
+    assert bool(((yd[fin] - ref[fin]).abs() <= 2.0 ** -8 * ref[fin].abs() + 1e-4).all())
+
+
 # extents, c, k, filter, stride, padding: two, three and four output rows of 64 channels that span more than 2^31 and 2^32 bytes
 WIDE = [((4, 6000000), 2, 64, 3, 1, 1), ((5, 17000002), 1, 64, 3, 2, 1), ((4, 12000000), 2, 64, 3, 1, 1)]
 
