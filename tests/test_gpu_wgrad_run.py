@@ -44,3 +44,39 @@ def test_weight_and_bias_gradient(n, sp, c, k, off):
     assert float((dw.double() - ref).norm()) <= 2e-6 * float(ref.norm())
     assert float((db.double() - refb).norm()) <= 2e-6 * float(refb.norm())
     assert torch.equal(dw, dw2)
+
+
+@pytest.mark.parametrize("n,sp,c,k", [(n, sp, c, k) for n, sp, c, k, off in CASES if off == 0 and sp[1] <= 126] + [(2, (16, 32), 64, 64), (5, (8, 16), 320, 64)])
+def test_infinities_and_nan_of_x(n, sp, c, k):
+    """Pixels that are not finite at the corners and edges of images and inside, each in a channel of its own: they reach the taps that
+    read them, and the other entries have the values that they have without them."""
+    import torch
+    import paper_1807_02037_amd as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + c + k)
+    h, w = sp
+    x, dy = [torch.randn((n, h, w, q), generator=g, device="cuda").to(torch.bfloat16) for q in (c, k)]
+    dy[dy < -1.2] = 0
+    inf, nan = float("inf"), float("nan")
+    spots = [(0, 0, 0, inf), (n - 1, h - 1, w - 1, -inf), (n // 2, 0, w - 1, inf), (n // 2, h - 1, 0, nan), (0, h // 2, w - 1, inf), (n - 1, h // 2, 0, inf),
+             (0, h - 1, w // 2, -inf), (n - 1, 0, w // 2, inf), (n // 2, h // 2, w // 2, nan), (0, h // 3, w // 3, inf)]
+    for i, (a, r, q, v) in enumerate(spots):
+        x[a, r, q, 1 + 4 * i] = v
+    d = L.conv_desc(n, sp, c, k, (3, 3), 1, 1, 0)
+    ws = torch.empty(L.conv_workspace_bytes(d, L.abi.CONV_WGRAD_BIAS), dtype=torch.uint8, device="cuda")
+    dw, db = torch.empty((3, 3, c, k), device="cuda"), torch.empty((k,), device="cuda")
+    L.conv_wgrad_bias(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    # tap by tap over the positions whose pixel lies in the image
+    xc, dyc = x.double().cpu(), dy.double().cpu()
+    ref = torch.empty((3, 3, c, k), dtype=torch.float64)
+    for r in range(3):
+        for q in range(3):
+            h0, h1, w0, w1 = max(1 - r, 0), min(h + 1 - r, h), max(1 - q, 0), min(w + 1 - q, w)
+            ref[r, q] = xc[:, h0 + r - 1:h1 + r - 1, w0 + q - 1:w1 + q - 1].reshape(-1, c).t() @ dyc[:, h0:h1, w0:w1].reshape(-1, k)
+    got, fin = dw.double().cpu(), torch.isfinite(ref)
+    assert not bool(fin.all()) and bool(fin.any())
+    assert torch.equal(torch.nan_to_num(got[~fin], 0.5, 1.0, -1.0), torch.nan_to_num(ref[~fin], 0.5, 1.0, -1.0))
+    assert float((got[fin] - ref[fin]).norm()) <= 2e-6 * float(ref[fin].norm())
+    refb = dyc.reshape(-1, k).sum(dim=0)
+    assert float((db.double().cpu() - refb).norm()) <= 2e-6 * float(refb.norm())
