@@ -5,7 +5,9 @@
 // position are then `span` whole groups from the position's own on, every position at a 16-byte step, and the LDS transpose
 // read delivers them as MFMA operands, 8 * span (padded) elements of the reduction's other side per filter row, with nothing
 // gathered (what bounds wgrad_small.hip).  The first padding element of a group is 1: its row of the product is the
-// column sum of dy, the bias / shift gradient, for nothing.  dy goes straight to LDS (buffer loads that write it).
+// column sum of dy, the bias / shift gradient, for nothing.  dy goes straight to LDS (buffer loads that write it).  Positions of a
+// tile's last group of 16 that are none of its row's would meet dy = 0 with real pixels, which makes NaN of infinite ones: their x
+// is masked there, and rows below the last are left out.
 //
 // A work-group of eight waves, one per compute unit, owns the whole filter gradient and a run of tiles of up to 256 positions; a wave
 // takes 32 output channels (all rows of the product) and every fourth 16 positions; dy of the next two tiles and x of the next
@@ -137,8 +139,8 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(WStemP p) {
     for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 
   // 16 positions: operands, read one turn ahead of their products
-  struct Frag { bf16x8 y, x[JT]; };
-  const int turns = (p.th * p.gpr - g + 3) / 4;                   // of this wave, per tile
+  struct Frag { bf16x8 y, x[JT]; int left; };                     // left: positions from the first of the 16 to the end of the row
+  int tw_at = begin % p.tiles_w, th_at = begin / p.tiles_w % p.tiles_h;      // the tile that is multiplied
   if (begin < end) {
     fetch(xr0, 0);
     if (begin + 1 < end) fetch(xr1, 1);
@@ -155,18 +157,30 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(WStemP p) {
     if (t + 2 < end) fetch(xr, ybuf == 0 ? 2 : ybuf - 1);
     const unsigned char* sx = lds_st + xbuf * WT_X;
     const unsigned char* sy = lds_st + 2 * WT_X + ybuf * WT_Y;
+    const int row_len = p.OW - tw_at * p.tw < p.tw ? p.OW - tw_at * p.tw : p.tw, rows_in = p.OH - th_at * p.th < p.th ? p.OH - th_at * p.th : p.th;
+    const int turns = (rows_in * p.gpr - g + 3) / 4;              // of this wave
+    if (++tw_at == p.tiles_w) { tw_at = 0; if (++th_at == p.tiles_h) th_at = 0; }
     int r = 0, c = g;                                             // row and group of 16 of the next turn
     while (c >= p.gpr) { c -= p.gpr; ++r; }
     auto load = [&](Frag& f) {
       const unsigned char* xq = sx + r * p.stride * x_pitch + c * 256;
       const unsigned char* yq = sy + (r * p.gpr + c) * 16 * WT_PIX_B;
+      f.left = row_len - c * 16;
       f.y = wt_frag(yq + ya[0], yq + ya[1]);
 #pragma unroll
       for (int j = 0; j < JT; ++j) f.x[j] = wt_frag(xq + xa[j], xq + xa[j] + 64);
       c += 4;
       while (c >= p.gpr) { c -= p.gpr; ++r; }
     };
-    auto mul = [&](const Frag& f) {
+    auto mul = [&](Frag& f) {
+      if (f.left < 16) {                                          // uniform
+        const int n = f.left - 8 * (lane >> 5);
+        v4u m;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) m[w] = (2 * w < n ? 0xffffu : 0u) | (2 * w + 1 < n ? 0xffff0000u : 0u);
+#pragma unroll
+        for (int j = 0; j < JT; ++j) f.x[j] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(v4u, f.x[j]) & m);
+      }
 #pragma unroll
       for (int j = 0; j < JT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.x[j], f.y, acc[j], 0, 0, 0);
     };

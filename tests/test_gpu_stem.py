@@ -95,6 +95,46 @@ def test_forward_of_infinities_and_nan(n, sp, c, k, f, stride, pad, off):
     assert bool(((yd[fin] - ref[fin]).abs() <= 2.0 ** -8 * ref[fin].abs() + 1e-4).all())
 
 
+@pytest.mark.parametrize("n,sp,c,k,f,stride,pad", [case[:7] for case in CASES if case[2] * case[5] == 6 and not case[7]] +
+                         [(2, (48, 48), 3, 64, 7, 2, 3), (3, (33, 262), 3, 64, 7, 2, 3), (5, (70, 30), 3, 64, 3, 2, 1)])
+def test_weight_gradient_of_infinities_and_nan(n, sp, c, k, f, stride, pad):
+    """One pixel that is not finite, at the corners, edges and inside: it reaches the taps that read it, and the other entries have the
+    values that they have without it."""
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k + f)
+    h, w = sp
+    osp = tuple((e + 2 * pad - f) // stride + 1 for e in sp)
+    x = torch.randn((n,) + sp + (c,), generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn((n,) + osp + (k,), generator=g, device="cuda").to(torch.bfloat16)
+    d = L.conv_desc(n, sp, c, k, (f, f), stride, pad, 0)
+    ws = torch.empty(L.conv_workspace_bytes(d, A.CONV_WGRAD_BIAS), dtype=torch.uint8, device="cuda")
+    dw, db = torch.empty((f, f, c, k), device="cuda"), torch.empty((k,), device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    dyd = dy.double().cpu().reshape(-1, k)
+    refb = dyd.sum(0)
+    inf = float("inf")
+    for a, r, q, v in [(0, 0, 0, inf), (n - 1, h - 1, w - 1, -inf), (0, h - 1, 0, float("nan")), (n - 1, 0, w - 1, inf), (0, h // 2, w - 2, inf), (0, max(h - 2, 0), w // 2, -inf),
+                       (n - 1, h // 2, min(w // 2 + 1, w - 1), inf), (0, min(17, h - 1), min(33, w - 1), inf)]:
+        xi = x.clone()
+        xi[a, r, q, c - 1] = v
+        L.conv_wgrad_bias(d, xi.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws.data_ptr(), s)
+        torch.cuda.synchronize()
+        xp = torch.nn.functional.pad(xi.double().cpu(), (0, 0, pad, pad, pad, pad))
+        ref = torch.empty((f, f, c, k), dtype=torch.float64)
+        for i in range(f):
+            for j in range(f):
+                cut = xp[:, i:i + (osp[0] - 1) * stride + 1:stride, j:j + (osp[1] - 1) * stride + 1:stride].reshape(-1, c)
+                ref[i, j] = cut.t() @ dyd
+        got, fin = dw.double().cpu(), torch.isfinite(ref)
+        assert bool(fin.any())
+        assert torch.equal(torch.nan_to_num(got[~fin], 0.5, 1.0, -1.0), torch.nan_to_num(ref[~fin], 0.5, 1.0, -1.0)), (a, r, q)
+        assert float((got[fin] - ref[fin]).norm()) <= 2e-6 * float(ref[fin].norm()), (a, r, q)
+        assert float((db.double().cpu() - refb).norm()) <= 2e-6 * float(refb.norm())
+
+
 # extents, c, k, filter, stride, padding: two, three and four output rows of 64 channels that span more than 2^31 and 2^32 bytes
 WIDE = [((4, 6000000), 2, 64, 3, 1, 1), ((5, 17000002), 1, 64, 3, 2, 1), ((4, 12000000), 2, 64, 3, 1, 1)]
 
