@@ -10,7 +10,7 @@
 // results leave through wave_epilogue.
 //
 // The elements under a run's zero weights are pixels beside the window, and zero times an infinity or a NaN is a NaN.  The input rows are
-// looked at on their way to LDS (two operations a dword, 46.0 -> 47.4 us at 64 images of 224 x 224); a tile that holds such a value masks those elements out, so
+// looked at on their way to LDS (two operations a dword, 45.7 -> 46.5 us at 64 images of 224 x 224); a tile that holds such a value masks those elements out, so
 // that it reaches the outputs whose window contains it and no others.
 //
 // What bounds it is memory, 122 MB for 64 images of 224 x 224 (21 us at the rate of a large copy): 87 -> 43 us; 64 images of 48 x 48
@@ -136,8 +136,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
     for (int i = 0; i < ST_NI; ++i)
 #pragma unroll
       for (int h = 0; h < ST_NH; ++h) {
-        top = __builtin_elementwise_max(top, __builtin_bit_cast(v2us, next[i][h] & 0x7fff7fffu));
-        if (wave + 4 * i < sp.rows && 64 * h < sp.pd) raw[(wave + 4 * i) * sp.pitch + lane + 64 * h] = next[i][h];
+        if (wave + 4 * i < sp.rows && 64 * h < sp.pd) {           // uniform
+          raw[(wave + 4 * i) * sp.pitch + lane + 64 * h] = next[i][h];
+          top = __builtin_elementwise_max(top, __builtin_bit_cast(v2us, next[i][h] & 0x7fff7fffu));
+        }
       }
     if (top[0] >= 0x7f80 || top[1] >= 0x7f80) not_finite = t + 1;
     int n, oh0, ow0;
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
           for (int j = 0; j < 2; ++j) acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks][j], xf, acc[0][j], 0, 0, 0);
         }
       };
-      if (masked) products(std::true_type{});                     // uniform
+      if (__builtin_expect(masked, 0)) products(std::true_type{});                     // uniform
       else products(std::false_type{});
       auto out_off = [&](int r) -> unsigned {                     // r: row of the 32 positions
         int d, e;
