@@ -135,12 +135,13 @@ __global__ __launch_bounds__(TB) void ce_wide_kernel(const uint16_t* z, const in
   __syncthreads();
   float se = 0.f;
   for (int c = threadIdx.x; c < classes; c += TB) se += __expf(bf2f(zr[c]) - mx);
+  const int l = lab[r];
+  const float zl = part && threadIdx.x == 0 ? bf2f(zr[l]) : 0.f;    // before the barrier: dz may be z
   const float tot = block_sum(se, sh);
   if (threadIdx.x == 0) bc = tot;
   __syncthreads();
   se = bc;
-  const int l = lab[r];
-  if (part && threadIdx.x == 0) part[r] = mx + __logf(se) - bf2f(zr[l]);
+  if (part && threadIdx.x == 0) part[r] = mx + __logf(se) - zl;
   if (dz) {
     for (int c = threadIdx.x; c < classes; c += TB) {
       float g = (__expf(bf2f(zr[c]) - mx) / se - (c == l ? 1.f : 0.f)) * inv_rows;

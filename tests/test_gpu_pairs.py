@@ -154,6 +154,27 @@ def test_loss_has_the_same_bits_apart(kind, n, c):
     assert torch.equal(got[0][1], got[1][1])
 
 
+@pytest.mark.parametrize("kind,n,c", [("mse", 300, 16), ("mse", 50000, 128), ("ce", 300, 16), ("ce", 300000, 4), ("ce", 70, 1000), ("ce", 2000, 129), ("ce", 5000, 65)])
+def test_gradient_over_the_tensor_it_comes_from(kind, n, c):
+    """The gradient bound to the memory of y (or z): the loss of the same pass has the bits it has with a tensor of its own."""
+    import torch
+    got = []
+    for in_place in (False, True):
+        b = Built()
+        A = b.A
+        y = rnd(8, (n, c))
+        t = rnd(9, (n, c)) if kind == "mse" else torch.arange(n, dtype=torch.int32, device="cuda") * 7 % c
+        vy, vt = b.var("y", y, A.VAR_PARAM), b.var("t", t, A.VAR_TARGET)
+        b.op("loss", A.OP_MSE if kind == "mse" else A.OP_SOFTMAX_CE, [vy, vt], phase=A.FWD)
+        dy = y if in_place else torch.full_like(y, float("nan"))
+        b.op("dy", A.OP_MSE_GRAD if kind == "mse" else A.OP_SOFTMAX_CE_GRAD, [vy, vt], out=dy)
+        value, st = b.step()
+        assert st.n_kernels == 2
+        got.append((value, dy.clone()))
+    assert got[0][0] == got[1][0]
+    assert torch.equal(got[0][1], got[1][1])
+
+
 def test_executor_allocates_no_device_memory():
     """A head of 72 classes over a million positions keeps one partial sum a position: 4 MB, which come out of the arena."""
     import torch
