@@ -384,7 +384,7 @@ __global__ __launch_bounds__(TB) void maxpool3s2_fwd_kernel(PoolP p, const uint4
     float v[8];
     unpack8(q[k], v);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) best[e] = fmaxf(best[e], v[e]);       // a NaN is passed over
+    for (int e = 0; e < 8; ++e) best[e] = v[e] > best[e] ? v[e] : best[e];   // the first of equals (-0 and 0); a NaN is passed over
   }
   uint32_t w[4];
 #pragma unroll

@@ -66,6 +66,7 @@ def test_forward_and_gradient(n, sp, c, win, stride, pad, mask):
     osp = [(e + 2 * p - w) // s + 1 for e, w, s, p in zip(sp, w3, s3, p3)]
     rng = np.random.default_rng(c + sp[1])
     x = rng.integers(-2, 3, (n,) + sp + (c,)).astype(np.float32)
+    x[(x == 0) & (rng.random(x.shape) < 0.5)] = -0.0             # equal to 0: the first of them is the maximum
     spots = rng.random(x.shape)
     x[spots < 0.04] = np.nan
     x[(spots > 0.04) & (spots < 0.08)] = -np.inf
@@ -84,4 +85,5 @@ def test_forward_and_gradient(n, sp, c, win, stride, pad, mask):
     torch.cuda.synchronize()
     best, ref, mag = reference(x, dyd.float().cpu().numpy(), w3, s3, p3, mask, win == 3)
     assert np.array_equal(y.float().cpu().numpy(), best)
+    assert np.array_equal(np.signbit(y.float().cpu().numpy()), np.signbit(best))
     assert (np.abs(dx.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -22 * mag).all()
