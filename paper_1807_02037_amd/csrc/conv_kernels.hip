@@ -1142,6 +1142,15 @@ hipError_t conv_fwd(const ConvGeom& g, const void* x, const void* w, const Epilo
   if (rf_eligible(p)) return launch_rf(p, s);
   static const bool no_halo = getenv("LMS_NO_HALO") != nullptr;   // tuning aid, as in launch_igemm
   if (!no_halo && flat_eligible(p)) return launch_flat(p, s);
+  if (!no_halo && !aligned16(w, nullptr)) {                       // the same with a filter that has to be brought to a 16-byte boundary first
+    IgemmP q = p;
+    q.B = (const uint16_t*)ws;
+    if (flat_eligible(q)) {
+      launch_pack_filter((const uint16_t*)w, nullptr, (uint16_t*)ws, g.taps(), g.c, g.k, 0, s);
+      const hipError_t e = hipGetLastError();
+      return e == hipSuccess ? launch_flat(q, s) : e;
+    }
+  }
   if (conv_stem_eligible(p)) return launch_conv_stem(p, s);
   if (conv_small_eligible(p)) return launch_conv_small(p, s);
   p.B = (const uint16_t*)ws;

@@ -51,3 +51,26 @@ def test_tensors_between_vector_boundaries(n, sp, c, k, filt, stride, pad, shift
     for name, got, ref, bf16 in zip(("y", "dx", "dw", "db"), run(shift), run(0), (True, True, False, False)):
         rms = float(ref.square().mean().sqrt())
         assert bool(((got - ref).abs() <= (2.0 ** -7 * ref.abs() if bf16 else 0) + 2.0 ** -14 * (ref.abs() + rms)).all()), name
+
+
+@pytest.mark.parametrize("shift", [1, 2, 4])
+@pytest.mark.parametrize("n,sp,c,k", [(3, (45, 37), 72, 40), (60, (14, 14), 264, 256), (2, (23, 21), 264, 136), (1, (13, 13, 12), 96, 144), (9, (88, 88), 72, 24)])
+def test_filter_between_vector_boundaries(n, sp, c, k, shift):
+    """A 3x3 or 3x3x3 filter that starts between 16-byte boundaries: the forward pass takes the kernel that it takes otherwise, the same bits."""
+    import torch
+    import paper_1807_02037_amd as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k)
+    filt = (3,) * len(sp)
+    x = torch.randn((n,) + sp + (c,), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randn(filt + (c, k), generator=g, device="cuda").to(torch.bfloat16)
+    moved = torch.empty(w.numel() + 8, dtype=torch.bfloat16, device="cuda")[shift:shift + w.numel()].copy_(w.reshape(-1))
+    d = L.conv_desc(n, sp, c, k, filt, 1, 1, 0)
+    ws = torch.empty(L.conv_workspace_bytes(d, L.abi.CONV_FWD), dtype=torch.uint8, device="cuda")
+    out = []
+    for t in (w, moved):
+        y = torch.full((n,) + sp + (k,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        L.conv_fwd(d, x.data_ptr(), t.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        out.append(y)
+    assert bool(torch.isfinite(out[0]).all()) and torch.equal(out[0], out[1])
