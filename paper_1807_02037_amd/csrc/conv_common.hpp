@@ -175,15 +175,13 @@ int wgrad_patch_splits(long long batch, const int* asp, const int* osp, const in
 hipError_t launch_wgrad_patch(const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* asp,
                               const int* osp, const int* filt, const int* pad, int cx, int ky, float* cs_part, hipStream_t s);
 
-// Partial filters that the workspace of a layer of wgrad_run.hip has room for: one per work-group of 64 x 64 filter entries on
-// patches of 8 x 16 positions, of which two images of at most 8 x 7 share one.  Workspaces count in what a memory budget holds: they keep
-// their size where fewer are written.
-long long wgrad_patch_room(long long batch, int h, int w, int cx, int ky);
-// 2-D 3x3 weight gradient that keeps the extents, at least 48 channels on both sides (wgrad_run.hip); part and cs_part as above.
-bool wgrad_run_eligible(long long batch, const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky);
-int wgrad_run_splits(long long batch, const int* osp, int cx, int ky);
-hipError_t launch_wgrad_run(const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* osp, int cx, int ky, float* cs_part,
-                            hipStream_t s);
+// 2-D 3x3 weight gradient that keeps the extents, at least 48 channels on both sides, both tensors on 16-byte boundaries
+// (wgrad_run.hip); part and cs_part as above.  At most as many partial filters as wgrad_patch_splits: workspaces count in what a memory
+// budget holds, and tensors on other boundaries take the patches.
+struct RunPlan { int kt, ctiles, ktiles, splits, q_per_split; long long q; };     // splits 0: not this kernel's
+RunPlan wgrad_run_plan(long long batch, const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky);
+hipError_t launch_wgrad_run(const RunPlan& plan, const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* osp, int cx, int ky,
+                            float* cs_part, hipStream_t s);
 
 // Pointwise (1x1, no padding, any stride) forward convolution and data gradient (conv_pw.hip).  p.B is the filter as
 // stored, [c][k] (data gradient: times the scale).

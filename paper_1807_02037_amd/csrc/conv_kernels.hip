@@ -920,8 +920,8 @@ bool wgrad_use_small(int cx, int ky, const int* asp, const int* osp, const int* 
 
 // The kernel that a weight gradient runs on and the number of partial filters it leaves: the launch and the workspace size
 // both follow this one choice.
-enum WgradRoute { WGRAD_TINY, WGRAD_STEM, WGRAD_SMALL, WGRAD_ROWS, WGRAD_PATCH, WGRAD_GENERAL };
-struct WgradPlan { WgradRoute route; int splits; };
+enum WgradRoute { WGRAD_TINY, WGRAD_STEM, WGRAD_SMALL, WGRAD_ROWS, WGRAD_RUN, WGRAD_PATCH, WGRAD_GENERAL };
+struct WgradPlan { WgradRoute route; int splits; RunPlan run{}; };
 WgradPlan wgrad_plan(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad,
                      int transpose) {
   static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;   // tuning aid
@@ -934,6 +934,8 @@ WgradPlan wgrad_plan(long long rows, int cx, int ky, const int* asp, const int* 
     if (wgrad_rows_eligible(cx, ky, asp, filt, stride, pad)) return {WGRAD_ROWS, wgrad_rows_splits(rows, cx, ky)};
     if (!no_patch && wgrad_patch_eligible(cx, ky, filt, stride)) {
       const long long batch = rows / ((long long)osp[0] * osp[1] * osp[2]);
+      const RunPlan run = wgrad_run_plan(batch, asp, osp, filt, pad, cx, ky);
+      if (run.splits > 0) return {WGRAD_RUN, run.splits, run};
       return {WGRAD_PATCH, wgrad_patch_splits(batch, asp, osp, filt, pad, cx, ky)};
     }
   }
@@ -968,6 +970,8 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
   WgradPlan plan = wgrad_plan(rows, cx, ky, asp, osp, filt, stride, pad, transpose);
   if (plan.route == WGRAD_ROWS && !aligned16(X, DY)) plan.route = WGRAD_GENERAL;     // the workspace has room for its partial filters
   if (plan.route == WGRAD_STEM && (((uintptr_t)X & 3) != 0 || !aligned16(nullptr, DY))) plan = {WGRAD_SMALL, wgrad_small_splits(rows, osp)};
+  const long long batch = rows / ((long long)osp[0] * osp[1] * osp[2]);
+  if (plan.route == WGRAD_RUN && !aligned16(X, DY)) plan = {WGRAD_PATCH, wgrad_patch_splits(batch, asp, osp, filt, pad, cx, ky)};
   const int splits = plan.splits;
   const long long per = (long long)filt[0] * filt[1] * filt[2] * cx * ky;
   if (plan.route == WGRAD_TINY) {
@@ -984,7 +988,8 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
     if (plan.route == WGRAD_STEM) e = launch_wgrad_stem(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
     else if (plan.route == WGRAD_SMALL) e = launch_wgrad_small(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
     else if (plan.route == WGRAD_ROWS) e = launch_wgrad_rows(X, DY, part, rows, cx, ky, asp, osp, stride, cs, s);
-    else e = launch_wgrad_patch(X, DY, part, rows / ((long long)osp[0] * osp[1] * osp[2]), asp, osp, filt, pad, cx, ky, cs, s);
+    else if (plan.route == WGRAD_RUN) e = launch_wgrad_run(plan.run, X, DY, part, batch, osp, cx, ky, cs, s);
+    else e = launch_wgrad_patch(X, DY, part, batch, asp, osp, filt, pad, cx, ky, cs, s);
     if (e != hipSuccess) return e;
     colsum_done = cs != nullptr;
     return launch_wgrad_reduce(ws, dw, per, splits, s, cs, colsum_out, ky);
@@ -1024,9 +1029,9 @@ uint64_t conv_wgrad_ws(const ConvGeom& g, bool with_colsum) {
   uint64_t splits = (uint64_t)plan.splits;
   // the other specialised kernels keep room for the general one's partial filters as well: which geometries fit the static
   // scratch array is known to callers
-  if (plan.route == WGRAD_PATCH) {
-    if (wgrad_run_eligible(g.n, g.in_sp, g.out_sp, g.filt, g.pad, g.c, g.k)) splits = (uint64_t)wgrad_patch_room(g.n, g.out_sp[1], g.out_sp[2], g.c, g.k);
-  } else {
+  if (plan.route == WGRAD_RUN) {
+    splits = (uint64_t)wgrad_patch_splits(g.n, g.in_sp, g.out_sp, g.filt, g.pad, g.c, g.k);      // tensors on other boundaries
+  } else if (plan.route != WGRAD_PATCH) {
     if (plan.route == WGRAD_STEM) splits = (uint64_t)wgrad_small_splits(g.out_rows(), g.out_sp);
     const uint64_t gs = (uint64_t)wgrad_split(g.out_rows(), g.taps(), g.c, g.k).splits;
     if (gs > splits) splits = gs;

@@ -351,9 +351,7 @@ __global__ __launch_bounds__(RUN_NT, 2) void wgrad_run_kernel(WRunP p) {
   }
 }
 
-struct RunPlan { int kt, ctiles, ktiles, splits, q_per_split; long long q; };
-
-RunPlan run_plan_kt(long long batch, int h, int w, int cx, int ky, int kt) {
+RunPlan run_plan_kt(long long batch, int h, int w, int cx, int ky, int kt, long long room) {
   RunPlan r;
   r.kt = kt;
   r.ctiles = (cx + 63) / 64; r.ktiles = (ky + kt - 1) / kt;
@@ -366,7 +364,6 @@ RunPlan run_plan_kt(long long batch, int h, int w, int cx, int ky, int kt) {
   const long long units = (r.q + 31) / 32, most = r.q < 96 ? 1 : r.q / 96;
   if (splits > most) splits = most;
   // ... and no more of them than the workspace has room for
-  const long long room = wgrad_patch_room(batch, h, w, cx, ky);
   if (splits > room) splits = room;
   const long long per = (units + splits - 1) / splits;
   r.q_per_split = (int)(per * 32 < 0x7fffffff ? per * 32 : 0x7fffffff);
@@ -378,8 +375,8 @@ RunPlan run_plan_kt(long long batch, int h, int w, int cx, int ky, int kt) {
 // filters (0.27 us a MB, written and added), and 1.3 us to add two more groups' sums.  Both parameter gradients, us, 64 / 32: 64 -> 64 at
 // 56 x 56, batch 64 33.9 / 32.2; 256 -> 256 at 14 x 14, batch 8 22.0 / 19.1, batch 256 73.6 / 82.3; 64 -> 184, 12 x 12, batch 89 20.5 / 17.4;
 // 128 -> 128, 28 x 28, batch 128 45.9 / 48.0; 208 -> 136, 9 x 7, batch 7 (as many partial filters) 12.4 / 13.0.
-RunPlan run_plan(long long batch, int h, int w, int cx, int ky) {
-  const RunPlan a = run_plan_kt(batch, h, w, cx, ky, 64), b = run_plan_kt(batch, h, w, cx, ky, 32);
+RunPlan run_plan(long long batch, int h, int w, int cx, int ky, long long room) {
+  const RunPlan a = run_plan_kt(batch, h, w, cx, ky, 64, room), b = run_plan_kt(batch, h, w, cx, ky, 32, room);
   auto cost = [&](const RunPlan& r, double step) { return r.q_per_split * step / STEP + 0.27e-6 * 36 * cx * ky * r.splits; };
   return cost(b, 1.28) + 1.3 < cost(a, 2.05) ? b : a;
 }
@@ -387,24 +384,23 @@ RunPlan run_plan(long long batch, int h, int w, int cx, int ky) {
 }  // namespace
 
 // Offsets within a work-group's part of the run have 31 bits.
-bool wgrad_run_eligible(long long batch, const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky) {
+RunPlan wgrad_run_plan(long long batch, const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky) {
   static const bool off = getenv("LMS_NO_WGRAD_RUN") != nullptr;   // tuning aid
-  if (off || filt[0] != 1 || filt[1] != 3 || filt[2] != 3 || pad[0] != 0 || pad[1] != 1 || pad[2] != 1 || asp[0] != 1) return false;
-  if (asp[1] != osp[1] || asp[2] != osp[2] || cx < 48 || ky < 48 || (cx & 7) != 0 || (ky & 7) != 0) return false;
+  const RunPlan none{};
+  if (off || filt[0] != 1 || filt[1] != 3 || filt[2] != 3 || pad[0] != 0 || pad[1] != 1 || pad[2] != 1 || asp[0] != 1) return none;
+  if (asp[1] != osp[1] || asp[2] != osp[2] || cx < 48 || ky < 48 || (cx & 7) != 0 || (ky & 7) != 0) return none;
   const int h = asp[1], w = asp[2];
-  if (w > 126 || batch < 1 || batch * (h + 1LL) * (w + 1) >= 0x40000000LL) return false;
-  const RunPlan r = run_plan(batch, h, w, cx, ky);
+  if (w > 126 || batch < 1 || batch * (h + 1LL) * (w + 1) >= 0x40000000LL) return none;
+  const RunPlan r = run_plan(batch, h, w, cx, ky, wgrad_patch_splits(batch, asp, osp, filt, pad, cx, ky));
   return (r.q_per_split + 1024LL + 2LL * (h + 1) * (w + 1)) * (cx > ky ? cx : ky) * 2 < 0x7fffffffLL && (long long)r.ctiles * r.ktiles * r.splits < 0x7fffff00LL &&
-         36LL * cx * ky < 0x40000000LL;
+         36LL * cx * ky < 0x40000000LL ? r : none;
 }
 
-int wgrad_run_splits(long long batch, const int* osp, int cx, int ky) { return run_plan(batch, osp[1], osp[2], cx, ky).splits; }
-
-hipError_t launch_wgrad_run(const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* osp, int cx, int ky, float* cs_part, hipStream_t s) {
+hipError_t launch_wgrad_run(const RunPlan& r, const uint16_t* X, const uint16_t* DY, float* part, long long batch, const int* osp, int cx, int ky,
+                            float* cs_part, hipStream_t s) {
   WRunP p{};
   p.X = X; p.DY = DY; p.part = part; p.cs_part = cs_part;
   p.batch = (int)batch; p.H = osp[1]; p.W = osp[2]; p.cx = cx; p.ky = ky;
-  const RunPlan r = run_plan(batch, p.H, p.W, cx, ky);
   p.ctiles = r.ctiles; p.ktiles = r.ktiles; p.splits = r.splits;
   p.q_total = (int)r.q; p.q_per_split = r.q_per_split;
   const int wp = p.W + 1, img = (p.H + 1) * wp, left = STEP % img, images = STEP / img;

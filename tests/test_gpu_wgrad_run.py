@@ -11,6 +11,8 @@ CASES = [
     (1, (1, 1), 48, 48, 0), (17, (1, 5), 64, 64, 0), (9, (5, 1), 64, 56, 0), (70, (3, 3), 64, 64, 0), (1, (7, 15), 64, 64, 0), (1, (15, 7), 64, 72, 0),
     (2, (5, 126), 56, 128, 0), (1, (3, 127), 64, 64, 0), (3, (63, 63), 64, 64, 0), (1, (126, 126), 48, 200, 0), (40, (7, 7), 512, 72, 0),
     (60, (14, 14), 256, 256, 0), (8, (56, 56), 64, 64, 0), (12, (30, 31), 192, 320, 0), (3, (14, 14), 64, 64, 1), (2, (20, 30), 128, 72, 3),
+    # maps of which two share a patch where the tensors start between 16-byte boundaries: an odd number of images, one, all rows of a patch
+    (5, (7, 7), 64, 64, 1), (1, (7, 7), 64, 136, 4), (41, (8, 7), 128, 72, 2), (30, (3, 5), 48, 64, 1), (6, (8, 8), 64, 64, 1),
 ]
 
 

@@ -60,6 +60,18 @@ def test_partials_fit_the_workspace():
         assert splits * (per + k) * 4 <= L.conv_workspace_bytes(d, A.CONV_WGRAD_BIAS) or (filt[0] == 1 and k <= 8), what
 
 
+@pytest.mark.parametrize("n,sp,c,k", [(64, (56, 56), 64, 64), (8, (14, 14), 256, 256), (50, (7, 7), 64, 128), (51, (8, 7), 64, 64), (300, (7, 7), 128, 128), (3, (20, 30), 136, 72)])
+def test_patches_of_unaligned_tensors_fill_the_compute_units(n, sp, c, k):
+    """3x3 layers whose tensors start between 16-byte boundaries take patches of 8 x 16 positions, two images of at most 8 x 7 to a patch, and a
+    work-group per compute unit where there are as many patches: their number of partial filters."""
+    patches = (n + 1) // 2 if sp[0] <= 8 and sp[1] <= 7 else n * -(-sp[0] // 8) * -(-sp[1] // 16)
+    tiles = -(-c // 64) * -(-k // 64)
+    per = -(-patches // min(patches, -(-256 // tiles)))
+    ext, one = ints((1,) + sp), ints((1, 3, 3))
+    got = host("_ZN3lms18wgrad_patch_splitsExPKiS1_S1_S1_ii", ctypes.c_int, ctypes.c_longlong(n), ext, ext, one, ints((0, 1, 1)), ctypes.c_int(c), ctypes.c_int(k))
+    assert got == -(-patches // per)
+
+
 # first layers whose rows are and are not shorter than a segment, and one geometry of every other kernel; n, extents, c, k, filter, stride, pad
 GUARDED = [
     (1, (80, 80, 80), 1, 32, 3, 1, 1), (8, (100, 100), 1, 32, 3, 1, 1), (2, (224, 224), 3, 64, 3, 1, 1), (1, (40, 40, 72), 1, 32, 3, 1, 1),
