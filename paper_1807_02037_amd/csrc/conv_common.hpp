@@ -211,10 +211,20 @@ hipError_t launch_wgrad_small(const uint16_t* X, const uint16_t* DY, float* part
                               const int* osp, const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s);
 
 // The same for 2-D layers whose stride times channels is six (wgrad_stem.hip); at most as many splits as wgrad_small.hip.
-bool wgrad_stem_eligible(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad);
-int wgrad_stem_splits(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad);
-hipError_t launch_wgrad_stem(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp, const int* osp,
-                             const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s);
+struct StemGradPlan {
+  const uint16_t* X;
+  const uint16_t* DY;
+  float* part;
+  float* cs_part;              // partial column sums of dy [split][ky], or null
+  int cx, ky, H, W, OH, OW, filt, stride, pad_h, pad_w;      // filt: rows of the filter; stride: of rows
+  int run, lead, span;         // elements of a filter row, zero elements before them, groups they lie in
+  int th, tw, gpr;             // tile: rows, positions, groups of 16 of a row
+  int rows, gw, groups;        // staged rows of x, groups of one, of a tile
+  int tiles_h, tiles_w, tiles, tiles_per_split, splits;
+  unsigned gw_magic, pix_magic, span_magic;      // v / gw = v * gw_magic >> 20, and so for 16 gpr and span
+};
+bool wgrad_stem_plan(StemGradPlan& p, long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad);
+hipError_t launch_wgrad_stem(StemGradPlan p, const uint16_t* X, const uint16_t* DY, float* part, float* cs_part, hipStream_t s);
 
 // Streaming weight gradient for 1x1 filters without padding (wgrad_rows.hip): per-split partial filters [split][cx][ky].
 bool wgrad_rows_eligible(int cx, int ky, const int* asp, const int* filt, const int* stride, const int* pad);

@@ -921,14 +921,15 @@ bool wgrad_use_small(int cx, int ky, const int* asp, const int* osp, const int* 
 // The kernel that a weight gradient runs on and the number of partial filters it leaves: the launch and the workspace size
 // both follow this one choice.
 enum WgradRoute { WGRAD_TINY, WGRAD_STEM, WGRAD_SMALL, WGRAD_ROWS, WGRAD_RUN, WGRAD_PATCH, WGRAD_GENERAL };
-struct WgradPlan { WgradRoute route; int splits; RunPlan run{}; };
+struct WgradPlan { WgradRoute route; int splits; RunPlan run{}; StemGradPlan stem{}; };
 WgradPlan wgrad_plan(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad,
                      int transpose) {
   static const bool no_patch = getenv("LMS_NO_WGRAD_PATCH") != nullptr;   // tuning aid
   if (!transpose) {
     if (wgrad_tiny_eligible(cx, ky, filt, stride, pad)) return {WGRAD_TINY, wgrad_tiny_wgs(rows, cx)};
     if (wgrad_use_small(cx, ky, asp, osp, filt, stride)) {
-      if (wgrad_stem_eligible(rows, cx, ky, asp, osp, filt, stride, pad)) return {WGRAD_STEM, wgrad_stem_splits(rows, cx, ky, asp, osp, filt, stride, pad)};
+      StemGradPlan stem{};
+      if (wgrad_stem_plan(stem, rows, cx, ky, asp, osp, filt, stride, pad)) return {WGRAD_STEM, stem.splits, {}, stem};
       return {WGRAD_SMALL, wgrad_small_splits(rows, osp)};
     }
     if (wgrad_rows_eligible(cx, ky, asp, filt, stride, pad)) return {WGRAD_ROWS, wgrad_rows_splits(rows, cx, ky)};
@@ -985,7 +986,7 @@ hipError_t launch_wgrad_dw(const uint16_t* X, const uint16_t* DY, float* dw, voi
     float* part = reinterpret_cast<float*>(ws);
     float* cs = side ? colsum_part(ws, splits, per) : nullptr;
     hipError_t e;
-    if (plan.route == WGRAD_STEM) e = launch_wgrad_stem(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
+    if (plan.route == WGRAD_STEM) e = launch_wgrad_stem(plan.stem, X, DY, part, cs, s);
     else if (plan.route == WGRAD_SMALL) e = launch_wgrad_small(X, DY, part, rows, cx, ky, asp, osp, filt, stride, pad, cs, s);
     else if (plan.route == WGRAD_ROWS) e = launch_wgrad_rows(X, DY, part, rows, cx, ky, asp, osp, stride, cs, s);
     else if (plan.route == WGRAD_RUN) e = launch_wgrad_run(plan.run, X, DY, part, batch, osp, cx, ky, cs, s);

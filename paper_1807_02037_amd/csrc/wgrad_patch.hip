@@ -644,14 +644,14 @@ __global__ __launch_bounds__(NTHREADS, 1) void wgrad_patch64_kernel(WPatchP p) {
 
 // 64 x 64 channel tile: 2-D filters with at least 48 channels on both sides
 bool wide_tile(const int* filt, int cx, int ky) {
-  if (getenv("LMS_NO_WGRAD_WIDE")) return false;
-  return filt[0] == 1 && cx >= 48 && ky >= 48 && (cx & 7) == 0;
+  static const bool off = getenv("LMS_NO_WGRAD_WIDE") != nullptr;     // tuning aid
+  return !off && filt[0] == 1 && cx >= 48 && ky >= 48 && (cx & 7) == 0;
 }
 
 // Two images per patch (the PK form of the 64 x 64 kernel): same-size 3 x 3 convolution on maps at most 7 wide and 8 high.
 bool pair_packed(const int* asp, const int* osp, const int* filt, const int* pad, int cx, int ky) {
-  if (getenv("LMS_NO_WGRAD_PAIRS")) return false;   // tuning aid
-  return wide_tile(filt, cx, ky) && osp[2] <= 7 && osp[1] <= 8 && asp[1] == osp[1] && asp[2] == osp[2] && pad[2] == 1;
+  static const bool off = getenv("LMS_NO_WGRAD_PAIRS") != nullptr;    // tuning aid
+  return !off && wide_tile(filt, cx, ky) && osp[2] <= 7 && osp[1] <= 8 && asp[1] == osp[1] && asp[2] == osp[2] && pad[2] == 1;
 }
 
 // Channel counts whose rows are 16-byte vectors take the kernel with two groups of waves; it addresses a patch (six input
@@ -687,8 +687,8 @@ PatchGrid patch_grid(long long batch, const int* asp, const int* osp, const int*
   // (32 x 32 tiles) measured 5 % faster on the 3D U-Net step than four; with two groups of waves in one that is one, and
   // no more than one, which is what its LDS leaves room for (240 x 80 at 29 x 25 x 27: 264 of them 65 us, 240 47)
   const bool one = tile == 32 && grouped(asp, osp, cx, ky);
-  long long target = tile == 64 || one ? 256 : 512;
-  if (const char* e = getenv("LMS_WGRAD_PATCH_WGS")) target = atoll(e);
+  static const char* const wgs = getenv("LMS_WGRAD_PATCH_WGS");       // tuning aid
+  const long long target = wgs ? atoll(wgs) : tile == 64 || one ? 256 : 512;
   long long splits = one ? target / wg : (target + wg - 1) / wg;
   if (splits > g.patches) splits = g.patches;
   if (splits < 1) splits = 1;

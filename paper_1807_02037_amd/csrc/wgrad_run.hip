@@ -381,6 +381,15 @@ RunPlan run_plan(long long batch, int h, int w, int cx, int ky, long long room) 
   return cost(b, 1.28) + 1.3 < cost(a, 2.05) ? b : a;
 }
 
+template <int KT, bool CS>
+hipError_t launch_run_t(const WRunP& p, unsigned grid, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_run_kernel<KT, CS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, RunTile<KT>::LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((wgrad_run_kernel<KT, CS>), dim3(grid), dim3(RUN_NT), RunTile<KT>::LDS, s, p);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 // Offsets within a work-group's part of the run have 31 bits.
@@ -409,14 +418,8 @@ hipError_t launch_wgrad_run(const RunPlan& r, const uint16_t* X, const uint16_t*
   p.above = (STEP + img - 1) / img;
   const int tiles = r.ctiles * r.ktiles;
   const unsigned grid = (unsigned)(tiles > 1 ? xcd_grid((long long)tiles * r.splits) : r.splits);
-  auto run = [&](auto kernel, int lds) -> hipError_t {
-    const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(RUN_NT), lds, s, p);
-    return hipGetLastError();
-  };
-  if (r.kt == 64) return cs_part ? run(wgrad_run_kernel<64, true>, RunTile<64>::LDS) : run(wgrad_run_kernel<64, false>, RunTile<64>::LDS);
-  return cs_part ? run(wgrad_run_kernel<32, true>, RunTile<32>::LDS) : run(wgrad_run_kernel<32, false>, RunTile<32>::LDS);
+  if (r.kt == 64) return cs_part ? launch_run_t<64, true>(p, grid, s) : launch_run_t<64, false>(p, grid, s);
+  return cs_part ? launch_run_t<32, true>(p, grid, s) : launch_run_t<32, false>(p, grid, s);
 }
 
 }  // namespace lms

@@ -36,19 +36,6 @@ constexpr int WT_X = WT_NX * WT_NT * 16, WT_Y = WT_PIX * WT_PIX_B;
 constexpr int WT_LDS = 2 * WT_X + 3 * WT_Y;
 constexpr int WT_YV = WT_PIX * 8 / WT_NT;            // loads of dy per thread and tile
 
-struct WStemP {
-  const uint16_t* X;
-  const uint16_t* DY;
-  float* part;
-  float* cs_part;              // partial column sums of dy [split][ky], or null
-  int cx, ky, H, W, OH, OW, filt, stride, pad_h, pad_w;      // filt: rows of the filter; stride: of rows
-  int run, lead, span;         // elements of a filter row, zero elements before them, groups they lie in
-  int th, tw, gpr;             // tile: rows, positions, groups of 16 of a row
-  int rows, gw, groups;        // staged rows of x, groups of one, of a tile
-  int tiles_h, tiles_w, tiles, tiles_per_split;
-  unsigned gw_magic, pix_magic, span_magic;      // v / gw = v * gw_magic >> 20, and so for 16 gpr and span
-};
-
 __device__ __forceinline__ v2u wt_tr(const unsigned char* q) {
   return __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q));
 }
@@ -59,7 +46,7 @@ __device__ __forceinline__ bf16x8 wt_frag(const unsigned char* a, const unsigned
 
 // JT: 32-row tiles of the padded (filter row, element) index.
 template <int JT>
-__global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(WStemP p) {
+__global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(StemGradPlan p) {
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_st[];
   const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kq = wave8 & 1, g = wave8 >> 1;                       // 32 output channels; turn among the groups of 16 positions
@@ -250,8 +237,19 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(WStemP p) {
   if (p.cs_part && lane >= 32 && k < p.ky) p.cs_part[(long long)blockIdx.x * p.ky + k] = acc[0][2];
 }
 
-bool wstem_plan(WStemP& p, long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad) {
-  if (cx < 1 || cx > 4 || stride[2] * cx != 6 || asp[0] != 1 || osp[0] != 1 || filt[0] != 1 || pad[0] != 0 || ky > 64 || (ky & 7) != 0) return false;
+template <int JT>
+hipError_t launch_stem_t(const StemGradPlan& p, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_stem_kernel<JT>), hipFuncAttributeMaxDynamicSharedMemorySize, WT_LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(wgrad_stem_kernel<JT>, dim3((unsigned)p.splits), dim3(WT_NT), WT_LDS, s, p);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool wgrad_stem_plan(StemGradPlan& p, long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad) {
+  static const bool off = getenv("LMS_NO_WGRAD_STEM") != nullptr;     // tuning aid
+  if (off || cx < 1 || cx > 4 || stride[2] * cx != 6 || asp[0] != 1 || osp[0] != 1 || filt[0] != 1 || pad[0] != 0 || ky > 64 || (ky & 7) != 0) return false;
   if ((asp[2] * cx & 1) != 0 || 2LL * asp[1] * asp[2] * cx >= 0x7fffffffLL) return false;
   p.cx = cx; p.ky = ky; p.H = asp[1]; p.W = asp[2]; p.OH = osp[1]; p.OW = osp[2];
   p.filt = filt[1]; p.stride = stride[1]; p.pad_h = pad[1]; p.pad_w = pad[2];
@@ -286,38 +284,16 @@ bool wstem_plan(WStemP& p, long long rows, int cx, int ky, const int* asp, const
   if (splits > tiles) splits = tiles;
   if (splits < 1) splits = 1;
   p.tiles_per_split = (int)((tiles + splits - 1) / splits);
-  return true;
+  p.splits = (int)((tiles + p.tiles_per_split - 1) / p.tiles_per_split);
+  return tiles > 0;
 }
 
-}  // namespace
-
-bool wgrad_stem_eligible(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad) {
-  static const bool off = getenv("LMS_NO_WGRAD_STEM") != nullptr;     // tuning aid
-  WStemP p{};
-  return !off && wstem_plan(p, rows, cx, ky, asp, osp, filt, stride, pad);
-}
-int wgrad_stem_splits(long long rows, int cx, int ky, const int* asp, const int* osp, const int* filt, const int* stride, const int* pad) {
-  WStemP p{};
-  if (!wstem_plan(p, rows, cx, ky, asp, osp, filt, stride, pad) || p.tiles <= 0) return 1;
-  return (p.tiles + p.tiles_per_split - 1) / p.tiles_per_split;
-}
-
-hipError_t launch_wgrad_stem(const uint16_t* X, const uint16_t* DY, float* part, long long rows, int cx, int ky, const int* asp, const int* osp,
-                             const int* filt, const int* stride, const int* pad, float* cs_part, hipStream_t s) {
-  WStemP p{};
-  if (!wstem_plan(p, rows, cx, ky, asp, osp, filt, stride, pad)) return hipErrorInvalidValue;
+hipError_t launch_wgrad_stem(StemGradPlan p, const uint16_t* X, const uint16_t* DY, float* part, float* cs_part, hipStream_t s) {
   p.X = X; p.DY = DY; p.part = part; p.cs_part = cs_part;
   const int jt = (p.filt * p.span * 8 + 31) / 32;
-  const dim3 grid((unsigned)wgrad_stem_splits(rows, cx, ky, asp, osp, filt, stride, pad));
-  auto run = [&](auto kernel) -> hipError_t {
-    const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(kernel, grid, dim3(WT_NT), WT_LDS, s, p);
-    return hipGetLastError();
-  };
-  if (jt <= 2) return run(wgrad_stem_kernel<2>);
-  if (jt <= 4) return run(wgrad_stem_kernel<4>);
-  return run(wgrad_stem_kernel<7>);
+  if (jt <= 2) return launch_stem_t<2>(p, s);
+  if (jt <= 4) return launch_stem_t<4>(p, s);
+  return launch_stem_t<7>(p, s);
 }
 
 }  // namespace lms
