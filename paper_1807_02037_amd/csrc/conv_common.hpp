@@ -54,6 +54,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// The larger of m and the largest magnitude of a; NaN if one of them is: v_maximum3_f32.
+__device__ __forceinline__ float magnitude(const f32x16& a, float m) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) m = __builtin_elementwise_maximum(m, __builtin_fabsf(a[v]));
+  return m;
+}
+
 constexpr int BK = 32;        // reduction elements per stage
 constexpr int LDA = BK + 8;   // LDS row pitch (bf16): 80 bytes, keeps 16-byte reads conflict-free
 constexpr int NTHREADS = 256;

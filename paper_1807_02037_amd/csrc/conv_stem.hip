@@ -9,9 +9,10 @@
 // stays in registers (both halves of 64 outputs), the input rows of the next tile are on their way while one is multiplied, and
 // results leave through wave_epilogue.
 //
-// The elements under a run's zero weights are pixels beside the window, and zero times an infinity or a NaN is a NaN.  The input rows are
-// looked at on their way to LDS (two operations a dword, 45.7 -> 46.5 us at 64 images of 224 x 224); a tile that holds such a value masks those elements out, so
-// that it reaches the outputs whose window contains it and no others.
+// The elements under a run's zero weights are pixels beside the window, and zero times an infinity or a NaN is a NaN.  A sum that is
+// finite met no such value; 32 positions with one that is not are multiplied again with those elements masked, so that an
+// infinity or a NaN reaches the outputs whose window contains it and no others (the look at the sums: 45.6 -> 46.6 us at 64 images of
+// 224 x 224; at the input rows on their way to LDS, before the next ones are asked for, 47.4).
 //
 // What bounds it is memory, 122 MB for 64 images of 224 x 224 (21 us at the rate of a large copy): 87 -> 43 us; 64 images of 48 x 48
 // 24 -> 9.
@@ -30,7 +31,6 @@ namespace {
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
-typedef unsigned short v2us __attribute__((ext_vector_type(2)));
 typedef unsigned v4ua __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int ST_NI = 4, ST_NH = 7;                  // rows a wave stages, dwords a lane has of each
@@ -61,7 +61,6 @@ template <int KS>
 __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
   __shared__ __attribute__((aligned(16))) unsigned raw[ST_ROWS * ST_PD];
   __shared__ __attribute__((aligned(16))) unsigned char epi[ST_EPI];
-  __shared__ int not_finite;                                      // 1 + the last tile with infinities or NaN among its inputs
   static_assert(KS * 16 * ST_LDW * 2 <= ST_EPI, "the filter is staged where the results go later");
   const IgemmP& p = sp.g;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -70,7 +69,6 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
 
   // ---- the filter: row 8 g + i of LDS holds element i of group g, zeros outside the run; then both halves as fragments ----
   uint16_t* sW = reinterpret_cast<uint16_t*>(epi);
-  if (tid == 0) not_finite = 0;
   for (int v = tid; v < KS * 16 * 8; v += NTHREADS) {
     const int j = v >> 3, cv = v & 7, grp = j >> 3, kh = grp / sp.rc, e = (grp - kh * sp.rc) * 8 + (j & 7) - sp.lead;
     uint4 w = make_uint4(0, 0, 0, 0);
@@ -91,7 +89,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     const int grp = 2 * ks + half, kh = grp / sp.rc;
-    g_off[ks] = grp < sp.chunks ? kh * sp.pitch * 4 + (grp - kh * sp.rc) * 16 : 0;      // zero weights: any elements (masked where one is not finite)
+    g_off[ks] = grp < sp.chunks ? kh * sp.pitch * 4 + (grp - kh * sp.rc) * 16 : 0;      // zero weights: any elements (masked where a sum is not finite)
   }
 
   // ---- input rows: wave w stages rows w, w + 4, ..., a lane every 64th dword ----
@@ -131,17 +129,11 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
   if (t < sp.tiles) load(t);
   for (; t < sp.tiles; t += step) {
     __syncthreads();                                              // the rows (and the filter) have been read
-    v2us top = {0, 0};                                            // largest magnitudes of even and odd elements
 #pragma unroll
     for (int i = 0; i < ST_NI; ++i)
 #pragma unroll
-      for (int h = 0; h < ST_NH; ++h) {
-        if (wave + 4 * i < sp.rows && 64 * h < sp.pd) {           // uniform
-          raw[(wave + 4 * i) * sp.pitch + lane + 64 * h] = next[i][h];
-          top = __builtin_elementwise_max(top, __builtin_bit_cast(v2us, next[i][h] & 0x7fff7fffu));
-        }
-      }
-    if (top[0] >= 0x7f80 || top[1] >= 0x7f80) not_finite = t + 1;
+      for (int h = 0; h < ST_NH; ++h)
+        if (wave + 4 * i < sp.rows && 64 * h < sp.pd) raw[(wave + 4 * i) * sp.pitch + lane + 64 * h] = next[i][h];
     int n, oh0, ow0;
     place(t, n, oh0, ow0);
     if (t + step < sp.tiles) load(t + step);
@@ -149,7 +141,6 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
     const int tw = p.osp[2] - ow0 < sp.tw ? p.osp[2] - ow0 : sp.tw, th = p.osp[1] - oh0 < sp.th ? p.osp[1] - oh0 : sp.th;
     const long long row0 = ((long long)n * p.osp[1] + oh0) * p.osp[2] + ow0;
     const EpiBuffers eb(p, row0, (p.M - row0) * p.nout * 2);
-    const bool masked = __builtin_amdgcn_readfirstlane(not_finite) == t + 1;
 #pragma unroll 1
     for (int i = 0; i < ST_UNITS; ++i) {
       const int u0 = (wave + 4 * i) * 32;
@@ -163,11 +154,11 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
       const bool in = at(u0 + (lane & 31), dr, dc);
       const unsigned char* x = reinterpret_cast<const unsigned char*>(raw) + (in ? dr * p.stride[1] * sp.pitch * 4 + dc * p.stride[2] * c * 2 : 0);
       f32x16 acc[1][2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
       auto products = [&](auto masked_c) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
           v4ua q = *reinterpret_cast<const v4ua*>(x + g_off[ks]);
@@ -186,8 +177,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void conv_stem_kernel(StemP sp) {
           for (int j = 0; j < 2; ++j) acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks][j], xf, acc[0][j], 0, 0, 0);
         }
       };
-      if (__builtin_expect(masked, 0)) products(std::true_type{});                     // uniform
-      else products(std::false_type{});
+      products(std::false_type{});
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(magnitude(acc[0][0], magnitude(acc[0][1], 0.f)) < __builtin_inff())) != 0, 0))
+        products(std::true_type{});
       auto out_off = [&](int r) -> unsigned {                     // r: row of the 32 positions
         int d, e;
         return at(u0 + r, d, e) ? col + (unsigned)((d * p.osp[2] + e) * p.nout * 2) : DMA_OOB;

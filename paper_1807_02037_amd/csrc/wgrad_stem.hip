@@ -6,8 +6,8 @@
 // read delivers them as MFMA operands, 8 * span (padded) elements of the reduction's other side per filter row, with nothing
 // gathered (what bounds wgrad_small.hip).  The first padding element of a group is 1: its row of the product is the
 // column sum of dy, the bias / shift gradient, for nothing.  dy goes straight to LDS (buffer loads that write it).  Positions of a
-// tile's last group of 16 that are none of its row's would meet dy = 0 with real pixels, which makes NaN of infinite ones: their x
-// is masked there, and rows below the last are left out.
+// tile's last group of 16 that are none of its row's would meet dy = 0 with real pixels, which makes NaN of infinite ones: where tiles
+// do not fill rows and maps in whole groups (RAGGED) their x is masked, and rows below the last are left out.
 //
 // A work-group of eight waves, one per compute unit, owns the whole filter gradient and a run of tiles of up to 256 positions; a wave
 // takes 32 output channels (all rows of the product) and every fourth 16 positions; dy of the next two tiles and x of the next
@@ -45,7 +45,7 @@ __device__ __forceinline__ bf16x8 wt_frag(const unsigned char* a, const unsigned
 }
 
 // JT: 32-row tiles of the padded (filter row, element) index.
-template <int JT>
+template <int JT, bool RAGGED>
 __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(StemGradPlan p) {
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_st[];
   const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(StemGradPlan p) {
     for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 
   // 16 positions: operands, read one turn ahead of their products
-  struct Frag { bf16x8 y, x[JT]; int left; };                     // left: positions from the first of the 16 to the end of the row
+  struct Frag { bf16x8 y, x[JT]; int left; };                     // left (RAGGED): positions from the first of the 16 to the end of the row
   int tw_at = begin % p.tiles_w, th_at = begin / p.tiles_w % p.tiles_h;      // the tile that is multiplied
   if (begin < end) {
     fetch(xr0, 0);
@@ -144,15 +144,19 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(StemGradPlan p) {
     if (t + 2 < end) fetch(xr, ybuf == 0 ? 2 : ybuf - 1);
     const unsigned char* sx = lds_st + xbuf * WT_X;
     const unsigned char* sy = lds_st + 2 * WT_X + ybuf * WT_Y;
-    const int row_len = p.OW - tw_at * p.tw < p.tw ? p.OW - tw_at * p.tw : p.tw, rows_in = p.OH - th_at * p.th < p.th ? p.OH - th_at * p.th : p.th;
+    int row_len = p.tw, rows_in = p.th;
+    if constexpr (RAGGED) {
+      if (p.OW - tw_at * p.tw < row_len) row_len = p.OW - tw_at * p.tw;
+      if (p.OH - th_at * p.th < rows_in) rows_in = p.OH - th_at * p.th;
+      if (++tw_at == p.tiles_w) { tw_at = 0; if (++th_at == p.tiles_h) th_at = 0; }
+    }
     const int turns = (rows_in * p.gpr - g + 3) / 4;              // of this wave
-    if (++tw_at == p.tiles_w) { tw_at = 0; if (++th_at == p.tiles_h) th_at = 0; }
     int r = 0, c = g;                                             // row and group of 16 of the next turn
     while (c >= p.gpr) { c -= p.gpr; ++r; }
     auto load = [&](Frag& f) {
       const unsigned char* xq = sx + r * p.stride * x_pitch + c * 256;
       const unsigned char* yq = sy + (r * p.gpr + c) * 16 * WT_PIX_B;
-      f.left = row_len - c * 16;
+      if constexpr (RAGGED) f.left = row_len - c * 16;
       f.y = wt_frag(yq + ya[0], yq + ya[1]);
 #pragma unroll
       for (int j = 0; j < JT; ++j) f.x[j] = wt_frag(xq + xa[j], xq + xa[j] + 64);
@@ -160,13 +164,15 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(StemGradPlan p) {
       while (c >= p.gpr) { c -= p.gpr; ++r; }
     };
     auto mul = [&](Frag& f) {
-      if (f.left < 16) {                                          // uniform
-        const int n = f.left - 8 * (lane >> 5);
-        v4u m;
+      if constexpr (RAGGED) {
+        if (f.left < 16) {                                          // uniform
+          const int n = f.left - 8 * (lane >> 5);
+          v4u m;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) m[w] = (2 * w < n ? 0xffffu : 0u) | (2 * w + 1 < n ? 0xffff0000u : 0u);
+          for (int w = 0; w < 4; ++w) m[w] = (2 * w < n ? 0xffffu : 0u) | (2 * w + 1 < n ? 0xffff0000u : 0u);
 #pragma unroll
-        for (int j = 0; j < JT; ++j) f.x[j] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(v4u, f.x[j]) & m);
+          for (int j = 0; j < JT; ++j) f.x[j] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(v4u, f.x[j]) & m);
+        }
       }
 #pragma unroll
       for (int j = 0; j < JT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.x[j], f.y, acc[j], 0, 0, 0);
@@ -237,11 +243,12 @@ __global__ __launch_bounds__(WT_NT, 2) void wgrad_stem_kernel(StemGradPlan p) {
   if (p.cs_part && lane >= 32 && k < p.ky) p.cs_part[(long long)blockIdx.x * p.ky + k] = acc[0][2];
 }
 
-template <int JT>
+template <int JT, bool RAGGED>
 hipError_t launch_stem_t(const StemGradPlan& p, hipStream_t s) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_stem_kernel<JT>), hipFuncAttributeMaxDynamicSharedMemorySize, WT_LDS);
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_stem_kernel<JT, RAGGED>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, WT_LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(wgrad_stem_kernel<JT>, dim3((unsigned)p.splits), dim3(WT_NT), WT_LDS, s, p);
+  hipLaunchKernelGGL((wgrad_stem_kernel<JT, RAGGED>), dim3((unsigned)p.splits), dim3(WT_NT), WT_LDS, s, p);
   return hipGetLastError();
 }
 
@@ -291,9 +298,10 @@ bool wgrad_stem_plan(StemGradPlan& p, long long rows, int cx, int ky, const int*
 hipError_t launch_wgrad_stem(StemGradPlan p, const uint16_t* X, const uint16_t* DY, float* part, float* cs_part, hipStream_t s) {
   p.X = X; p.DY = DY; p.part = part; p.cs_part = cs_part;
   const int jt = (p.filt * p.span * 8 + 31) / 32;
-  if (jt <= 2) return launch_stem_t<2>(p, s);
-  if (jt <= 4) return launch_stem_t<4>(p, s);
-  return launch_stem_t<7>(p, s);
+  const bool ragged = p.tw % 16 != 0 || p.tw * p.tiles_w != p.OW || p.th * p.tiles_h != p.OH;
+  if (jt <= 2) return ragged ? launch_stem_t<2, true>(p, s) : launch_stem_t<2, false>(p, s);
+  if (jt <= 4) return ragged ? launch_stem_t<4, true>(p, s) : launch_stem_t<4, false>(p, s);
+  return ragged ? launch_stem_t<7, true>(p, s) : launch_stem_t<7, false>(p, s);
 }
 
 }  // namespace lms
