@@ -25,3 +25,14 @@ def to_oracle_graph(g):
     for e in g.edges():
         og.edges.append(OEdge(e.src, e.dst, ACTIONS[e.action], e.slot))
     return og, infos
+
+
+def kernel_names(call):
+    """Names of the kernels that a call launches, as the profiler sees them."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages() if "lms::" in e.key]

@@ -76,9 +76,11 @@ CASES = [
     ("5x5_s2_even", 2, (12, 16), 16, 24, (5, 5), 2, 2),
     ("3d_3x3x3_s2_even", 1, (8, 6, 10), 16, 32, (3, 3, 3), 2, 1),
     ("1x1_s2_56_c256_k512", 1, (56, 56), 256, 512, (1, 1), 2, 0),
-    # enough patches for the resident-filter kernel (several per compute unit), ragged in every axis
-    ("rf_3x3_64_64_ragged", 24, (50, 70), 64, 64, (3, 3), 1, 1),
+    # enough patches for the resident-filter kernel (several per compute unit; 2-D rows of more than 87 positions), ragged in every axis
+    ("rf_3x3_64_64_ragged", 16, (50, 101), 64, 64, (3, 3), 1, 1),
     ("rf_3d_32_32_ragged", 2, (36, 60, 70), 32, 32, (3, 3, 3), 1, 1),
+    # as many patches with shorter rows: the kernel on runs of positions
+    ("3x3_64_64_rows_of_70", 24, (50, 70), 64, 64, (3, 3), 1, 1),
 ]
 IDS = [c[0] for c in CASES]
 
@@ -276,8 +278,10 @@ RF_CASES = [c for c in CASES if c[0].startswith("rf_")]
 @pytest.mark.parametrize("terms", ["res_only", "addend_only", "mask_only"])
 def test_resident_filter_kernel_single_epilogue_terms(case, terms):
     """The resident-filter kernel is compiled once per combination of epilogue terms (tensor added, ReLU mask,
-    per-channel coefficients); the combinations with exactly one tensor term are not reached by the tests above."""
+    per-channel coefficients); the combinations with exactly one tensor term are not reached by the tests above.  The kernel's name
+    shows that the case still takes it."""
     import torch
+    from helpers import kernel_names
     import paper_1807_02037_amd as L
     A = L.abi
     name, n, in_sp, c, k, filt, stride, pad = case
@@ -292,7 +296,7 @@ def test_resident_filter_kernel_single_epilogue_terms(case, terms):
         y = torch.full(ref.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
         ws = torch.empty(max(L.conv_workspace_bytes(d, A.CONV_FWD), 256), dtype=torch.uint8, device="cuda")
         dx, dw, dr = dev_bf16(x), dev_bf16(w), dev_bf16(res)
-        L.conv_fwd(d, dx.data_ptr(), dw.data_ptr(), None, None, dr.data_ptr(), y.data_ptr(), ws.data_ptr(), s)
+        names = kernel_names(lambda: L.conv_fwd(d, dx.data_ptr(), dw.data_ptr(), None, None, dr.data_ptr(), y.data_ptr(), ws.data_ptr(), s))
         got = host(y)
     else:
         yshape = ops.conv_fwd(x[:1] * 0, w, stride, pad).shape
@@ -309,8 +313,9 @@ def test_resident_filter_kernel_single_epilogue_terms(case, terms):
         ddy, dw = dev_bf16(dy), dev_bf16(w)
         da = dev_bf16(addend) if addend is not None else None
         dm = dev_bf16(mask) if mask is not None else None
-        L.conv_dgrad(d, ddy.data_ptr(), dw.data_ptr(), None, da.data_ptr() if da is not None else None,
-                     dm.data_ptr() if dm is not None else None, out.data_ptr(), ws.data_ptr(), s)
+        names = kernel_names(lambda: L.conv_dgrad(d, ddy.data_ptr(), dw.data_ptr(), None, da.data_ptr() if da is not None else None,
+                                                  dm.data_ptr() if dm is not None else None, out.data_ptr(), ws.data_ptr(), s))
         got = host(out)
+    assert any("conv_rf_kernel" in v for v in names), names
     assert np.isfinite(got).all()
     assert rel_err(got, ref) <= 1e-2, rel_err(got, ref)
