@@ -1523,12 +1523,13 @@ hipError_t maxpool_fwd(const ConvGeom& g, const void* x, void* y, hipStream_t s)
 hipError_t maxpool_bwd(const ConvGeom& g, const void* dy, const void* x, int mask_relu, void* dx, hipStream_t s) {
   if (pool3s2_fast(g) && (((uintptr_t)dy | (uintptr_t)x | (uintptr_t)dx) & 15) == 0) {
     const int th = (g.in_sp[1] + P3_IN - 1) / P3_IN, tw = (g.in_sp[2] + P3_IN - 1) / P3_IN;
-    const long long blocks = (long long)g.n * th * tw;
     const int cgroups = (g.c / 8 + 7) / 8;
-    if (blocks < 0x7fffffffLL && cgroups < 65536) {
-      hipLaunchKernelGGL(maxpool3s2_bwd_kernel, dim3((unsigned)blocks, (unsigned)cgroups), dim3(TB), 0, s, pool_params(g), (const uint4*)dy,
-                         (const uint4*)x, mask_relu, (uint4*)dx, th, tw);
-      return hipGetLastError();
+    if (cgroups < 65536) {
+      const int64_t per = (int64_t)g.out_sp[1] * g.out_sp[2] * (g.c / 8), in_per = (int64_t)g.in_sp[1] * g.in_sp[2] * (g.c / 8);
+      return pool_launches(g.n, (int64_t)th * tw * TB, [&](int64_t u, int64_t take) {
+        hipLaunchKernelGGL(maxpool3s2_bwd_kernel, dim3((unsigned)(take * th * tw), (unsigned)cgroups), dim3(TB), 0, s, pool_params(g), (const uint4*)dy + u * per,
+                           (const uint4*)x + u * in_per, mask_relu, (uint4*)dx + u * in_per, th, tw);
+      });
     }
   }
   if (pool2_fast(g)) return launch_pool2<1>(g, x, dy, mask_relu, dx, s);

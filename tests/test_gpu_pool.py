@@ -3,16 +3,10 @@ odd and even, channel counts that fill no group of 64, windows of 1 or 2 per axi
 NaN (passed over: a window of nothing else names nobody, or its first element without overlap).  Reference: the window walked in
 row-major order, strictly greater wins; forward exact, gradient one bf16 rounding of a sum of at most four terms (2^-8, and 2^-22
 of the terms' magnitudes for the order of fp32 sums)."""
-import ctypes
-
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
-
-
-class Geom(ctypes.Structure):
-    _fields_ = [("n", ctypes.c_int64)] + [(f, ctypes.c_int * 3) for f in ("in_sp", "out_sp", "filt", "stride", "pad")] + [("c", ctypes.c_int), ("k", ctypes.c_int)]
 
 
 def reference(x, dy, win, stride, pad, mask, overlap):
@@ -47,6 +41,27 @@ def reference(x, dy, win, stride, pad, mask, overlap):
     return best, dx, mag
 
 
+def run(L, n, sp, osp, c, w3, s3, p3, flat, mask, x, dy, y, dx):
+    """One step of a graph of the two pooling operations, everything in the caller's tensors."""
+    import torch
+    A = L.abi
+    g, cut = L.Graph(), 1 if flat else 0
+    attr = dict(filt=w3[cut:], stride=s3[2], pad=p3[2])
+    shape = lambda ext: (n,) + tuple(ext)[cut:] + (c,)
+    vx, vdy = g.add_variable("x", A.BF16, shape(sp), A.VAR_INPUT), g.add_variable("dy", A.BF16, shape(osp), A.VAR_CONST)
+    ny = g.add_op("y", A.OP_MAXPOOL, [vx], **attr)
+    ndx = g.add_op("dx", A.OP_MAXPOOL_BWD, [vdy, vx], A.BWD, flags=A.F_MASK if mask else 0, **attr)
+    for node in (ny, ndx):
+        g.set_external(node)
+    need = g.memory_need()[1]
+    arena, pool, st = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda"), L.api.PinnedPool(256), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ex = L.Executor(g, arena.data_ptr(), need, pool.ptr, 256, *[st.cuda_stream] * 3, 0)
+    for node, t in ((vx, x), (vdy, dy), (ny, y), (ndx, dx)):
+        ex.bind(node, t.data_ptr())
+    ex.step()
+
+
 # n, extents, c, window, stride, padding
 CASES = [
     (2, (1, 1, 1), 8, 3, 2, 1), (2, (1, 1, 7), 16, 3, 2, 1), (1, (1, 9, 1), 8, 3, 2, 1), (2, (1, 16, 16), 72, 3, 2, 1), (1, (1, 17, 15), 64, 3, 2, 1),
@@ -77,13 +92,35 @@ def test_forward_and_gradient(n, sp, c, win, stride, pad, mask):
     xd = dev(x)
     dyd = dev(rng.standard_normal([n] + osp + [c]).astype(np.float32))
     y, dx = torch.empty_like(dyd), torch.full_like(xd, 7.0)
-    g = Geom(n, *[(ctypes.c_int * 3)(*v) for v in (sp, osp, w3, s3, p3)], c, c)
-    lib, st = ctypes.CDLL(L.abi.lib()._name), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
-    assert lib._ZN3lms11maxpool_fwdERKNS_8ConvGeomEPKvPvP12ihipStream_t(ctypes.byref(g), ptr(xd), ptr(y), st) == 0
-    assert lib._ZN3lms11maxpool_bwdERKNS_8ConvGeomEPKvS4_iPvP12ihipStream_t(ctypes.byref(g), ptr(dyd), ptr(xd), mask, ptr(dx), st) == 0
-    torch.cuda.synchronize()
+    run(L, n, sp, osp, c, w3, s3, p3, flat, mask, xd, dyd, y, dx)
     best, ref, mag = reference(x, dyd.float().cpu().numpy(), w3, s3, p3, mask, win == 3)
     assert np.array_equal(y.float().cpu().numpy(), best)
     assert np.array_equal(np.signbit(y.float().cpu().numpy()), np.signbit(best))
     assert (np.abs(dx.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -22 * mag).all()
+
+
+@pytest.mark.parametrize("n,hw,c,win,stride,pad", [((1 << 28) + 3, 1, 64, 3, 2, 1), ((1 << 28) + 5, 1, 64, 1, 1, 0), (1 << 26, 2, 72, 2, 2, 0)])
+def test_more_than_two_to_the_31_vectors(n, hw, c, win, stride, pad):
+    """Tensors of more vectors than a launch has threads, in several launches: maps of one pixel, whose maximum is the pixel, and of 2 x 2."""
+    import torch
+    import paper_1807_02037_amd as L
+    shape = (n, 1, hw, hw, c)
+    pattern = torch.randn(1 << 20, generator=torch.Generator().manual_seed(c)).to(torch.bfloat16).cuda()
+
+    def fill(shape, shift):
+        t = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+        for i, part in enumerate(t.view(-1).split(1 << 30)):
+            part.copy_(pattern.roll(shift + 977 * i).repeat((part.numel() >> 20) + 1)[:part.numel()])
+        return t
+    x, dy = fill(shape, 0), fill((n, 1, 1, 1, c), 31)
+    y, dx = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    run(L, n, (1, hw, hw), (1, 1, 1), c, [1, win, win], [1, stride, stride], [0, pad, pad], True, 0, x, dy, y, dx)
+    torch.cuda.synchronize()
+    for a, b, gy, gx in zip(*[t.view(n, -1, c).split(1 << 22) for t in (x, dy, y, dx)]):
+        best = a.amax(dim=1, keepdim=True)
+        assert torch.equal(gy, best)
+        if hw == 1:
+            assert torch.equal(gx, b)
+        else:
+            first = (a == best).cumsum(dim=1) * (a == best) == 1
+            assert torch.equal(gx, torch.where(first, b, torch.zeros_like(a)))
