@@ -202,3 +202,63 @@ def test_executor_allocates_no_device_memory():
     loss, st = b.ex.step()
     assert torch.cuda.mem_get_info()[0] == before
     assert st.n_kernels == 2 and abs(loss - 4.28) < 1.0
+
+
+@pytest.mark.parametrize("kind", ["mse", "ce"])
+def test_mask_other_than_the_tensor_itself(kind):
+    import torch
+    n, c = 333, 24
+    b = Built()
+    A = b.A
+    y, mask = rnd(11, (n, c)), rnd(12, (n, c))
+    t = rnd(13, (n, c)) if kind == "mse" else torch.arange(n, dtype=torch.int32, device="cuda") % c
+    vy, vt, vm = b.var("y", y, A.VAR_PARAM), b.var("t", t, A.VAR_TARGET), b.var("m", mask, A.VAR_CONST)
+    b.op("loss", A.OP_MSE if kind == "mse" else A.OP_SOFTMAX_CE, [vy, vt], phase=A.FWD)
+    dy = torch.full_like(y, float("nan"))
+    b.op("dy", A.OP_MSE_GRAD if kind == "mse" else A.OP_SOFTMAX_CE_GRAD, [vy, vt, vm], out=dy, flags=A.F_MASK)
+    loss, st = b.step()
+    yd = y.double()
+    if kind == "mse":
+        ref, g = float(((yd - t.double()) ** 2).mean()), 2.0 / y.numel() * (yd - t.double())
+    else:
+        ref = float(torch.nn.functional.cross_entropy(yd, t.long()))
+        g = (torch.softmax(yd, -1) - torch.nn.functional.one_hot(t.long(), c)) / n
+    g = torch.where(mask > 0, g, torch.zeros_like(g))
+    assert st.n_kernels == 2 and abs(loss - ref) <= 1e-5 * abs(ref)
+    assert bool(((dy.double() - g).abs() <= 2.0 ** -8 * g.abs() + 1e-6 / n).all())
+
+
+@pytest.mark.parametrize("first", ["scale", "dot"])
+@pytest.mark.parametrize("why", ["second in the arena", "another raw gradient", "control edge"])
+def test_affine_gradients_that_run_apart(first, why):
+    """The second result in the arena (its block is not there when the first runs), two raw gradients, an operation in between that the
+    second waits for: two launches, the same values."""
+    import torch
+    rows, k, f32 = 80, 24, torch.float32
+    b = Built()
+    A = b.A
+    raw, w, scale = rnd(14, (1, 1, rows, k), f32), rnd(15, (1, 1, rows, k)), rnd(16, (k,), f32)
+    vraw, vw, vs = b.var("raw", raw, A.VAR_CONST), b.var("w", w, A.VAR_PARAM), b.var("s", scale, A.VAR_PARAM)
+    raw2 = rnd(17, tuple(raw.shape), f32) if why == "another raw gradient" else raw
+    vraw2 = b.var("raw2", raw2, A.VAR_CONST) if why == "another raw gradient" else vraw
+    outs = {"scale": torch.full_like(raw, float("nan")), "dot": torch.full_like(scale, float("nan"))}
+    order = ["scale", "dot"] if first == "scale" else ["dot", "scale"]
+    nodes = []
+    for i, q in enumerate(order):
+        src = vraw if i == 0 else vraw2
+        if i == 1 and why == "control edge":
+            other = b.op("between", A.OP_SCALE_COLS, [vraw, vs], out=torch.empty_like(raw))
+        nodes.append(b.op(q, A.OP_SCALE_COLS if q == "scale" else A.OP_DOT_COLS, [src, vs if q == "scale" else vw],
+                          out=None if i == 1 and why == "second in the arena" else outs[q]))
+    if why == "control edge":
+        b.g.add_control_edge(other, nodes[1])
+    _, st = b.step()
+    if why == "second in the arena":
+        off = b.ex.tensor_ptr(nodes[1]) - b.arena.data_ptr()
+        outs[order[1]] = b.arena[off:off + outs[order[1]].numel() * 4].view(f32).view(outs[order[1]].shape)
+    by = {order[0]: raw, order[1]: raw2}
+    assert torch.equal(outs["scale"], by["scale"] * scale)
+    terms = by["dot"].double() * w.double()
+    assert bool(((outs["dot"].double() - terms.sum((0, 1, 2))).abs() <= 1e-5 * terms.abs().sum((0, 1, 2))).all())
+    if why != "control edge":
+        assert st.n_kernels == 2
