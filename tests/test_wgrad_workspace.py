@@ -21,8 +21,41 @@ def host(name, ret, *args):
     return f(*args)
 
 
+class RunPlan(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int) for f in ("kt", "ctiles", "ktiles", "splits", "q_per_split")] + [("q", ctypes.c_longlong)]
+
+
+class StemGradPlan(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_void_p) for f in ("X", "DY", "part", "cs_part")] + [(f, ctypes.c_int) for f in (
+        "cx", "ky", "H", "W", "OH", "OW", "filt", "stride", "pad_h", "pad_w", "run", "lead", "span", "th", "tw", "gpr", "rows", "gw", "groups", "tiles_h",
+        "tiles_w", "tiles", "tiles_per_split", "splits")] + [(f, ctypes.c_uint) for f in ("gw_magic", "pix_magic", "span_magic")]
+
+
+def aligned_splits(n, sp, c, k, filt, stride, pad):
+    """Splits of the two kernels that only take tensors on 16-byte boundaries, before the others are asked; 0: neither takes it."""
+    if len(sp) == 3:
+        return 0
+    osp = [(e + 2 * pad - f) // stride + 1 for e, f in zip(sp, filt)]
+    a3, o3, f3, s3, p3 = ints((1,) + sp), ints([1] + osp), ints((1,) + tuple(filt)), ints((1, stride, stride)), ints((0, pad, pad))
+    i32, i64 = ctypes.c_int, ctypes.c_longlong
+    patch = host("_ZN3lms20wgrad_patch_eligibleEiiPKiS1_", ctypes.c_bool, i32(c), i32(k), f3, s3)
+    if host("_ZN3lms20wgrad_small_eligibleEiiPKiS1_S1_", ctypes.c_bool, i32(c), i32(k), a3, f3, s3) and (osp[1] >= 64 or not patch):
+        p = StemGradPlan()
+        took = host("_ZN3lms15wgrad_stem_planERNS_12StemGradPlanExiiPKiS3_S3_S3_S3_", ctypes.c_bool, ctypes.byref(p), i64(n * osp[0] * osp[1]), i32(c), i32(k), a3, o3, f3, s3, p3)
+        if took:
+            assert 1 <= p.splits <= 256 and p.tiles_per_split * p.splits >= p.tiles > p.tiles_per_split * (p.splits - 1)
+            assert p.groups <= 3 * 512 and p.rows * p.gw == p.groups and p.th * p.gpr * 16 <= 256 and p.tiles_w * p.tw >= p.OW and p.tiles_h * p.th >= p.OH
+        return p.splits if took else 0
+    if not patch or filt != (3, 3) or stride != 1:
+        return 0
+    r = host("_ZN3lms14wgrad_run_planExPKiS1_S1_S1_ii", RunPlan, i64(n), a3, o3, f3, p3, i32(c), i32(k))
+    if r.splits:
+        assert (r.splits - 1) * r.q_per_split < r.q <= r.splits * r.q_per_split and r.q_per_split % 32 == 0 and r.q == n * (sp[0] + 1) * (sp[1] + 1)
+    return r.splits
+
+
 def written(n, sp, c, k, filt, stride, pad):
-    """Splits of the kernel that the launch takes, in its order of choice (the general kernel: at least one)."""
+    """Splits of the kernel that the launch takes, in its order of choice (the general kernel: at least one), for tensors on any boundary."""
     ext = lambda v: (1,) * (3 - len(v)) + tuple(v)
     nd = len(sp)
     osp = ext([(e + 2 * pad - f) // stride + 1 for e, f in zip(sp, filt)])
@@ -43,7 +76,7 @@ def written(n, sp, c, k, filt, stride, pad):
 
 
 def test_partials_fit_the_workspace():
-    rng = random.Random(5)
+    rng, taken = random.Random(5), dict(stem=0, run=0, other=0)
     for _ in range(20000):
         nd = rng.choice((2, 2, 3))
         filt = (rng.choice((1, 3, 3, 7 if nd == 2 else 2)),) * nd
@@ -53,11 +86,14 @@ def test_partials_fit_the_workspace():
         k = rng.choice((1, 8, 32, 64, rng.randint(1, 80), 8 * rng.randint(1, 64)))
         n = rng.randint(1, 9)
         d = L.conv_desc(n, sp, c, k, filt, stride, pad, 0)
-        splits = written(n, sp, c, k, filt, stride, pad)
+        wide = aligned_splits(n, sp, c, k, filt, stride, pad)
+        taken["stem" if wide and c <= 4 else "run" if wide else "other"] += 1
+        splits = max(wide, written(n, sp, c, k, filt, stride, pad))
         per = c * k * filt[0] ** nd
         what = (n, sp, c, k, filt, stride, pad, splits)
         assert splits * per * 4 <= L.conv_workspace_bytes(d, A.CONV_WGRAD), what
         assert splits * (per + k) * 4 <= L.conv_workspace_bytes(d, A.CONV_WGRAD_BIAS) or (filt[0] == 1 and k <= 8), what
+    assert min(taken.values()) >= 50, taken
 
 
 @pytest.mark.parametrize("n,sp,c,k", [(64, (56, 56), 64, 64), (8, (14, 14), 256, 256), (50, (7, 7), 64, 128), (51, (8, 7), 64, 64), (300, (7, 7), 128, 128), (3, (20, 30), 136, 72)])
