@@ -1,4 +1,4 @@
-// Types shared by the convolution kernel files (internal).
+// Types and conversions shared by the kernel files (internal).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -48,7 +48,7 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-// Two floats -> two bf16 (round to nearest even) in one 32-bit word, low half first: v_cvt_pk_bf16_f32.
+// Two floats -> two bf16 (round to nearest even, NaN stays NaN) in one 32-bit word, low half first: v_cvt_pk_bf16_f32.
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   f32x2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));

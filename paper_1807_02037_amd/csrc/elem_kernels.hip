@@ -6,18 +6,11 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "conv_common.hpp"
 
 namespace lms {
 
 namespace {
-
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
 
 inline unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 constexpr int TB = 256;
@@ -33,13 +26,6 @@ __device__ __forceinline__ void unpack8(const uint4& q, float (&f)[8]) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
   for (int e = 0; e < 8; ++e) f[e] = __uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
-}
-
-// Two floats -> two bf16 (nearest even, NaN stays NaN) in one word, low half first: v_cvt_pk_bf16_f32.
-__device__ __forceinline__ uint32_t pack_bf2(float a, float b) {
-  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
 }
 
 // Sum of v over the block in a fixed tree order; result valid in thread 0.
@@ -502,7 +488,7 @@ __global__ __launch_bounds__(TB) void maxpool3s2_bwd_kernel(PoolP p, const uint4
       }
       if ((i & 1) && !col1) continue;
       if ((i >> 1) && !row1) continue;
-      out[at[i]] = make_uint4(pack_bf2(g[i][0], g[i][1]), pack_bf2(g[i][2], g[i][3]), pack_bf2(g[i][4], g[i][5]), pack_bf2(g[i][6], g[i][7]));
+      out[at[i]] = make_uint4(pack_bf16x2(g[i][0], g[i][1]), pack_bf16x2(g[i][2], g[i][3]), pack_bf16x2(g[i][4], g[i][5]), pack_bf16x2(g[i][6], g[i][7]));
     }
   }
 }
