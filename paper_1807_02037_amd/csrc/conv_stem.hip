@@ -14,8 +14,9 @@
 // infinity or a NaN reaches the outputs whose window contains it and no others (the look at the sums: 45.6 -> 46.6 us at 64 images of
 // 224 x 224; at the input rows on their way to LDS, before the next ones are asked for, 47.4).
 //
-// What bounds it is memory, 122 MB for 64 images of 224 x 224 (21 us at the rate of a large copy): 87 -> 43 us; 64 images of 48 x 48
-// 24 -> 9.
+// 64 images of 224 x 224: 87 -> 46 us against 21 for its 122 MB at the rate of a large copy; 64 images of 48 x 48 24 -> 10.  At 256 images of
+// 224 x 224 it moves 535 MB at 3.3 TB/s with the matrix pipes busy 18 % of the cycles and LDS active in 25 %: what bounds it is the chain of a
+// tile (rows to LDS, barrier, products, epilogue: 16 other vector instructions per product) on two work-groups a compute unit.
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>

@@ -18,11 +18,13 @@
 // ahead of their products, and the three taps of a filter row are cut out of the same three reads: nine products take eleven
 // reads of 8 bytes a lane.
 //
-// What bounds it is the matrix rate (without its LDS reads the kernel is 1 us faster, without the loads of x and dy 8 us, of 66
-// at 256 -> 256), on the layers with one tile the partial filters, written and added.  Both parameter gradients, us, patches of
-// 8 x 16 positions / this kernel: 256 -> 256 at 14 x 14, batch 256 93 -> 74 (804 TFLOP/s); 128 -> 128 at 28 x 28, batch 128 57 -> 46;
-// 512 -> 512 at 7 x 7, batch 256 92 -> 81; 64 -> 64 at 56 x 56, batch 64 36 -> 32; 384 -> 320 at 9 x 9, batch 210 218 -> 58; 88 -> 88 layers
-// of 4 Ki positions 13 -> 13.
+// What bounds it, on the layers with many positions, is no single pipe: at 14 x 14 and larger the matrix pipes are busy 37 % of the cycles
+// (936 TFLOP/s with the zero column and row, 0.59 of what a loop on registers reaches on random operands), LDS is active in 27 %, two
+// fifths of that bank conflicts of the transpose reads; without its LDS reads the kernel is 1 us faster, without the loads of x and dy 8 us, of 66
+// at 256 -> 256.  Two waves a SIMD meet at a barrier every 128 positions.  On the layers with one tile it is the partial filters, written
+// and added.  Both parameter gradients, us, patches of 8 x 16 positions / this kernel: 256 -> 256 at 14 x 14, batch 256 93 -> 74 (804
+// TFLOP/s); 128 -> 128 at 28 x 28, batch 128 57 -> 46; 512 -> 512 at 7 x 7, batch 256 92 -> 81; 64 -> 64 at 56 x 56, batch 64 36 -> 32;
+// 384 -> 320 at 9 x 9, batch 210 218 -> 58; 88 -> 88 layers of 4 Ki positions 13 -> 13.
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
