@@ -9,7 +9,8 @@
 // At a position that is none of dy's (zero column or row, behind the work-group's part) dy = 0 meets real pixels of x, which makes NaN of
 // infinite ones in taps that never read them.  Such a sum is not finite, and a sum that is finite met no such pixel: a work-group
 // that ends with one that is not goes over its part again with x masked at those positions, so that infinities and NaN
-// reach the entries that read them and no others (256 -> 256, 14 x 14, batch 256 81 -> 195 us with one infinity).  Finite tensors pay for the look at the sums alone, 0.3 us (16.3 -> 16.6 at 256 -> 256, 14 x 14, batch 8).
+// reach the entries that read them and no others (256 -> 256, 14 x 14, batch 256 81 -> 195 us with one infinity).  Finite tensors pay for
+// the look at the sums alone, 0.3 us (16.3 -> 16.6 at 256 -> 256, 14 x 14, batch 8).
 //
 // A work-group of eight waves, one per compute unit, owns 64 input channels x KT output channels of all nine taps and a part of
 // the run.  A wave has one 32 x 32 block of them (nine accumulators); the groups of waves that cover the tile take turns at
