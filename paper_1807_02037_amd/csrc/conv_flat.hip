@@ -4,8 +4,8 @@
 // tile is padded: patches of 8 x 16 positions are 77 % full on the 14 x 14, 28 x 28 and 7 x 7 maps of ResNet-50 and fill worse
 // still on odd extents.  The input pixels that the nine taps of a tile touch are one contiguous run of BM + 2 W + 2 rows;
 // for every block of 32 channels the run goes straight to LDS (buffer loads that write LDS) while the block before it is
-// multiplied, and a tap is a shift by kh * W + kw pixels.  Where a tap leaves the image, the lane reads a pixel of zeros
-// instead: its nine addresses are worked out once per tile.  The filter streams through a ring of LDS buffers one
+// multiplied, and a tap is a shift by kh * W + kw pixels.  Where a tap leaves the image, the lane reads zeros instead, from the
+// LDS banks its pixel would have come from: its nine addresses are worked out once per tile.  The filter streams through a ring of LDS buffers one
 // filter row (three taps x BN x 32 channels) a stage, one barrier each.  Products are taken transposed and leave through
 // wave_epilogue.  The forward pass reads the filter as it is stored, through the LDS transpose read: packing it first was a launch of
 // 3 to 5 us (us, packed / as stored: 72 -> 40 at 45 x 37, batch 3 12.5 / 8.8; 256 -> 256 at 14 x 14, batch 256 64.8 / 61.7, 16^3 30.6 /
@@ -54,7 +54,7 @@ struct FlatTile {
   static constexpr int LPR = WTN / 8, RPI = 64 / LPR, QV = 32 / RPI;
 };
 
-// Input pixels of a tile, the pixel of zeros behind them (64 bytes, any slot), rounded to the 16 pixels a wave loads at once.
+// Input pixels of a tile, rounded to the 16 pixels a wave loads at once, and 256 bytes of zeros (all banks) behind them.
 __host__ __device__ inline int flat_pixels(int bm, int w) { return (bm + 2 * w + 2 + 15) / 16 * 16; }
 __host__ __device__ inline int flat_abuf(int bm, int w) { return flat_pixels(bm, w) * 64 + 256; }
 
@@ -133,8 +133,11 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
     }
   };
   // ---- filter loads.  Data gradient: row (tap of the filter row, output channel), channel slot g at g ^ ((n >> 2) & 3).  Forward: the
-  // filter as stored, row (tap, input channel) of BN output channels for the transpose read; of 64, pairs of slots are permuted
-  // by the row so that the four rows of a read fall into different banks ----
+  // filter as stored, row (tap, input channel) of BN output channels for the transpose read.  LDS serves 32 lanes of that read at a
+  // time, four rows x 64 bytes; rows of 64 channels swap their halves every two rows, so that the four fall into different banks
+  // (a swap of neighbouring slots, made for four rows x 32 bytes, cost a conflict in every read, and with the zeros at one place 43 % of
+  // the LDS cycles were conflicts; us: 512 -> 512 at 7 x 7, batch 32 17.2 / 15.3, 256 -> 256 at 16^3 24.6 / 23.9, 96 -> 160 at 23 x 21,
+  // batch 16 8.2 / 7.6; nothing where a launch has two rounds of tiles) ----
   const v4u rs_b = buffer_rsrc(p.B, (long long)(9 * KD) * p.nout * p.red * 2);
   unsigned b_off[BV];
   int b_k[BV];
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       b_off[j] = tl < 3 && n0 + nr < p.nout ? (unsigned)(((tl * p.nout + n0 + nr) * p.red + b_k[j]) * 2) : DMA_OOB;
     } else {
       constexpr int SPR = T::BN / 8;
-      const int row = v / SPR, g = v % SPR, tl = row / BK, ch = (T::BN == 64 ? ((g >> 1) ^ ((row >> 1) & 3)) << 1 | (g & 1) : g) * 8;
+      const int row = v / SPR, g = v % SPR, tl = row / BK, ch = (T::BN == 64 ? g ^ ((row & 2) << 1) : g) * 8;
       b_k[j] = row % BK;
       b_off[j] = tl < 3 && n0 + ch < p.nout ? (unsigned)(((tl * p.red + b_k[j]) * p.nout + n0 + ch) * 2) : DMA_OOB;
     }
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
 
   // ---- LDS read addresses: per 32-position group and tap the pixel, or the zeros ----
   int a_rd[TM][9], a_d[TM];                                       // a_d: depth of the lane's position
-  const int a_zero = npix * 64 + (lane & 3) * 64;
+  const int a_zero = npix * 64;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int r = wm * T::WTM + i * 32 + (lane & 31);
@@ -177,7 +180,8 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       for (int kw = 0; kw < 3; ++kw) {
         const int pix = r + kh * W + kw;
         const bool in = (unsigned)(h + kh - 1) < (unsigned)H && (unsigned)(w + kw - 1) < (unsigned)W;
-        a_rd[i][kh * 3 + kw] = in ? pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4) : a_zero;
+        const int at = pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4);
+        a_rd[i][kh * 3 + kw] = in ? at : a_zero + (at & 255);
       }
   }
   // data gradient: per 16 channels of the reduction; forward: their first four rows of the lane's half, and the next four
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
         b_rd[j][i] = nr * 64 + (((i * 2 + half) ^ ((nr >> 2) & 3)) << 4);
       } else {
         const int li = lane & 15, lg = lane >> 4, row = (lg >> 1) * 8 + (li >> 2) + 4 * i, pair = wn * (T::WTN / 16) + j * 2 + (lg & 1);
-        b_rd[j][i] = row * T::BN * 2 + ((T::BN == 64 ? pair ^ ((row >> 1) & 3) : pair) << 5) + (li & 3) * 8;
+        b_rd[j][i] = row * T::BN * 2 + ((T::BN == 64 ? pair ^ (row & 2) : pair) << 5) + (li & 3) * 8;
       }
     }
   }
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       for (int i = 0; i < TM; ++i) {
         const bool in = (unsigned)(a_d[i] + kd - 1) < (unsigned)p.osp[0];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) a_cur[i][q] = in ? a_rd[i][q] : a_zero;
+        for (int q = 0; q < 9; ++q) a_cur[i][q] = in ? a_rd[i][q] : a_zero + (a_rd[i][q] & 255);
       }
     }
     const int (&ar)[TM][9] = P3D ? a_cur : a_rd;
