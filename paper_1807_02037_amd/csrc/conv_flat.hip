@@ -49,7 +49,7 @@ struct FlatTile {
   static_assert(WM * WN == 4, "four waves a group");
   static constexpr int BV = (3 * BN * 4 + NTHREADS - 1) / NTHREADS;       // filter loads per thread and stage
   static constexpr int B_STAGE = BV * NTHREADS * 16;
-  static constexpr int NB = NB_;                                  // filter ring, 2 or 3 stages
+  static constexpr int NB = NB_;                                  // filter ring, 2 to 4 stages
   static constexpr int MAXPIX = AV * NTHREADS / 4;                // input pixels at most
   static constexpr int LPR = WTN / 8, RPI = 64 / LPR, QV = 32 / RPI;
 };
@@ -120,17 +120,21 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
   const int wpix = __builtin_amdgcn_readfirstlane(wave * 16);
   // block vb of the layer: channel block vb / KD, input plane vb % KD; the group takes vb = grp, grp + G, ...
   const int nblocks = ((p.red + BK - 1) / BK) * KD, nlocal = (nblocks + G - 1) / G;
-  auto fetch_a = [&](int lb) {
+  struct Run { bool ok; unsigned in, so; };                       // what the loads of a block share: channels there, pixels there, offset
+  auto run_a = [&](int lb) {
     const int vb = lb * G + grp, chunk = vb / KD, kd = vb % KD;
-    const bool ok = vb < nblocks && chunk * BK + ag * 8 < p.red;
     unsigned in = a_in[0];
     if constexpr (P3D) in = kd == 0 ? a_in[0] : (kd == 1 ? a_in[1] : a_in[2]);
-    const unsigned so = (P3D ? kd * a_plane : 0) + chunk * (BK * 2);
+    return Run{vb < nblocks && chunk * BK + ag * 8 < p.red, in, (P3D ? kd * a_plane : 0) + chunk * (BK * 2)};
+  };
+  auto load_a = [&](const Run& r, int lb, int j) {
+    const unsigned dst = j * (NTHREADS / 4) + wpix < npix ? ldsA_w + (lb & 1) * abuf + j * NTHREADS * 16 : ldsX_u;   // uniform
+    load_lds16(rs_a, dst, r.ok && ((r.in >> j) & 1) ? a_off : DMA_OOB, (unsigned)(j * (NTHREADS / 4) * p.red * 2) + r.so);
+  };
+  auto fetch_a = [&](int lb) {
+    const Run r = run_a(lb);
 #pragma unroll
-    for (int j = 0; j < AV; ++j) {
-      const unsigned dst = j * (NTHREADS / 4) + wpix < npix ? ldsA_w + (lb & 1) * abuf + j * NTHREADS * 16 : ldsX_u;   // uniform
-      load_lds16(rs_a, dst, ok && ((in >> j) & 1) ? a_off : DMA_OOB, (unsigned)(j * (NTHREADS / 4) * p.red * 2) + so);
-    }
+    for (int j = 0; j < AV; ++j) load_a(r, lb, j);
   };
   // ---- filter loads.  Data gradient: row (tap of the filter row, output channel), channel slot g at g ^ ((n >> 2) & 3).  Forward: the
   // filter as stored, row (tap, input channel) of BN output channels for the transpose read.  LDS serves 32 lanes of that read at a
@@ -157,17 +161,23 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
   }
   const unsigned b_chunk = (unsigned)(FLIP ? BK * 2 : BK * 2 * p.nout);
   const unsigned ldsB_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
-  auto fetch_b = [&](int lb, int u, int buf) {
+  struct Row { bool ok; int c0; unsigned so; };                   // of a filter row
+  auto row_b = [&](int lb, int u) {
     const int vb = lb * G + grp, chunk = vb / KD, kd = FLIP ? KD - 1 - vb % KD : vb % KD;
-    const unsigned so = (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk;
+    return Row{vb < nblocks, chunk * BK, (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk};
+  };
+  auto load_b = [&](const Row& r, int buf, int j) {
+    load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, r.ok && r.c0 + b_k[j] < p.red ? b_off[j] : DMA_OOB, r.so);
+  };
+  auto fetch_b = [&](int lb, int u, int buf) {
+    const Row r = row_b(lb, u);
 #pragma unroll
-    for (int j = 0; j < BV; ++j)
-      load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, vb < nblocks && chunk * BK + b_k[j] < p.red ? b_off[j] : DMA_OOB, so);
+    for (int j = 0; j < BV; ++j) load_b(r, buf, j);
   };
 
   // ---- LDS read addresses: per 32-position group and tap the pixel, or the zeros ----
   int a_rd[TM][9], a_d[TM];                                       // a_d: depth of the lane's position
-  const int a_zero = npix * 64;
+  const int a_zero = npix * 64 + (lane & 3) * 64;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int r = wm * T::WTM + i * 32 + (lane & 31);
@@ -181,7 +191,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
         const int pix = r + kh * W + kw;
         const bool in = (unsigned)(h + kh - 1) < (unsigned)H && (unsigned)(w + kw - 1) < (unsigned)W;
         const int at = pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4);
-        a_rd[i][kh * 3 + kw] = in ? at : a_zero + (at & 255);
+        a_rd[i][kh * 3 + kw] = in ? at : npix * 64 + (at & 255);
       }
   }
   // data gradient: per 16 channels of the reduction; forward: their first four rows of the lane's half, and the next four
@@ -211,6 +221,9 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
   // Stage st = 3 lb + u multiplies filter row u of the group's block lb.  It asks for the input of block lb + 1 (at u = 0,
   // into the buffer of block lb - 1), then for the filter row NB - 1 stages on; so when stage st begins, what it needs is
   // older than the filter rows asked for in the NB - 2 stages before it, and than the next input among them.
+  // SPREAD: with three buffers or more the loads go out a few at a time between the products, since with all at the head of a stage every wave of the
+  // compute unit stands behind them before its first product; beyond the last block they write zeros, for a branch around them
+  // costs what they gain.  With two buffers a load has one stage to arrive in and goes first, and so it does where a step is one product.
   const int nstages = 3 * nlocal;
   fetch_a(0);
 #pragma unroll
@@ -222,11 +235,14 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
     const int left = nstages - 1 - (3 * lb + u);                  // stages after this one
     const bool more = lb + 1 < nlocal;
     constexpr bool a_newer = u > 0 && u <= NB - 2;                // the next input was asked for in the last NB - 2 stages
-    if (left == 0) wait_barrier<0>();
+    constexpr bool SPREAD = NB > 2 && TM * TN > 1;
+    constexpr int NEXT_A = u == 0 ? AV : 0, LOADS = NEXT_A + BV, PER = (LOADS + 5) / 6;
+    if constexpr (SPREAD) wait_barrier<(NB - 2) * BV + (a_newer ? AV : 0)>();
+    else if (left == 0) wait_barrier<0>();
     else if (a_newer && more) wait_barrier<(NB - 2) * BV + AV>();
     else wait_barrier<(NB - 2) * BV>();
-    if (u == 0 && more) fetch_a(lb + 1);
-    if (left >= NB - 1) {
+    if (!SPREAD && u == 0 && more) fetch_a(lb + 1);
+    if (!SPREAD && left >= NB - 1) {
       constexpr int fu = (u + NB - 1) % 3;
       fetch_b(lb + (u + NB - 1) / 3, fu, (bbuf + NB - 1) % NB);
     }
@@ -236,10 +252,12 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       for (int i = 0; i < TM; ++i) {
         const bool in = (unsigned)(a_d[i] + kd - 1) < (unsigned)p.osp[0];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) a_cur[i][q] = in ? a_rd[i][q] : a_zero + (a_rd[i][q] & 255);
+        for (int q = 0; q < 9; ++q) a_cur[i][q] = in ? a_rd[i][q] : a_zero;      // a whole plane: most lanes of a read
       }
     }
     const int (&ar)[TM][9] = P3D ? a_cur : a_rd;
+    const Run ra = run_a(lb + 1);
+    const Row rb = row_b(lb + (u + NB - 1) / 3, (u + NB - 1) % 3);
     const unsigned char* b = sB + bbuf * T::B_STAGE;
     const unsigned char* a = sA + (lb & 1) * abuf;
     // operands are read this many steps ahead of their products: with one product a step the LDS latency shows
@@ -266,7 +284,16 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[st % (DEPTH + 1)][j], af[st % (DEPTH + 1)][i], acc[i][j], 0, 0, 0);
+      if constexpr (SPREAD) {
+#pragma unroll
+        for (int q = st * PER; q < (st + 1) * PER && q < LOADS; ++q) {
+          if (q < NEXT_A) load_a(ra, lb + 1, q);
+          else load_b(rb, (bbuf + NB - 1) % NB, q - NEXT_A);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    if constexpr (SPREAD) return;
     constexpr int READS = TM + (FLIP ? TN : 2 * TN);
     __builtin_amdgcn_sched_group_barrier(0x100, READS * DEPTH, 0);
 #pragma unroll
@@ -282,7 +309,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       constexpr int bi = decltype(b_c)::value;
       if (lb0 + bi < nlocal) unrolled<3>([&](auto u) { stage(lb0 + bi, u, std::integral_constant<int, (3 * bi + decltype(u)::value) % NB>{}); });
     });
-  __syncthreads();                                                // LDS is free
+  wait_barrier<0>();                                              // LDS is free
   if constexpr (G > 1) {
     float4* sums = reinterpret_cast<float4*>(flat_smem);
     auto slot = [&](int g, int i, int j, int q) -> float4& { return sums[((((g - 1) * 4 + wave) * TM + i) * TN + j) * 256 + q * 64 + lane]; };
@@ -333,7 +360,10 @@ hipError_t launch_flat_t(IgemmP& p, hipStream_t s) {
 }
 
 typedef FlatTile<256, 64, 4, 1, 8, 2> Flat256x64;
+typedef FlatTile<256, 64, 4, 1, 6, 3> Flat256x64n3;
 typedef FlatTile<128, 64, 2, 2, 6, 2> Flat128x64;
+typedef FlatTile<128, 64, 2, 2, 6, 3> Flat128x64n3;
+typedef FlatTile<128, 64, 2, 2, 4, 4> Flat128x64n4;
 typedef FlatTile<64, 64, 2, 2, 6, 3> Flat64;
 typedef FlatTile<64, 64, 2, 2, 5, 3, 2> Flat64g2;
 typedef FlatTile<256, 32, 4, 1, 8, 2> Flat256x32;
@@ -376,9 +406,28 @@ bool patches_win(const IgemmP& p) {
   return flat_tiles(p, 256, 32) > 512 && full >= 0.95;
 }
 
+// The longest ring that leaves room for a second work-group on a compute unit (us, forward / data gradient, ring of two, loads at the
+// head of a stage / three, loads spread / four: 256 x 64: 256 -> 256, 14 x 14, batch 256 62.1 / 65.6, 58.8 / 63.9; 512 -> 512, 14 x 14, batch 96 87 / 96,
+// 80 / 89; 128 -> 128, 28 x 28, batch 128 33.9 / 39.3, 31.7 / 37.9; 128 -> 128, 32^3 30.9 / 29.8, 28.1 / 28.7; 64 -> 64, 56 x 56, where
+// three leave no room, 24 / 30 for one work-group.  128 x 64: 256 -> 256, 14 x 14, batch 32 15.6 / 19.1, 13.3 / 17.0, 12.5 / 16.2; 512 -> 512, 7 x 7, batch
+// 64 27.3 / 32.4, 20.1 / 26.1, 18.3 / 24.2; 128 -> 128, 24^3 21.5 / 21.8, 20.0 / 19.0, 19.8 / 19.1).
+template <typename T>
+bool pair_fits(int w) { return flat_group_lds<T>(w) <= 81920 && flat_pixels(T::BM, w) <= T::MAXPIX; }
+template <bool P3D, bool FLIP>
+hipError_t launch_256x64(IgemmP& p, hipStream_t s) {
+  if (pair_fits<Flat256x64n3>(p.osp[2])) return launch_flat_t<Flat256x64n3, P3D, FLIP>(p, s);
+  return launch_flat_t<Flat256x64, P3D, FLIP>(p, s);
+}
+template <bool P3D, bool FLIP>
+hipError_t launch_128x64(IgemmP& p, hipStream_t s) {
+  if (pair_fits<Flat128x64n4>(p.osp[2])) return launch_flat_t<Flat128x64n4, P3D, FLIP>(p, s);
+  if (pair_fits<Flat128x64n3>(p.osp[2])) return launch_flat_t<Flat128x64n3, P3D, FLIP>(p, s);
+  return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
+}
+
 template <bool P3D, bool FLIP>
 hipError_t launch_flat_f(IgemmP& p, hipStream_t s) {
-  // us, forward / data gradient; before: patches of 8 x 16 or 4 x 4 x 8 positions, or the general kernel where they fill badly.
+  // us, forward / data gradient, rings of two and of three for 64 x 64 and the filter packed first; before: patches of 8 x 16 or 4 x 4 x 8 positions, or the general kernel where they fill badly.
   //                                                     before         256 x 64     128 x 64    64 x 64     64 x 64, two groups
   //   2-D 256 -> 256, 14 x 14, batch 256                81 / 85        65 / 68      69 / 73     89 / 93     107 / 118
   //   2-D 512 -> 512, 7 x 7, batch 256                  81 / 88        62 / 67      77 / 84     98 / 105    108 / 116
@@ -397,12 +446,12 @@ hipError_t launch_flat_f(IgemmP& p, hipStream_t s) {
   const bool wide = wide_fits(p.osp[2]);
   if (p.nout <= 32) return narrow_256(p) ? launch_flat_t<Flat256x32, P3D, FLIP>(p, s) : launch_flat_t<Flat128x32, P3D, FLIP>(p, s);
   if (!wide && long_fits(p.osp[2]) && flat_tiles(p, 256, 32) >= 512) return launch_flat_t<Flat256x32, P3D, FLIP>(p, s);
-  if (wide && flat_tiles(p, 256, 64) >= 256) return launch_flat_t<Flat256x64, P3D, FLIP>(p, s);
-  if (flat_tiles(p, 128, 64) >= 256) return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
+  if (wide && flat_tiles(p, 256, 64) >= 256) return launch_256x64<P3D, FLIP>(p, s);
+  if (flat_tiles(p, 128, 64) >= 256) return launch_128x64<P3D, FLIP>(p, s);
   const int blocks = (p.red + BK - 1) / BK * (P3D ? 3 : 1);
   if (blocks >= 8) {
     if (flat_tiles(p, 64, 64) <= 256) return launch_flat_t<Flat64g2, P3D, FLIP>(p, s);
-    if (flat_tiles(p, 64, 64) <= 512) return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
+    if (flat_tiles(p, 64, 64) <= 512) return launch_128x64<P3D, FLIP>(p, s);
   }
   return launch_flat_t<Flat64, P3D, FLIP>(p, s);
 }
