@@ -16,12 +16,14 @@
 // the run.  A wave has one 32 x 32 block of them (nine accumulators); the groups of waves that cover the tile take turns at
 // 16 positions each, and their sums meet in LDS.  x goes from memory straight into a ring of pixels in LDS, each pixel once, dy
 // into three buffers, both two steps of 128 positions ahead; the operands are read with the LDS transpose read, one round
-// ahead of their products, and the three taps of a filter row are cut out of the same three reads: nine products take eleven
-// reads of 8 bytes a lane.
+// ahead of their products.  Of a filter row the first and the last tap are read, from 16-byte aligned registers each, and the middle one is
+// cut out of the two: nine products take fourteen reads of 8 bytes a lane and twelve shifts (cutting the last tap out as well took
+// three reads less and twelve register moves more; with the bank conflicts below, 256 -> 256 at 14 x 14, batch 256 81.0 / 79.8, 128 -> 128 at 28 x 28,
+// batch 64 30.6 / 29.8, 512 -> 512 at 7 x 7, batch 256 81.3 / 79.6).
 //
 // What bounds it, on the layers with many positions, is no single pipe: at 14 x 14 and larger the matrix pipes are busy 37 % of the cycles
-// (936 TFLOP/s with the zero column and row, 0.59 of what a loop on registers reaches on random operands), LDS is active in 27 %, two
-// fifths of that bank conflicts of the transpose reads; without its LDS reads the kernel is 1 us faster, without the loads of x and dy 8 us, of 66
+// (936 TFLOP/s with the zero column and row, 0.59 of what a loop on registers reaches on random operands), LDS is active in 20 %, without
+// bank conflicts in the reads (with pairs of 16-byte slots permuted, which fits reads of 16 lanes at a time and not of 32, two fifths of 27 %); without its LDS reads the kernel is 1 us faster, without the loads of x and dy 8 us, of 66
 // at 256 -> 256.  Two waves a SIMD meet at a barrier every 128 positions.  On the layers with one tile it is the partial filters, written
 // and added.  Both parameter gradients, us, patches of 8 x 16 positions / this kernel: 256 -> 256 at 14 x 14, batch 256 93 -> 74 (804
 // TFLOP/s); 128 -> 128 at 28 x 28, batch 128 57 -> 46; 512 -> 512 at 7 x 7, batch 256 92 -> 81; 64 -> 64 at 56 x 56, batch 64 36 -> 32;
@@ -90,9 +92,9 @@ __global__ __launch_bounds__(RUN_NT, 2) void wgrad_run_kernel(WRunP p) {
   const int qlen = p.q_total - q0 < p.q_per_split ? p.q_total - q0 : p.q_per_split;
   const int steps = (qlen + STEP - 1) / STEP;
 
-  // ---- this thread's vectors of a step: pixel tid / 8 (and 64 on), 16-byte slot tid % 8; pairs of slots are permuted by
-  // the pixel so that the four rows of a transpose read fall into different banks (32 channels of dy: they do anyway) ----
-  const int px = tid >> 3, ch = ((((tid & 7) >> 1) ^ ((px >> 1) & 3)) << 1 | (tid & 1)) * 8;
+  // ---- this thread's vectors of a step: pixel tid / 8 (and 64 on), 16-byte slot tid % 8; every two pixels the halves of one are
+  // swapped, so that the four pixels x 64 bytes that LDS serves at a time fall into different banks (32 channels of dy: they do anyway) ----
+  const int px = tid >> 3, ch = ((tid & 7) ^ ((px & 2) << 1)) * 8;
   const int y_px = KT == 64 ? px : tid >> 2, y_c = KT == 64 ? ch : (tid & 3) * 8;
   const bool xc_ok = c0 + ch < p.cx, yc_ok = k0 + y_c < p.ky;
   const int xs = q0 - STEP;                                       // x is there from the step before the first on
@@ -156,18 +158,17 @@ __global__ __launch_bounds__(RUN_NT, 2) void wgrad_run_kernel(WRunP p) {
   // ---- LDS read addresses: a 16-lane group reads four pixels (lane / 4) x 16 channels; tap (kh, 0) of a position is
   // 8 a + b pixels into the step before its own: b here, 8 a with the step and the 16 positions in a scalar ----
   const int li = lane & 15, lg = lane >> 4, row = (lg >> 1) * 8 + (li >> 2);
-  auto at = [&](int r, int pair) { return r * PIX_B + ((pair ^ ((r >> 1) & 3)) << 5) + (li & 3) * 8; };
+  auto at = [&](int r, int pair) { return r * PIX_B + ((pair ^ (r & 2)) << 5) + (li & 3) * 8; };
   const int xpair = cq * 2 + (lg & 1), ypair = kq * 2 + (lg & 1);
-  int xa[3][2], ya[2], xb[3];
+  int xa[3][2], ya, xb[3];
 #pragma unroll
   for (int kh = 0; kh < 3; ++kh) {
     const int s = STEP - 1 + (kh - 1) * Wp;
     xb[kh] = s & ~7;
     xa[kh][0] = at((s & 7) + row, xpair);
-    xa[kh][1] = at((s & 7) + row + 4, xpair);
+    xa[kh][1] = at((s & 7) + row + 2, xpair);
   }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) ya[i] = KT == 64 ? at(row + 4 * i, ypair) : (row + 4 * i) * T::Y_PIX + (lg & 1) * 32 + (li & 3) * 8;
+  ya = KT == 64 ? at(row, ypair) : row * T::Y_PIX + (lg & 1) * 32 + (li & 3) * 8;
 
   f32x16 acc[9], cs;
 #pragma unroll
@@ -177,20 +178,22 @@ __global__ __launch_bounds__(RUN_NT, 2) void wgrad_run_kernel(WRunP p) {
   int base, ybuf;                                                 // ring pixel of the step, buffer of its dy
   // 16 positions: operands as they come from LDS, and their products.  They are read one round ahead: with reads and products
   // in turn each of the four waits of a round cost an LDS round trip.
-  struct Frag { v2u y[2], x[3][3]; };
+  struct Frag { v2u y[2], x[3][2][2]; };
   auto load = [&](Frag& f, int j) {
     const int ks = G * j + g;
     const unsigned char* sy = lds_run + T::LDS_X + ybuf * T::Y_BUF + ks * 16 * T::Y_PIX;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) f.y[i] = tr_read(sy + ya[i]);
+    for (int i = 0; i < 2; ++i) f.y[i] = tr_read(sy + ya + 4 * i * T::Y_PIX);
 #pragma unroll
     for (int kh = 0; kh < 3; ++kh) {
       int s = base + ks * 16 + xb[kh];
       if (s >= RING) s -= RING;
       const unsigned char* sx = lds_run + s * PIX_B;
-      f.x[kh][0] = tr_read(sx + xa[kh][0]);
-      f.x[kh][1] = tr_read(sx + xa[kh][1]);
-      f.x[kh][2] = tr_read(sx + xa[kh][0] + 8 * PIX_B);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        f.x[kh][0][i] = tr_read(sx + xa[kh][0] + 4 * i * PIX_B);
+        f.x[kh][1][i] = tr_read(sx + xa[kh][1] + 4 * i * PIX_B);
+      }
     }
   };
   // masked: the positions of step st, round j that are dy's keep their x
@@ -209,10 +212,10 @@ __global__ __launch_bounds__(RUN_NT, 2) void wgrad_run_kernel(WRunP p) {
     const bf16x8 yf = __builtin_bit_cast(bf16x8, v4u{f.y[0][0], f.y[0][1], f.y[1][0], f.y[1][1]});
 #pragma unroll
     for (int kh = 0; kh < 3; ++kh) {
-      const unsigned u[5] = {f.x[kh][0][0], f.x[kh][0][1], f.x[kh][1][0], f.x[kh][1][1], f.x[kh][2][0]};      // two positions a word
-      const v4u f0 = {u[0], u[1], u[2], u[3]}, f2 = {u[1], u[2], u[3], u[4]};
-      const v4u f1 = {__builtin_amdgcn_alignbit(u[1], u[0], 16), __builtin_amdgcn_alignbit(u[2], u[1], 16),
-                      __builtin_amdgcn_alignbit(u[3], u[2], 16), __builtin_amdgcn_alignbit(u[4], u[3], 16)};
+      const v4u f0 = {f.x[kh][0][0][0], f.x[kh][0][0][1], f.x[kh][0][1][0], f.x[kh][0][1][1]};      // two positions a word
+      const v4u f2 = {f.x[kh][1][0][0], f.x[kh][1][0][1], f.x[kh][1][1][0], f.x[kh][1][1][1]};
+      const v4u f1 = {__builtin_amdgcn_alignbit(f2[0], f0[0], 16), __builtin_amdgcn_alignbit(f2[1], f0[1], 16),
+                      __builtin_amdgcn_alignbit(f2[2], f0[2], 16), __builtin_amdgcn_alignbit(f2[3], f0[3], 16)};
       acc[kh * 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f0 & m), yf, acc[kh * 3], 0, 0, 0);
       acc[kh * 3 + 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f2 & m), yf, acc[kh * 3 + 2], 0, 0, 0);
       acc[kh * 3 + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f1 & m), yf, acc[kh * 3 + 1], 0, 0, 0);
