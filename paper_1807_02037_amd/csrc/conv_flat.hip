@@ -309,7 +309,8 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       constexpr int bi = decltype(b_c)::value;
       if (lb0 + bi < nlocal) unrolled<3>([&](auto u) { stage(lb0 + bi, u, std::integral_constant<int, (3 * bi + decltype(u)::value) % NB>{}); });
     });
-  wait_barrier<0>();                                              // LDS is free
+  if constexpr (NB > 2 && TM * TN > 1) wait_loads();              // the zeros beyond the last block
+  __syncthreads();                                                // LDS is free
   if constexpr (G > 1) {
     float4* sums = reinterpret_cast<float4*>(flat_smem);
     auto slot = [&](int g, int i, int j, int q) -> float4& { return sums[((((g - 1) * 4 + wave) * TM + i) * TN + j) * 256 + q * 64 + lane]; };
@@ -407,9 +408,9 @@ bool patches_win(const IgemmP& p) {
 }
 
 // The longest ring that leaves room for a second work-group on a compute unit (us, forward / data gradient, ring of two, loads at the
-// head of a stage / three, loads spread / four: 256 x 64: 256 -> 256, 14 x 14, batch 256 62.1 / 65.6, 58.8 / 63.9; 512 -> 512, 14 x 14, batch 96 87 / 96,
+// head of a stage / three, loads spread / four: 256 x 64: 256 -> 256, 14 x 14, batch 256 59.8 / 65.8, 56.6 / 63.6; 512 -> 512, 14 x 14, batch 96 87 / 96,
 // 80 / 89; 128 -> 128, 28 x 28, batch 128 33.9 / 39.3, 31.7 / 37.9; 128 -> 128, 32^3 30.9 / 29.8, 28.1 / 28.7; 64 -> 64, 56 x 56, where
-// three leave no room, 24 / 30 for one work-group.  128 x 64: 256 -> 256, 14 x 14, batch 32 15.6 / 19.1, 13.3 / 17.0, 12.5 / 16.2; 512 -> 512, 7 x 7, batch
+// three leave no room, 24 / 30 for one work-group.  128 x 64: 256 -> 256, 14 x 14, batch 32 15.6 / 19.1, 13.0 / 16.7, 11.4 / 15.5; 512 -> 512, 7 x 7, batch
 // 64 27.3 / 32.4, 20.1 / 26.1, 18.3 / 24.2; 128 -> 128, 24^3 21.5 / 21.8, 20.0 / 19.0, 19.8 / 19.1).
 template <typename T>
 bool pair_fits(int w) { return flat_group_lds<T>(w) <= 81920 && flat_pixels(T::BM, w) <= T::MAXPIX; }

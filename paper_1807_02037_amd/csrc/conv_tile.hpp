@@ -16,6 +16,10 @@ __device__ __forceinline__ void wait_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// Nothing of this wave's loads to LDS is in flight.  A __syncthreads() behind it, and not a wait_barrier, tells the compiler that the loads it
+// knows have come back: without that it waits for each where it is used, and with it for the stores before it.
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // LDS bytes that wave_epilogue needs per wave: 32 positions x WTN channels of fp32, rows 16 bytes apart modulo 256.
 constexpr int epi_wave_bytes(int wtn) { return 32 * (wtn + 4) * 4; }
 

@@ -18,6 +18,10 @@ CASES = [
     (9, (75, 120), 200, 72), (8, (76, 121), 40, 64), (1, (40, 43, 41), 40, 32), (1, (42, 40, 41), 40, 72), (2, (20, 41, 87), 24, 72),
     # between one and two of the 64 x 64 tiles for a compute unit, long reduction: 128 x 64; one at most: two groups
     (3, (45, 37), 256, 256), (2, (23, 21), 264, 136),
+    # rings of filter rows: 256 x 64 with three up to rows of 39 and two beyond, 128 x 64 with four up to 55, three up to 103, two beyond;
+    # one block of the reduction, fewer stages than a ring holds, and several
+    (22, (40, 39), 24, 72), (22, (39, 40), 72, 72), (9, (43, 55), 24, 72), (9, (43, 56), 72, 72), (4, (53, 103), 24, 72), (4, (53, 104), 72, 72),
+    (1, (27, 28, 29), 24, 72), (1, (33, 32, 33), 40, 72),
 ]
 
 
