@@ -40,8 +40,9 @@ __device__ __forceinline__ int pw_swz(int row) { return (row >> 1) & 7; }
 
 enum { PW_FWD = 0, PW_DGRAD = 1, PW_UP = 2 };
 
-template <int BM_, int BN_, int WM_, int WN_>
+template <int BM_, int BN_, int WM_, int WN_, int BUFS_ = 2>
 struct PwTile {
+  static constexpr int BUFS = BUFS_;                              // stages in LDS
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int NT = 64 * WM * WN;                         // threads
   static constexpr int WTM = BM / WM, WTN = BN / WN;              // outputs of a wave
@@ -50,7 +51,7 @@ struct PwTile {
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int AV = A_BYTES / (16 * NT), BV = B_BYTES / (16 * NT);   // loads per thread and stage
   static constexpr int EPI_WAVE = epi_wave_bytes(WTN);
-  static constexpr int LDS_BYTES = 2 * STAGE > WM * WN * EPI_WAVE ? 2 * STAGE : WM * WN * EPI_WAVE;
+  static constexpr int LDS_BYTES = BUFS * STAGE > WM * WN * EPI_WAVE ? BUFS * STAGE : WM * WN * EPI_WAVE;
   static constexpr int LPR = WTN / 8;                             // lanes per output row in the epilogue
   static constexpr int RPI = 64 / LPR;                            // rows per instruction
   static constexpr int QV = 32 / RPI;                             // vectors per lane and 32 positions
@@ -62,6 +63,15 @@ __device__ __forceinline__ bf16x8 pw_tr_frag(const unsigned char* p0, const unsi
   const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p1);
   const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   return __builtin_bit_cast(bf16x8, r);
+}
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<N, I + 1>(f);
+  }
 }
 
 // Row of the strided grid (extents big) under row m of the small one (extents small).
@@ -187,15 +197,21 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   }
   const unsigned a_step = PK * 2, b_step = MODE == PW_DGRAD ? PK * 2 : (unsigned)(PK * p.nout * 2);
   const int niter = (p.red + PK - 1) / PK;
+  const unsigned lds_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
+  // the last stage may be partial: zeros, whatever lies behind, and nothing but zeros in the stages after it
+  auto load_a = [&](int it, int buf, int j) {
+    const bool whole = (it + 1) * PK <= p.red;
+    load_lds16(rs_a, lds_w + buf * T::STAGE + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : DMA_OOB, it * a_step);
+  };
+  auto load_b = [&](int it, int buf, int j) {
+    const bool whole = (it + 1) * PK <= p.red;
+    load_lds16(rs_b, lds_w + buf * T::STAGE + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : DMA_OOB, it * b_step);
+  };
   auto fetch = [&](int it, int buf) {
-    const unsigned a = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024) + buf * T::STAGE;
-    const bool whole = (it + 1) * PK <= p.red;                    // the last stage may be partial: zeros, whatever lies behind
 #pragma unroll
-    for (int j = 0; j < AV; ++j)
-      load_lds16(rs_a, a + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : DMA_OOB, it * a_step);
+    for (int j = 0; j < AV; ++j) load_a(it, buf, j);
 #pragma unroll
-    for (int j = 0; j < BV; ++j)
-      load_lds16(rs_b, a + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : DMA_OOB, it * b_step);
+    for (int j = 0; j < BV; ++j) load_b(it, buf, j);
   };
 
   // ---- LDS read addresses ----
@@ -227,13 +243,16 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  fetch(0, 0);                                                    // red >= 32: pw_channels
+  constexpr int AHEAD = T::BUFS - 1;                              // stages asked for ahead
+#pragma unroll
+  for (int it = 0; it < AHEAD; ++it) fetch(it, it);               // red >= 32: pw_channels
   auto stage = [&](int it, auto buf_c) {
-    constexpr int buf = decltype(buf_c)::value;
+    constexpr int buf = decltype(buf_c)::value, next = (buf + AHEAD) % T::BUFS;
     // stage `it` has landed; the barrier says so for every wave, and that every wave is done with the buffer that the
-    // next request writes
-    wait_barrier<0>();
-    if (it + 1 < niter) fetch(it + 1, buf ^ 1);
+    // next request writes.  With three buffers the loads go out between the products, beyond the last stage too (no branch).
+    constexpr bool SPREAD = T::BUFS > 2;
+    wait_barrier<(AHEAD - 1) * (AV + BV)>();
+    if (!SPREAD && it + 1 < niter) fetch(it + 1, next);
     const unsigned char* a = pw_smem + buf * T::STAGE;
     const unsigned char* b = a + T::A_BYTES;
     constexpr int NKS = PK / 16;
@@ -255,7 +274,17 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
+      if constexpr (SPREAD) {
+        constexpr int PER = (AV + BV + NKS - 1) / NKS;
+#pragma unroll
+        for (int q = ks * PER; q < (ks + 1) * PER && q < AV + BV; ++q) {
+          if (q < BV) load_b(it + AHEAD, next, q);
+          else load_a(it + AHEAD, next, q - BV);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    if constexpr (SPREAD) return;
     constexpr int NRD = TM + (MODE == PW_DGRAD ? 1 : 2) * TN;     // LDS reads of a step
     __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);
 #pragma unroll
@@ -264,10 +293,11 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
       __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
     }
   };
-  for (int it = 0; it < niter; it += 2) {
-    stage(it, std::integral_constant<int, 0>{});
-    if (it + 1 < niter) stage(it + 1, std::integral_constant<int, 1>{});
-  }
+  for (int it = 0; it < niter; it += T::BUFS)
+    unrolled<T::BUFS>([&](auto k) {
+      if (it + decltype(k)::value < niter) stage(it + decltype(k)::value, k);
+    });
+  if constexpr (T::BUFS > 2) wait_loads();
   __syncthreads();                                                // the ring is free for the epilogue
 
   wave_epilogue<T::WTN, TM, TN>(p, eb, acc, pw_smem + wave * T::EPI_WAVE, pre_add, pre_mask, UP ? up_n : n, n < nv, er, out_off);
@@ -332,7 +362,7 @@ hipError_t launch_pw_t(IgemmP& p, hipStream_t s) {
   if (mt * p.ntiles_n > 0x7fffff00LL || p.M >= 0x7fffffffLL) return hipErrorInvalidValue;
   p.ntiles = (int)(mt * p.ntiles_n);
   const int grid = 8 * ((p.ntiles + 7) / 8);
-  const int ring = p.red > PK ? 2 * T::STAGE : T::STAGE, epi = T::WM * T::WN * T::EPI_WAVE;
+  const int ring = p.red > PK || T::BUFS > 2 ? T::BUFS * T::STAGE : T::STAGE, epi = T::WM * T::WN * T::EPI_WAVE;
   hipLaunchKernelGGL((pw_kernel<T, MODE, STRIDED>), dim3(grid), dim3(T::NT), ring > epi ? ring : epi, s, p);
   return hipGetLastError();
 }
@@ -341,6 +371,7 @@ typedef PwTile<128, 128, 2, 2> Tile0;
 typedef PwTile<64, 128, 2, 2> Tile1;
 typedef PwTile<128, 64, 2, 2> Tile2;
 typedef PwTile<64, 64, 2, 2> Tile3;
+typedef PwTile<256, 128, 4, 2, 3> Tile4;
 
 // Tile by shape (us on ResNet-50 layers, three sets of tensors in turn so that nothing stays cached; batch 128 at 56 x 56 and
 // 28 x 28, 256 below; before: 128-position tiles staged through registers, data gradients of narrowing layers on the general
@@ -353,14 +384,28 @@ typedef PwTile<64, 64, 2, 2> Tile3;
 //   data gradient 256 <- 64, 56 x 56         134      147      130     135     138     mask and addend in, short reduction:
 //   data gradient 1024 <- 256, 14 x 14       105       96       89      91      93     more work-groups in flight
 //   forward 400 -> 176, 16 x 21 x 24          14.4     12.4     11.0    11.8     9.8   few tiles: smaller ones fill the chip
-// Products with a ReLU mask and at most 512 reduction channels take 64 x 128, others 128 x 128, and both step down
+// Products with a ReLU mask and less than 384 reduction channels take 64 x 128 (with 384 and 512: data gradient 640 <- 384, 28 x 28, batch 128
+// 64 x 128 107.8, 128 x 128 99.1; 256 <- 512, batch 100 51.5 / 48.2, with addend 57.1 / 52.6; but under a stride 256 <- 512, 56 x 56, batch 128 147.8 / 159.8, so there up to 512), others 128 x 128, and both step down
 // to tiles of which there are at least 256, one per compute unit.
+//   Long reductions: what arrives in LDS is the bound, the rows of x that two work-groups share and the filter, which the L2s deliver
+// behind the misses of the activations (a loop of nothing but these loads: 512 tiles of 128 rows x 2 KB once 27 us, twice with the filter
+// 42, whatever number of stages ahead).  256 x 128 takes the filter half as often; one work-group of eight waves, three stages in LDS, loads between
+// the products.  us, 128 x 128 / 256 x 128: forward 1024 -> 256, 14 x 14, batch 256, residual 49.9 / 42.8, 512 without 85 / 80; 640 -> 640, 28 x 28, batch
+// 128 120 / 113; 768 -> 256, 14 x 14, batch 300 38.5 / 34.9; 576 -> 256, 28 x 28, batch 128 55.6 / 53.8; 2048 -> 512, 7 x 7, batch 256 (196 tiles) 28.5 /
+// 28.6; data gradient 256 <- 1024, 14 x 14, batch 256 56.1 / 49.1, 128 <- 768, batch 300 34.5 / 32.5; but 640 <- 640, 28 x 28, batch 128
+// 131.6 / 134, 512 -> 512, 14 x 14, batch 200 28.7 / 30.9.
+//   153 to 192 columns waste a quarter or more of two 128-wide tiles (us, 128 x 128 or 64 x 128 / 128 x 64: forward 320 -> 160, 28 x 28, batch 64 17.4 / 14.2;
+// 96 -> 192, 40^3 12.5 / 10.8; data gradient 192 <- 512, 14 x 14, batch 200 22.4 / 21.5; but 64 -> 144, 56 x 56, batch 128 52.4 / 58.2, and 800 -> 168, 14 x 14,
+// batch 60, 276 tiles, 11.2 / 12.6).
 template <int MODE, bool STRIDED>
 hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   const long long cols = (MODE == PW_UP ? (long long)p.up[0] * p.up[1] * p.up[2] : 1) * p.nout;
   auto tiles = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * ((cols + bn - 1) / bn); };
   if (cols <= 64) return tiles(128, 64) >= 256 ? launch_pw_t<Tile2, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
-  if (!(p.mask && p.red <= 512) && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);
+  if (cols > 152 && cols <= 192 && tiles(128, 64) >= 768) return launch_pw_t<Tile2, MODE, STRIDED>(p, s);
+  if constexpr (!STRIDED && MODE != PW_UP)
+    if (p.red >= (MODE == PW_DGRAD ? 768 : 576) && tiles(256, 128) >= 256) return launch_pw_t<Tile4, MODE, STRIDED>(p, s);
+  if (!(p.mask && p.red < (STRIDED ? 513 : 384)) && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);
   return tiles(64, 128) >= 256 ? launch_pw_t<Tile1, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
 }
 

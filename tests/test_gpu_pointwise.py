@@ -36,6 +36,9 @@ CASES = [
     (2, (15, 16), 1032, 1024, 2),
     (32, (56, 57), 296, 72, 2),        # beyond the caches, rows in whole lines and not
     (32, (56, 57), 320, 72, 2),
+    # long reductions on 256 x 128 tiles, whole and partial last stages; 153 to 192 columns on 128 x 64; masked, 384 channels, 128 x 128
+    (1, (181, 182), 600, 264, 1), (1, (181, 181), 576, 136, 1), (1, (130, 253), 264, 776, 1), (1, (181, 182), 72, 160, 1), (1, (181, 182), 192, 40, 1),
+    (2, (256, 258), 64, 168, 2), (1, (181, 183), 136, 384, 1),
 ]
 
 
