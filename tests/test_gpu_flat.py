@@ -22,6 +22,8 @@ CASES = [
     # one block of the reduction, fewer stages than a ring holds, and several
     (22, (40, 39), 24, 72), (22, (39, 40), 72, 72), (9, (43, 55), 24, 72), (9, (43, 56), 72, 72), (4, (53, 103), 24, 72), (4, (53, 104), 72, 72),
     (1, (27, 28, 29), 24, 72), (1, (33, 32, 33), 40, 72),
+    # weight gradient of a volume, patches of a work-group: eight, nine (a ring of four), and a last one with fewer
+    (1, (64, 64, 64), 32, 32), (1, (65, 64, 64), 32, 32), (1, (64, 33, 47), 40, 72), (2, (21, 35, 30), 72, 104),
 ]
 
 
