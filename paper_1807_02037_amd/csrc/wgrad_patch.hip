@@ -331,15 +331,13 @@ struct GPatch {
   static constexpr int LDS_BYTES = 4 * BUF > SUMS ? 4 * BUF : SUMS;
 };
 
-template <int P3D, bool CS, bool XCD>
+template <int P3D, bool CS>
 __global__ __launch_bounds__(GP_NT, 2) void wgrad_patch_group_kernel(WPatchP p) {
   typedef WPatch<P3D> PT;
   typedef GPatch<P3D> GP;
   constexpr int XV = GP::XV, YV = GP::YV;
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_gp[];
-  // XCD: the tiles of one split, which read the same patches, half lines each, and neighbouring splits, which share halos, on one XCD
-  int b = XCD ? xcd_order(p.cchunks * p.ktiles * p.splits) : (int)blockIdx.x;
-  if (XCD && b < 0) return;
+  int b = blockIdx.x;
   const int cc = b % p.cchunks; b /= p.cchunks;
   const int kt = b % p.ktiles; b /= p.ktiles;
   const int split = b;
@@ -857,15 +855,13 @@ hipError_t launch_with_lds(const WPatchP& p, bool xcd, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The tiles of a split on one XCD beyond 4 MiB of x and dy, what an L2 holds: us, in turn / so, 64 -> 64 at 32^3 25.3 / 23.4, 32 -> 64 at 28 x 28, batch 64
-// 13.5 / 13.1; but 72 -> 40 at 45 x 37, batch 3 10.5 / 10.8, 128 -> 128 at 16^3 20.0 / 20.5, and of one tile 32 -> 32 at 64^3 27.7 / 28.0.
+// On the small layers an XCD for the tiles of a split gains where they run alone (64 -> 64 at 32^3 25.3 / 23.4 us) and loses inside a step, where what
+// they read has just been written (the U-Net step at 64^3, all layers of at most eight patches, 574.7 / 578.6).
 template <int P3D, bool CS>
 hipError_t launch_grouped(const WPatchP& p, hipStream_t s) {
   if constexpr (P3D)
     if (p.patches_per_split > 8) return launch_with_lds<wgrad_patch_ring_kernel<CS>, RPatch::LDS_BYTES>(p, true, s);
-  const double bytes = 2.0 * p.batch * ((double)p.asp[0] * p.asp[1] * p.asp[2] * p.cx + (double)p.osp[0] * p.osp[1] * p.osp[2] * p.ky);
-  if (p.cchunks * p.ktiles > 1 && bytes > 4 << 20) return launch_with_lds<wgrad_patch_group_kernel<P3D, CS, true>, GPatch<P3D>::LDS_BYTES>(p, true, s);
-  return launch_with_lds<wgrad_patch_group_kernel<P3D, CS, false>, GPatch<P3D>::LDS_BYTES>(p, false, s);
+  return launch_with_lds<wgrad_patch_group_kernel<P3D, CS>, GPatch<P3D>::LDS_BYTES>(p, false, s);
 }
 
 struct PatchGrid { int tiles[3]; long long patches; int splits, per_split; bool pairs; };
