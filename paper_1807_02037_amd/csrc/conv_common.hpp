@@ -170,6 +170,10 @@ hipError_t launch_halo(IgemmP& p, hipStream_t s);
 bool flat_eligible(const IgemmP& p);
 hipError_t launch_flat(IgemmP& p, hipStream_t s);
 
+// The same layers where tiles are few: the reduction of a tile split among its waves (conv_split.hip).
+bool split_eligible(const IgemmP& p);
+hipError_t launch_split(IgemmP& p, hipStream_t s);
+
 // Resident-filter kernel for 2-D 3x3 64->64 and 3-D 3x3x3 32->32 channels, stride 1 (conv_rf.hip).
 bool rf_eligible(const IgemmP& p);
 hipError_t launch_rf(IgemmP& p, hipStream_t s);

@@ -474,6 +474,7 @@ bool flat_eligible(const IgemmP& p) {
 }
 
 hipError_t launch_flat(IgemmP& p, hipStream_t s) {
+  if (split_eligible(p)) return launch_split(p, s);               // few tiles, or one for a compute unit
   if (p.filt[0] == 3) return p.mode == 1 ? launch_flat_f<true, true>(p, s) : launch_flat_f<true, false>(p, s);
   return p.mode == 1 ? launch_flat_f<false, true>(p, s) : launch_flat_f<false, false>(p, s);
 }

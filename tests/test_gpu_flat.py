@@ -22,6 +22,10 @@ CASES = [
     # one block of the reduction, fewer stages than a ring holds, and several
     (22, (40, 39), 24, 72), (22, (39, 40), 72, 72), (9, (43, 55), 24, 72), (9, (43, 56), 72, 72), (4, (53, 103), 24, 72), (4, (53, 104), 72, 72),
     (1, (27, 28, 29), 24, 72), (1, (33, 32, 33), 40, 72),
+    # the reduction of a tile split among its waves: tiles of 32 and of 64 positions, fewer units than waves, partial units, columns beyond the last
+    # tile, and the shapes beside the rule
+    (1, (56, 56), 64, 72), (1, (6, 7, 8), 128, 64), (1, (10, 10, 10), 48, 56), (3, (7, 7), 512, 320), (1, (3, 3, 87), 64, 64), (1, (1, 120), 64, 128),
+    (1, (16, 16, 17), 256, 232), (1, (13, 14, 15), 104, 256), (32, (7, 7), 520, 512), (9, (20, 20), 64, 136), (1, (25, 25, 26), 64, 64), (1, (20, 20, 20), 128, 96),
     # weight gradient of a volume, patches of a work-group: eight, nine (a ring of four), and a last one with fewer
     (1, (64, 64, 64), 32, 32), (1, (65, 64, 64), 32, 32), (1, (64, 33, 47), 40, 72), (2, (21, 35, 30), 72, 104),
 ]
