@@ -164,7 +164,8 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
   struct Row { bool ok; int c0; unsigned so; };                   // of a filter row
   auto row_b = [&](int lb, int u) {
     const int vb = lb * G + grp, chunk = vb / KD, kd = FLIP ? KD - 1 - vb % KD : vb % KD;
-    return Row{vb < nblocks, chunk * BK, (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk};
+    const bool ok = vb < nblocks;                                 // beyond the last block no offset beyond the buffer either
+    return Row{ok, chunk * BK, ok ? (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk : 0};
   };
   auto load_b = [&](const Row& r, int buf, int j) {
     load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, r.ok && r.c0 + b_k[j] < p.red ? b_off[j] : DMA_OOB, r.so);

@@ -198,14 +198,15 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
   const unsigned a_step = PK * 2, b_step = MODE == PW_DGRAD ? PK * 2 : (unsigned)(PK * p.nout * 2);
   const int niter = (p.red + PK - 1) / PK;
   const unsigned lds_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
-  // the last stage may be partial: zeros, whatever lies behind, and nothing but zeros in the stages after it
+  // the last stage may be partial: zeros, whatever lies behind, and nothing but zeros in the stages after it (whose scalar offset is 0: one
+  // beyond the buffer would have to be compared with what is left of it)
   auto load_a = [&](int it, int buf, int j) {
     const bool whole = (it + 1) * PK <= p.red;
-    load_lds16(rs_a, lds_w + buf * T::STAGE + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : DMA_OOB, it * a_step);
+    load_lds16(rs_a, lds_w + buf * T::STAGE + j * T::NT * 16, whole || it * PK + a_k[j] < p.red ? a_off[j] : DMA_OOB, it < niter ? it * a_step : 0);
   };
   auto load_b = [&](int it, int buf, int j) {
     const bool whole = (it + 1) * PK <= p.red;
-    load_lds16(rs_b, lds_w + buf * T::STAGE + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : DMA_OOB, it * b_step);
+    load_lds16(rs_b, lds_w + buf * T::STAGE + T::A_BYTES + j * T::NT * 16, whole || it * PK + b_k[j] < p.red ? b_off[j] : DMA_OOB, it < niter ? it * b_step : 0);
   };
   auto fetch = [&](int it, int buf) {
 #pragma unroll

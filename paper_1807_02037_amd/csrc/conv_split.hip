@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256, 1) void conv_split_kernel(IgemmP p) {
     for (int j = 0; j < BV; ++j) {
       unsigned v = b_fwd;
       if constexpr (FLIP) v = chunk * CB + (j & 1 ? ch_o : ch_e) < p.red ? (j & 1 ? b_bwd_o : b_bwd_e) : DMA_OOB;
-      load_lds16(rs_b, ldsB + slot + j * 1024, j * 8 < rows ? v : DMA_OOB, so);
+      load_lds16(rs_b, ldsB + slot + j * 1024, j * 8 < rows ? v : DMA_OOB, j * 8 < rows ? so : 0);      // no scalar offset beyond the buffer
       so += step;
     }
   };

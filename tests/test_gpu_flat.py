@@ -22,6 +22,7 @@ CASES = [
     # one block of the reduction, fewer stages than a ring holds, and several
     (22, (40, 39), 24, 72), (22, (39, 40), 72, 72), (9, (43, 55), 24, 72), (9, (43, 56), 72, 72), (4, (53, 103), 24, 72), (4, (53, 104), 72, 72),
     (1, (27, 28, 29), 24, 72), (1, (33, 32, 33), 40, 72),
+    (9, (43, 55), 8, 40), (22, (40, 39), 8, 72),
     # the reduction of a tile split among its waves: tiles of 32 and of 64 positions, fewer units than waves, partial units, columns beyond the last
     # tile, and the shapes beside the rule
     (1, (56, 56), 64, 72), (1, (6, 7, 8), 128, 64), (1, (10, 10, 10), 48, 56), (3, (7, 7), 512, 320), (1, (3, 3, 87), 64, 64), (1, (1, 120), 64, 128),
