@@ -4,8 +4,8 @@
 // tile is padded: patches of 8 x 16 positions are 77 % full on the 14 x 14, 28 x 28 and 7 x 7 maps of ResNet-50 and fill worse
 // still on odd extents.  The input pixels that the nine taps of a tile touch are one contiguous run of BM + 2 W + 2 rows;
 // for every block of 32 channels the run goes straight to LDS (buffer loads that write LDS) while the block before it is
-// multiplied, and a tap is a shift by kh * W + kw pixels.  Where a tap leaves the image, the lane reads zeros instead, from the
-// LDS banks its pixel would have come from: its nine addresses are worked out once per tile.  The filter streams through a ring of LDS buffers one
+// multiplied, and a tap is a shift by kh * W + kw pixels.  Where a tap leaves the image, the lane reads zeros instead, with the longer filter
+// rings from the LDS banks its pixel would have come from: its nine addresses are worked out once per tile.  The filter streams through a ring of LDS buffers one
 // filter row (three taps x BN x 32 channels) a stage, one barrier each.  Products are taken transposed and leave through
 // wave_epilogue.  The forward pass reads the filter as it is stored, through the LDS transpose read: packing it first was a launch of
 // 3 to 5 us (us, packed / as stored: 72 -> 40 at 45 x 37, batch 3 12.5 / 8.8; 256 -> 256 at 14 x 14, batch 256 64.8 / 61.7, 16^3 30.6 /
@@ -50,6 +50,10 @@ struct FlatTile {
   static constexpr int BV = (3 * BN * 4 + NTHREADS - 1) / NTHREADS;       // filter loads per thread and stage
   static constexpr int B_STAGE = BV * NTHREADS * 16;
   static constexpr int NB = NB_;                                  // filter ring, 2 to 4 stages
+  // Loads between the products (stage).  Only tiles that do so pay for an address of zeros per tap and an offset for blocks that are not there: the
+  // others got nothing from them and lost, in volumes with at most 32 outputs, 2 % (us, forward, without / with: 32 -> 32 at 18 x 18 x 19
+  // 6.3 / 6.4, 224 -> 24 at 17^3 24.2 / 24.8).
+  static constexpr bool SPREAD = NB > 2 && TM * TN > 1;
   static constexpr int MAXPIX = AV * NTHREADS / 4;                // input pixels at most
   static constexpr int LPR = WTN / 8, RPI = 64 / LPR, QV = 32 / RPI;
 };
@@ -164,8 +168,9 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
   struct Row { bool ok; int c0; unsigned so; };                   // of a filter row
   auto row_b = [&](int lb, int u) {
     const int vb = lb * G + grp, chunk = vb / KD, kd = FLIP ? KD - 1 - vb % KD : vb % KD;
-    const bool ok = vb < nblocks;                                 // beyond the last block no offset beyond the buffer either
-    return Row{ok, chunk * BK, ok ? (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk : 0};
+    const bool ok = vb < nblocks;                                 // beyond the last block no offset beyond the buffer either (without SPREAD only the
+                                                                  // block that a second group lacks is asked for, whose offset lies inside)
+    return Row{ok, chunk * BK, !T::SPREAD || ok ? (unsigned)(kd * 3 + u) * 3 * p.nout * p.red * 2 + chunk * b_chunk : 0};
   };
   auto load_b = [&](const Row& r, int buf, int j) {
     load_lds16(rs_b, ldsB_w + buf * T::B_STAGE + j * NTHREADS * 16, r.ok && r.c0 + b_k[j] < p.red ? b_off[j] : DMA_OOB, r.so);
@@ -192,7 +197,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
         const int pix = r + kh * W + kw;
         const bool in = (unsigned)(h + kh - 1) < (unsigned)H && (unsigned)(w + kw - 1) < (unsigned)W;
         const int at = pix * 64 + ((half ^ ((pix >> 2) & 3)) << 4);
-        a_rd[i][kh * 3 + kw] = in ? at : npix * 64 + (at & 255);
+        a_rd[i][kh * 3 + kw] = in ? at : T::SPREAD ? npix * 64 + (at & 255) : a_zero;
       }
   }
   // data gradient: per 16 channels of the reduction; forward: their first four rows of the lane's half, and the next four
@@ -236,14 +241,13 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
     const int left = nstages - 1 - (3 * lb + u);                  // stages after this one
     const bool more = lb + 1 < nlocal;
     constexpr bool a_newer = u > 0 && u <= NB - 2;                // the next input was asked for in the last NB - 2 stages
-    constexpr bool SPREAD = NB > 2 && TM * TN > 1;
     constexpr int NEXT_A = u == 0 ? AV : 0, LOADS = NEXT_A + BV, PER = (LOADS + 5) / 6;
-    if constexpr (SPREAD) wait_barrier<(NB - 2) * BV + (a_newer ? AV : 0)>();
+    if constexpr (T::SPREAD) wait_barrier<(NB - 2) * BV + (a_newer ? AV : 0)>();
     else if (left == 0) wait_barrier<0>();
     else if (a_newer && more) wait_barrier<(NB - 2) * BV + AV>();
     else wait_barrier<(NB - 2) * BV>();
-    if (!SPREAD && u == 0 && more) fetch_a(lb + 1);
-    if (!SPREAD && left >= NB - 1) {
+    if (!T::SPREAD && u == 0 && more) fetch_a(lb + 1);
+    if (!T::SPREAD && left >= NB - 1) {
       constexpr int fu = (u + NB - 1) % 3;
       fetch_b(lb + (u + NB - 1) / 3, fu, (bbuf + NB - 1) % NB);
     }
@@ -285,7 +289,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[st % (DEPTH + 1)][j], af[st % (DEPTH + 1)][i], acc[i][j], 0, 0, 0);
-      if constexpr (SPREAD) {
+      if constexpr (T::SPREAD) {
 #pragma unroll
         for (int q = st * PER; q < (st + 1) * PER && q < LOADS; ++q) {
           if (q < NEXT_A) load_a(ra, lb + 1, q);
@@ -294,7 +298,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if constexpr (SPREAD) return;
+    if constexpr (T::SPREAD) return;
     constexpr int READS = TM + (FLIP ? TN : 2 * TN);
     __builtin_amdgcn_sched_group_barrier(0x100, READS * DEPTH, 0);
 #pragma unroll
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
       constexpr int bi = decltype(b_c)::value;
       if (lb0 + bi < nlocal) unrolled<3>([&](auto u) { stage(lb0 + bi, u, std::integral_constant<int, (3 * bi + decltype(u)::value) % NB>{}); });
     });
-  if constexpr (NB > 2 && TM * TN > 1) wait_loads();              // the zeros beyond the last block
+  if constexpr (T::SPREAD) wait_loads();                          // the zeros beyond the last block
   __syncthreads();                                                // LDS is free
   if constexpr (G > 1) {
     float4* sums = reinterpret_cast<float4*>(flat_smem);
