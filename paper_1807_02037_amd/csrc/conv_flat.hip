@@ -416,7 +416,9 @@ bool patches_win(const IgemmP& p) {
 // head of a stage / three, loads spread / four: 256 x 64: 256 -> 256, 14 x 14, batch 256 59.8 / 65.8, 56.6 / 63.6; 512 -> 512, 14 x 14, batch 96 87 / 96,
 // 80 / 89; 128 -> 128, 28 x 28, batch 128 33.9 / 39.3, 31.7 / 37.9; 128 -> 128, 32^3 30.9 / 29.8, 28.1 / 28.7; 64 -> 64, 56 x 56, where
 // three leave no room, 24 / 30 for one work-group.  128 x 64: 256 -> 256, 14 x 14, batch 32 15.6 / 19.1, 13.0 / 16.7, 11.4 / 15.5; 512 -> 512, 7 x 7, batch
-// 64 27.3 / 32.4, 20.1 / 26.1, 18.3 / 24.2; 128 -> 128, 24^3 21.5 / 21.8, 20.0 / 19.0, 19.8 / 19.1).
+// 64 27.3 / 32.4, 20.1 / 26.1, 18.3 / 24.2; 128 -> 128, 24^3 21.5 / 21.8, 20.0 / 19.0, 19.8 / 19.1).  With 128 x 64 one or two blocks of the
+// reduction are over before a long ring pays (us, ring of two / three or four: forward 32 -> 104, 62 x 62, batch 5 6.35 / 6.65, 24 -> 72, 43 x 55, batch 9 6.3 / 6.5; data gradient
+// 64 <- 56, 26 x 72, batch 25 8.6 / 8.9; 64 -> 64, 40 x 40, batch 32 8.1 / 7.8 by itself, but in a network 9.1 / 9.5).
 template <typename T>
 bool pair_fits(int w) { return flat_group_lds<T>(w) <= 81920 && flat_pixels(T::BM, w) <= T::MAXPIX; }
 template <bool P3D, bool FLIP>
@@ -426,9 +428,11 @@ hipError_t launch_256x64(IgemmP& p, hipStream_t s) {
 }
 template <bool P3D, bool FLIP>
 hipError_t launch_128x64(IgemmP& p, hipStream_t s) {
-  if (pair_fits<Flat128x64n4>(p.osp[2])) return launch_flat_t<Flat128x64n4, P3D, FLIP>(p, s);
-  if (pair_fits<Flat128x64n3>(p.osp[2])) return launch_flat_t<Flat128x64n3, P3D, FLIP>(p, s);
-  return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
+  const int blocks = (p.red + BK - 1) / BK * (P3D ? 3 : 1);
+  if (blocks >= 3 && pair_fits<Flat128x64n4>(p.osp[2])) return launch_flat_t<Flat128x64n4, P3D, FLIP>(p, s);
+  if (blocks >= 3 && pair_fits<Flat128x64n3>(p.osp[2])) return launch_flat_t<Flat128x64n3, P3D, FLIP>(p, s);
+  if constexpr (P3D) return hipErrorInvalidValue;                 // rows of at most 87 (flat_eligible): three fit
+  else return launch_flat_t<Flat128x64, P3D, FLIP>(p, s);
 }
 
 template <bool P3D, bool FLIP>

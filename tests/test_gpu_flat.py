@@ -18,8 +18,8 @@ CASES = [
     (9, (75, 120), 200, 72), (8, (76, 121), 40, 64), (1, (40, 43, 41), 40, 32), (1, (42, 40, 41), 40, 72), (2, (20, 41, 87), 24, 72),
     # between one and two of the 64 x 64 tiles for a compute unit, long reduction: 128 x 64; one at most: two groups
     (3, (45, 37), 256, 256), (2, (23, 21), 264, 136),
-    # rings of filter rows: 256 x 64 with three up to rows of 39 and two beyond, 128 x 64 with four up to 55, three up to 103, two beyond;
-    # one block of the reduction, fewer stages than a ring holds, and several
+    # rings of filter rows: 256 x 64 with three up to rows of 39 and two beyond, 128 x 64 with four up to 55, three up to 103, two beyond and
+    # for one or two blocks of the reduction in the plane
     (22, (40, 39), 24, 72), (22, (39, 40), 72, 72), (9, (43, 55), 24, 72), (9, (43, 56), 72, 72), (4, (53, 103), 24, 72), (4, (53, 104), 72, 72),
     (1, (27, 28, 29), 24, 72), (1, (33, 32, 33), 40, 72),
     (9, (43, 55), 8, 40), (22, (40, 39), 8, 72),
@@ -75,3 +75,41 @@ def test_all_directions(n, sp, c, k):
         assert bool(((got.double().reshape(ref.shape) - ref).abs() <= ref.abs() * 2.0 ** -8 + mag * 2.0 ** -18).all())
     assert float((dw.double() - rdw).norm() / rdw.norm().clamp_min(1e-30)) <= 2e-6
     assert float((db.double() - dyd.sum(0)).norm() / dyd.sum(0).norm()) <= 2e-6
+
+
+# n, extents, c, k, direction, part of the kernel's name
+KERNELS = [
+    # tiles of 128 x 64, one and two blocks of the reduction in the plane: a ring of two filter rows; from three blocks on four, three where four do not fit, two beyond; 256 x 64
+    (9, (43, 55), 24, 72, "fwd", "FlatTile<128, 64, 2, 2, 6, 2,"), (9, (43, 55), 40, 72, "fwd", "FlatTile<128, 64, 2, 2, 6, 2,"),
+    (9, (43, 55), 72, 72, "fwd", "FlatTile<128, 64, 2, 2, 4, 4,"), (9, (43, 56), 40, 72, "fwd", "FlatTile<128, 64, 2, 2, 6, 2,"),
+    (9, (43, 56), 72, 72, "dgrad", "FlatTile<128, 64, 2, 2, 6, 3,"), (4, (53, 104), 72, 72, "fwd", "FlatTile<128, 64, 2, 2, 6, 2,"), (1, (27, 28, 29), 24, 72, "fwd", "FlatTile<128, 64, 2, 2, 4, 4,"),
+    (22, (39, 39), 24, 72, "fwd", "FlatTile<256, 64, 4, 1, 6, 3,"), (22, (40, 40), 72, 72, "fwd", "FlatTile<256, 64, 4, 1, 8, 2,"),
+]
+
+
+def pointers(n, sp, c, k, make):
+    """x, dy, w, and outputs of all directions as this file's layers have them; workspace; descriptor."""
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    filt = (3,) * len(sp)
+    x, dy, w = make(n, *sp, c), make(n, *sp, k), make(*filt, c, k)
+    d = L.conv_desc(n, sp, c, k, filt, 1, 1, 0)
+    ws = torch.empty(max(L.conv_workspace_bytes(d, q) for q in (A.CONV_FWD, A.CONV_DGRAD, A.CONV_WGRAD_BIAS)) + 256, dtype=torch.uint8, device="cuda")
+    return x, dy, w, torch.full_like(dy, float("nan")), torch.full_like(x, float("nan")), ws, d
+
+
+@pytest.mark.parametrize("n,sp,c,k,direction,part", KERNELS)
+def test_kernel_of_a_layer(n, sp, c, k, direction, part):
+    """Each rule of the choice between the kernels on both of its sides, by the kernel's name."""
+    import torch
+    from helpers import kernel_names
+    import paper_1807_02037_amd as L
+    x, dy, w, y, dx, ws, d = pointers(n, sp, c, k, lambda *shape: torch.zeros(shape, dtype=torch.bfloat16, device="cuda"))
+    dw, db = torch.empty((3,) * len(sp) + (c, k), device="cuda"), torch.empty((k,), device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    call = {"fwd": lambda: L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), s),
+            "dgrad": lambda: L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), None, None, None, dx.data_ptr(), ws.data_ptr(), s),
+            "wgrad": lambda: L.conv_wgrad_bias(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws.data_ptr(), s)}[direction]
+    names = kernel_names(call)
+    assert any(part in v for v in names), names
