@@ -280,12 +280,15 @@ hipError_t launch_split_t(IgemmP& p, hipStream_t s) {
 // Positions of a tile, 0: not here.  A unit is padded to 64 channels, so they have to be mostly there (72 -> 136 at 14 x 14, batch 10 6.1 / 6.5,
 // 96 -> 96 at 20 x 20, batch 3 5.8 / 6.0, but at 10^3 48 -> 48 9.6 / 7.3).  Tiles of 32 positions fill the chip where there are too few of 64.  In the
 // plane one tile of 64 positions a compute unit pays in long data gradients only (forward / data gradient 512 -> 512 at 7 x 7, batch 32 15.6 / 21.1,
-// 16.2 / 19.9; 256 -> 256 at 14 x 14, batch 16 10.0 / 14.4, 9.9 / 14.4), and in volumes with units that are full (128 <- 96 at 20^3 12.2 / 13.0).
+// 16.2 / 19.9; 256 -> 256 at 14 x 14, batch 16 10.0 / 14.4, 9.9 / 14.4), and in volumes with units that are full (128 <- 96 at 20^3 12.2 / 13.0).  In
+// the plane three units leave a wave idle and six the sums to pay for: forward passes of one block of 64 channels and data gradients of
+// up to 160 channels lose (forward 64 -> 120 at 8 x 8, batch 5 4.6 / 5.1, 56 -> 88 at 9 x 9, batch 11 4.9 / 5.2; data gradient 112 <- 64 at 9 x 9,
+// batch 4 7.9 / 8.4, 56 <- 160 at 10 x 10, batch 8 10.6 / 11.0, 344 <- 120 at 12 x 12, batch 3 6.4 / 6.6).
 int split_rows(const IgemmP& p) {
   const bool p3d = p.filt[0] == 3;
   const long long cols = (p.nout + SPLIT_BN - 1) / SPLIT_BN, t32 = (p.M + 31) / 32 * cols, t64 = (p.M + 63) / 64 * cols;
   const int padded = (p.red + CB - 1) / CB * CB;
-  if (p.nout <= 32 || t64 > 256) return 0;
+  if (p.nout <= 32 || t64 > 256 || (!p3d && p.red <= (p.mode == 1 ? 160 : CB))) return 0;
   if (t32 <= 256) return (p3d ? 4 * p.red >= 3 * padded : 5 * p.red >= 4 * padded) ? 32 : 0;
   return (p3d ? 4 * p.red > 3 * padded : p.mode == 1 && p.red >= 512) ? 64 : 0;
 }

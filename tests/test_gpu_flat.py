@@ -25,7 +25,7 @@ CASES = [
     (9, (43, 55), 8, 40), (22, (40, 39), 8, 72),
     # the reduction of a tile split among its waves: tiles of 32 and of 64 positions, fewer units than waves, partial units, columns beyond the last
     # tile, and the shapes beside the rule
-    (1, (56, 56), 64, 72), (1, (6, 7, 8), 128, 64), (1, (10, 10, 10), 48, 56), (3, (7, 7), 512, 320), (1, (3, 3, 87), 64, 64), (1, (1, 120), 64, 128),
+    (1, (56, 56), 64, 72), (1, (30, 31), 104, 184), (1, (6, 7, 8), 128, 64), (1, (10, 10, 10), 48, 56), (3, (7, 7), 512, 320), (1, (3, 3, 87), 64, 64), (1, (1, 120), 64, 128),
     (1, (16, 16, 17), 256, 232), (1, (13, 14, 15), 104, 256), (32, (7, 7), 520, 512), (9, (20, 20), 64, 136), (1, (25, 25, 26), 64, 64), (1, (20, 20, 20), 128, 96),
     # weight gradient of a volume, patches of a work-group: eight, nine (a ring of four), and a last one with fewer
     (1, (64, 64, 64), 32, 32), (1, (65, 64, 64), 32, 32), (1, (64, 33, 47), 40, 72), (2, (21, 35, 30), 72, 104),
@@ -84,6 +84,11 @@ KERNELS = [
     (9, (43, 55), 72, 72, "fwd", "FlatTile<128, 64, 2, 2, 4, 4,"), (9, (43, 56), 40, 72, "fwd", "FlatTile<128, 64, 2, 2, 6, 2,"),
     (9, (43, 56), 72, 72, "dgrad", "FlatTile<128, 64, 2, 2, 6, 3,"), (4, (53, 104), 72, 72, "fwd", "FlatTile<128, 64, 2, 2, 6, 2,"), (1, (27, 28, 29), 24, 72, "fwd", "FlatTile<128, 64, 2, 2, 4, 4,"),
     (22, (39, 39), 24, 72, "fwd", "FlatTile<256, 64, 4, 1, 6, 3,"), (22, (40, 40), 72, 72, "fwd", "FlatTile<256, 64, 4, 1, 8, 2,"),
+    # the split reduction: tiles of 32 positions, of 64, and the layers beside it
+    (2, (20, 21), 120, 136, "fwd", "SplitTile<1>"), (1, (56, 56), 64, 72, "fwd", "conv_flat_kernel"), (1, (30, 31), 104, 184, "dgrad", "SplitTile<1>"),
+    (2, (20, 21), 136, 120, "dgrad", "conv_flat_kernel"), (2, (20, 21), 136, 160, "dgrad", "conv_flat_kernel"), (1, (6, 7, 8), 56, 40, "fwd", "SplitTile<1>"),
+    (1, (15, 16, 16), 256, 232, "fwd", "SplitTile<2>"), (1, (15, 16, 16), 256, 232, "dgrad", "SplitTile<2>"), (32, (7, 7), 512, 520, "dgrad", "SplitTile<2>"),
+    (32, (7, 7), 520, 512, "fwd", "conv_flat_kernel"), (1, (16, 16, 17), 256, 232, "fwd", "conv_flat_kernel"),
 ]
 
 
