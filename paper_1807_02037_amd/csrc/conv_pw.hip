@@ -8,7 +8,8 @@
 // memory straight to LDS (16-byte buffer loads that write LDS: no registers, no LDS store instructions; offsets beyond
 // the descriptor read zeros, so ragged tiles need no branches), 64 reduction channels a stage (a whole 128-byte line of
 // a row: with 32 every line crossed from the L2 twice) in two buffers with one barrier per stage; the second work-group
-// of the compute unit covers what one stage of lookahead does not (three buffers and one work-group: 40 % slower).  The
+// of the compute unit covers what one stage of lookahead does not (with 128 x 128 three buffers and one work-group were
+// 40 % slower; 256 x 128 has them, see launch_pw_shape).  The
 // filter stays as it lies in memory: the forward pass reads its [c][k] tile with the gfx950 LDS transpose read, the data
 // gradient reads rows [c][k] as they are ([n][r] for it).  A wave of the widest tile owns 64 x 64 outputs, one LDS read
 // per product.  Products are taken transposed (filter fragment first): a lane holds four consecutive channels of a
@@ -391,13 +392,23 @@ typedef PwTile<256, 128, 4, 2, 3> Tile4;
 //   Long reductions: what arrives in LDS is the bound, the rows of x that two work-groups share and the filter, which the L2s deliver
 // behind the misses of the activations (a loop of nothing but these loads: 512 tiles of 128 rows x 2 KB once 27 us, twice with the filter
 // 42, whatever number of stages ahead).  256 x 128 takes the filter half as often; one work-group of eight waves, three stages in LDS, loads between
-// the products.  us, 128 x 128 / 256 x 128: forward 1024 -> 256, 14 x 14, batch 256, residual 49.9 / 42.8, 512 without 85 / 80; 640 -> 640, 28 x 28, batch
-// 128 120 / 113; 768 -> 256, 14 x 14, batch 300 38.5 / 34.9; 576 -> 256, 28 x 28, batch 128 55.6 / 53.8; 2048 -> 512, 7 x 7, batch 256 (196 tiles) 28.5 /
-// 28.6; data gradient 256 <- 1024, 14 x 14, batch 256 56.1 / 49.1, 128 <- 768, batch 300 34.5 / 32.5; but 640 <- 640, 28 x 28, batch 128
-// 131.6 / 134, 512 -> 512, 14 x 14, batch 200 28.7 / 30.9.
+// the products: see long_lines.
 //   153 to 192 columns waste a quarter or more of two 128-wide tiles (us, 128 x 128 or 64 x 128 / 128 x 64: forward 320 -> 160, 28 x 28, batch 64 17.4 / 14.2;
 // 96 -> 192, 40^3 12.5 / 10.8; data gradient 192 <- 512, 14 x 14, batch 200 22.4 / 21.5; but 64 -> 144, 56 x 56, batch 128 52.4 / 58.2, and 800 -> 168, 14 x 14,
 // batch 60, 276 tiles, 11.2 / 12.6).
+
+// 256 x 128 tiles, of which a compute unit holds one: where the activation comes from memory (from 88 MB on three of them exceed the last-level
+// cache) in whole lines and the columns fill their tiles by more than three quarters, or where there is one column of tiles and its last round is
+// three quarters full.  1200 layers with at least 256 such tiles, time against 128 x 128 or 64 x 128: those 201 0.93 (two 3 to 4 % slower) and those 69 0.96
+// (one 5 % slower); of the others, 0.83 to 1.52, 415 lose (us, forward 656 -> 752, 7 x 7, batch 221 17.2 / 26.2; 640 -> 256 at 256 x 140
+// 22.5 / 24.9; data gradient 224 <- 784, 35 x 35, batch 28, addend 37.5 / 44.9) and 236 would gain.  Forward 1024 -> 256, 14 x 14, batch 256, residual
+// 49.9 / 42.8; data gradient 256 <- 1024 56.1 / 49.1; beyond 512 columns the masks and addends of data gradients outweigh it (656 <- 1024 5 % slower).
+bool long_lines(const IgemmP& p, long long cols, bool dgrad) {
+  const long long ct = (cols + 127) / 128, tiles = (p.M + 255) / 256 * ct;
+  if (tiles < 256 || 256LL * (p.red > p.nout ? p.red : p.nout) >= 0x3fffffffLL) return false;    // 32-bit offsets into the rows of a tile
+  if (ct == 1) return p.red >= (dgrad ? 768 : 576) && 4 * tiles >= 3 * ((tiles + 255) / 256 * 256);
+  return p.red >= 960 && (p.red & 63) == 0 && 2LL * p.M * p.red >= 88000000 && 4 * cols > 3 * 128 * ct && !(dgrad && cols > 512);
+}
 template <int MODE, bool STRIDED>
 hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   const long long cols = (MODE == PW_UP ? (long long)p.up[0] * p.up[1] * p.up[2] : 1) * p.nout;
@@ -405,7 +416,7 @@ hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   if (cols <= 64) return tiles(128, 64) >= 256 ? launch_pw_t<Tile2, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
   if (cols > 152 && cols <= 192 && tiles(128, 64) >= 768) return launch_pw_t<Tile2, MODE, STRIDED>(p, s);
   if constexpr (!STRIDED && MODE != PW_UP)
-    if (p.red >= (MODE == PW_DGRAD ? 768 : 576) && tiles(256, 128) >= 256) return launch_pw_t<Tile4, MODE, STRIDED>(p, s);
+    if (long_lines(p, cols, MODE == PW_DGRAD)) return launch_pw_t<Tile4, MODE, STRIDED>(p, s);
   if (!(p.mask && p.red < (STRIDED ? 513 : 384)) && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);
   return tiles(64, 128) >= 256 ? launch_pw_t<Tile1, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
 }

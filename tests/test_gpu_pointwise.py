@@ -36,7 +36,9 @@ CASES = [
     (2, (15, 16), 1032, 1024, 2),
     (32, (56, 57), 296, 72, 2),        # beyond the caches, rows in whole lines and not
     (32, (56, 57), 320, 72, 2),
-    # long reductions on 256 x 128 tiles, whole and partial last stages; 153 to 192 columns on 128 x 64; masked, 384 channels, 128 x 128
+    # long reductions on 256 x 128 tiles: one column of them with a partial last stage, and whole lines from memory
+    (1, (313, 314), 600, 104, 1), (1, (313, 314), 104, 776, 1), (1, (207, 208), 1024, 232, 1), (1, (207, 208), 232, 1024, 1),
+    # long reductions on other tiles; 153 to 192 columns; masked, 384 channels
     (1, (181, 182), 600, 264, 1), (1, (181, 181), 576, 136, 1), (1, (130, 253), 264, 776, 1), (1, (181, 182), 72, 160, 1), (1, (181, 182), 192, 40, 1),
     (2, (256, 258), 64, 168, 2), (1, (181, 183), 136, 384, 1),
 ]
@@ -116,3 +118,35 @@ def test_positions_do_not_leak_into_each_other(c, k):
     want = torch.full_like(dx, float(k))
     want[0, 2, 2] = float("nan")
     assert np.array_equal(dx.float().cpu().numpy(), want.float().cpu().numpy(), equal_nan=True)
+
+
+# n, extents, c, k, stride, direction, mask, tile: each rule of launch_pw_shape on both of its sides
+TILES = [
+    # 256 x 128: whole lines from memory; partial lines, less than 88 MB, columns that do not fill their tiles, wide data gradients beside them
+    (256, (14, 14), 1024, 256, 1, "fwd", 0, "256, 128, 4, 2, 3"), (256, (14, 14), 256, 1024, 1, "dgrad", 1, "256, 128, 4, 2, 3"),
+    (256, (14, 14), 1032, 256, 1, "fwd", 0, "128, 128, 2, 2"), (200, (14, 14), 1024, 256, 1, "fwd", 0, "128, 128, 2, 2"), (256, (14, 14), 896, 256, 1, "fwd", 0, "128, 128, 2, 2"),
+    (256, (14, 14), 1024, 136, 1, "fwd", 0, "128, 128, 2, 2"), (256, (14, 14), 520, 1024, 1, "dgrad", 1, "128, 128, 2, 2"),
+    (221, (7, 7), 656, 752, 1, "fwd", 0, "128, 128, 2, 2"), (28, (35, 35), 224, 784, 1, "dgrad", 1, "128, 128, 2, 2"),
+    # one column of them, the last round three quarters full and not
+    (1, (256, 384), 600, 128, 1, "fwd", 0, "256, 128, 4, 2, 3"), (1, (256, 383), 600, 128, 1, "fwd", 0, "128, 128, 2, 2"),
+    (1, (256, 384), 104, 776, 1, "dgrad", 0, "256, 128, 4, 2, 3"), (1, (256, 383), 104, 776, 1, "dgrad", 0, "128, 128, 2, 2"),
+]
+
+
+@pytest.mark.parametrize("n,sp,c,k,stride,direction,mask,tile", TILES)
+def test_tile_of_a_layer(n, sp, c, k, stride, direction, mask, tile):
+    import torch
+    from helpers import kernel_names
+    import paper_1807_02037_amd as L
+    osp = tuple((e - 1) // stride + 1 for e in sp)
+    x, dy = (torch.zeros((n,) + v, dtype=torch.bfloat16, device="cuda") for v in (sp + (c,), osp + (k,)))
+    w, ws = torch.zeros((c, k), dtype=torch.bfloat16, device="cuda"), torch.empty(1 << 24, dtype=torch.uint8, device="cuda")
+    d = L.conv_desc(n, sp, c, k, (1,) * len(sp), stride, 0, 0)
+    assert ws.numel() >= max(L.conv_workspace_bytes(d, q) for q in (L.abi.CONV_FWD, L.abi.CONV_DGRAD))
+    s = torch.cuda.current_stream().cuda_stream
+    if direction == "fwd":
+        names = kernel_names(lambda: L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, dy.data_ptr(), ws.data_ptr(), s))
+    else:
+        dx = torch.empty_like(x)
+        names = kernel_names(lambda: L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), None, None, x.data_ptr() if mask else None, dx.data_ptr(), ws.data_ptr(), s))
+    assert any("PwTile<%s" % tile in v for v in names), names
