@@ -393,9 +393,6 @@ typedef PwTile<256, 128, 4, 2, 3> Tile4;
 // behind the misses of the activations (a loop of nothing but these loads: 512 tiles of 128 rows x 2 KB once 27 us, twice with the filter
 // 42, whatever number of stages ahead).  256 x 128 takes the filter half as often; one work-group of eight waves, three stages in LDS, loads between
 // the products: see long_lines.
-//   153 to 192 columns waste a quarter or more of two 128-wide tiles (us, 128 x 128 or 64 x 128 / 128 x 64: forward 320 -> 160, 28 x 28, batch 64 17.4 / 14.2;
-// 96 -> 192, 40^3 12.5 / 10.8; data gradient 192 <- 512, 14 x 14, batch 200 22.4 / 21.5; but 64 -> 144, 56 x 56, batch 128 52.4 / 58.2, and 800 -> 168, 14 x 14,
-// batch 60, 276 tiles, 11.2 / 12.6).
 
 // 256 x 128 tiles, of which a compute unit holds one: where the activation comes from memory (from 88 MB on three of them exceed the last-level
 // cache) in whole lines and the columns fill their tiles by more than three quarters, or where there is one column of tiles and its last round is
@@ -409,12 +406,23 @@ bool long_lines(const IgemmP& p, long long cols, bool dgrad) {
   if (ct == 1) return p.red >= (dgrad ? 768 : 576) && 4 * tiles >= 3 * ((tiles + 255) / 256 * 256);
   return p.red >= 960 && (p.red & 63) == 0 && 2LL * p.M * p.red >= 88000000 && 4 * cols > 3 * 128 * ct && !(dgrad && cols > 512);
 }
+
+// 160 and 192 columns waste a quarter or more of two 128-wide tiles, and three of 64 store whole halves of lines, which those of 168 to 184
+// columns do not (forward 48 -> 184, 108 x 108, batch 72 103 / 183 us).  It pays while the reduction is short and the epilogue has little to read and
+// write.  1000 layers of 160 to 192 columns, reductions of 32 to 1024, time against 128 x 128 or 64 x 128: those 336 0.87 (four 2 to 5 % slower, all under a
+// stride; us, forward 64 -> 160, 56 x 56, batch 11 8.6 / 5.9, 96 -> 192, batch 29 16.1 / 13.7; data gradient 160 <- 224, 14 x 14, batch 438 21.8 / 18.1);
+// of the others 303 lose and 233 would gain.  Transposed convolutions store shorter pieces of rows and were not measured.
+bool half_lines(const IgemmP& p, long long cols, long long rows) {
+  const double bytes = 2.0 * (double)rows * p.nout * (1 + (p.add != nullptr) + (p.mask != nullptr));
+  return cols > 152 && cols <= 192 && (cols & 31) == 0 && p.red <= 256 && (bytes <= 60e6 || (cols <= 160 && p.red <= 192)) && (p.M + 127) / 128 >= 256;
+}
+
 template <int MODE, bool STRIDED>
 hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   const long long cols = (MODE == PW_UP ? (long long)p.up[0] * p.up[1] * p.up[2] : 1) * p.nout;
   auto tiles = [&](int bm, int bn) { return ((p.M + bm - 1) / bm) * ((cols + bn - 1) / bn); };
   if (cols <= 64) return tiles(128, 64) >= 256 ? launch_pw_t<Tile2, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
-  if (cols > 152 && cols <= 192 && tiles(128, 64) >= 768) return launch_pw_t<Tile2, MODE, STRIDED>(p, s);
+  if (MODE != PW_UP && half_lines(p, cols, MODE == PW_DGRAD && STRIDED ? p.M_out : p.M)) return launch_pw_t<Tile2, MODE, STRIDED>(p, s);
   if constexpr (!STRIDED && MODE != PW_UP)
     if (long_lines(p, cols, MODE == PW_DGRAD)) return launch_pw_t<Tile4, MODE, STRIDED>(p, s);
   if (!(p.mask && p.red < (STRIDED ? 513 : 384)) && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);

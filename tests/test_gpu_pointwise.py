@@ -38,6 +38,7 @@ CASES = [
     (32, (56, 57), 320, 72, 2),
     # long reductions on 256 x 128 tiles: one column of them with a partial last stage, and whole lines from memory
     (1, (313, 314), 600, 104, 1), (1, (313, 314), 104, 776, 1), (1, (207, 208), 1024, 232, 1), (1, (207, 208), 232, 1024, 1),
+    (2, (256, 258), 160, 64, 2),       # 128 x 64 tiles for 160 columns, under a stride
     # long reductions on other tiles; 153 to 192 columns; masked, 384 channels
     (1, (181, 182), 600, 264, 1), (1, (181, 181), 576, 136, 1), (1, (130, 253), 264, 776, 1), (1, (181, 182), 72, 160, 1), (1, (181, 182), 192, 40, 1),
     (2, (256, 258), 64, 168, 2), (1, (181, 183), 136, 384, 1),
@@ -130,6 +131,11 @@ TILES = [
     # one column of them, the last round three quarters full and not
     (1, (256, 384), 600, 128, 1, "fwd", 0, "256, 128, 4, 2, 3"), (1, (256, 383), 600, 128, 1, "fwd", 0, "128, 128, 2, 2"),
     (1, (256, 384), 104, 776, 1, "dgrad", 0, "256, 128, 4, 2, 3"), (1, (256, 383), 104, 776, 1, "dgrad", 0, "128, 128, 2, 2"),
+    # 160 and 192 columns, short reductions, little for the epilogue: 128 x 64
+    (64, (28, 28), 256, 160, 1, "fwd", 0, "128, 64, 2, 2"), (64, (28, 28), 264, 160, 1, "fwd", 0, "128, 128, 2, 2"), (64, (28, 28), 64, 168, 1, "fwd", 0, "128, 128, 2, 2"),
+    (64, (28, 28), 192, 40, 1, "dgrad", 1, "128, 64, 2, 2"), (128, (28, 28), 192, 40, 1, "dgrad", 1, "64, 128, 2, 2"), (128, (28, 28), 160, 40, 1, "dgrad", 1, "128, 64, 2, 2"),
+    (64, (28, 28), 168, 64, 1, "dgrad", 0, "128, 128, 2, 2"), (41, (28, 28), 160, 64, 1, "dgrad", 0, "128, 128, 2, 2"), (64, (48, 48), 64, 160, 2, "fwd", 0, "128, 64, 2, 2"),
+    (64, (48, 48), 160, 64, 2, "dgrad", 1, "128, 64, 2, 2"), (64, (48, 48), 168, 64, 2, "dgrad", 1, "64, 128, 2, 2"),
 ]
 
 
