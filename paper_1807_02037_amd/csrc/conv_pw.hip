@@ -386,9 +386,11 @@ typedef PwTile<256, 128, 4, 2, 3> Tile4;
 //   data gradient 256 <- 64, 56 x 56         134      147      130     135     138     mask and addend in, short reduction:
 //   data gradient 1024 <- 256, 14 x 14       105       96       89      91      93     more work-groups in flight
 //   forward 400 -> 176, 16 x 21 x 24          14.4     12.4     11.0    11.8     9.8   few tiles: smaller ones fill the chip
-// Products with a ReLU mask and less than 384 reduction channels take 64 x 128 (with 384 and 512: data gradient 640 <- 384, 28 x 28, batch 128
-// 64 x 128 107.8, 128 x 128 99.1; 256 <- 512, batch 100 51.5 / 48.2, with addend 57.1 / 52.6; but under a stride 256 <- 512, 56 x 56, batch 128 147.8 / 159.8, so there up to 512), others 128 x 128, and both step down
-// to tiles of which there are at least 256, one per compute unit.
+// Products with a ReLU mask and at most 512 reduction channels take 64 x 128, others 128 x 128, and both step down to tiles of which there are at
+// least 256, one per compute unit.  From 384 channels on masked ones take 128 x 128 too, but under a stride, where the last round of two a compute unit is at least three
+// quarters full.  900 layers, time against 64 x 128: those 592 0.92 (three 3 to 6 % slower); of the others, up to 1.17, 182 lose and 59 would gain (us, data
+// gradient 640 <- 384, 28 x 28, batch 128 107.8 / 99.1; 256 <- 512, batch 100 51.5 / 48.2, with addend 57.1 / 52.6; but 400 <- 464, 23 x 23, batch 31, 516
+// tiles 18.2 / 21.2; 136 <- 512, 64 x 64, batch 4, 256 tiles 9.2 / 10.5; under a stride 256 <- 512, 56 x 56, batch 128 147.8 / 159.8).
 //   Long reductions: what arrives in LDS is the bound, the rows of x that two work-groups share and the filter, which the L2s deliver
 // behind the misses of the activations (a loop of nothing but these loads: 512 tiles of 128 rows x 2 KB once 27 us, twice with the filter
 // 42, whatever number of stages ahead).  256 x 128 takes the filter half as often; one work-group of eight waves, three stages in LDS, loads between
@@ -425,7 +427,8 @@ hipError_t launch_pw_shape(IgemmP& p, hipStream_t s) {
   if (MODE != PW_UP && half_lines(p, cols, MODE == PW_DGRAD && STRIDED ? p.M_out : p.M)) return launch_pw_t<Tile2, MODE, STRIDED>(p, s);
   if constexpr (!STRIDED && MODE != PW_UP)
     if (long_lines(p, cols, MODE == PW_DGRAD)) return launch_pw_t<Tile4, MODE, STRIDED>(p, s);
-  if (!(p.mask && p.red < (STRIDED ? 513 : 384)) && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);
+  const bool narrow = p.mask && p.red <= 512 && (STRIDED || p.red < 384 || 4 * tiles(128, 128) < 3 * ((tiles(128, 128) + 511) / 512 * 512));
+  if (!narrow && tiles(128, 128) >= 256) return launch_pw_t<Tile0, MODE, STRIDED>(p, s);
   return tiles(64, 128) >= 256 ? launch_pw_t<Tile1, MODE, STRIDED>(p, s) : launch_pw_t<Tile3, MODE, STRIDED>(p, s);
 }
 

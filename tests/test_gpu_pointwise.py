@@ -136,6 +136,10 @@ TILES = [
     (64, (28, 28), 192, 40, 1, "dgrad", 1, "128, 64, 2, 2"), (128, (28, 28), 192, 40, 1, "dgrad", 1, "64, 128, 2, 2"), (128, (28, 28), 160, 40, 1, "dgrad", 1, "128, 64, 2, 2"),
     (64, (28, 28), 168, 64, 1, "dgrad", 0, "128, 128, 2, 2"), (41, (28, 28), 160, 64, 1, "dgrad", 0, "128, 128, 2, 2"), (64, (48, 48), 64, 160, 2, "fwd", 0, "128, 64, 2, 2"),
     (64, (48, 48), 160, 64, 2, "dgrad", 1, "128, 64, 2, 2"), (64, (48, 48), 168, 64, 2, "dgrad", 1, "64, 128, 2, 2"),
+    # masked, 384 to 512 channels: 128 x 128 where the last round is three quarters full, 64 x 128 where it is not, for less, and under a stride
+    (32, (28, 28), 256, 384, 1, "dgrad", 1, "128, 128, 2, 2"), (31, (28, 28), 256, 384, 1, "dgrad", 1, "64, 128, 2, 2"), (32, (28, 28), 256, 376, 1, "dgrad", 1, "64, 128, 2, 2"),
+    (31, (23, 23), 464, 400, 1, "dgrad", 1, "64, 128, 2, 2"), (31, (23, 23), 464, 400, 1, "dgrad", 0, "128, 128, 2, 2"), (31, (23, 23), 464, 520, 1, "dgrad", 1, "128, 128, 2, 2"),
+    (32, (55, 55), 256, 384, 2, "dgrad", 1, "64, 128, 2, 2"),
 ]
 
 
