@@ -472,8 +472,8 @@ __global__ __launch_bounds__(GP_NT, 2) void wgrad_patch_group_kernel(WPatchP p) 
 // The same for volumes of more than eight patches a work-group: the groups take turns at 16 positions of one patch, and three more patches
 // are on their way, a load at a time between the products, for a patch and its halo in 64-byte pieces of lines take 3 us to arrive and 0.9 to multiply.
 // The tiles of a split run on one XCD: they read the same patches, half lines each, and neighbouring splits their halos.  Both parameter
-// gradients, us, the kernel above / this one: 64 -> 64 at 64^3 75.5 / 67.2, batch 2 131 / 120; 96 -> 96 at 40^3 48.3 / 43.1; 64 -> 32 at 80^3 79 / 70;
-// but with eight patches and less 256 -> 256 at 16^3 30.3 / 31.1, 32 -> 32 at 64^3 29.2 / 29.9.
+// gradients, us, the kernel above / this one (and the mapping to XCDs): 64 -> 64 at 64^3 75.5 / 67.2, batch 2 131 / 120; 96 -> 96 at 40^3 48.3 / 43.1;
+// 64 -> 32 at 80^3 79 / 70.  Where it runs and where it loses: ring_wins.
 struct RPatch {
   typedef WPatch<1> PT;
   static constexpr int PIX = GP_NT / 4;                           // pixels a load
@@ -482,6 +482,8 @@ struct RPatch {
   static constexpr int TAPS = 27;
   static constexpr int SUMS = TAPS * 4096;
   static constexpr int LDS_BYTES = RING * BUF > SUMS ? RING * BUF : SUMS;
+  static_assert(XV + YV <= 8 / 2, "a load behind each 16 positions of a group, and the waits count them all");
+  static_assert(LDS_BYTES <= 163840, "what a compute unit has");
 };
 
 template <bool CS>
@@ -857,10 +859,19 @@ hipError_t launch_with_lds(const WPatchP& p, bool xcd, hipStream_t s) {
 
 // On the small layers an XCD for the tiles of a split gains where they run alone (64 -> 64 at 32^3 25.3 / 23.4 us) and loses inside a step, where what
 // they read has just been written (the U-Net step at 64^3, all layers of at most eight patches, 574.7 / 578.6).
+//   The ring pays where the patches come from beyond the L2s: 800 layers of 9 to 60 patches a work-group, time against the group kernel: from 20 MB of x and dy on with
+// two chunks of input channels that are mostly there, and from 32 MB on with any two tiles, 0.78 to 1.01 (mean 0.92 of 438); the others 0.87 to 1.28, 99
+// of them would gain (us, 128 -> 152 at 22^3, 6 MB 30.4 / 38.9; 96 -> 160 at 29 x 29 x 30, 13 MB 40.3 / 41.5; 48 -> 176 at 27^3 28.6 / 33.5; of one
+// tile 16 -> 16 at 78^3, batch 2, 61 MB 52.8 / 55.3).
+bool ring_wins(const WPatchP& p) {
+  const double bytes = 2.0 * p.batch * ((double)p.asp[0] * p.asp[1] * p.asp[2] * p.cx + (double)p.osp[0] * p.osp[1] * p.osp[2] * p.ky);
+  return p.patches_per_split > 8 && ((p.cx > 52 && bytes >= 20e6) || (p.cx >= 24 && p.cchunks * p.ktiles > 1 && bytes >= 32e6));
+}
+
 template <int P3D, bool CS>
 hipError_t launch_grouped(const WPatchP& p, hipStream_t s) {
   if constexpr (P3D)
-    if (p.patches_per_split > 8) return launch_with_lds<wgrad_patch_ring_kernel<CS>, RPatch::LDS_BYTES>(p, true, s);
+    if (ring_wins(p)) return launch_with_lds<wgrad_patch_ring_kernel<CS>, RPatch::LDS_BYTES>(p, true, s);
   return launch_with_lds<wgrad_patch_group_kernel<P3D, CS>, GPatch<P3D>::LDS_BYTES>(p, false, s);
 }
 

@@ -27,8 +27,9 @@ CASES = [
     # tile, and the shapes beside the rule
     (1, (56, 56), 64, 72), (1, (30, 31), 104, 184), (1, (6, 7, 8), 128, 64), (1, (10, 10, 10), 48, 56), (3, (7, 7), 512, 320), (1, (3, 3, 87), 64, 64), (1, (1, 120), 64, 128),
     (1, (16, 16, 17), 256, 232), (1, (13, 14, 15), 104, 256), (32, (7, 7), 520, 512), (9, (20, 20), 64, 136), (1, (25, 25, 26), 64, 64), (1, (20, 20, 20), 128, 96),
-    # weight gradient of a volume, patches of a work-group: eight, nine (a ring of four), and a last one with fewer
+    # weight gradient of a volume, patches of a work-group: eight, nine, and a last one with fewer; a ring of four: nine, ten, twenty
     (1, (64, 64, 64), 32, 32), (1, (65, 64, 64), 32, 32), (1, (64, 33, 47), 40, 72), (2, (21, 35, 30), 72, 104),
+    (1, (36, 64, 64), 64, 32), (1, (40, 64, 32), 64, 64), (1, (37, 63, 62), 56, 40),
 ]
 
 
@@ -89,6 +90,10 @@ KERNELS = [
     (2, (20, 21), 136, 120, "dgrad", "conv_flat_kernel"), (2, (20, 21), 136, 160, "dgrad", "conv_flat_kernel"), (1, (6, 7, 8), 56, 40, "fwd", "SplitTile<1>"),
     (1, (15, 16, 16), 256, 232, "fwd", "SplitTile<2>"), (1, (15, 16, 16), 256, 232, "dgrad", "SplitTile<2>"), (32, (7, 7), 512, 520, "dgrad", "SplitTile<2>"),
     (32, (7, 7), 520, 512, "fwd", "conv_flat_kernel"), (1, (16, 16, 17), 256, 232, "fwd", "conv_flat_kernel"),
+    # the weight gradient's ring: from 20 MB on, from 32 MB with few input channels, more than eight patches a work-group, more than one tile
+    (1, (36, 64, 64), 64, 32, "wgrad", "wgrad_patch_ring_kernel"), (1, (32, 64, 64), 64, 32, "wgrad", "wgrad_patch_group_kernel"), (1, (40, 64, 32), 64, 64, "wgrad", "wgrad_patch_ring_kernel"),
+    (1, (39, 64, 31), 64, 64, "wgrad", "wgrad_patch_group_kernel"), (1, (64, 64, 64), 40, 64, "wgrad", "wgrad_patch_ring_kernel"), (1, (36, 64, 64), 40, 64, "wgrad", "wgrad_patch_group_kernel"),
+    (1, (64, 64, 80), 32, 32, "wgrad", "wgrad_patch_group_kernel"), (1, (22, 22, 22), 128, 152, "wgrad", "wgrad_patch_group_kernel"),
 ]
 
 
