@@ -18,108 +18,11 @@
 #include "kernels.hpp"
 #include "conv_common.hpp"
 #include "conv_dma.hpp"
+#include "wgrad_patch.hpp"
 
 namespace lms {
 
 namespace {
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unrolled<N, I + 1>(f);
-  }
-}
-
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef short v8s __attribute__((ext_vector_type(8)));
-
-struct WPatchP {
-  const uint16_t* X;
-  const uint16_t* DY;
-  float* part;
-  int batch;
-  int asp[3], osp[3], filt[3], pad[3];
-  int cx, ky, taps;
-  int cchunks, ktiles, splits;
-  int tiles[3];
-  int patches;             // batch * tiles (pairs of images in the packed form of the 64 x 64 kernel)
-  int patches_per_split;
-  unsigned x_bytes, y_bytes;   // tensor sizes if both are below 2 GiB (32-bit buffer offsets), else 0
-  float* cs_part;              // partial column sums of dy [split][ky] on the side, or null
-};
-
-constexpr int LDX = 32;    // LDS row pitch in bf16 elements: 64 bytes = 16 banks, so the four rows of a transpose read cover all 64 banks (no conflicts measured)
-
-template <int P3D>
-struct WPatch {
-  static constexpr int TD = P3D ? 4 : 1, TH = P3D ? 4 : 8, TW = P3D ? 8 : 16;
-  static constexpr int HH = TH + 2, HW = TW + 2;
-  static constexpr int MAXPIX = (TD + (P3D ? 2 : 0)) * HH * HW;
-  static constexpr int MAXT = P3D ? 7 : 3;          // taps per wave at most
-};
-
-__device__ __forceinline__ bf16x8 tr_frag(const uint16_t* p0, const uint16_t* p1) {
-  // two transpose reads: positions 0..3 and 4..7 of this lane's half
-  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p0);
-  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p1);
-  const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(bf16x8, r);
-}
-
-// Wave w owns the contiguous taps [TAPS*w/4, TAPS*(w+1)/4).  The taps kw = 0, 1, 2 of one filter row (kd, kh) read
-// the positions p .. p+9 of one halo row: where a wave has several of them, the 12 positions p .. p+11 are fetched
-// once (three transpose reads) and the fragments of the three taps are cut out in registers.
-// CS: also ones x dy, the column sums (wave 0, which has one tap less than the others).
-// G groups of waves take turns at 16 positions; g: this one.  between(i): after the products of the group's i-th 16 positions.
-template <int P3D, int W, bool CS = false, int G = 1, typename F>
-__device__ __forceinline__ void wgrad_patch_mma(const uint16_t* sX, const uint16_t* sY, f32x16 (&acc)[WPatch<P3D>::MAXT], int src_off,
-                                                int half, f32x16* cs, int g, F&& between) {
-  typedef WPatch<P3D> PT;
-  constexpr int TAPS = P3D ? 27 : 9;
-  constexpr int LO = TAPS * W / 4, HI = TAPS * (W + 1) / 4;
-#pragma unroll
-  for (int i = 0; i < 8 / G; ++i) {
-    // positions q0 .. q0+7 of this lane's half: one row (or half row) of the patch, contiguous in the halo tile
-    const int q0 = (i * G + g) * 16 + 8 * half;
-    const int pw = q0 % PT::TW, ph = (q0 / PT::TW) % PT::TH, pd = q0 / (PT::TW * PT::TH);
-    const uint16_t* xb = sX + ((pd * PT::HH + ph) * PT::HW + pw) * LDX + src_off;
-    const uint16_t* yb = sY + q0 * LDX + src_off;
-    const bf16x8 bfr = tr_frag(yb, yb + 4 * LDX);
-    if constexpr (CS) {
-      const __bf16 o = (__bf16)1.f;
-      const bf16x8 ones = {o, o, o, o, o, o, o, o};
-      *cs = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bfr, *cs, 0, 0, 0);
-    }
-#pragma unroll
-    for (int row = LO / 3; row <= (HI - 1) / 3; ++row) {
-      const int k_lo = (LO > row * 3 ? LO : row * 3) - row * 3, k_hi = (HI < row * 3 + 3 ? HI : row * 3 + 3) - row * 3;   // kw range
-      const uint16_t* xr = xb + ((row / 3) * PT::HH + (row % 3)) * PT::HW * LDX;
-      if (k_hi - k_lo == 1) {
-        const bf16x8 af = tr_frag(xr + k_lo * LDX, xr + (k_lo + 4) * LDX);
-        acc[row * 3 + k_lo - LO] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr, acc[row * 3 + k_lo - LO], 0, 0, 0);
-      } else {
-        typedef unsigned v2u __attribute__((ext_vector_type(2)));
-        typedef unsigned v4u __attribute__((ext_vector_type(4)));
-        const v2u r0 = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)xr));
-        const v2u r1 = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(xr + 4 * LDX)));
-        const v2u r2 = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(xr + 8 * LDX)));
-        const unsigned u[6] = {r0[0], r0[1], r1[0], r1[1], r2[0], r2[1]};     // two positions per word
-#pragma unroll
-        for (int kw = k_lo; kw < k_hi; ++kw) {
-          v4u f;
-          if (kw == 0) f = v4u{u[0], u[1], u[2], u[3]};
-          else if (kw == 2) f = v4u{u[1], u[2], u[3], u[4]};
-          else f = v4u{__builtin_amdgcn_alignbit(u[1], u[0], 16), __builtin_amdgcn_alignbit(u[2], u[1], 16),
-                       __builtin_amdgcn_alignbit(u[3], u[2], 16), __builtin_amdgcn_alignbit(u[4], u[3], 16)};
-          acc[row * 3 + kw - LO] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f), bfr, acc[row * 3 + kw - LO], 0, 0, 0);
-        }
-      }
-    }
-    between(i);
-  }
-}
 
 // CS: the work-groups of input-channel tile 0 also add up the gradient vectors they stage (every position of dy lies in
 // exactly one patch): the bias / shift gradient without another pass over dy (two launches less; 64 -> 64 channels at
@@ -319,7 +222,6 @@ __global__ __launch_bounds__(NTHREADS, 2) void wgrad_patch_kernel(WPatchP p) {
 // again: with the groups' sums added first there is one per compute unit instead of two (27 x 32 x 32 filters: 28 MB each
 // way instead of 56).  Both parameter gradients, us: 64 -> 64 at 64^3 77 -> 74, 32 -> 32 38 -> 33,
 // 128 -> 128 at 32^3 52 -> 46, 256 -> 256 at 16^3 37 -> 33.
-constexpr int GP_NT = 512;
 template <int P3D>
 struct GPatch {
   typedef WPatch<P3D> PT;
@@ -425,183 +327,6 @@ __global__ __launch_bounds__(GP_NT, 2) void wgrad_patch_group_kernel(WPatchP p) 
       if (r + 1 < rounds) fetch(r + 1, (r + 1) & 1);
       const uint16_t* sX = reinterpret_cast<const uint16_t*>(lds_gp + (g * 2 + (r & 1)) * GP::BUF);
       wgrad_patch_mma<P3D, W, CS && W == 0>(sX, sX + GP::X_BYTES / 2, acc, src_off, half, &cs, 0, [](int) {});
-    }
-    // ---- group 1 leaves its sums in LDS, group 0 adds them and writes ----
-    float4* sums = reinterpret_cast<float4*>(lds_gp);
-    __syncthreads();
-    if (g == 1) {
-#pragma unroll
-      for (int j = 0; j < TAP_N; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          sums[((TAP_LO + j) * 4 + q) * 64 + lane] = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
-    }
-    __syncthreads();
-    if (g == 0) {
-#pragma unroll
-      for (int j = 0; j < TAP_N; ++j) {
-        float* out = p.part + ((long long)split * p.taps + TAP_LO + j) * p.cx * p.ky;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 t = sums[((TAP_LO + j) * 4 + q) * 64 + lane];
-          const float v[4] = {acc[j][4 * q] + t.x, acc[j][4 * q + 1] + t.y, acc[j][4 * q + 2] + t.z, acc[j][4 * q + 3] + t.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int c = c0 + 8 * q + 4 * (lane >> 5) + e, k = k0 + (lane & 31);
-            if (c < p.cx && k < p.ky) out[(long long)c * p.ky + k] = v[e];
-          }
-        }
-      }
-    }
-    if (CS && cc == 0) {
-      float* sh = reinterpret_cast<float*>(lds_gp);
-      __syncthreads();                                            // the sums above have been read
-      if (W == 0 && lane < 32) sh[g * 32 + lane] = cs[0];         // every row of the product with ones is the sum
-      __syncthreads();
-      if (tid < 32 && k0 + tid < p.ky) p.cs_part[(long long)split * p.ky + k0 + tid] = sh[tid] + sh[32 + tid];
-    }
-  };
-  switch (wave) {
-    case 0: run(std::integral_constant<int, 0>{}); break;
-    case 1: run(std::integral_constant<int, 1>{}); break;
-    case 2: run(std::integral_constant<int, 2>{}); break;
-    default: run(std::integral_constant<int, 3>{}); break;
-  }
-}
-
-// The same for volumes of more than eight patches a work-group: the groups take turns at 16 positions of one patch, and three more patches
-// are on their way, a load at a time between the products, for a patch and its halo in 64-byte pieces of lines take 3 us to arrive and 0.9 to multiply.
-// The tiles of a split run on one XCD: they read the same patches, half lines each, and neighbouring splits their halos.  Both parameter
-// gradients, us, the kernel above / this one (and the mapping to XCDs): 64 -> 64 at 64^3 75.5 / 67.2, batch 2 131 / 120; 96 -> 96 at 40^3 48.3 / 43.1;
-// 64 -> 32 at 80^3 79 / 70.  Where it runs and where it loses: ring_wins.
-struct RPatch {
-  typedef WPatch<1> PT;
-  static constexpr int PIX = GP_NT / 4;                           // pixels a load
-  static constexpr int XV = (PT::MAXPIX + 4 + PIX - 1) / PIX, YV = 128 / PIX;        // loads per thread and patch
-  static constexpr int X_BYTES = XV * PIX * 64, Y_BYTES = 128 * 64, BUF = X_BYTES + Y_BYTES, RING = 4;
-  static constexpr int TAPS = 27;
-  static constexpr int SUMS = TAPS * 4096;
-  static constexpr int LDS_BYTES = RING * BUF > SUMS ? RING * BUF : SUMS;
-  static_assert(XV + YV <= 8 / 2, "a load behind each 16 positions of a group, and the waits count them all");
-  static_assert(LDS_BYTES <= 163840, "what a compute unit has");
-};
-
-template <bool CS>
-__global__ __launch_bounds__(GP_NT, 2) void wgrad_patch_ring_kernel(WPatchP p) {
-  typedef WPatch<1> PT;
-  typedef RPatch GP;
-  constexpr int XV = GP::XV, YV = GP::YV, RING = GP::RING;
-  extern __shared__ __attribute__((aligned(256))) unsigned char lds_gp[];
-  int b = xcd_order(p.cchunks * p.ktiles * p.splits);
-  if (b < 0) return;
-  const int cc = b % p.cchunks; b /= p.cchunks;
-  const int kt = b % p.ktiles; b /= p.ktiles;
-  const int split = b;
-  const int c0 = cc * 32, k0 = kt * 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = wave8 >> 2, wave = wave8 & 3;
-  const int hd = PT::TD + p.filt[0] - 1;
-  const int halo_pix = hd * PT::HH * PT::HW;
-  const int li = lane & 15, lg = lane >> 4;
-  const int src_off = (li >> 2) * LDX + 16 * (lg & 1) + 4 * (li & 3);
-  const int half = lg >> 1;
-
-  // this thread's vectors of a patch: position relative to the patch origin (input: origin - pad), byte offset from it
-  const int vch = (tid & 3) * 8;
-  const bool xc_ok = c0 + vch < p.cx, yc_ok = k0 + vch < p.ky;
-  int xj[XV], yj[YV];                                             // coordinates, 8 bits each
-  unsigned x_off[XV], y_off[YV];
-#pragma unroll
-  for (int j = 0; j < XV; ++j) {
-    const int pix = (tid >> 2) + j * GP::PIX;
-    const int w = pix % PT::HW, h = (pix / PT::HW) % PT::HH, d = pix / (PT::HW * PT::HH);
-    xj[j] = w | h << 8 | d << 16;
-    x_off[j] = pix < halo_pix && xc_ok ? (unsigned)((((d * p.asp[1] + h) * p.asp[2] + w) * p.cx + c0 + vch) * 2) : DMA_OOB;
-  }
-#pragma unroll
-  for (int j = 0; j < YV; ++j) {
-    const int q = (tid >> 2) + j * GP::PIX;
-    const int w = q % PT::TW, h = (q / PT::TW) % PT::TH, d = q / (PT::TW * PT::TH);
-    yj[j] = w | h << 8 | d << 16;
-    y_off[j] = yc_ok ? (unsigned)((((d * p.osp[1] + h) * p.osp[2] + w) * p.ky + k0 + vch) * 2) : DMA_OOB;
-  }
-
-  const int pbegin = split * p.patches_per_split;
-  const int pend = (pbegin + p.patches_per_split < p.patches) ? pbegin + p.patches_per_split : p.patches;
-  const int rounds = pend > pbegin ? pend - pbegin : 0;
-  int tw, th, td, nb;                                             // the next patch (uniform)
-  {
-    unsigned t = (unsigned)pbegin;
-    tw = (int)(t % (unsigned)p.tiles[2]); t /= (unsigned)p.tiles[2];
-    th = (int)(t % (unsigned)p.tiles[1]); t /= (unsigned)p.tiles[1];
-    td = (int)(t % (unsigned)p.tiles[0]);
-    nb = (int)(t / (unsigned)p.tiles[0]);
-  }
-  auto advance = [&]() {
-    if (++tw == p.tiles[2]) { tw = 0; if (++th == p.tiles[1]) { th = 0; if (++td == p.tiles[0]) { td = 0; ++nb; } } }
-  };
-  const unsigned lds_w = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_gp + wave8 * 1024);
-  struct Fetch { v4u rx, ry; int o0[3], i0[3]; };                 // what the loads of a patch share
-  auto fetch_patch = [&]() __attribute__((always_inline)) {
-    Fetch f;
-    const int o[3] = {td * PT::TD, th * PT::TH, tw * PT::TW};
-#pragma unroll
-    for (int i = 0; i < 3; ++i) { f.o0[i] = o[i]; f.i0[i] = o[i] - p.pad[i]; }
-    f.rx = buffer_rsrc(p.X + (((long long)nb * p.asp[0] + f.i0[0]) * p.asp[1] + f.i0[1]) * (long long)p.asp[2] * p.cx + (long long)f.i0[2] * p.cx, 0x7fffffff);
-    f.ry = buffer_rsrc(p.DY + (((long long)nb * p.osp[0] + o[0]) * p.osp[1] + o[1]) * (long long)p.osp[2] * p.ky + (long long)o[2] * p.ky, 0x7fffffff);
-    advance();
-    return f;
-  };
-  auto load_one = [&](const Fetch& f, int r, int j) __attribute__((always_inline)) {
-    const unsigned lds = lds_w + (r % RING) * GP::BUF;
-    if (j < XV) {
-      const bool ok = (unsigned)(f.i0[0] + (xj[j] >> 16)) < (unsigned)p.asp[0] && (unsigned)(f.i0[1] + ((xj[j] >> 8) & 255)) < (unsigned)p.asp[1] &&
-                      (unsigned)(f.i0[2] + (xj[j] & 255)) < (unsigned)p.asp[2];
-      load_lds16(f.rx, lds + j * (GP::PIX * 64), ok ? x_off[j] : DMA_OOB, 0);
-    } else {
-      const int y = yj[j - XV];
-      const bool ok = f.o0[0] + (y >> 16) < p.osp[0] && f.o0[1] + ((y >> 8) & 255) < p.osp[1] && f.o0[2] + (y & 255) < p.osp[2];
-      load_lds16(f.ry, lds + GP::X_BYTES + (j - XV) * (GP::PIX * 64), ok ? y_off[j - XV] : DMA_OOB, 0);
-    }
-  };
-
-  // Everything from the sums on is written once per wave of a group: with one loop around a switch over the waves, the
-  // sums of its four branches had to be moved into the same registers (250 of them, and spills).
-  auto run = [&](auto wave_c) {
-    constexpr int W = decltype(wave_c)::value;
-    constexpr int TAP_LO = GP::TAPS * W / 4, TAP_N = GP::TAPS * (W + 1) / 4 - TAP_LO;
-    f32x16 acc[PT::MAXT], cs;
-#pragma unroll
-    for (int j = 0; j < PT::MAXT; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) cs[v] = 0.f;
-    constexpr int LOADS = XV + YV;
-    auto fetch = [&](int r) {
-      const Fetch f = fetch_patch();
-      unrolled<LOADS>([&](auto j) { load_one(f, r, decltype(j)::value); });
-    };
-#pragma unroll 1
-    for (int r = 0; r < RING - 1 && r < rounds; ++r) fetch(r);
-    auto patch = [&](int r, auto&& between) {
-      const uint16_t* sX = reinterpret_cast<const uint16_t*>(lds_gp + (r % RING) * GP::BUF);
-      wgrad_patch_mma<1, W, CS && W == 0, 2>(sX, sX + GP::X_BYTES / 2, acc, src_off, half, &cs, g, between);
-    };
-    // this patch has landed, and the one before it, whose place the next loads take, has been read
-    int r = 0;
-#pragma unroll 1
-    for (; r + RING - 1 < rounds; ++r) {
-      wait_barrier<(RING - 2) * LOADS>();
-      const Fetch f = fetch_patch();
-      patch(r, [&](int i) { if (i < LOADS) load_one(f, r + RING - 1, i); });
-    }
-#pragma unroll 1
-    for (int left = (rounds < RING - 1 ? rounds : RING - 1) - 1; left >= 0; --left) {     // the last ones
-      if (left == 0) wait_barrier<0>();
-      else if (left == 1) wait_barrier<LOADS>();
-      else wait_barrier<(RING - 2) * LOADS>();
-      patch(rounds - 1 - left, [](int) {});
     }
     // ---- group 1 leaves its sums in LDS, group 0 adds them and writes ----
     float4* sums = reinterpret_cast<float4*>(lds_gp);
@@ -848,31 +573,17 @@ bool grouped(const int* asp, const int* osp, int cx, int ky) {
   return (cx & 7) == 0 && 2LL * ((5LL * asp[1] + 10) * asp[2] + 18) * cx < 0x7fffffffLL && 2LL * ((3LL * osp[1] + 8) * osp[2] + 16) * ky < 0x7fffffffLL;
 }
 
-template <void (*KERNEL)(WPatchP), int LDS>
-hipError_t launch_with_lds(const WPatchP& p, bool xcd, hipStream_t s) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-  if (attr != hipSuccess) return attr;
-  const long long wgs = (long long)p.cchunks * p.ktiles * p.splits;
-  hipLaunchKernelGGL(KERNEL, dim3((unsigned)(xcd ? xcd_grid(wgs) : wgs)), dim3(GP_NT), LDS, s, p);
-  return hipGetLastError();
-}
-
 // On the small layers an XCD for the tiles of a split gains where they run alone (64 -> 64 at 32^3 25.3 / 23.4 us) and loses inside a step, where what
 // they read has just been written (the U-Net step at 64^3, all layers of at most eight patches, 574.7 / 578.6).
-//   The ring pays where the patches come from beyond the L2s: 800 layers of 9 to 60 patches a work-group, time against the group kernel: from 20 MB of x and dy on with
-// two chunks of input channels that are mostly there, and from 32 MB on with any two tiles, 0.78 to 1.01 (mean 0.92 of 438); the others 0.87 to 1.28, 99
-// of them would gain (us, 128 -> 152 at 22^3, 6 MB 30.4 / 38.9; 96 -> 160 at 29 x 29 x 30, 13 MB 40.3 / 41.5; 48 -> 176 at 27^3 28.6 / 33.5; of one
-// tile 16 -> 16 at 78^3, batch 2, 61 MB 52.8 / 55.3).
-bool ring_wins(const WPatchP& p) {
-  const double bytes = 2.0 * p.batch * ((double)p.asp[0] * p.asp[1] * p.asp[2] * p.cx + (double)p.osp[0] * p.osp[1] * p.osp[2] * p.ky);
-  return p.patches_per_split > 8 && ((p.cx > 52 && bytes >= 20e6) || (p.cx >= 24 && p.cchunks * p.ktiles > 1 && bytes >= 32e6));
-}
-
 template <int P3D, bool CS>
 hipError_t launch_grouped(const WPatchP& p, hipStream_t s) {
-  if constexpr (P3D)
-    if (ring_wins(p)) return launch_with_lds<wgrad_patch_ring_kernel<CS>, RPatch::LDS_BYTES>(p, true, s);
-  return launch_with_lds<wgrad_patch_group_kernel<P3D, CS>, GPatch<P3D>::LDS_BYTES>(p, false, s);
+  if (P3D && wgrad_ring_wins(p)) return launch_wgrad_ring(p, s);
+  constexpr int LDS = GPatch<P3D>::LDS_BYTES;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_patch_group_kernel<P3D, CS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((wgrad_patch_group_kernel<P3D, CS>), dim3((unsigned)(p.cchunks * p.ktiles * p.splits)), dim3(GP_NT), LDS, s, p);
+  return hipGetLastError();
 }
 
 struct PatchGrid { int tiles[3]; long long patches; int splits, per_split; bool pairs; };
