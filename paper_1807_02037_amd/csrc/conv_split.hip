@@ -296,7 +296,8 @@ int split_rows(const IgemmP& p) {
 template <bool P3D, bool FLIP>
 hipError_t launch_split_f(IgemmP& p, hipStream_t s) {
   if (split_rows(p) == 32) return launch_split_t<SplitTile<1>, P3D, FLIP>(p, s);
-  return launch_split_t<SplitTile<2>, P3D, FLIP>(p, s);
+  if constexpr (P3D || FLIP) return launch_split_t<SplitTile<2>, P3D, FLIP>(p, s);
+  else return hipErrorInvalidValue;                               // in the plane 64 positions are for data gradients: split_rows
 }
 
 }  // namespace
