@@ -123,3 +123,76 @@ def test_kernel_of_a_layer(n, sp, c, k, direction, part):
             "wgrad": lambda: L.conv_wgrad_bias(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), db.data_ptr(), ws.data_ptr(), s)}[direction]
     names = kernel_names(call)
     assert any(part in v for v in names), names
+
+
+# n, extents, c, k: the split reduction with every term of the epilogues.  Tiles of 64 positions in both directions with several chunks and a
+# partial last one of either reduction; in the plane for the data gradient; tiles of 32
+SPLIT = [(1, (15, 16, 16), 256, 232), (1, (15, 16, 16), 232, 256), (32, (7, 7), 512, 520), (2, (20, 21), 120, 168), (1, (9, 10, 11), 192, 72)]
+
+
+@pytest.mark.parametrize("n,sp,c,k", SPLIT)
+def test_split_reduction_epilogues(n, sp, c, k):
+    import torch
+    import paper_1807_02037_amd as L
+    A = L.abi
+    nd = len(sp)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c + k)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    x, dy, w, y, dx, ws, _ = pointers(n, sp, c, k, rnd)
+    w = (w.float() / (c * 3 ** nd) ** 0.5).to(torch.bfloat16)
+    res, addend, mask = rnd(*dy.shape), rnd(*x.shape), rnd(*x.shape)
+    scale, shift = 1 + 0.1 * torch.randn(k, generator=g, device="cuda"), torch.randn(k, generator=g, device="cuda")
+    d = L.conv_desc(n, sp, c, k, (3,) * nd, 1, 1, A.F_RELU | A.F_AFFINE | A.F_RES)
+    ws = torch.empty(max(L.conv_workspace_bytes(d, q) for q in (A.CONV_FWD, A.CONV_DGRAD)) + 256, dtype=torch.uint8, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), scale.data_ptr(), shift.data_ptr(), res.data_ptr(), y.data_ptr(), ws.data_ptr(), s)
+    L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), scale.data_ptr(), addend.data_ptr(), mask.data_ptr(), dx.data_ptr(), ws.data_ptr(), s)
+    torch.cuda.synchronize()
+    pad = [0, 0] + [1, 1] * nd
+    xp, dyp = torch.nn.functional.pad(x.double(), pad), torch.nn.functional.pad(dy.double(), pad)
+    wd, wsd = w.double(), (w.float() * scale).to(torch.bfloat16).double()
+    ry, rdx = torch.zeros_like(dy, dtype=torch.float64).reshape(-1, k), torch.zeros_like(x, dtype=torch.float64).reshape(-1, c)
+    ay, adx = ry.clone(), rdx.clone()
+    for tap in torch.cartesian_prod(*[torch.arange(3)] * nd).tolist():
+        xt = xp[(slice(None),) + tuple(slice(t, t + e) for t, e in zip(tap, sp))].reshape(-1, c)
+        dt = dyp[(slice(None),) + tuple(slice(2 - t, 2 - t + e) for t, e in zip(tap, sp))].reshape(-1, k)
+        ry += xt @ wd[tuple(tap)]
+        ay += xt.abs() @ wd[tuple(tap)].abs()
+        rdx += dt @ wsd[tuple(tap)].t()
+        adx += dt.abs() @ wsd[tuple(tap)].abs().t()
+    ry, ay = ry * scale.double() + shift.double() + res.double().reshape(-1, k), ay * scale.double()
+    rdx = (rdx + addend.double().reshape(-1, c)) * (mask.double().reshape(-1, c) > 0)
+    # one bf16 rounding, fp32 sums of up to 27 * 256 exact products (2^-18 of their magnitudes) and the terms added in fp32
+    for got, ref, mag in ((y, ry.clamp_min(0), ay + ry.abs() + 8), (dx, rdx, adx + 8)):
+        assert bool(((got.double().reshape(ref.shape) - ref).abs() <= ref.abs() * 2.0 ** -8 + mag * 2.0 ** -18).all())
+
+
+@pytest.mark.parametrize("n,sp,c,k", [(1, (15, 16, 16), 256, 232), (1, (9, 10, 11), 192, 72), (2, (20, 21), 120, 168), (32, (7, 7), 512, 520), (3, (45, 37), 72, 40)])
+def test_infinities_and_nan_stay_in_their_windows(n, sp, c, k):
+    """Tiles are runs of positions: a tap beyond the edge of an image reads a pixel of another row or image and has to replace it by zeros, infinities and NaN included."""
+    import torch
+    import paper_1807_02037_amd as L
+    nd = len(sp)
+    x, dy, w, y, dx, ws, d = pointers(n, sp, c, k, lambda *shape: torch.ones(shape, dtype=torch.bfloat16, device="cuda"))
+    w *= 2.0 ** -4
+    values = (float("nan"), float("inf"), float("-inf"))
+    first, last, side = (0,) + (0,) * nd, (n - 1,) + tuple(e - 1 for e in sp), (n // 2, sp[0] // 2) + (0,) * (nd - 2) + (sp[-1] - 1,)
+    for at, v in zip((first, side, last), values):
+        x[at + (c // 2,)] = v
+        dy[at + (k - 1,)] = v
+    s = torch.cuda.current_stream().cuda_stream
+    L.conv_fwd(d, x.data_ptr(), w.data_ptr(), None, None, None, y.data_ptr(), ws.data_ptr(), s)
+    L.conv_dgrad(d, dy.data_ptr(), w.data_ptr(), None, None, None, dx.data_ptr(), ws.data_ptr(), s)
+    torch.cuda.synchronize()
+    for t, out, red in ((x, y, c), (dy, dx, k)):
+        # ones everywhere: a finite output is a sixteenth of the taps inside times the channels, in bf16; others are the sum of what their window holds
+        pos = t.double().sum(-1)
+        special = torch.where(torch.isfinite(pos), torch.zeros_like(pos), pos)
+        inside = torch.nn.functional.pad(torch.ones_like(pos), [1, 1] * nd)
+        sp_p = torch.nn.functional.pad(special, [1, 1] * nd)
+        taps = torch.cartesian_prod(*[torch.arange(3)] * nd).tolist()
+        cut = lambda a, tap: a[(slice(None),) + tuple(slice(q, q + e) for q, e in zip(tap, sp))]
+        want = sum(cut(inside, tap) for tap in taps) * red / 16 + sum(cut(sp_p, tap) for tap in taps)
+        want = want.to(torch.bfloat16).unsqueeze(-1).expand_as(out)
+        assert bool(((out == want) | (out.isnan() & want.isnan())).all())
