@@ -23,23 +23,6 @@ namespace lms {
 
 namespace {
 
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unrolled<N, I + 1>(f);
-  }
-}
-
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ bf16x8 flat_tr_frag(const unsigned char* q0, const unsigned char* q1) {
-  const v2u a = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q0));
-  const v2u b = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q1));
-  return __builtin_bit_cast(bf16x8, v4u{a[0], a[1], b[0], b[1]});
-}
-
 template <int BM_, int BN_, int WM_, int WN_, int AV_, int NB_, int G_ = 1>
 struct FlatTile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, G = G_;
@@ -274,7 +257,7 @@ __global__ __launch_bounds__(T::NT, 2) void conv_flat_kernel(IgemmP p) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         if constexpr (FLIP) bfr[st % (DEPTH + 1)][j] = *reinterpret_cast<const bf16x8*>(b + b_rd[j][ks] + tl * T::BN * 64);
-        else bfr[st % (DEPTH + 1)][j] = flat_tr_frag(b + b_rd[j][0] + (tl * BK + ks * 16) * T::BN * 2, b + b_rd[j][1] + (tl * BK + ks * 16) * T::BN * 2);
+        else bfr[st % (DEPTH + 1)][j] = tr_frag(b + b_rd[j][0] + (tl * BK + ks * 16) * T::BN * 2, b + b_rd[j][1] + (tl * BK + ks * 16) * T::BN * 2);
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i) af[st % (DEPTH + 1)][i] = *reinterpret_cast<const bf16x8*>(a + (ar[i][tap] ^ (ks * 32)));

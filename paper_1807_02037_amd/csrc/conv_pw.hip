@@ -32,8 +32,6 @@ namespace lms {
 
 namespace {
 
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef short v8s __attribute__((ext_vector_type(8)));
 
 constexpr int PK = 64;        // reduction channels per stage
 constexpr int SL = PK / 8;    // 16-byte slots of a row of PK channels
@@ -58,22 +56,6 @@ struct PwTile {
   static constexpr int QV = 32 / RPI;                             // vectors per lane and 32 positions
   static constexpr int OCC = 163840 / LDS_BYTES * (NT / 256) < 4 ? 163840 / LDS_BYTES * (NT / 256) : 4;   // waves per SIMD
 };
-
-__device__ __forceinline__ bf16x8 pw_tr_frag(const unsigned char* p0, const unsigned char* p1) {
-  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p0);
-  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p1);
-  const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(bf16x8, r);
-}
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unrolled<N, I + 1>(f);
-  }
-}
 
 // Row of the strided grid (extents big) under row m of the small one (extents small).
 __device__ __forceinline__ long long pw_strided_row(long long m, const int* small, const int* big, const int* stride) {
@@ -263,7 +245,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void pw_kernel(IgemmP p) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         if constexpr (MODE == PW_DGRAD) bfr[ks & 1][j] = *reinterpret_cast<const bf16x8*>(b + b_rd[j][ks]);
-        else bfr[ks & 1][j] = pw_tr_frag(b + b_rd[j][ks], b + b_rd[j][ks] + 4 * ROWB);
+        else bfr[ks & 1][j] = tr_frag(b + b_rd[j][ks], b + b_rd[j][ks] + 4 * ROWB);
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i) af[ks & 1][i] = *reinterpret_cast<const bf16x8*>(a + a_rd[ks] + i * 64 * PK);

@@ -22,22 +22,6 @@ namespace lms {
 
 namespace {
 
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
-
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unrolled<N, I + 1>(f);
-  }
-}
-
-__device__ __forceinline__ bf16x8 tr_frag(const unsigned char* q) {          // rows q and four rows (of 128 bytes) on
-  const v2u a = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q));
-  const v2u b = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(q + 512)));
-  return __builtin_bit_cast(bf16x8, v4u{a[0], a[1], b[0], b[1]});
-}
 
 // At most N of this wave's memory loads may still be in flight, and its LDS reads have come back.
 template <int N>
@@ -194,7 +178,7 @@ __global__ __launch_bounds__(256, 1) void conv_split_kernel(IgemmP p) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[set][ks][j] = tr_frag(b + b_rd[j] + ks * 16 * LINE);
+        for (int j = 0; j < TN; ++j) bfr[set][ks][j] = tr_frag(b + b_rd[j] + ks * 16 * LINE, b + b_rd[j] + (ks * 16 + 4) * LINE);
 #pragma unroll
         for (int i = 0; i < TM; ++i) af[set][ks][i] = *reinterpret_cast<const bf16x8*>(sA + (a_cur[i][kw] ^ ((hf * 2 + ks) * 32)));
       }

@@ -1,5 +1,7 @@
 // Barrier and epilogue of the convolution kernels that move operands and results through buffers and LDS (internal).
 #pragma once
+#include <type_traits>
+
 #include "conv_common.hpp"
 
 namespace lms {
@@ -8,6 +10,27 @@ namespace {
 constexpr unsigned DMA_OOB = 0x80000000u;        // a buffer offset outside every buffer
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef short v4s __attribute__((ext_vector_type(4)));
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<N, I + 1>(f);
+  }
+}
+
+// Eight values of a column as an operand: two LDS transpose reads, of the four rows at q0 and the four at q1 of this lane's half.
+__device__ __forceinline__ v2u tr_read(const void* q) {
+  return __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)q));
+}
+__device__ __forceinline__ bf16x8 tr_frag(const void* q0, const void* q1) {
+  const v2u a = tr_read(q0), b = tr_read(q1);
+  return __builtin_bit_cast(bf16x8, v4u{a[0], a[1], b[0], b[1]});
+}
+
 // At most N of this wave's memory loads may still be in flight, and its LDS reads have come back; then every wave of the
 // work-group has got here.
 template <int N>

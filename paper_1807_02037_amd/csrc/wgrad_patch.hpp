@@ -25,9 +25,6 @@ hipError_t launch_wgrad_ring(const WPatchP& p, hipStream_t s);
 
 namespace {
 
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef short v8s __attribute__((ext_vector_type(8)));
-
 constexpr int GP_NT = 512; // threads of the kernels with two groups of four waves
 constexpr int LDX = 32;    // LDS row pitch in bf16 elements: 64 bytes = 16 banks, so the four rows of a transpose read cover all 64 banks (no conflicts measured)
 
@@ -38,14 +35,6 @@ struct WPatch {
   static constexpr int MAXPIX = (TD + (P3D ? 2 : 0)) * HH * HW;
   static constexpr int MAXT = P3D ? 7 : 3;          // taps per wave at most
 };
-
-__device__ __forceinline__ bf16x8 tr_frag(const uint16_t* p0, const uint16_t* p1) {
-  // two transpose reads: positions 0..3 and 4..7 of this lane's half
-  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p0);
-  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p1);
-  const v8s r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(bf16x8, r);
-}
 
 // Wave w owns the contiguous taps [TAPS*w/4, TAPS*(w+1)/4).  The taps kw = 0, 1, 2 of one filter row (kd, kh) read
 // the positions p .. p+9 of one halo row: where a wave has several of them, the 12 positions p .. p+11 are fetched
@@ -79,11 +68,9 @@ __device__ __forceinline__ void wgrad_patch_mma(const uint16_t* sX, const uint16
         const bf16x8 af = tr_frag(xr + k_lo * LDX, xr + (k_lo + 4) * LDX);
         acc[row * 3 + k_lo - LO] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfr, acc[row * 3 + k_lo - LO], 0, 0, 0);
       } else {
-        typedef unsigned v2u __attribute__((ext_vector_type(2)));
-        typedef unsigned v4u __attribute__((ext_vector_type(4)));
-        const v2u r0 = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)xr));
-        const v2u r1 = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(xr + 4 * LDX)));
-        const v2u r2 = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(xr + 8 * LDX)));
+        const v2u r0 = tr_read(xr);
+        const v2u r1 = tr_read(xr + 4 * LDX);
+        const v2u r2 = tr_read(xr + 8 * LDX);
         const unsigned u[6] = {r0[0], r0[1], r1[0], r1[1], r2[0], r2[1]};     // two positions per word
 #pragma unroll
         for (int kw = k_lo; kw < k_hi; ++kw) {

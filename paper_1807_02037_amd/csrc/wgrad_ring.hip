@@ -16,15 +16,6 @@ namespace lms {
 
 namespace {
 
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unrolled<N, I + 1>(f);
-  }
-}
-
 struct RPatch {
   typedef WPatch<1> PT;
   static constexpr int PIX = GP_NT / 4;                           // pixels a load

@@ -41,8 +41,6 @@ namespace lms {
 
 namespace {
 
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 constexpr int RUN_NT = 512, STEP = 128, PIX_B = 128;
 constexpr int RING = 5 * STEP, RING_PAD = 32;                     // pixels of x in LDS; first ones once more behind the end
@@ -66,10 +64,6 @@ struct WRunP {
   int inc_h, inc_w, inc_m;     // a step of 128 positions: rows, columns, pixels in memory
   int above;                   // images that hold the step before the first image
 };
-
-__device__ __forceinline__ v2u tr_read(const unsigned char* p) {
-  return __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p));
-}
 
 template <int KT, bool CS>
 __global__ __launch_bounds__(RUN_NT, 2) void wgrad_run_kernel(WRunP p) {
