@@ -371,7 +371,7 @@ typedef PwTile<256, 128, 4, 2, 3> Tile4;
 // Products with a ReLU mask and at most 512 reduction channels take 64 x 128, others 128 x 128, and both step down to tiles of which there are at
 // least 256, one per compute unit.  From 384 channels on masked ones take 128 x 128 too, but under a stride, where the last round of two a compute unit is at least three
 // quarters full.  900 layers, time against 64 x 128: those 592 0.92 (three 3 to 6 % slower); of the others, up to 1.17, 182 lose and 59 would gain (us, data
-// gradient 640 <- 384, 28 x 28, batch 128 107.8 / 99.1; 256 <- 512, batch 100 51.5 / 48.2, with addend 57.1 / 52.6; but 400 <- 464, 23 x 23, batch 31, 516
+// gradient 640 <- 384, 28 x 28, batch 128 107.3 / 97.5; 256 <- 512, batch 100 48.5 / 44.5, with addend 57.1 / 52.6; but 400 <- 464, 23 x 23, batch 31, 516
 // tiles 18.2 / 21.2; 136 <- 512, 64 x 64, batch 4, 256 tiles 9.2 / 10.5; under a stride 256 <- 512, 56 x 56, batch 128 147.8 / 159.8).
 //   Long reductions: what arrives in LDS is the bound, the rows of x that two work-groups share and the filter, which the L2s deliver
 // behind the misses of the activations (a loop of nothing but these loads: 512 tiles of 128 rows x 2 KB once 27 us, twice with the filter
@@ -383,7 +383,7 @@ typedef PwTile<256, 128, 4, 2, 3> Tile4;
 // three quarters full.  1200 layers with at least 256 such tiles, time against 128 x 128 or 64 x 128: those 201 0.93 (two 3 to 4 % slower) and those 69 0.96
 // (one 5 % slower); of the others, 0.83 to 1.52, 415 lose (us, forward 656 -> 752, 7 x 7, batch 221 17.2 / 26.2; 640 -> 256 at 256 x 140
 // 22.5 / 24.9; data gradient 224 <- 784, 35 x 35, batch 28, addend 37.5 / 44.9) and 236 would gain.  Forward 1024 -> 256, 14 x 14, batch 256, residual
-// 49.9 / 42.8; data gradient 256 <- 1024 56.1 / 49.1; beyond 512 columns the masks and addends of data gradients outweigh it (656 <- 1024 5 % slower).
+// 51.0 / 45.5 (all directions of the layer in turn 167 / 164); data gradient 256 <- 1024 56.9 / 51.5; beyond 512 columns the masks and addends of data gradients outweigh it (656 <- 1024 5 % slower).
 bool long_lines(const IgemmP& p, long long cols, bool dgrad) {
   const long long ct = (cols + 127) / 128, tiles = (p.M + 255) / 256 * ct;
   if (tiles < 256 || 256LL * (p.red > p.nout ? p.red : p.nout) >= 0x3fffffffLL) return false;    // 32-bit offsets into the rows of a tile

@@ -6,7 +6,8 @@
 // 40.  Here a wave owns the whole tile and every fourth unit of the reduction: one filter row (three taps) x 64 input channels.  It loads
 // the unit's input (rows of positions, whole 128-byte lines) and its filter, four kilobytes a stage and five stages ahead, into LDS of its own, waits for
 // nothing but its own loads, and reads one operand of 1 KiB a product, half of what four waves of 32 x 32 read.  At the end the four
-// sums meet in LDS in the order of the waves.  What bounds it is what arrives in LDS: 33 KB a unit, 100 of 135 B/ns a compute unit takes.
+// sums meet in LDS in the order of the waves.  No pipe is full: at 256 -> 256, 16^3 36 units of 33 KB arrive in 21.5 us, 55 B/ns on average of the 124 that
+// four waves with as much in flight take from an L2; what fills the rest of its one round was not taken apart.
 // us, forward / data gradient, conv_flat.hip / here: 256 -> 256 at 16^3 26.8 / 25.1, 23.1 / 21.4; 256 -> 256 at 14^3 21.9 / 22.1, 18.1 / 18.3;
 // tiles of 32 positions: 192 -> 192 at 12^3 17.8 / 17.5, 12.6 / 13.3; 128 -> 128 at 16^3 13.6 / 13.2, 10.6 / 11.0; 64 -> 128 at 16^3 10.0 / 12.8, 7.8 / 10.3;
 // 256 -> 256 at 14 x 14, batch 8 9.5 / 14.1, 8.1 / 13.0; 512 -> 512 at 7 x 7, batch 4 14.8 / 20.5, 14.2 / 17.2.

@@ -1,8 +1,8 @@
 // Weight gradient of 3x3x3 stride-1 convolutions, patch-tiled as in wgrad_patch.hip, for large volumes: the two groups of waves take turns at 16 positions of one patch, and three more patches
 // are on their way, a load at a time between the products, for a patch and its halo in 64-byte pieces of lines take 3 us to arrive and 0.9 to multiply.
 // The tiles of a split run on one XCD: they read the same patches, half lines each, and neighbouring splits their halos.  Both parameter
-// gradients, us, wgrad_patch_group_kernel / this one (and the mapping to XCDs): 64 -> 64 at 64^3 75.5 / 67.2, batch 2 131 / 120; 96 -> 96 at 40^3 48.3 / 43.1;
-// 64 -> 32 at 80^3 79 / 70.  Where it runs and where it loses: wgrad_ring_wins.
+// gradients, us, wgrad_patch_group_kernel / this one (and the mapping to XCDs): 64 -> 64 at 64^3 71.6 / 65.4, batch 2 130 / 118; 96 -> 96 at 40^3 48.7 / 43.8;
+// 64 -> 32 at 80^3 76 / 68.  Where it runs and where it loses: wgrad_ring_wins.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
